@@ -452,3 +452,103 @@ def run(state):
         return state["result"]
     return {"step": _step, "draft": _draft, "tree": _draft_tree, "verify": _verify, "accept": _accept,
             "finish": _finish}[state["case"]["kind"]](state)
+
+
+# ------------------------------------------------------------------ the same results in 64 bits
+def _attend(q, k, v, keep=None):
+    """q [rows, Hq, d], k and v [n, Hkv, d] in 64 bits, keep [rows, n] or None: (out, lse)."""
+    rows, Hq, d = q.shape
+    n, Hkv = k.shape[0], k.shape[1]
+    g = Hq // Hkv
+    out, lse = torch.empty_like(q), torch.empty((rows, Hq), dtype=q.dtype, device=q.device)
+    for c in range(Hkv):
+        qc = q[:, c * g:(c + 1) * g].reshape(rows * g, d)
+        sc = (qc @ k[:, c].t().contiguous()).view(rows, g, n) / math.sqrt(d)
+        if keep is not None:
+            sc.masked_fill_(~keep[:, None, :], -math.inf)
+        lse[:, c * g:(c + 1) * g] = torch.logsumexp(sc, dim=2)
+        p = torch.softmax(sc, dim=2).view(rows * g, n)
+        out[:, c * g:(c + 1) * g] = (p @ v[:, c].contiguous()).view(rows, g, d)
+    return out, lse
+
+
+def _exact_draft_attn(s, q, k, v):
+    cu, ct, w = s["draft_cu"], s["cu_text"], s["case"]["window"]
+    outs, lses = [], []
+    for b in range(s["case"]["B"]):
+        at = s["text_idx"][int(ct[b]):int(ct[b + 1])][-w:].long() + int(cu[b])
+        o, l = _attend(q[b:b + 1], k[at].double(), v[at].double())
+        outs.append(o)
+        lses.append(l)
+    return torch.cat(outs), torch.cat(lses)
+
+
+def _exact_verify(s, parents):
+    c = s["case"]
+    n_q = c["n_q"]
+    outs, lses = [], []
+    sees = []                             # draft rows that a draft row may attend: itself and its ancestors
+    for b in range(c["B"]):
+        m = torch.zeros((n_q, n_q), dtype=torch.bool)
+        for i in range(n_q):
+            a = i
+            while a >= 0:
+                m[i, a] = True
+                a = int(parents[b, a])
+        sees.append(m.cuda())
+    for (k, v), q in zip(s["layers"], s["q"]):
+        o, l = torch.empty(q.shape, dtype=torch.float64, device="cuda"), torch.empty(q.shape[:2], dtype=torch.float64, device="cuda")
+        for b in range(c["B"]):
+            t0, t1 = int(s["cu"][b]), int(s["cu"][b + 1])
+            keep = torch.ones((n_q, t1 - t0), dtype=torch.bool, device="cuda")
+            keep[:, t1 - t0 - n_q:] = sees[b]
+            r = slice(b * n_q, (b + 1) * n_q)
+            o[r], l[r] = _attend(q[r].double(), k[t0:t1].double(), v[t0:t1].double(), keep)
+        outs.append(o)
+        lses.append(l)
+    return outs, [l for l, x in zip(lses, s["lse"]) if x is not None]
+
+
+def _exact_draft(s):
+    c = s["case"]
+    Hq, Hkv, d, M = c["Hq"], c["Hkv"], c["d"], c["B"]
+    z = torch.cat([s["embed"][s["tok"].long()], s["h_prev"]], dim=1).double() @ s["w_fc"].double().t() + s["b_fc"].double()
+    x = z * torch.rsqrt((z * z).mean(dim=1, keepdim=True) + 1e-6) * s["norm"].double()
+    f = (x @ s["w_qkv"].double().t() + s["b_qkv"].double()).view(M, Hq + 2 * Hkv, d)
+    cos, sin = s["cos"].double()[:, None], s["sin"].double()[:, None]
+    lo, hi = f[..., :d // 2], f[..., d // 2:]
+    turned = torch.cat([lo * cos - hi * sin, hi * cos + lo * sin], dim=2)
+    kv = s["draft_kv"].double()
+    rows = torch.from_numpy(s["kv_rows"].astype(np.int64)).cuda()
+    kv[0, 0, rows] = turned[:, Hq:Hq + Hkv]
+    kv[0, 1, rows] = f[:, Hq + Hkv:]
+    q = turned[:, :Hq].contiguous()
+    return z, q, kv, _exact_draft_attn(s, q, kv[0, 0], kv[0, 1])
+
+
+def _exact_tree(s):
+    c = s["case"]
+    w, tops = c["width"], []
+    W = s["W"].double()
+    for level in range(c["depth"]):
+        rows = s["rows"][:1] if level == 0 else s["rows"][1 + (level - 1) * w:1 + level * w]
+        logp = torch.log_softmax(rows.double() @ W.t(), dim=1)
+        tops.append((None, torch.topk(logp, w, dim=1).values))
+    return tops, None
+
+
+def exact(case, seed):
+    """What run() returns, where that is a computed number, in 64 bits; token ids, paths, parents
+    and moved rows are none."""
+    kind = case["kind"]
+    if kind in ("accept", "finish"):
+        return None
+    s = prepare({**case, "graph": 0}, seed)
+    if kind == "draft":
+        return _exact_draft(s)
+    if kind == "tree":
+        return _exact_tree(s)
+    verified = _exact_verify(s, _parents(case, seed)[0])
+    if kind == "verify":
+        return verified
+    return _exact_draft_attn(s, s["dq"].double(), s["dk"], s["dv"]), verified, None
