@@ -2,6 +2,7 @@
 // kernel selection and launches.  No device allocation, no synchronisation, no device reads.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -103,6 +104,45 @@ bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
   return verify_partial_mfma_supported(d->dtype, d->head_dim) &&
          d->kv_stride_token < (1ll << 24) &&
          total_tokens * d->kv_stride_token * 2 < (1ll << 31);
+}
+
+// Splits per sequence in proportion to its length (at least one), within the budget of about one
+// workgroup per compute unit that plan_chunk aims at; each sequence is then cut into equal pieces,
+// so that every workgroup of the call streams about the same number of bytes.  Returns the longest
+// piece in tokens.
+int plan_splits(const sparrow_attn_desc *d, const int32_t *cu_seqlens, int32_t B, int32_t n_q, int64_t total,
+                bool mfma, SeqTable *tab) {
+  const int chunk0 = plan_chunk(d, n_q, total, mfma);
+  const int slot_budget = (int)((total + chunk0 - 1) / chunk0);
+  memset(tab, 0, sizeof(*tab));
+  for (int b = 0; b <= B; ++b) tab->cu_len[b] = cu_seqlens[b];
+  int chunk = 0;
+  int ns[SPARROW_MAX_BATCH];
+  int used = 0;
+  for (int b = 0; b < B; ++b) {
+    const int len = cu_seqlens[b + 1] - cu_seqlens[b];
+    ns[b] = (int)((int64_t)len * slot_budget / (total > 0 ? total : 1));
+    if (ns[b] < 1) ns[b] = 1;
+    used += ns[b];
+  }
+  // hand the slots lost to rounding down to the sequences with the longest pieces
+  while (used < slot_budget) {
+    int worst = 0;
+    double worst_len = -1.0;
+    for (int b = 0; b < B; ++b) {
+      const double piece = (double)(cu_seqlens[b + 1] - cu_seqlens[b]) / ns[b];
+      if (piece > worst_len) { worst_len = piece; worst = b; }
+    }
+    ++ns[worst];
+    ++used;
+  }
+  for (int b = 0; b < B; ++b) {
+    const int len = cu_seqlens[b + 1] - cu_seqlens[b];
+    tab->cu_split[b + 1] = tab->cu_split[b] + ns[b];
+    const int piece = split_len(len, ns[b]);
+    if (piece > chunk) chunk = piece;
+  }
+  return chunk;
 }
 
 // Workspace split: partial outputs first, then (max, sum) pairs, each rounded up to 256 bytes.
@@ -407,10 +447,15 @@ int sparrow_draft_window_attn(const sparrow_attn_desc *desc, const void *q, cons
 size_t sparrow_verify_attn_workspace(const sparrow_attn_desc *desc, int32_t B, int32_t n_q,
                                      int64_t total_tokens) {
   if (check_desc(desc) != SPARROW_OK || B <= 0 || n_q <= 0 || total_tokens <= 0) return 0;
+  auto bytes = [&](bool mfma) {
+    const int chunk = plan_chunk(desc, n_q, total_tokens, mfma);
+    const int64_t max_slots = (total_tokens + chunk - 1) / chunk + B;
+    return verify_ws_bytes(desc, max_slots, n_q, mfma);
+  };
   const bool mfma = use_mfma_verify(desc, total_tokens);
-  const int chunk = plan_chunk(desc, n_q, total_tokens, mfma);
-  const int64_t max_slots = (total_tokens + chunk - 1) / chunk + B;
-  return verify_ws_bytes(desc, max_slots, n_q, mfma);
+  size_t need = bytes(mfma);
+  if (mfma && desc->head_dim == 64) need = std::max(need, bytes(false));   // either kernel's partials fit
+  return need;
 }
 
 int sparrow_verify_attn(const sparrow_attn_desc *desc, const void *q, const void *k,
@@ -447,45 +492,24 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
     return fail(SPARROW_ERR_INVALID_ARG, "parent_stride = %d must be 0 (one shared tree) or at least n_q = %d",
                 desc->parent_stride, n_q);
   const int64_t total = (int64_t)cu_seqlens[B] - cu_seqlens[0];   // the figure the workspace query is given
-  const bool mfma = use_mfma_verify(desc, total);
-  // Splits per sequence in proportion to its length (at least one), within the budget of about one
-  // workgroup per compute unit that plan_chunk aims at; each sequence is then cut into equal
-  // pieces, so that every workgroup of the call streams about the same number of bytes.
-  const int chunk0 = plan_chunk(desc, n_q, total, mfma);
-  const int slot_budget = (int)((total + chunk0 - 1) / chunk0);
+  bool mfma = use_mfma_verify(desc, total);
   SeqTable tab;
-  memset(&tab, 0, sizeof(tab));
-  for (int b = 0; b <= B; ++b) tab.cu_len[b] = cu_seqlens[b];
-  int chunk = 0;
-  {
-    int ns[SPARROW_MAX_BATCH];
-    int used = 0;
-    for (int b = 0; b < B; ++b) {
-      const int len = cu_seqlens[b + 1] - cu_seqlens[b];
-      ns[b] = (int)((int64_t)len * slot_budget / (total > 0 ? total : 1));
-      if (ns[b] < 1) ns[b] = 1;
-      used += ns[b];
-    }
-    // hand the slots lost to rounding down to the sequences with the longest pieces
-    while (used < slot_budget) {
-      int worst = 0;
-      double worst_len = -1.0;
-      for (int b = 0; b < B; ++b) {
-        const double piece = (double)(cu_seqlens[b + 1] - cu_seqlens[b]) / ns[b];
-        if (piece > worst_len) { worst_len = piece; worst = b; }
-      }
-      ++ns[worst];
-      ++used;
-    }
-    for (int b = 0; b < B; ++b) {
-      const int len = cu_seqlens[b + 1] - cu_seqlens[b];
-      tab.cu_split[b + 1] = tab.cu_split[b] + ns[b];
-      const int piece = split_len(len, ns[b]);
-      if (piece > chunk) chunk = piece;
+  int chunk = plan_splits(desc, cu_seqlens, B, n_q, total, mfma, &tab);
+  size_t need = verify_ws_bytes(desc, tab.cu_split[B], n_q, mfma);
+  // Heads of 64 go to the plain-ALU kernels where only their partials fit the scratch at hand: those
+  // have no padding to 64 rows (64 sequences of one row over 64 KV heads: 1 MB against 37 MB).  The
+  // static scratch also refuses what it cannot hold for them, so its limit is one rule per shape.
+  if (mfma && desc->head_dim == 64) {
+    SeqTable tab_g;
+    const int chunk_g = plan_splits(desc, cu_seqlens, B, n_q, total, false, &tab_g);
+    const size_t need_g = verify_ws_bytes(desc, tab_g.cu_split[B], n_q, false);
+    const size_t have = static_ws ? (size_t)SPARROW_STATIC_WS_BYTES : workspace ? workspace_bytes : 0;
+    if ((need > have && need_g <= have) || (static_ws && need_g > have)) {
+      mfma = false;
+      tab = tab_g; chunk = chunk_g; need = need_g;
     }
   }
   const int n_slots = tab.cu_split[B];
-  const size_t need = verify_ws_bytes(desc, n_slots, n_q, mfma);
   if (static_ws) {
     if (need > (size_t)SPARROW_STATIC_WS_BYTES)
       return fail(SPARROW_ERR_UNSUPPORTED,

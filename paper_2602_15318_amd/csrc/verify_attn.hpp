@@ -51,7 +51,7 @@ __device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int B, int slot)
 // Partial pass, plain-ALU version: any supported dtype / head_dim.
 hipError_t launch_verify_partial_generic(int dtype, const VerifyArgs &a, const SeqTable &tab,
                                          hipStream_t st);
-// Partial pass, matrix-core version: bf16, head_dim 128.
+// Partial pass, matrix-core version: bf16, head_dim 64 or 128.
 bool verify_partial_mfma_supported(int dtype, int head_dim);
 hipError_t launch_verify_partial_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
 // Workgroups per (split, KV head) for R = n_q * (Hq / Hkv) rows.

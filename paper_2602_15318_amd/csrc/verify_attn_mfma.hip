@@ -1,4 +1,4 @@
-// Verification attention, matrix-core partial pass: bf16, head_dim 128, gfx950.
+// Verification attention, matrix-core partial pass: bf16, head_dim 128 or 64, gfx950.
 //
 // One workgroup (8 wavefronts) owns one (context split, KV head, block of 64 rows); a row is a
 // (draft row, query head of the group) pair, so all rows of a block share the K/V stream.
@@ -28,9 +28,6 @@ namespace sparrow {
 namespace {
 
 constexpr int kTile = 32;                 // tokens per tile
-constexpr int kRowBytes = 256;            // one K or V row of a head: 128 bf16
-constexpr int kTileBytes = kTile * kRowBytes;
-constexpr int kSub = 1;                   // 32-token tiles per stream per step
 constexpr int kRowsPerWG = 64;
 constexpr int kMlFloats = 3;              // per row of a partial: max, sum, output scale
 constexpr int kStreams = 2;
@@ -42,7 +39,12 @@ constexpr float kSlack = 8.0f;            // log2 units a score may exceed a row
 // reads of 16 rows x 32 bytes): no conflict cycle on any of them.  Variants that also fold bit 3
 // of the row in (so that rows r and r + 8 land on different chunks) doubled the cycles of the
 // 16-byte operand reads -- two thirds of the kernel's LDS cycles were bank conflicts with it.
-__device__ __forceinline__ int swz(int row) { return (row & 7) << 1; }
+// With 128-byte rows (head_dim 64) two consecutive rows share the 256 bytes of one bank line, so the
+// parity of the row picks the half line and the next two bits the swizzle: the eight rows r .. r+7
+// land on eight different 16-byte columns, as they do with 256-byte rows.
+template <int kD> __device__ __forceinline__ int swz(int row) {
+  return kD == 128 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
+}
 
 __device__ __forceinline__ bf16x8 lds_read_b128(const unsigned char *p) {
   return *reinterpret_cast<const bf16x8 *>(p);
@@ -81,12 +83,28 @@ struct PieceTable {
   int32_t piece[SPARROW_MAX_BATCH];
 };
 
-template <int kPrefetch, int kQT>
+// Heads of 64 keep the intermediate state of an attention row in 32 bits (as the plain-ALU kernel
+// does): probabilities enter the output MFMA as the sum of two bf16 terms, row sums are added up on
+// the vector ALU, split partials are stored in fp32.  Heads of 128 round probabilities to bf16 and
+// partials to fp16.  The second output MFMA of a tile is hidden: with 64-wide heads a token brings
+// half the bytes and the same number of scores, and the kernel waits for memory or for the softmax.
+template <int kD> constexpr bool kWideState = kD == 64;
+
+// kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
+// tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
+template <int kD, int kPrefetch, int kQT>
 __global__ void __launch_bounds__(256 * kStreams)
 verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, int flat) {
+  constexpr int kSub = 128 / kD;                           // 32-token tiles per stream per step
+  constexpr int kRowBytes = 2 * kD;                        // one K or V row of a head
+  constexpr int kChunks = kD / 8;                          // 16-byte chunks of a row
+  constexpr int kLdRows = 256 / kChunks;                   // token rows that one load of a stream covers
+  constexpr int kSlabs = 2 * kSub;                         // 16-token slabs of a step
+  constexpr int kKS = kD / 32, kMT = kD / 16;              // MFMA k-steps of a score, 16-wide d-tiles
+  constexpr bool kWide = kWideState<kD>;
   // [stream][buf][K,V][kSub tiles]; after the main loop the first 34 KB are reused for the merge
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  constexpr int kStepBytes = kSub * kTileBytes;            // K (or V) rows of one stream step
+  constexpr int kStepBytes = kSub * kTile * kRowBytes;     // K (or V) rows of one stream step
   auto lds_at = [&](int strm_, int buf, int kv) {
     return lds + ((strm_ * 2 + buf) * 2 + kv) * kStepBytes;
   };
@@ -155,30 +173,30 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   const unsigned int row_bytes = (unsigned int)a.stride_tok * 2u;
 
   // ---- loader: in step `st` stream `strm` owns tiles (st*kStreams + strm)*kSub .. +kSub, i.e.
-  // 32*kSub consecutive tokens; thread -> rows tid/16 + 16 j, 16-byte chunk tid%16.  Rows past
+  // 32*kSub consecutive tokens; thread -> rows tid/kChunks + kLdRows j, 16-byte chunk tid%kChunks.  Rows past
   // the end of the split are clamped to its last token (loaded, never used), so every load is
   // unconditional and the number of loads in flight is a compile-time constant at every wait.
-  const int ld_row = tid >> 4, ld_ch = tid & 15;
-  constexpr int kLd = 2 * kSub;                       // 16-row slabs per step (per K and per V)
+  const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
+  constexpr int kLd = kSub * kTile / kLdRows;         // loads per step (per K and per V)
   u32x4 stage[kPrefetch][2 * kLd];
   auto issue = [&](int st, u32x4 *sg) {
     const int tb = t0 + (st * kStreams + strm) * kSub * kTile;
 #pragma unroll
     for (int j = 0; j < kLd; ++j) {
-      const int r = min(tb + ld_row + 16 * j, t1 - 1);
+      const int r = min(tb + ld_row + kLdRows * j, t1 - 1);
       const unsigned int o = (unsigned int)r * row_bytes + (unsigned int)ld_ch * 16u;
       sg[j] = __builtin_nontemporal_load((const u32x4 *)(Kg + o));
       sg[kLd + j] = __builtin_nontemporal_load((const u32x4 *)(Vg + o));
     }
   };
-  // row r of the step lands at byte r*256 + ((chunk ^ swz(r)) * 16); swz depends on r mod 16 only
-  const int st_off = ld_row * kRowBytes + ((ld_ch ^ swz(ld_row)) << 4);
+  // row r of the step lands at byte r*kRowBytes + ((chunk ^ swz(r)) * 16); swz depends on r mod 8 only
+  const int st_off = ld_row * kRowBytes + ((ld_ch ^ swz<kD>(ld_row)) << 4);
   auto stash = [&](int buf, const u32x4 *sg) {
     unsigned char *kb = lds_at(strm, buf, 0), *vb = lds_at(strm, buf, 1);
 #pragma unroll
     for (int j = 0; j < kLd; ++j) {
-      *reinterpret_cast<u32x4 *>(kb + st_off + 16 * j * kRowBytes) = sg[j];
-      *reinterpret_cast<u32x4 *>(vb + st_off + 16 * j * kRowBytes) = sg[kLd + j];
+      *reinterpret_cast<u32x4 *>(kb + st_off + kLdRows * j * kRowBytes) = sg[j];
+      *reinterpret_cast<u32x4 *>(vb + st_off + kLdRows * j * kRowBytes) = sg[kLd + j];
     }
   };
 
@@ -203,16 +221,16 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     h[qt] = row_ok[qt] ? c * g + rho % g : 0;
   }
 
-  bf16x8 qreg[kQT][4];
+  bf16x8 qreg[kQT][kKS];
   {
-    u32x4 qv[kQT][4];
+    u32x4 qv[kQT][kKS];
 #pragma unroll
     for (int qt = 0; qt < kQT; ++qt) {
       // rows past R read row 0 (in bounds) and are zeroed below
       const int64_t qrow = row_ok[qt] ? ((int64_t)b * a.n_q + i_row[qt]) * a.Hq + h[qt] : 0;
-      const bf16_t *qp = (const bf16_t *)a.q + qrow * 128 + 8 * c4;
+      const bf16_t *qp = (const bf16_t *)a.q + qrow * kD + 8 * c4;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) qv[qt][ks] = *(const u32x4 *)(qp + 32 * ks);
+      for (int ks = 0; ks < kKS; ++ks) qv[qt][ks] = *(const u32x4 *)(qp + 32 * ks);
     }
     // The memory pipeline of a compute unit serves requests in issue order and a wavefront
     // issues all its loads back to back: without this barrier the look-ahead of the wavefronts
@@ -229,7 +247,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 #pragma unroll
     for (int qt = 0; qt < kQT; ++qt)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
+      for (int ks = 0; ks < kKS; ++ks) {
         if (!row_ok[qt]) qv[qt][ks] = (u32x4){0u, 0u, 0u, 0u};
         qreg[qt][ks] = __builtin_bit_cast(bf16x8, qv[qt][ks]);
       }
@@ -248,17 +266,17 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 
   // LDS read offsets
   const int k_off = n * kRowBytes;                 // + 16-row slab, chunk (4*ks + c4) ^ swz(n)
-  const int k_swz = swz(n);
+  const int k_swz = swz<kD>(n);
   const int s16 = lane & 15;                       // source lane index within the 16-lane group
   const int v_row = 4 * c4 + (s16 >> 2);           // token within a 16-token slab
-  const int v_swz = swz(v_row);
+  const int v_swz = swz<kD>(v_row);
   const int v_off = v_row * kRowBytes + ((s16 & 1) << 3);   // + chunk (2*mt + ((s16>>1)&1)) ^ swz
   const int v_chb = (s16 >> 1) & 1;
 
   float m_run[kQT];
   f32x4 l_acc[kQT];       // running sum of a row's exponentials, the same value in all 4 entries
-  f32x4 o_acc[kQT][8];
-  constexpr bool kMfmaRowSum = true;
+  f32x4 o_acc[kQT][kMT];
+  constexpr bool kMfmaRowSum = !kWide;
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
@@ -267,7 +285,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     m_run[qt] = kNegBig;
     l_acc[qt] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt) o_acc[qt][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < kMT; ++mt) o_acc[qt][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
 
   // One step of one stream: 32*kSub tokens against the wavefront's 16 rows, one joint softmax
@@ -277,21 +295,21 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     const unsigned char *Ks = lds_at(strm, buf, 0);
     const unsigned char *Vs = lds_at(strm, buf, 1);
     const int tb = t0 + (st * kStreams + strm) * kSub * kTile;
-    f32x4 s[NA][kLd];
+    f32x4 s[NA][kSlabs];
     // Tree instances raise the wavefront's priority for their MFMA phases: the other wavefront of
     // the SIMD is then in its softmax, and the matrix pipe stays fed (-3 % on the 60-node tree).
     constexpr bool kPrio = kQT > 1;
     if (kPrio) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int j = 0; j < kLd; ++j) {
-      bf16x8 ka[4];
+    for (int j = 0; j < kSlabs; ++j) {
+      bf16x8 ka[kKS];
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < kKS; ++ks)
         ka[ks] = lds_read_b128(Ks + j * 16 * kRowBytes + k_off + (((4 * ks + c4) ^ k_swz) << 4));
 #pragma unroll
       for (int qt = 0; qt < NA; ++qt) s[qt][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
+      for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
         for (int qt = 0; qt < NA; ++qt)
           s[qt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks], qreg[qt][ks], s[qt][j], 0, 0, 0);
@@ -303,11 +321,12 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     const bool edge = tb + kSub * kTile > min(t1, L);   // uniform: split end or draft rows in reach
     if (kQT > 1) __builtin_amdgcn_sched_barrier(0);     // keep the V^T reads below the softmax
     bf16x8 pb[NA][kSub];
+    bf16x8 pl[kWide ? NA : 1][kSub];                    // kWide: what pb leaves of the probability
 #pragma unroll
     for (int qt = 0; qt < NA; ++qt) {
-      float sc[4 * kLd];
+      float sc[4 * kSlabs];
 #pragma unroll
-      for (int j = 0; j < kLd; ++j)
+      for (int j = 0; j < kSlabs; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) sc[4 * j + i] = s[qt][j][i];
       if (edge) {
@@ -317,7 +336,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         int tb_e = tb;
         asm volatile("" : "+s"(tb_e));
 #pragma unroll
-        for (int j = 0; j < kLd; ++j)
+        for (int j = 0; j < kSlabs; ++j)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int tok = tb_e + 16 * j + 4 * c4 + i;
@@ -328,7 +347,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
       }
       float mx = sc[0];
 #pragma unroll
-      for (int e = 1; e < 4 * kLd; ++e) mx = fmaxf(mx, sc[e]);
+      for (int e = 1; e < 4 * kSlabs; ++e) mx = fmaxf(mx, sc[e]);
       mx *= a.scale_log2;
       // The reference point m of a row moves only when some score of the wavefront's tile lies
       // more than kSlack above it (exponentials then stay below 2^kSlack, far from overflow, and
@@ -340,7 +359,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         m_run[qt] = m_new;
         if (kMfmaRowSum) l_acc[qt] *= alpha; else l_acc[qt][0] *= alpha;
 #pragma unroll
-        for (int mt = 0; mt < 8; ++mt) o_acc[qt][mt] *= alpha;
+        for (int mt = 0; mt < kMT; ++mt) o_acc[qt][mt] *= alpha;
       }
 #pragma unroll
       for (int u = 0; u < kSub; ++u) {
@@ -349,7 +368,16 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         for (int e = 0; e < 8; ++e) {
           const float p = fast_exp2(fmaf(sc[8 * u + e], a.scale_log2, -m_run[qt]));
           if (!kMfmaRowSum) psum += p;
-          pb[qt][u][e] = (__bf16)p;
+          if (kWide) {
+            // p = hi + lo: hi the leading 8 bits (cut off, so that lo has p's sign), lo the next 8.
+            // Where hi is not zero lo is at least 2^-126, far below p, so that an infinite V gives
+            // an infinity here and no 0 * inf.
+            const float hi = __uint_as_float(__float_as_uint(p) & 0xffff0000u);
+            pb[qt][u][e] = (__bf16)hi;
+            pl[qt][u][e] = (__bf16)fmaxf(p - hi, fminf(hi, 0x1p-126f));
+          } else {
+            pb[qt][u][e] = (__bf16)p;
+          }
         }
         // row sums on the matrix cores: every row of ones . P^T is the sum over the 32 tokens
         // (kMfmaRowSum off: per-lane sums on the vector ALU, merged across the four lanes at the end)
@@ -362,7 +390,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     if (kQT > 1) __builtin_amdgcn_sched_barrier(0);
     if (kPrio) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int mt = 0; mt < 8; ++mt) {
+    for (int mt = 0; mt < kMT; ++mt) {
       const int ch = ((2 * mt + v_chb) ^ v_swz) << 4;
       if (kQT > 1 && mt == 4) __builtin_amdgcn_sched_barrier(0);    // at most 4 d-tiles of V^T in flight
 #pragma unroll
@@ -371,8 +399,10 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         const bf16x4 vb = lds_read_tr(Vs + (2 * u + 1) * 16 * kRowBytes + v_off + ch);
         const bf16x8 vt = __builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
-        for (int qt = 0; qt < NA; ++qt)
+        for (int qt = 0; qt < NA; ++qt) {
           o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pb[qt][u], o_acc[qt][mt], 0, 0, 0);
+          if (kWide) o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pl[qt][u], o_acc[qt][mt], 0, 0, 0);
+        }
       }
     }
     if (kPrio) __builtin_amdgcn_s_setprio(0);
@@ -415,14 +445,14 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   // register layout: [slot][kv head][row block][wavefront][pair of d-tiles][lane] x 8 halves, so
   // that every store instruction writes 1 KB of contiguous memory.
   f32x4 *mo = reinterpret_cast<f32x4 *>(lds);                                  // [w][mt][lane]
-  float *mm = reinterpret_cast<float *>(lds + 4 * 8 * 64 * 16);                // [w][lane][m,l]
+  float *mm = reinterpret_cast<float *>(lds + 4 * kMT * 64 * 16);              // [w][lane][m,l]
 #pragma unroll
   for (int qt = 0; qt < kQT; ++qt) {
     const float l_mine = kMfmaRowSum ? l_acc[qt][0] : quad_sum(l_acc[qt][0]);
     __syncthreads();                    // all tile reads (and the previous merge) done: LDS is free
     if (strm == 1) {
 #pragma unroll
-      for (int mt = 0; mt < 8; ++mt) mo[(w * 8 + mt) * 64 + lane] = o_acc[qt][mt];
+      for (int mt = 0; mt < kMT; ++mt) mo[(w * kMT + mt) * 64 + lane] = o_acc[qt][mt];
       mm[(w * 64 + lane) * 2] = m_run[qt];
       mm[(w * 64 + lane) * 2 + 1] = l_mine;
     }
@@ -439,23 +469,36 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
       const float l_tot = l_mine * a0 + l1 * a1;
       const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;
       const float s0 = a0 * inv_l, s1 = a1 * inv_l;
+      if (kWide) {
+        // fp32 partials: [unit][wavefront][d-tile][lane] x 4 floats
+        f32x4 *po = reinterpret_cast<f32x4 *>(a.part_o) + (unit * 4 + w) * (kMT * 64) + lane;
+#pragma unroll
+        for (int mt = 0; mt < kMT; ++mt)
+          __builtin_nontemporal_store(o_acc[qt][mt] * s0 + mo[(w * kMT + mt) * 64 + lane] * s1, &po[mt * 64]);
+        if (c4 == 0) {
+          float *pml = a.part_ml + (unit * kRowsPerWG + 16 * w + n) * kMlFloats;
+          __builtin_nontemporal_store(m_new, &pml[0]);
+          __builtin_nontemporal_store(l_tot, &pml[1]);
+        }
+        continue;
+      }
       float amax = 0.f;
 #pragma unroll
-      for (int mt = 0; mt < 8; ++mt) {
-        o_acc[qt][mt] = o_acc[qt][mt] * s0 + mo[(w * 8 + mt) * 64 + lane] * s1;
+      for (int mt = 0; mt < kMT; ++mt) {
+        o_acc[qt][mt] = o_acc[qt][mt] * s0 + mo[(w * kMT + mt) * 64 + lane] * s1;
 #pragma unroll
         for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fabsf(o_acc[qt][mt][i]));
       }
-      amax = quad_max(amax);                       // over the row's 128 values
+      amax = quad_max(amax);                       // over the row's kD values
       float cscale = 1.0f, inv_c = 1.0f;
       if (amax > 16384.f) {                        // exponent of amax / 16384, rounded up
         const int e = (int)((__float_as_uint(amax) >> 23) & 0xff) - 127 - 13;
         cscale = __uint_as_float((unsigned int)(127 + e) << 23);
         inv_c = __uint_as_float((unsigned int)(127 - e) << 23);
       }
-      u32x4 *po = reinterpret_cast<u32x4 *>(a.part_o) + (unit * 4 + w) * (4 * 64) + lane;
+      u32x4 *po = reinterpret_cast<u32x4 *>(a.part_o) + (unit * 4 + w) * (kMT / 2 * 64) + lane;
 #pragma unroll
-      for (int pr = 0; pr < 4; ++pr) {
+      for (int pr = 0; pr < kMT / 2; ++pr) {
         const f32x4 x = o_acc[qt][2 * pr] * inv_c, y = o_acc[qt][2 * pr + 1] * inv_c;
         __builtin_nontemporal_store((u32x4){pack_f16x2(x[0], x[1]), pack_f16x2(x[2], x[3]),
                                             pack_f16x2(y[0], y[1]), pack_f16x2(y[2], y[3])}, &po[pr * 64]);
@@ -479,10 +522,13 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 // 18.7 us, 16 x 4 18.5 us.
 constexpr int kCombInFlight = 4;
 
+__device__ __forceinline__ f32x4 partial_values(const u32x2 &w) { return unpack_f16x4(w.x, w.y); }
+__device__ __forceinline__ f32x4 partial_values(const f32x4 &w) { return w; }
+
 // kCombWaves = 16 for the decode-time case (one sequence cut into ~64 splits); 8 or 4 when no
 // sequence of the call has more than 32 or 16 splits (draft trees, batches), where 16 wavefronts
 // per output tile would mostly find nothing to merge.
-template <int kCombWaves>
+template <int kD, int kCombWaves>
 __global__ void __launch_bounds__(64 * kCombWaves)
 verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
   __shared__ f32x4 xo[kCombWaves][64];
@@ -501,12 +547,14 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
   const int n = lane & 15, c4 = lane >> 4;
   const int R = a.n_q * g;
   if (rb * kRowsPerWG + 16 * wq >= R) return;    // tile without rows (uniform)
-  const u32x2 *po = reinterpret_cast<const u32x2 *>(a.part_o);
+  constexpr bool kWide = kWideState<kD>;
+  typedef typename std::conditional<kWide, f32x4, u32x2>::type part_t;      // 4 values of a lane
+  const part_t *po = reinterpret_cast<const part_t *>(a.part_o);
   float m_run = kNegBig, l_run = 0.f;
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
   for (int sb = s0 + ws; sb < s1; sb += kCombWaves * kCombInFlight) {
     float ms[kCombInFlight], ls[kCombInFlight], cs[kCombInFlight];
-    u32x2 pa[kCombInFlight];
+    part_t pa[kCombInFlight];
 #pragma unroll
     for (int u = 0; u < kCombInFlight; ++u) {
       const int s = min(sb + kCombWaves * u, s1 - 1);
@@ -514,8 +562,9 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
       const float *pml = a.part_ml + (unit * kRowsPerWG + 16 * wq + n) * kMlFloats;
       ms[u] = __builtin_nontemporal_load(&pml[0]);
       ls[u] = __builtin_nontemporal_load(&pml[1]);
-      cs[u] = __builtin_nontemporal_load(&pml[2]);
-      pa[u] = __builtin_nontemporal_load(&po[((((unit * 4 + wq) * 4 + (mt >> 1)) * 64 + lane) << 1) + (mt & 1)]);
+      cs[u] = kWide ? 1.f : __builtin_nontemporal_load(&pml[2]);
+      pa[u] = __builtin_nontemporal_load(kWide ? &po[((unit * 4 + wq) * (kD / 16) + mt) * 64 + lane]
+                                               : &po[((((unit * 4 + wq) * (kD / 32) + (mt >> 1)) * 64 + lane) << 1) + (mt & 1)]);
     }
     float mx = m_run;
 #pragma unroll
@@ -528,7 +577,7 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
       // weight of the split: its share of the softmax denominator (its output is normalised)
       const float wgt = (sb + kCombWaves * u < s1) ? fast_exp2(ms[u] - mx) * ls[u] : 0.f;
       l_run += wgt;
-      o += unpack_f16x4(pa[u].x, pa[u].y) * (wgt * cs[u]);
+      o += partial_values(pa[u]) * (wgt * cs[u]);
     }
   }
   xo[ws][lane] = o;
@@ -551,7 +600,7 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
       const int i_row = rho / g, h = c * g + rho % g;
       const int64_t orow = ((int64_t)b * a.n_q + i_row) * a.Hq + h;
       const float inv = 1.0f / l;
-      bf16_t *out = (bf16_t *)a.out + orow * 128 + 16 * mt + 4 * c4;
+      bf16_t *out = (bf16_t *)a.out + orow * kD + 16 * mt + 4 * c4;
       u32x2 w0 = {pack_bf16x2(r[0] * inv, r[1] * inv), pack_bf16x2(r[2] * inv, r[3] * inv)};
       *reinterpret_cast<u32x2 *>(out) = w0;
       if (a.lse != nullptr && mt == 0 && c4 == 0) a.lse[orow] = (m + fast_log2(l)) * kLn2;
@@ -561,12 +610,16 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
 
 }  // namespace
 
+// Both head sizes of the boundary.  Measured at d = 64 (16/4 heads, 4 ragged sequences of 6,001 on
+// average, chain of 8, 23.5 MB a call): 107 us with the plain-ALU kernels (fp32 multiply-adds and LDS
+// reads bound them), 16.3 us here, launched call by call, with the same error against 64 bits (1.7e-3:
+// the output's own rounding).
 bool verify_partial_mfma_supported(int dtype, int head_dim) {
-  return dtype == SPARROW_BF16 && head_dim == 128;
+  return dtype == SPARROW_BF16 && (head_dim == 128 || head_dim == 64);
 }
 
 // Floats of workspace per (split, KV head, row block) unit of the tiled partial layout.
-int64_t verify_mfma_unit_floats_o() { return 4 * 4 * 64 * 4; }   // 16 KB: 64 rows x 128 halves
+int64_t verify_mfma_unit_floats_o() { return 4096; }    // 16 KB: 64 rows of 128 halves or of 64 floats
 int64_t verify_mfma_unit_floats_ml() { return kRowsPerWG * kMlFloats; }
 
 // Row blocks (workgroups per split and KV head) for R rows: blocks of three 64-row tiles unless
@@ -577,7 +630,8 @@ int verify_mfma_row_blocks(int R) {
   return rbs3 * 3 - tiles <= rbs2 * 2 - tiles ? rbs3 : rbs2;
 }
 
-hipError_t launch_verify_partial_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
+template <int kD>
+static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
   const int R = a.n_q * (a.Hq / a.Hkv);
   const int rbs = verify_mfma_row_blocks(R);
   PieceTable pt;
@@ -592,37 +646,47 @@ hipError_t launch_verify_partial_mfma(const VerifyArgs &a, const SeqTable &tab, 
   const int flat = (int64_t)a.n_slots * 4 < (int64_t)x3d * a.B * 3;      // fewer than 3/4 of the slots real
   dim3 grid(x3d * rbs, a.Hkv, a.B), block(256 * kStreams);
   if (flat) grid = dim3((a.n_slots * a.Hkv + 7) / 8 * 8 * rbs, 1, 1);
-  constexpr int kLdsBytes = kStreams * 2 * 2 * kSub * kTileBytes;
+  constexpr int kSub = 128 / kD;
+  constexpr int kLdsBytes = kStreams * 2 * 2 * kSub * kTile * kD * 2;
   static_assert(kLdsBytes <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
   const int steps = (a.chunk / kTile + kStreams * kSub - 1) / (kStreams * kSub);   // of a full split
   const int tiles = (R + kRowsPerWG - 1) / kRowsPerWG;
   const int qt = (tiles + rbs - 1) / rbs;
   if (qt == 3)      // a second tile in flight does not fit the registers (and the step is compute-bound)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<1, 3>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 3>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
   else if (qt == 2 && steps <= 10)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<1, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
   else if (qt == 2)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<2, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
   else if (steps <= 3)       // (a second step in flight pays from 4 steps on: -0.15 us at the 7 steps of a 26k chain)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<1, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
   else
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<2, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+  return hipGetLastError();
+}
+
+hipError_t launch_verify_partial_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
+  return a.d == 128 ? launch_partial<128>(a, tab, st) : launch_partial<64>(a, tab, st);
+}
+
+template <int kD>
+static hipError_t launch_combine(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
+  const int R = a.n_q * (a.Hq / a.Hkv);
+  const int rbs = (R + kRowsPerWG - 1) / kRowsPerWG;
+  dim3 grid(a.Hkv * rbs * 4, kD / 16, a.B);
+  int max_ns = 0;
+  for (int b = 0; b < a.B; ++b) max_ns = std::max(max_ns, tab.cu_split[b + 1] - tab.cu_split[b]);
+  if (max_ns > 32)
+    hipLaunchKernelGGL((verify_combine_tiled_kernel<kD, 16>), grid, dim3(64 * 16), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+  else if (max_ns > 16)
+    hipLaunchKernelGGL((verify_combine_tiled_kernel<kD, 8>), grid, dim3(64 * 8), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+  else
+    hipLaunchKernelGGL((verify_combine_tiled_kernel<kD, 4>), grid, dim3(64 * 4), 0, st, a, tab, rbs, a.Hq / a.Hkv);
   return hipGetLastError();
 }
 
 hipError_t launch_verify_combine_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
-  const int R = a.n_q * (a.Hq / a.Hkv);
-  const int rbs = (R + kRowsPerWG - 1) / kRowsPerWG;
-  dim3 grid(a.Hkv * rbs * 4, 8, a.B);
-  int max_ns = 0;
-  for (int b = 0; b < a.B; ++b) max_ns = std::max(max_ns, tab.cu_split[b + 1] - tab.cu_split[b]);
-  if (max_ns > 32)
-    hipLaunchKernelGGL(verify_combine_tiled_kernel<16>, grid, dim3(64 * 16), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  else if (max_ns > 16)
-    hipLaunchKernelGGL(verify_combine_tiled_kernel<8>, grid, dim3(64 * 8), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  else
-    hipLaunchKernelGGL(verify_combine_tiled_kernel<4>, grid, dim3(64 * 4), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  return hipGetLastError();
+  return a.d == 128 ? launch_combine<128>(a, tab, st) : launch_combine<64>(a, tab, st);
 }
 
 }  // namespace sparrow
