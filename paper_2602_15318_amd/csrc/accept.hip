@@ -82,26 +82,26 @@ __global__ void __launch_bounds__(256) lm_head_generic_kernel(AcceptArgs a) {
   }
 }
 
-// One workgroup of 16 wavefronts: wavefront w reduces the candidates of rows w, w+16, ... (64 lanes
-// stride over the row's candidates, then a butterfly), then one thread per sequence walks the
-// chain / tree.
+// One workgroup of 16 wavefronts per sequence: wavefront w reduces the candidates of its rows w,
+// w+16, ... (64 lanes stride over the row's candidates, then a butterfly), then one thread walks the
+// sequence's chain / tree.  (One workgroup for all sequences took 18 us at 8 x 31 rows.)
 __global__ void __launch_bounds__(1024) accept_finalize_kernel(AcceptArgs a) {
-  __shared__ int32_t tgt[kAcceptMaxRows];
-  __shared__ int32_t dr_s[kAcceptMaxRows], par_s[kAcceptMaxRows];
-  const int tid = threadIdx.x;
+  __shared__ int32_t tgt[SPARROW_MAX_NQ + 1];
+  __shared__ int32_t dr_s[SPARROW_MAX_NQ], par_s[SPARROW_MAX_NQ];
+  const int tid = threadIdx.x, b = blockIdx.x;
   const int w = tid >> 6, lane = tid & 63;
-  // draft tokens and parents of every sequence into LDS while the candidates are being reduced:
+  const int n_rows = a.n_q + 1, base = b * n_rows;
+  // draft tokens and parents of the sequence into LDS while the candidates are being reduced:
   // the walk below is a chain of dependent reads and should not pay a memory round trip each
-  if (tid < a.B * a.n_q) {
-    const int j = tid % a.n_q, b = tid / a.n_q;
-    dr_s[tid] = a.draft_ids[tid];
-    par_s[tid] = a.parent ? a.parent[(int64_t)b * a.parent_stride + j] : j - 1;
+  if (tid < a.n_q) {
+    dr_s[tid] = a.draft_ids[b * a.n_q + tid];
+    par_s[tid] = a.parent ? a.parent[(int64_t)b * a.parent_stride + tid] : tid - 1;
   }
   // two rows per wavefront at a time (rows r and r + 16): their candidate loads are in flight
   // together, and the 64-lane argmax runs on the vector ALU (maximum, then the lowest index
   // among the lanes that hold it)
   constexpr int kU = 16;                                 // independent loads in flight per lane and row
-  for (int r0 = w; r0 < a.M; r0 += 32) {
+  for (int r0 = w; r0 < n_rows; r0 += 32) {
     float bv[2];
     int bi[2];
 #pragma unroll
@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(1024) accept_finalize_kernel(AcceptArgs a) {
       int i[2][kU];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int r = min(r0 + 16 * h, a.M - 1);         // the second row may not exist: a valid duplicate
+        const int r = base + min(r0 + 16 * h, n_rows - 1);   // the second row may not exist: a valid duplicate
         const float *cv = a.cand_val + (int64_t)r * a.n_cand;
         const int32_t *ci = a.cand_idx + (int64_t)r * a.n_cand;
 #pragma unroll
@@ -133,29 +133,26 @@ __global__ void __launch_bounds__(1024) accept_finalize_kernel(AcceptArgs a) {
       const int r = r0 + 16 * h;
       const float wv = wave_max_valu(bv[h]);
       const int wi = wave_min_valu(bv[h] == wv ? bi[h] : 0x7fffffff);
-      if (lane == 0 && r < a.M) { tgt[r] = wi; a.target_ids[r] = wi; }
+      if (lane == 0 && r < n_rows) { tgt[r] = wi; a.target_ids[base + r] = wi; }
     }
   }
   __syncthreads();
-  if (tid < a.B) {
-    const int b = tid;
-    const int32_t *t = tgt + b * (a.n_q + 1);
-    const int32_t *dr = dr_s + b * a.n_q, *par = par_s + b * a.n_q;
+  if (tid == 0) {
     int32_t *path = a.accept_path + (int64_t)b * a.n_q;
     int cur = -1, len = 0;
     // every accepted node has a larger index than its parent: at most n_q steps
     for (;;) {
-      const int tok = t[cur + 1];
+      const int tok = tgt[cur + 1];
       int next = -1;
       for (int j = cur + 1; j < a.n_q; ++j) {
-        if (par[j] == cur && dr[j] == tok) { next = j; break; }
+        if (par_s[j] == cur && dr_s[j] == tok) { next = j; break; }
       }
       if (next < 0) break;
       path[len++] = next;
       cur = next;
     }
     a.accept_len[b] = len;
-    a.bonus_id[b] = t[cur + 1];
+    a.bonus_id[b] = tgt[cur + 1];
     for (int j = len; j < a.n_q; ++j) path[j] = -1;
   }
 }
@@ -170,7 +167,7 @@ hipError_t launch_lm_head_generic(int dtype, const AcceptArgs &a, hipStream_t st
 }
 
 hipError_t launch_accept_finalize(const AcceptArgs &a, hipStream_t st) {
-  hipLaunchKernelGGL(accept_finalize_kernel, dim3(1), dim3(1024), 0, st, a);
+  hipLaunchKernelGGL(accept_finalize_kernel, dim3(a.B), dim3(1024), 0, st, a);
   return hipGetLastError();
 }
 

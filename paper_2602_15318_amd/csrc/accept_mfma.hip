@@ -1,20 +1,13 @@
 // Greedy acceptance, matrix-core lm_head pass: bf16, gfx950.
 //
 // logits[r, v] = sum_x hidden[r, x] * W[v, x] for the B*(n_q+1) verified rows r against the whole
-// vocabulary; 1.09 GB of weights for Qwen2.5-VL-7B, read exactly once, so the pass is bound by HBM
-// and organised around the weight stream:
-//   - one persistent workgroup (8 wavefronts) per compute unit; the 16 hidden rows of the current
-//     row block sit in LDS (XOR-swizzled 16-byte chunks) for the whole pass;
-//   - the vocabulary is cut into tiles of 16 rows, dealt round-robin to all wavefronts of the chip
-//     (at any moment the chip reads one contiguous region of W);
-//   - a wavefront streams its tile's rows straight from HBM into the A operand of
-//     v_mfma_f32_16x16x32_bf16 (lane = row + 16*kchunk: 16 rows x 64 contiguous bytes per load),
-//     16 loads (16 KB) in flight per wavefront, double buffered in registers; B = hidden^T from LDS;
-//   - logits never leave the registers: every lane keeps the best (value, lowest index) of the
-//     vocabulary rows it has seen for its column; one candidate per (wavefront, row) is written at
-//     the end and reduced by the finalize kernel.
-// More than 16 rows (trees, batches): the k-split kernel takes 32 rows per pass over W, the
-// fallback kernel 16.
+// vocabulary; 1.09 GB of weights for Qwen2.5-VL-7B, read exactly once per pass, so the pass is bound
+// by HBM and organised around the weight stream.  Logits never leave the registers unless the
+// caller needs them (sampling, top-k): every lane keeps the best (value, lowest index) of the
+// vocabulary rows it has seen for its column; one candidate per (workgroup, row) is written at the
+// end and reduced by the finalize kernel.
+#include <algorithm>
+
 #include "accept.hpp"
 #include "common.hpp"
 
@@ -22,139 +15,45 @@ namespace sparrow {
 
 namespace {
 
-constexpr int kLmWaves = 8;               // wavefronts per workgroup
-constexpr int kLmBlocks = 256;            // one workgroup per compute unit
-constexpr int kLmChunk = 16;              // k-steps (of 32 elements) per register buffer
-
-__global__ void __launch_bounds__(kLmWaves * 64)
-lm_head_mfma_kernel(AcceptArgs a, int row0) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char hid[];   // [16 rows][H] bf16, swizzled
-
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int n = lane & 15, c4 = lane >> 4;
-  const int H = a.H, V = a.V;
-  const int row_bytes = H * 2;
-  const int gw = blockIdx.x * kLmWaves + w;              // global wavefront = candidate slot
-  const int n_waves = gridDim.x * kLmWaves;
-  const int n_vt = (V + 15) / 16;                        // vocabulary tiles
-  const int my_tiles = n_vt > gw ? (n_vt - gw + n_waves - 1) / n_waves : 0;
-  const int chunks_per_tile = H / (32 * kLmChunk);
-  const int nq = my_tiles * chunks_per_tile;             // register-buffer chunks of this wavefront
-  const bf16_t *Wm = (const bf16_t *)a.lm_head;
-
-  // A-operand loads of chunk q: tile gw + (q / cpt) * n_waves, k-steps (q % cpt) * 16 .. +16.
-  // Unconditional (rows clamped to the last vocabulary row, chunk index clamped to the last chunk)
-  // so that the number of loads in flight is static.
-  auto issue = [&](int q, u32x4 *buf) {
-    const int qq = min(q, max(nq - 1, 0));
-    const int j = qq / chunks_per_tile, cidx = qq - j * chunks_per_tile;
-    const int v = min((gw + j * n_waves) * 16 + n, V - 1);
-    const bf16_t *p = Wm + (int64_t)v * H + cidx * (32 * kLmChunk) + 8 * c4;
-#pragma unroll
-    for (int s = 0; s < kLmChunk; ++s) buf[s] = __builtin_nontemporal_load((const u32x4 *)(p + 32 * s));
-  };
-  u32x4 bufA[kLmChunk], bufB[kLmChunk];
-  issue(0, bufA);
-
-  // hidden rows row0 .. row0+15 -> LDS (rows past M are zero)
-  {
-    const int cpr = H / 8;                               // 16-byte chunks per row
-    for (int e = tid; e < 16 * cpr; e += kLmWaves * 64) {
-      const int r = e / cpr, ch = e - r * cpr;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (row0 + r < a.M) v = *(const u32x4 *)((const bf16_t *)a.hidden + (int64_t)(row0 + r) * H + 8 * ch);
-      *reinterpret_cast<u32x4 *>(hid + r * row_bytes + (((ch & ~15) | ((ch & 15) ^ r)) << 4)) = v;
-    }
-  }
-  __syncthreads();
-
-  const unsigned char *hrow = hid + n * row_bytes;
-  float best = -INFINITY;
-  int best_i = 0x7fffffff;
-  f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-
-  auto compute = [&](int q, const u32x4 *buf) {
-    const int j = q / chunks_per_tile, cidx = q - j * chunks_per_tile;
-#pragma unroll
-    for (int s = 0; s < kLmChunk; s += 2) {
-      const int ch0 = 4 * (cidx * kLmChunk + s) + c4, ch1 = ch0 + 4;
-      const bf16x8 b0 = *reinterpret_cast<const bf16x8 *>(hrow + (((ch0 & ~15) | ((ch0 & 15) ^ n)) << 4));
-      const bf16x8 b1 = *reinterpret_cast<const bf16x8 *>(hrow + (((ch1 & ~15) | ((ch1 & 15) ^ n)) << 4));
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, buf[s]), b0, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, buf[s + 1]), b1, acc1, 0, 0, 0);
-    }
-    if (cidx == chunks_per_tile - 1) {     // tile finished: lane holds logits of rows 4*c4 + i, column n
-      const int vbase = (gw + j * n_waves) * 16 + 4 * c4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float lg = acc0[i] + acc1[i];
-        if (vbase + i < V && lg > best) { best = lg; best_i = vbase + i; }   // ascending: lowest wins
-        if (a.logits != nullptr && vbase + i < V && row0 + n < a.M)
-          a.logits[(int64_t)(row0 + n) * V + vbase + i] = lg;
-      }
-      acc0 = (f32x4){0.f, 0.f, 0.f, 0.f};
-      acc1 = (f32x4){0.f, 0.f, 0.f, 0.f};
-    }
-  };
-
-  for (int q = 0; q < nq; q += 2) {
-    issue(q + 1, bufB);
-    compute(q, bufA);
-    issue(q + 2, bufA);
-    if (q + 1 < nq) compute(q + 1, bufB);
-  }
-
-  // best over the four lanes of a column (lanes n, n+16, n+32, n+48): lowest index on equal value
-#pragma unroll
-  for (int o = 16; o <= 32; o <<= 1) {
-    const float ov = __shfl_xor(best, o, 64);
-    const int oi = __shfl_xor(best_i, o, 64);
-    if (ov > best || (ov == best && oi < best_i)) { best = ov; best_i = oi; }
-  }
-  if (c4 == 0 && row0 + n < a.M) {
-    a.cand_val[(int64_t)(row0 + n) * a.n_cand + gw] = best;
-    a.cand_idx[(int64_t)(row0 + n) * a.n_cand + gw] = best_i;
-  }
-}
-
-
-// ------------------------------------------------------------------------------------------------
-// k-split version, used when hidden = NW * 512 with NW <= 16 (3584 -> 7 wavefronts): the fast path.
-//
-// A workgroup of NW wavefronts owns groups of 64 consecutive vocabulary rows (4 MFMA tiles);
-// wavefront w owns the k-slice [512 w, 512 w + 512) of every row: its slice of the 16 hidden rows
-// lives in registers for the whole pass (16 B operands), and every load instruction of the
-// wavefront reads 1 KB that is contiguous in memory (the slice of one weight row), so the
-// workgroup as a whole sweeps 448 KB of W front to back.  The 16-row tile goes registers -> LDS
-// (private 16 KB per wavefront, XOR swizzled) -> A operands.  The wavefronts' partial logits of a
-// group are summed through LDS; wavefront g < 4 then owns the argmax bookkeeping of tile g.
+constexpr int kNumCU = 256;
+constexpr int kKsSlice = 512;             // k elements of a wavefront's slice of a row (1 KB)
 constexpr int kKsGroup = 4;               // vocabulary tiles (of 16 rows) per group
+constexpr int kKsWaves = 8;               // most wavefronts of a workgroup
 
+// k-split kernel: any hidden size up to 8,192 that is a multiple of 8.
+//
+// A row is cut into slices of 512 elements (the last one may be short: its missing columns are read
+// as zeros by the bounds check of the buffer loads); the nw wavefronts of a workgroup own one slice
+// each (SPW = 2: two, w and w + nw).  The wavefront's slice of the 16 hidden rows lives in registers
+// for the whole pass (16 B operands), and every load instruction of the wavefront reads 1 KB that is
+// contiguous in memory (the slice of one weight row), so the workgroup sweeps W front to back.  The
+// 16-row tile goes registers -> LDS (private 16 KB per wavefront, XOR swizzled) -> A operands.  The
+// wavefronts' partial logits of a group of tiles are summed through LDS; wavefront g then owns the
+// argmax bookkeeping of tile g of the group.
+//
+// nw = ceil(H / 512) (half of it above 4,096); as many workgroups per compute unit as their 20 KB of
+// LDS per wavefront allow, so that 80 to 128 KB of weights are in flight per compute unit whatever
+// H is.
+//
 // NB = blocks of 16 hidden rows handled in one pass over W (1 or 2); the vocabulary group is
-// kKsGroup / NB tiles so that the partial logits held in registers stay at 16 per lane.
-// halves = 2 (33 to 64 hidden rows): ONE pass over W for two blocks of 32 rows.  The workgroups
-// form pairs that stream the same vocabulary tiles, one for rows row0 .. row0+31, the other for
-// rows row0+32 .. row0+63; the two of a pair have indices 8 apart, i.e. they run at the same time
-// on the same XCD (workgroups are handed to the 8 XCDs round-robin), so the second fetch of a
-// weight tile is served by that XCD's L2 and HBM still sees the weights once.  (Only the speed
-// depends on that placement.)
-template <int NW, int NB>
-__global__ void __launch_bounds__(NW * 64)
-lm_head_ksplit_kernel(AcceptArgs a, int row0_arg, int halves) {
-  const int half = halves == 2 ? ((int)blockIdx.x >> 3) & 1 : 0;
-  const int wg = halves == 2 ? ((int)blockIdx.x >> 4) * 8 + ((int)blockIdx.x & 7) : (int)blockIdx.x;
-  const int n_wg = (int)gridDim.x / halves;            // streams of vocabulary tiles
-  const int row0 = row0_arg + 32 * half;
+// kKsGroup / NB tiles so that the partial logits in LDS stay at 4 KB per wavefront.
+// Measured: 152,064 x 3584 at 9 rows 167 us with the finalize pass (6.5 TB/s); 64,003 x 2048 at 9
+// rows 49 us, 32 rows 55 us; 151,936 x 2560 120 us.
+template <int SPW, int NB>
+__global__ void __launch_bounds__(kKsWaves * 64)
+lm_head_ksplit_kernel(AcceptArgs a, int row0) {
+  const int wg = (int)blockIdx.x, n_wg = (int)gridDim.x;      // streams of vocabulary tiles
   constexpr int G = kKsGroup / NB;          // vocabulary tiles per group
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  // [NW][16 KB] staging, then [NW][G][64] f32x4 partial logits
+  // [nw][16 KB] staging, then [NB][nw][G][64] f32x4 partial logits
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = (int)blockDim.x >> 6;
   const int n = lane & 15, c4 = lane >> 4;
   const int H = a.H, V = a.V;
-  const bf16_t *Wm = (const bf16_t *)a.lm_head;
+  const unsigned int row_bytes = (unsigned int)H * 2u;
   unsigned char *stg = smem + w * 16384;
-  f32x4 *red = reinterpret_cast<f32x4 *>(smem + NW * 16384);
+  f32x4 *red = reinterpret_cast<f32x4 *>(smem + nw * 16384);
 
   // Vocabulary tiles (16 rows) are dealt round-robin to the workgroups one by one, so that the
   // workgroups' shares differ by at most one tile (9,504 tiles over 256 workgroups: 38 against a
@@ -166,36 +65,46 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0_arg, int halves) {
 
   // tile t of this workgroup -> first vocabulary row
   auto tile_row0 = [&](int t) { return (wg + t * n_wg) * 16; };
-  // 16 loads of 1 KB: load r = the k-slice of row r of the tile (rows clamped to the last row).
-  // Issued unconditionally (tile index clamped) so that the number of loads in flight is static.
-  // one tile (16 KB per wavefront, 112 KB per compute unit) in flight: the weight stream already
-  // saturates HBM with that, a second tile in flight measured 2 us slower
-  constexpr int kBufs = 1;
-  u32x4 buf[kBufs][16];
-  auto issue = [&](int t, u32x4 *bp) {
-    const int v0 = tile_row0(min(t, max(n_tiles - 1, 0)));
+  // 16 loads of 1 KB: load r = the k-slice of row r of the tile (rows clamped to the last row), as
+  // buffer loads from the tile's first row: columns past H get an offset past the buffer's end and
+  // read as zero.  Issued unconditionally (tile index clamped) so that the number of loads in
+  // flight is static.  One tile (16 KB per wavefront) in flight: the weight stream already
+  // saturates HBM with that, a second tile in flight measured 2 us slower at H = 3584.
+  constexpr unsigned int kPastEnd = 0x80000000u;
+  unsigned int col_off[SPW];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int v = min(v0 + r, V - 1);
-      bp[r] = __builtin_nontemporal_load((const u32x4 *)(Wm + (int64_t)v * H + 512 * w + 8 * lane));
-    }
+  for (int sl = 0; sl < SPW; ++sl) {
+    const int k = kKsSlice * (w + sl * nw) + 8 * lane;
+    col_off[sl] = k < H ? (unsigned int)k * 2u : kPastEnd;
+  }
+  u32x4 buf[16];
+  auto issue = [&](int t, int sl) {
+    const int v0 = tile_row0(min(t, max(n_tiles - 1, 0)));
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const unsigned char *)a.lm_head + (int64_t)min(v0, V - 1) * row_bytes), (short)0, (int)0x7fffffff, 0x00027000);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      buf[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, col_off[sl], max(min(r, V - 1 - v0), 0) * row_bytes, 2);
   };
-  issue(0, buf[0]);
-  if (kBufs == 2) issue(1, buf[1]);
+  issue(0, 0);
 
-  // B operands: lane (n, c4) holds hidden[row0 + 16 nb + n][512 w + 32 ks + 8 c4 .. +8], ks = 0..15
-  bf16x8 hreg[NB][16];
+  // B operands: lane (n, c4) holds hidden[row0 + 16 nb + n][slice + 32 ks + 8 c4 .. +8], ks = 0..15
+  bf16x8 hreg[NB][SPW][16];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int row = row0 + 16 * nb + n;
     const bool ok = row < a.M;
-    // Rows past M (padding of the last block) take the data of valid rows, row % M: their results
-    // are never stored, and every lane then fetches a row of its own -- the paired workgroups of
-    // the 33-to-64-row pass keep in step only if their prologues take the same time (with all
-    // padding lanes on one row the pass took 330 us at 33 rows, with this 229 us)
-    const bf16_t *hp = (const bf16_t *)a.hidden + (int64_t)(ok ? row : row % a.M) * H + 512 * w + 8 * c4;
+    // rows past M (padding of the last block) take the data of valid rows: never stored
+    const bf16_t *hp = (const bf16_t *)a.hidden + (int64_t)(ok ? row : row % a.M) * H;
 #pragma unroll
-    for (int ks = 0; ks < 16; ++ks) hreg[nb][ks] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(hp + 32 * ks));
+    for (int sl = 0; sl < SPW; ++sl)
+#pragma unroll
+      for (int ks = 0; ks < 16; ++ks) {
+        const int k = kKsSlice * (w + sl * nw) + 32 * ks + 8 * c4;
+        u32x4 h = {0u, 0u, 0u, 0u};
+        if (k < H) h = *(const u32x4 *)(hp + k);
+        hreg[nb][sl][ks] = __builtin_bit_cast(bf16x8, h);
+      }
   }
 
   // staging: lane i of load r holds chunk i (16 bytes) of row r; stored at chunk position
@@ -205,11 +114,7 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0_arg, int halves) {
   int best_i[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) { best[nb] = -INFINITY; best_i[nb] = 0x7fffffff; }
-  auto tile_step = [&](int t, u32x4 *bp) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      *reinterpret_cast<u32x4 *>(stg + r * 1024 + (((lane & ~15) | ((lane & 15) ^ r)) << 4)) = bp[r];
-    issue(t + kBufs, bp);
+  for (int t = 0; t < n_tiles; ++t) {
     f32x4 acc[NB][2];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
@@ -217,32 +122,38 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0_arg, int halves) {
       acc[nb][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
-    for (int ks = 0; ks < 16; ks += 2) {
-      const int ch0 = 4 * ks + c4, ch1 = ch0 + 4;
-      const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch0 & ~15) | ((ch0 & 15) ^ n)) << 4));
-      const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch1 & ~15) | ((ch1 & 15) ^ n)) << 4));
+    for (int sl = 0; sl < SPW; ++sl) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        acc[nb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, hreg[nb][ks], acc[nb][0], 0, 0, 0);
-        acc[nb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, hreg[nb][ks + 1], acc[nb][1], 0, 0, 0);
+      for (int r = 0; r < 16; ++r)
+        *reinterpret_cast<u32x4 *>(stg + r * 1024 + (((lane & ~15) | ((lane & 15) ^ r)) << 4)) = buf[r];
+      issue(sl + 1 < SPW ? t : t + 1, sl + 1 < SPW ? sl + 1 : 0);
+#pragma unroll
+      for (int ks = 0; ks < 16; ks += 2) {
+        const int ch0 = 4 * ks + c4, ch1 = ch0 + 4;
+        const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch0 & ~15) | ((ch0 & 15) ^ n)) << 4));
+        const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch1 & ~15) | ((ch1 & 15) ^ n)) << 4));
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          acc[nb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, hreg[nb][sl][ks], acc[nb][0], 0, 0, 0);
+          acc[nb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, hreg[nb][sl][ks + 1], acc[nb][1], 0, 0, 0);
+        }
       }
     }
     const int g = t % G;
     // the tile's partial logits go to LDS at once ([row block][wavefront][tile of the group]: G * NB
     // = 4 slots per wavefront whatever NB), not into registers held for the whole group
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) red[((nb * NW + w) * G + g) * 64 + lane] = acc[nb][0] + acc[nb][1];
+    for (int nb = 0; nb < NB; ++nb) red[((nb * nw + w) * G + g) * 64 + lane] = acc[nb][0] + acc[nb][1];
     if (g == G - 1 || t == n_tiles - 1) {     // uniform over the workgroup
-      // sum the group's partial logits over the wavefronts; wavefront w <= g takes tile w of the
-      // group (the last group may hold fewer than G tiles)
+      // sum the group's partial logits over the wavefronts; the tiles of the group (the last group
+      // may hold fewer than G) are dealt to the wavefronts
       __syncthreads();
-      if (w <= g) {
-        const int vbase = tile_row0(t - g + w) + 4 * c4;
+      for (int tg = w; tg <= g; tg += nw) {
+        const int vbase = tile_row0(t - g + tg) + 4 * c4;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          f32x4 sum = red[((nb * NW + 0) * G + w) * 64 + lane];
-#pragma unroll
-          for (int ww = 1; ww < NW; ++ww) sum += red[((nb * NW + ww) * G + w) * 64 + lane];
+          f32x4 sum = red[((nb * nw + 0) * G + tg) * 64 + lane];
+          for (int ww = 1; ww < nw; ++ww) sum += red[((nb * nw + ww) * G + tg) * 64 + lane];
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (vbase + i < V && sum[i] > best[nb]) { best[nb] = sum[i]; best_i[nb] = vbase + i; }
@@ -256,97 +167,281 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0_arg, int halves) {
       }
       __syncthreads();   // reads done before the next partials are written
     }
-  };
-  // (unrolled by the number of register buffers so that each step names its own)
-  for (int t = 0; t < n_tiles; t += kBufs) {
-    tile_step(t, buf[0]);
-    if (kBufs == 2 && t + 1 < n_tiles) tile_step(t + 1, buf[kBufs - 1]);
   }
 
-  // a pair's workgroup leaves neutral candidates for the rows of the other half in its slots
-  if (halves == 2) {
-    const int other0 = row0_arg + 32 * (1 - half);
-    for (int e = tid; e < 32 * kKsGroup; e += NW * 64) {
-      const int row = other0 + e / kKsGroup;
-      if (row < a.M) {
-        const int slot = blockIdx.x * kKsGroup + e % kKsGroup;
-        a.cand_val[(int64_t)row * a.n_cand + slot] = -INFINITY;
-        a.cand_idx[(int64_t)row * a.n_cand + slot] = 0x7fffffff;
-      }
+  // one candidate per (workgroup, row): best over the four lanes of a column, then over the
+  // wavefronts through LDS (all partial logits have been read: the loop ends with a barrier)
+  float *cv = reinterpret_cast<float *>(red);                     // [nw][NB][16]
+  int *ci = reinterpret_cast<int *>(cv + nw * NB * 16);
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    float bv = best[nb];
+    int bi = best_i[nb];
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      const float ov = __shfl_xor(bv, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
     }
+    if (c4 == 0) { cv[(w * NB + nb) * 16 + n] = bv; ci[(w * NB + nb) * 16 + n] = bi; }
   }
-  // candidates: wavefronts 0..G-1 hold, per lane, the best of tiles g = w over all groups; the
-  // workgroup always fills kKsGroup candidate slots (the others stay at -inf)
-  if (w < kKsGroup) {
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      float bv = best[nb];
-      int bi = best_i[nb];
-#pragma unroll
-      for (int o = 16; o <= 32; o <<= 1) {
-        const float ov = __shfl_xor(bv, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-      }
-      const int row = row0 + 16 * nb + n;
-      if (c4 == 0 && row < a.M) {
-        const int slot = blockIdx.x * kKsGroup + w;
-        a.cand_val[(int64_t)row * a.n_cand + slot] = bv;
-        a.cand_idx[(int64_t)row * a.n_cand + slot] = bi;
-      }
+  __syncthreads();
+  if (tid < 16 * NB && row0 + tid < a.M) {
+    float bv = cv[tid];
+    int bi = ci[tid];
+    for (int ww = 1; ww < nw; ++ww) {
+      const float ov = cv[ww * NB * 16 + tid];
+      const int oi = ci[ww * NB * 16 + tid];
+      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
     }
+    a.cand_val[(int64_t)(row0 + tid) * a.n_cand + blockIdx.x] = bv;
+    a.cand_idx[(int64_t)(row0 + tid) * a.n_cand + blockIdx.x] = bi;
   }
 }
 
-template <int NW, int NB>
-hipError_t launch_ksplit_nb(const AcceptArgs &a, int row0, int halves, hipStream_t st) {
-  const int lds = NW * 16384 + NW * kKsGroup * 64 * 16;
-  static const hipError_t attr = hipFuncSetAttribute(
-      (const void *)lm_head_ksplit_kernel<NW, NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+int ksplit_waves(int H) {
+  const int slices = (H + kKsSlice - 1) / kKsSlice;
+  return slices <= kKsWaves ? slices : (slices + 1) / 2;
+}
+int ksplit_lds(int nw) { return nw * (16384 + kKsGroup * 64 * 16); }
+
+// Workgroups of a pass = candidates per row: as many as fit the compute units (160 KB of LDS, eight
+// wavefronts each), and no more than there are vocabulary tiles.
+int ksplit_grid(int H, int V) {
+  const int nw = ksplit_waves(H);
+  const int per_cu = std::min(160 * 1024 / ksplit_lds(nw), kKsWaves / nw);
+  const int tiles = (V + 15) / 16;
+  return std::min(kNumCU * per_cu, tiles);
+}
+
+template <int SPW, int NB>
+hipError_t launch_ksplit(const AcceptArgs &a, int row0, hipStream_t st) {
+  static const hipError_t attr = hipFuncSetAttribute((const void *)lm_head_ksplit_kernel<SPW, NB>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, ksplit_lds(kKsWaves));
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((lm_head_ksplit_kernel<NW, NB>), dim3(kLmBlocks), dim3(NW * 64), lds, st, a, row0, halves);
+  const int nw = ksplit_waves(a.H);
+  hipLaunchKernelGGL((lm_head_ksplit_kernel<SPW, NB>), dim3(a.n_cand), dim3(nw * 64), ksplit_lds(nw), st, a, row0);
   return hipGetLastError();
 }
 
-// One pass over W per 64 hidden rows by paired workgroups while more than 32 rows are left, then
-// one pass for the last 17 to 32 rows, or for the last 16 or fewer.
-template <int NW>
-hipError_t launch_ksplit(const AcceptArgs &a, hipStream_t st) {
-  for (int row0 = 0; row0 < a.M;) {
-    const int left = a.M - row0;
-    hipError_t e;
-    if (left > 32) { e = launch_ksplit_nb<NW, 2>(a, row0, 2, st); row0 += 64; }
-    else if (left > 16) { e = launch_ksplit_nb<NW, 2>(a, row0, 1, st); row0 += 32; }
-    else { e = launch_ksplit_nb<NW, 1>(a, row0, 1, st); row0 += 16; }
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+// ------------------------------------------------------------------------------------------------
+// Tiled kernel for more than 32 hidden rows (draft trees, batches): one pass over W whatever the
+// number of rows up to 256, two row blocks side by side above.
+//
+// A persistent workgroup of 4 wavefronts owns tiles of 128 vocabulary rows x BM hidden rows and walks
+// the hidden size in steps of BK; the wavefronts form a WV x WM grid.  Both operands of a step travel
+// memory -> registers (requested one step ahead) -> LDS (rows of 2 BK bytes, 16-byte chunks
+// XOR-swizzled as in the attention kernel) -> MFMA operands.  The LDS tile is single-buffered: two or
+// three workgroups share a compute unit, and one's MFMAs run under the other's loads and LDS traffic
+// (one workgroup of 8 wavefronts with two buffers and up to 4 steps in flight, whose phases do not
+// overlap: 401 us at 248 rows against 355).  Rows past V or M and columns past H come back as zeros
+// from the bounds check of the buffer loads, so no size has to be a multiple of anything.
+// Steps of 128 (256 contiguous bytes of a weight row) serve up to 128 rows, where the weight stream
+// is the bound; at 256 rows LDS and matrix cores are, and steps of 64 keep two workgroups on a
+// compute unit.  152,064 x 3584 with the finalize pass, against passes of 64 rows by pairs of k-split
+// workgroups: 33 rows 182 (229) us, 64 rows 185 (225), 128 rows 233 (430), 248 rows 355 (834).
+constexpr int kGmV = 128;                 // vocabulary rows of a tile
+constexpr int kGmWaves = 4;
+
+template <int BK> __device__ __forceinline__ int gm_swz(int row) {
+  return BK == 128 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
 }
 
-bool ksplit_ok(int H) { return H == 3584 || H == 4096; }
+template <int BM, int WV, int BK>
+__global__ void __launch_bounds__(kGmWaves * 64, 2)
+lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
+  constexpr int WM = kGmWaves / WV;
+  constexpr int NV = kGmV / WV / 16, NM = BM / WM / 16;      // 16-row tiles of a wavefront
+  constexpr int kRow = BK * 2, kChunks = BK / 8;             // bytes and 16-byte chunks of a row of a step
+  constexpr int kLdRows = kGmWaves * 64 / kChunks;                      // rows that one load of the workgroup covers
+  constexpr int kLdV = kGmV / kLdRows, kLdM = BM / kLdRows;  // loads of a thread per step
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wv = w / WM, wm = w % WM;
+  const int n = lane & 15, c4 = lane >> 4;
+  const int H = a.H, V = a.V;
+  const unsigned int row_bytes = (unsigned int)H * 2u;
+  // workgroups of one vocabulary stream (the row blocks) sit 8 indices apart: one XCD, one time
+  const int mb = ((int)blockIdx.x >> 3) % blocks_m;
+  const int stream = ((int)blockIdx.x >> 3) / blocks_m * 8 + ((int)blockIdx.x & 7);
+  const int n_streams = (int)gridDim.x / blocks_m;
+  const int row0 = mb * BM;
+  const int n_vt = (V + kGmV - 1) / kGmV;
+  const int n_tiles = n_vt > stream ? (n_vt - stream + n_streams - 1) / n_streams : 0;
+  const int nk = (H + BK - 1) / BK;
+  const int n_steps = n_tiles * nk;
+
+  // loader: thread -> rows tid/8 + 64 j, 16-byte chunk tid%8 of the step's 128 bytes of a row
+  const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
+  const unsigned int ld_off = (unsigned int)ld_row * row_bytes + (unsigned int)ld_ch * 16u;
+  const __amdgpu_buffer_rsrc_t rs_m = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((const unsigned char *)a.hidden + (int64_t)row0 * row_bytes), (short)0,
+      (int)(min(BM, a.M - row0) * row_bytes), 0x00027000);
+  u32x4 sg[kLdV + kLdM];
+  int is_tile = 0, is_k = 0;                                 // the step the next issue() fetches
+  auto issue = [&]() {
+    const int v0 = (stream + min(is_tile, max(n_tiles - 1, 0)) * n_streams) * kGmV;
+    const int rows = min(kGmV, max(V - v0, 0));
+    const __amdgpu_buffer_rsrc_t rs_v = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const unsigned char *)a.lm_head + (int64_t)min(v0, V - 1) * row_bytes), (short)0,
+        (int)(rows * row_bytes), 0x00027000);
+    const int k = is_k * BK + ld_ch * 8;
+    const unsigned int off = k < H ? ld_off + (unsigned int)is_k * (BK * 2) : 0x80000000u;
+#pragma unroll
+    for (int j = 0; j < kLdV; ++j)
+      sg[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_v, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 2);
+#pragma unroll
+    for (int j = 0; j < kLdM; ++j)
+      sg[kLdV + j] = __builtin_amdgcn_raw_buffer_load_b128(rs_m, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 0);
+    if (++is_k == nk) { is_k = 0; ++is_tile; }
+  };
+  const int st_off = ld_row * kRow + ((ld_ch ^ gm_swz<BK>(ld_row)) << 4);
+  auto stash = [&]() {
+    unsigned char *p = smem + st_off;
+#pragma unroll
+    for (int j = 0; j < kLdV + kLdM; ++j) *reinterpret_cast<u32x4 *>(p + kLdRows * j * kRow) = sg[j];
+  };
+
+  f32x4 acc[NV][NM];
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+#pragma unroll
+    for (int j = 0; j < NM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  float best[NM];
+  int best_i[NM];
+#pragma unroll
+  for (int j = 0; j < NM; ++j) { best[j] = -INFINITY; best_i[j] = 0x7fffffff; }
+  const int m_wave = row0 + wm * (NM * 16);                  // first hidden row of the wavefront
+  const bool live = m_wave < a.M;                            // a wavefront of padding rows only loads
+  const int rd_row = n * kRow, rd_swz = gm_swz<BK>(n);
+
+  int cp_tile = 0, cp_k = 0;
+  // One step: the operands of this step out of buffer `buf`, then (their latency covered) the next
+  // step's tiles out of the staging registers into the other buffer, then the MFMAs.
+  auto compute = [&]() {
+    if (live) {
+      const unsigned char *pv = smem + wv * (NV * 16 * kRow) + rd_row;
+      const unsigned char *pm = smem + (kGmV + wm * (NM * 16)) * kRow + rd_row;
+#pragma unroll
+      for (int ks = 0; ks < BK / 32; ++ks) {
+        const int ch = ((4 * ks + c4) ^ rd_swz) << 4;
+        bf16x8 av[NV], bm[NM];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) av[i] = *reinterpret_cast<const bf16x8 *>(pv + i * 16 * kRow + ch);
+#pragma unroll
+        for (int j = 0; j < NM; ++j) bm[j] = *reinterpret_cast<const bf16x8 *>(pm + j * 16 * kRow + ch);
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int j = 0; j < NM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bm[j], acc[i][j], 0, 0, 0);
+      }
+    }
+    if (++cp_k == nk) {                                      // tile finished
+      if (live) {
+        const int v0 = (stream + cp_tile * n_streams) * kGmV + wv * (NV * 16) + 4 * c4;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          const int vbase = v0 + 16 * i;
+#pragma unroll
+          for (int j = 0; j < NM; ++j) {
+            const int row = m_wave + 16 * j + n;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float lg = acc[i][j][e];
+              if (vbase + e < V && lg > best[j]) { best[j] = lg; best_i[j] = vbase + e; }   // ascending: lowest wins
+              if (a.logits != nullptr && vbase + e < V && row < a.M) a.logits[(int64_t)row * V + vbase + e] = lg;
+            }
+            acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+          }
+        }
+      }
+      cp_k = 0;
+      ++cp_tile;
+    }
+  };
+
+  issue();
+  for (int s = 0; s < n_steps; ++s) {
+    stash();
+    __syncthreads();
+    issue();
+    compute();
+    __syncthreads();
+  }
+
+  // one candidate per (workgroup, row): the four lanes of a column, then the WV wavefronts of a row
+  __syncthreads();
+  float *cv = reinterpret_cast<float *>(smem);               // [WV][BM]
+  int *ci = reinterpret_cast<int *>(smem + WV * BM * 4);
+#pragma unroll
+  for (int j = 0; j < NM; ++j) {
+    float bv = best[j];
+    int bi = best_i[j];
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      const float ov = __shfl_xor(bv, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    }
+    if (c4 == 0) { cv[wv * BM + wm * (NM * 16) + 16 * j + n] = bv; ci[wv * BM + wm * (NM * 16) + 16 * j + n] = bi; }
+  }
+  __syncthreads();
+  for (int r = tid; r < blocks_m * BM && r < a.M; r += kGmWaves * 64) {
+    float bv = -INFINITY;                                    // rows of the other block: a neutral candidate
+    int bi = 0x7fffffff;
+    if (r >= row0 && r < row0 + BM) {
+      for (int x = 0; x < WV; ++x) {
+        const float ov = cv[x * BM + r - row0];
+        const int oi = ci[x * BM + r - row0];
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+      }
+    }
+    a.cand_val[(int64_t)r * a.n_cand + blockIdx.x] = bv;
+    a.cand_idx[(int64_t)r * a.n_cand + blockIdx.x] = bi;
+  }
+}
+
+template <int BM, int WV, int BK>
+hipError_t launch_tiled(const AcceptArgs &a, hipStream_t st) {
+  constexpr int lds = (kGmV + BM) * BK * 2;
+  static_assert(lds <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
+  hipLaunchKernelGGL((lm_head_tiled_kernel<BM, WV, BK>), dim3(a.n_cand), dim3(kGmWaves * 64), lds, st, a, (a.M + BM - 1) / BM);
+  return hipGetLastError();
+}
+
+// Workgroups of the tiled kernel: two per compute unit (three at 64 rows, where registers and LDS
+// allow it), fewer if there are fewer tiles; a multiple of 8 per row block.
+int tiled_grid(int M, int V) {
+  const int blocks_m = (M + 255) / 256;
+  const int tiles = (V + kGmV - 1) / kGmV;
+  return std::min(kNumCU * (M > 64 ? 2 : 3), (tiles + 7) / 8 * 8 * blocks_m);
+}
+// Up to here the k-split kernel, whose hidden rows sit in registers: at 32 rows 169 us against 182.
+constexpr int kKsMaxRows = 32;
 
 }  // namespace
 
 bool lm_head_mfma_supported(int dtype, int M, int H, int V) {
   (void)M; (void)V;
-  // rows of W must split into whole register chunks, and the 16 hidden rows must fit in LDS
-  return dtype == SPARROW_BF16 && H % (32 * kLmChunk) == 0 && 16 * H * 2 <= 144 * 1024;
+  return dtype == SPARROW_BF16 && H % 8 == 0 && H <= 2 * kKsWaves * kKsSlice;     // two slices per wavefront
 }
 
-int accept_num_candidates(int, int, int H, int) {
-  return ksplit_ok(H) ? kLmBlocks * kKsGroup : kLmBlocks * kLmWaves;
-}
+int accept_num_candidates(int, int M, int H, int V) { return M > kKsMaxRows ? tiled_grid(M, V) : ksplit_grid(H, V); }
 
+// Up to 32 rows: one pass over W per 32 rows, or 16.  Above 4,096 the hidden rows of a wavefront's two
+// slices fill its registers at 16 rows: passes of 16.
 hipError_t launch_lm_head_mfma(const AcceptArgs &a, hipStream_t st) {
-  if (a.H == 3584) return launch_ksplit<7>(a, st);
-  if (a.H == 4096) return launch_ksplit<8>(a, st);
-  const int lds = 16 * a.H * 2;
-  static const hipError_t attr = hipFuncSetAttribute(
-      (const void *)lm_head_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
-  if (attr != hipSuccess) return attr;
-  for (int row0 = 0; row0 < a.M; row0 += 16) {
-    hipLaunchKernelGGL(lm_head_mfma_kernel, dim3(kLmBlocks), dim3(kLmWaves * 64), lds, st, a, row0);
-    hipError_t e = hipGetLastError();
+  if (a.M > 128) return launch_tiled<256, 1, 64>(a, st);
+  if (a.M > 64) return launch_tiled<128, 2, 128>(a, st);
+  if (a.M > kKsMaxRows) return launch_tiled<64, 2, 128>(a, st);
+  const bool wide = a.H > kKsWaves * kKsSlice;
+  for (int row0 = 0; row0 < a.M;) {
+    const int left = a.M - row0;
+    hipError_t e;
+    if (wide) { e = launch_ksplit<2, 1>(a, row0, st); row0 += 16; }
+    else if (left > 16) { e = launch_ksplit<1, 2>(a, row0, st); row0 += 32; }
+    else { e = launch_ksplit<1, 1>(a, row0, st); row0 += 16; }
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -1,0 +1,79 @@
+"""lm_head on the matrix cores for hidden sizes around the 512-element slice of a wavefront (8 to
+8,192, short last slices), row counts around the row blocks of a pass and vocabularies around the
+16-row tile: target tokens and top-k log-probabilities against a plain fp64 product."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sp():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2602_15318_amd as sp_
+    return sp_
+
+
+def _check(sp, H, V, M, seed):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    W = (torch.randn(V, H, generator=g, device="cuda") * H ** -0.5).to(torch.bfloat16)
+    hid = (torch.randn(M, H, generator=g, device="cuda") * 2.0).to(torch.bfloat16)
+    logits = hid.double() @ W.double().t()
+    # fp32 sums of H products: a random walk of H roundings of 2^-24, far below 64 * 2^-24 of the
+    # largest possible partial sum |hid| . |W|
+    tol = 64 * 2.0 ** -24 * float((hid.double().abs() @ W.double().abs().t()).max())
+    drafts = torch.zeros(M - 1, dtype=torch.int32, device="cuda")
+    if M <= 65:
+        got = sp.accept(hid, W, drafts, None, 1, M - 1)["target_ids"].long()
+    else:
+        # more rows than one sequence has: M sequences without draft rows
+        got = sp.accept(hid, W, drafts[:0], None, M, 0)["target_ids"].long()
+    assert int(got.min()) >= 0 and int(got.max()) < V
+    best = logits.max(dim=1).values
+    picked = logits.gather(1, got[:, None])[:, 0]
+    assert torch.all(best - picked <= 2 * tol), "a token that is not the row's best"
+    top = torch.topk(logits, min(2, V), dim=1).values
+    clear = (top[:, 0] - top[:, -1] > 2 * tol) if V > 1 else torch.ones(M, dtype=torch.bool, device="cuda")
+    assert torch.equal(got[clear], logits.argmax(dim=1)[clear])
+    k = min(4, V)
+    ids, logp = sp.draft_topk(hid, W, k)
+    ref = torch.topk(torch.log_softmax(logits, dim=1), k, dim=1).values
+    assert float((logp.double() - ref).abs().max()) <= 2 * tol + 2e-6
+    assert float((torch.log_softmax(logits, dim=1).gather(1, ids.long()) - ref).abs().max()) <= 2 * tol
+
+
+@pytest.mark.parametrize("H", [8, 264, 512, 520, 1016, 1536, 2048, 2560, 3072, 4096, 4104, 5120, 8192])
+@pytest.mark.parametrize("M,V", [(1, 5003), (17, 777), (33, 4096), (64, 15), (65, 2049)])
+def test_hidden_sizes(sp, H, V, M):
+    _check(sp, H, V, M, H + V + M)
+
+
+@pytest.mark.parametrize("H,V,M", [(3584, 152064, 9), (2048, 64003, 36), (2560, 32000, 16), (1024, 40000, 64)])
+def test_whole_vocabularies(sp, H, V, M):
+    _check(sp, H, V, M, 7)
+
+
+@pytest.mark.parametrize("H", [64, 328, 2048, 4104])
+@pytest.mark.parametrize("M,V", [(128, 130), (129, 5003), (256, 128), (257, 1000), (300, 4099), (512, 777)])
+def test_many_rows(sp, H, V, M):
+    _check(sp, H, V, M, H + V + M)
+
+
+def test_wider_than_the_matrix_core_kernels(sp):
+    _check(sp, 8704, 300, 3, 1)
+
+
+@pytest.mark.parametrize("H", [520, 5120])
+def test_columns_past_the_width_do_not_reach_the_result(sp, H):
+    """The last slice of a row is short: what lies behind the row in memory (the next row, here an
+    infinite one; other tensors behind the last row) must not leak into the sums."""
+    import torch
+    W = torch.ones(40, H, dtype=torch.bfloat16, device="cuda")
+    W[5] = float("inf")
+    hid = torch.full((3, H), 0.5, dtype=torch.bfloat16, device="cuda")
+    ids, _ = sp.draft_topk(hid, W[:5].contiguous(), 2)
+    assert ids.tolist() == [[0, 1]] * 3                      # all rows tie: the lowest ids
+    r = sp.accept(hid, W, torch.zeros(2, dtype=torch.int32, device="cuda"), None, 1, 2)
+    assert r["target_ids"].tolist() == [5] * 3               # and the infinite row is the only best one

@@ -19,7 +19,7 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
                               "test_gpu_parity_tree.py", "test_gpu_parity_hsr.py",
                               "test_gpu_parity_commit.py", "test_gpu_graph_and_passes.py")
 
-V64 = "test_gpu_verify_heads64.py"
+V64, LM = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py"
 
 COVERAGE = {
     # ---- verification attention, matrix cores (bf16): <head_dim, steps in flight, row tiles>
@@ -55,12 +55,15 @@ COVERAGE = {
     "draft_window_attn_kernel<unsigned short, 128>": (A, "test_c2_bf16_8k_chain5", "C2 to C5"),
     # ---- lm_head + argmax + acceptance
     "lm_head_generic_kernel<float>": (AC, "test_c1_fp32_accept", "C1"),
-    "lm_head_generic_kernel<unsigned short>": (AC, "test_accept_shapes", "bf16-520-777: hidden not a multiple of 512"),
-    "lm_head_mfma_kernel": (AC, "test_accept_shapes", "bf16-512-4096, bf16-1024-9000"),
-    "lm_head_ksplit_kernel<7, 1>": (AC, "test_c5_full_vocab_accept", "hidden 3584, at most 16 rows"),
-    "lm_head_ksplit_kernel<7, 2>": (AC, "test_accept_shapes", "bf16-3584-8192-8-6 / 8-7: 17-32 rows and the paired 64-row pass"),
-    "lm_head_ksplit_kernel<8, 1>": (AC, "test_accept_shapes", "bf16-4096-6000-1-8"),
-    "lm_head_ksplit_kernel<8, 2>": (AC, "test_accept_shapes", "bf16-4096-6000-4-7, 3-10, 8-7"),
+    "lm_head_generic_kernel<unsigned short>": (LM, "test_wider_than_the_matrix_core_kernels", "hidden above 8,192"),
+    # <slices per wavefront, blocks of 16 rows>
+    "lm_head_ksplit_kernel<1, 1>": (AC, "test_c5_full_vocab_accept", "at most 16 rows"),
+    "lm_head_ksplit_kernel<1, 2>": (AC, "test_accept_shapes", "bf16-1024-9000-4-7: 17-32 rows"),
+    "lm_head_ksplit_kernel<2, 1>": (LM, "test_hidden_sizes", "hidden above 4,096"),
+    # <hidden rows of a tile, wavefronts along the vocabulary, k elements of a step>
+    "lm_head_tiled_kernel<64, 2, 128>": (LM, "test_hidden_sizes", "33 and 64 rows"),
+    "lm_head_tiled_kernel<128, 2, 128>": (LM, "test_hidden_sizes", "65 rows"),
+    "lm_head_tiled_kernel<256, 1, 64>": (LM, "test_many_rows", "129 to 512 rows"),
     "accept_finalize_kernel": (AC, "test_accept_shapes", "every greedy case"),
     "logit_stats_kernel": (AS, "test_accept_sample_matches_oracle", "every stochastic case"),
     "accept_sample_kernel": (AS, "test_accept_sample_matches_oracle", "deterministic children"),
