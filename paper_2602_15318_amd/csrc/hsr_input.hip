@@ -13,7 +13,8 @@
 // so both halves of every rotary pair sit in the same tile (lanes l and l^32 of the result);
 // RMSNorm is folded in: gamma multiplies the activations on their way into the B operand, the
 // row's 1/rms (from the squares each wavefront sees in its own slices) scales the result.
-// Other shapes and fp32 run plain-ALU kernels (one wavefront per output feature or rotary pair).
+// Other hidden sizes in bf16: hsr_input_widths.hip.  fp32 runs plain-ALU kernels (one wavefront per
+// output feature or rotary pair).
 #include "common.hpp"
 #include "hsr_input.hpp"
 
@@ -364,7 +365,7 @@ draft_qkv_gemv_kernel(DraftQkvArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// plain-ALU versions: any dtype, any H.  One wavefront per output feature (FC) or rotary pair.
+// plain-ALU versions: fp32, any H.  One wavefront per output feature (FC) or rotary pair.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -488,9 +489,9 @@ hipError_t launch_hsr_fc(int dtype, const HsrFcArgs &a, hipStream_t st) {
     if (a.H == 7 * kSlice) return launch_skinny<hsr_fc_mfma_kernel<7, 2>>(skinny_lds_bytes(7, 1), grid, 7 * 64, a, st);
     if (a.H == 8 * kSlice) return launch_skinny<hsr_fc_mfma_kernel<8, 2>>(skinny_lds_bytes(8, 1), grid, 8 * 64, a, st);
   }
+  if (dtype == SPARROW_BF16) return launch_hsr_fc_any(a, st);
   const dim3 grid((a.H + 3) / 4);
-  if (dtype == SPARROW_BF16) hipLaunchKernelGGL(hsr_fc_generic_kernel<bf16_t>, grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(hsr_fc_generic_kernel<float>, grid, dim3(256), 0, st, a);
+  hipLaunchKernelGGL(hsr_fc_generic_kernel<float>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -510,9 +511,9 @@ hipError_t launch_draft_qkv(int dtype, const DraftQkvArgs &a, hipStream_t st) {
     if (a.H == 7 * kSlice) return launch_skinny<draft_qkv_mfma_kernel<7, 1>>(skinny_lds_bytes(7, 2), grid, 7 * 64, a, st);
     if (a.H == 8 * kSlice) return launch_skinny<draft_qkv_mfma_kernel<8, 1>>(skinny_lds_bytes(8, 2), grid, 8 * 64, a, st);
   }
+  if (dtype == SPARROW_BF16) return launch_draft_qkv_any(a, st);
   const dim3 grid((n_heads * (a.d / 2) + 3) / 4);
-  if (dtype == SPARROW_BF16) hipLaunchKernelGGL(draft_qkv_generic_kernel<bf16_t>, grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(draft_qkv_generic_kernel<float>, grid, dim3(256), 0, st, a);
+  hipLaunchKernelGGL(draft_qkv_generic_kernel<float>, grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -37,8 +37,10 @@ struct DraftQkvArgs {
   int32_t kv_rows[kHsrMaxRows];   // cache row that receives the K/V of new token m
 };
 
-bool hsr_mfma_supported(int dtype, int H);
 hipError_t launch_hsr_fc(int dtype, const HsrFcArgs &a, hipStream_t st);
 hipError_t launch_draft_qkv(int dtype, const DraftQkvArgs &a, hipStream_t st);
+// bf16, any hidden size
+hipError_t launch_hsr_fc_any(const HsrFcArgs &a, hipStream_t st);
+hipError_t launch_draft_qkv_any(const DraftQkvArgs &a, hipStream_t st);
 
 }  // namespace sparrow

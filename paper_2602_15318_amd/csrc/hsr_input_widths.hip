@@ -1,0 +1,428 @@
+// Input side of the draft model for any hidden size (a multiple of 8), bf16: the hidden-state-reuse
+// projection (Eq. 1) and the draft layer's RMSNorm / QKV / rotary step with the K/V append.  gfx950.
+// Hidden sizes of 7 and 8 whole slices of 512 have kernels of their own (hsr_input.hip), in which the
+// number of slices is a compile-time constant and no column needs a check: 6 rows at 3,584 take
+// 11.2 + 12.1 us there, 12.3 + 22.6 here.
+//
+// Both steps are skinny GEMMs (at most 64 activation rows), bound by the weight stream:
+//   - one workgroup per tile of 16 weight rows (grid.y = blocks of 16 activation rows);
+//   - a weight row is cut into slices of 512 elements (1 KB; the last one may be short: columns past
+//     its end read as zero by the bounds check of the buffer loads); wavefront w owns the slices w,
+//     w + nw, ...: every load instruction reads the slice of one weight row, 16 loads in flight,
+//     staged through a private, XOR-swizzled 16 KB LDS buffer into the A operand of
+//     v_mfma_f32_16x16x32_bf16; the B operand is the wavefront's slice of the activation rows, held
+//     in registers;
+//   - the partial sums of the wavefronts meet in LDS and wavefront 0 runs the epilogue.
+// For the QKV step the tile's 16 weight rows are features f..f+7 and f+d/2..f+d/2+7 of one head,
+// so both halves of every rotary pair sit in the same tile (lanes l and l^32 of the result);
+// RMSNorm is folded in: the activations enter the B operand multiplied by gamma, as the sum of two
+// bf16 terms (the product needs up to 16 bits), and the row's 1/rms (from the squares each wavefront
+// sees in its own slices) scales the result.
+// One activation row runs a wavefront per output feature or rotary pair instead.
+//
+// Measured (FC + QKV, one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64, six
+// rows 141 + 67 -> 9.3 + 9.9 us, one row 56 + 22 -> 7.3 + 6.8; hidden 5,120, 40/8 heads of 128, 16 rows
+// 823 + 447 -> 31.6 + 31.1 us; hidden 1,024, 16/4 heads of 64, six rows 36 + 21 -> 4.8 + 6.4.
+#include "common.hpp"
+#include "hsr_input.hpp"
+
+namespace sparrow {
+
+namespace {
+
+constexpr int kSlice = 512;               // k elements per wavefront slice (1 KB of bf16)
+
+constexpr int kMaxWaves = 8;              // wavefronts of a workgroup (16 KB of staging each)
+constexpr unsigned int kPastEnd = 0x80000000u;   // a buffer offset that reads as zero
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const bf16_t *first) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)first, (short)0, (int)0x7fffffff, 0x00027000);
+}
+
+// ---------------------------------------------------------------------------------------------
+// shared main loop over a tile of 16 weight rows.  Wavefront 0 gets D[4*c4 + i][n] = sum over K of
+// W[wrow(4*c4 + i)][k] * x[row0 + n][k], lane = n + 16*c4, and (kNorm) the sum of x[row0 + n][k]^2, and
+// runs epi(D, sum).  xload(m, k, ok): 8 consecutive bf16 of activation row m at column k (k % 8 == 0),
+// zeros if !ok.  With the norm folded in, the activations of a slice are taken in two halves of 256
+// columns: their two terms fill 64 registers per half beside the 64 of the weights in flight.
+// ---------------------------------------------------------------------------------------------
+template <bool kNorm, class WRow, class XLoad, class Epi>
+__device__ __forceinline__ void skinny_gemm(const bf16_t *W, int K, WRow wrow, XLoad xload, const bf16_t *gamma,
+                                            int row0, int M, unsigned char *smem, Epi epi) {
+  constexpr int kPart = kNorm ? 8 : 16;                      // k-steps of 32 fetched together
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = (int)blockDim.x >> 6;
+  const int n = lane & 15, c4 = lane >> 4;
+  const int n_slices = (K + kSlice - 1) / kSlice;
+  unsigned char *stg = smem + w * 16384;
+  f32x4 *red = reinterpret_cast<f32x4 *>(smem + nw * 16384);                        // [nw][64]
+  float *ssq_lds = reinterpret_cast<float *>(smem + nw * 16384 + nw * 1024);        // [nw][16]
+
+  u32x4 buf[16];
+  auto issue = [&](int s) {
+    const int first = wrow(0);
+    const __amdgpu_buffer_rsrc_t rs = weight_rows(W + (int64_t)first * K);
+    const int k = kSlice * s + 8 * lane;
+    const unsigned int off = k < K ? (unsigned int)k * 2u : kPastEnd;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      buf[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, (wrow(r) - first) * K * 2, 2);
+  };
+  const int m = row0 + n;
+  const bool m_ok = m < M;
+  const __amdgpu_buffer_rsrc_t rs_g = weight_rows(gamma);
+  float ssq = 0.f;
+  u32x4 xr[kPart], gr[kNorm ? kPart : 1];
+  auto load_x = [&](int k0) {
+#pragma unroll
+    for (int ks = 0; ks < kPart; ++ks) {
+      const int k = k0 + 32 * ks + 8 * c4;
+      xr[ks] = xload(m, k, m_ok && k < K);
+      if (kNorm) gr[ks] = __builtin_amdgcn_raw_buffer_load_b128(rs_g, k < K ? (unsigned int)k * 2u : kPastEnd, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // activations times gamma, in place: xr the leading 8 bits of the products (cut off), gr the next 8.
+  // The fused multiply-add leaves gr the product's sign and, by 2^-22 of the product, never zero: an
+  // infinite weight then gives an infinity, and no 0 * inf or inf - inf.
+  auto convert = [&]() {
+#pragma unroll
+    for (int ks = 0; ks < kPart; ++ks) {
+      float xf[8], gf[8], lo[8];
+      unsigned int hb[8];
+      Elem<bf16_t>::unpack(xr[ks], xf);
+      Elem<bf16_t>::unpack(gr[kNorm ? ks : 0], gf);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        ssq = fmaf(xf[e], xf[e], ssq);
+        const float u = xf[e] * gf[e];
+        hb[e] = __float_as_uint(u) & 0xffff0000u;
+        lo[e] = fmaf(__uint_as_float(hb[e]), -(1.0f - 0x1p-22f), u);
+      }
+      xr[ks] = (u32x4){(hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3], (hb[4] >> 16) | hb[5], (hb[6] >> 16) | hb[7]};
+      gr[kNorm ? ks : 0] = (u32x4){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]),
+                                   pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
+      // one k-step at a time: unpacked, all of them would need as many registers as the kernel has
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  const int a_base = n * 1024;            // A read: tile row n, 16-byte chunk 4*ks + c4
+  auto mul = [&](int part) {
+#pragma unroll
+    for (int kh = 0; kh < kPart; kh += 2) {
+      const int ch0 = 4 * (part * kPart + kh) + c4, ch1 = ch0 + 4;
+      const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch0 & ~15) | ((ch0 & 15) ^ n)) << 4));
+      const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch1 & ~15) | ((ch1 & 15) ^ n)) << 4));
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, __builtin_bit_cast(bf16x8, xr[kh]), acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, __builtin_bit_cast(bf16x8, xr[kh + 1]), acc[1], 0, 0, 0);
+      if (kNorm) {
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, __builtin_bit_cast(bf16x8, gr[kNorm ? kh : 0]), acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, __builtin_bit_cast(bf16x8, gr[kNorm ? kh + 1 : 0]), acc[1], 0, 0, 0);
+      }
+    }
+  };
+
+  issue(w);                               // (nw <= n_slices: every wavefront has a slice)
+  for (int s = w; s < n_slices; s += nw) {
+    load_x(kSlice * s);
+    // lane l of load r holds chunk l of row r; stored at chunk (l & ~15) | ((l & 15) ^ r) so that
+    // the A reads (16 rows, same chunk) spread over all banks
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      *reinterpret_cast<u32x4 *>(stg + r * 1024 + (((lane & ~15) | ((lane & 15) ^ r)) << 4)) = buf[r];
+    if (s + nw < n_slices) issue(s + nw);
+    if (kNorm) convert();
+    mul(0);
+    if (kNorm) {
+      load_x(kSlice * s + 256);
+      convert();
+      mul(1);
+    }
+  }
+  red[w * 64 + lane] = acc[0] + acc[1];
+  if (kNorm) {
+    ssq += lane_xor<16>(ssq, lane);
+    ssq += lane_xor<32>(ssq, lane);       // all four k-chunk lanes of row n now hold the slices' sum
+    if (c4 == 0) ssq_lds[w * 16 + n] = ssq;
+  }
+  __syncthreads();
+  if (w == 0) {
+    float s2 = 0.f;
+    if (kNorm)
+      for (int ww = 0; ww < nw; ++ww) s2 += ssq_lds[ww * 16 + n];
+    f32x4 sum = red[lane];
+    for (int ww = 1; ww < nw; ++ww) sum += red[ww * 64 + lane];
+    epi(sum, s2);
+  }
+}
+
+constexpr int skinny_lds_bytes(int nw) { return nw * 16384 + nw * 1024 + nw * 64; }
+
+// ---------------------------------------------------------------------------------------------
+// Eq. 1: z = FC(e (+) h)
+// ---------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(kMaxWaves * 64)
+hsr_fc_any_kernel(HsrFcArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tile = blockIdx.x, row0 = blockIdx.y * 16;
+  const int H = a.H;
+  const bf16_t *E = (const bf16_t *)a.embed, *Hp = (const bf16_t *)a.h_prev;
+  const int lane = threadIdx.x & 63, n = lane & 15, c4 = lane >> 4;
+  // the token id of this lane's activation row (clamped into the table)
+  const int m = row0 + n;
+  int tok = m < a.M ? a.token_ids[m] : 0;
+  tok = min(max(tok, 0), a.vocab - 1);
+  auto wrow = [&](int r) { return min(tile * 16 + r, H - 1); };    // (the last tile may be half empty)
+  // eight columns lie entirely in one half of the concatenation (H is a multiple of 8)
+  auto xload = [&](int mm, int k, bool ok) -> u32x4 {
+    const int kk = ok ? k : 0, mr = ok ? mm : 0;
+    const u32x4 v = *(const u32x4 *)(kk < H ? E + (int64_t)tok * H + kk : Hp + (int64_t)mr * H + (kk - H));
+    return ok ? v : (u32x4){0u, 0u, 0u, 0u};
+  };
+  const int f = tile * 16 + 4 * c4;
+  u32x2 bw = {0u, 0u};                    // fetched ahead of the weight stream
+  if (a.bias != nullptr && f < H) bw = *(const u32x2 *)((const bf16_t *)a.bias + f);
+  auto epi = [&](f32x4 r, float) {
+    if (m >= a.M || f >= H) return;
+    const u32x2 o = {pack_bf16x2(r[0] + bf16lo_to_f32(bw.x), r[1] + bf16hi_to_f32(bw.x)),
+                     pack_bf16x2(r[2] + bf16lo_to_f32(bw.y), r[3] + bf16hi_to_f32(bw.y))};
+    *(u32x2 *)((bf16_t *)a.z + (int64_t)m * H + f) = o;
+  };
+  skinny_gemm<false>((const bf16_t *)a.w, 2 * H, wrow, xload, nullptr, row0, a.M, smem, epi);
+}
+
+// ---------------------------------------------------------------------------------------------
+// draft layer input: RMSNorm, QKV, rotary embedding, scatter
+// ---------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(kMaxWaves * 64)
+draft_qkv_any_kernel(DraftQkvArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int row0 = blockIdx.y * 16;
+  const int H = a.H, d = a.d, half = d >> 1;
+  const int tiles_per_head = d >> 4;
+  const int lane = threadIdx.x & 63, n = lane & 15, c4 = lane >> 4;
+  const int m = row0 + n;
+  const bool m_ok = m < a.M;
+  // tile -> (head, group j of 8 features); tile row r: feature 8j + (r & 7) of the head's first
+  // half for r < 8, its rotary partner (+ d/2) for r >= 8
+  const int hd = (int)blockIdx.x / tiles_per_head, j = (int)blockIdx.x - hd * tiles_per_head;
+  auto wrow = [&](int r) { return hd * d + 8 * j + (r & 7) + (r >> 3) * half; };
+  const __amdgpu_buffer_rsrc_t rs_z = weight_rows((const bf16_t *)a.z);       // at most 64 rows
+  auto xload = [&](int mm, int k, bool ok) -> u32x4 {
+    return __builtin_amdgcn_raw_buffer_load_b128(rs_z, ok ? (unsigned int)(mm * H + k) * 2u : kPastEnd, 0, 0);
+  };
+  // lane (n, c4), entry i of a tile's result: tile row 4*c4 + i -> feature f0 + i of half `hi`
+  const int hi = c4 >> 1;
+  // epilogue operands, fetched ahead of the weight stream: bias, the token's rotary row, its
+  // cache row (the table is a kernel argument, read with uniform indices)
+  const int f0 = 8 * j + 4 * (c4 & 1);
+  u32x2 bw = {0u, 0u};
+  if (a.bias != nullptr) bw = *(const u32x2 *)((const bf16_t *)a.bias + hd * d + hi * half + f0);
+  const f32x4 cs = *(const f32x4 *)(a.rope_cos + (int64_t)(m_ok ? m : 0) * half + f0);
+  const f32x4 sn = *(const f32x4 *)(a.rope_sin + (int64_t)(m_ok ? m : 0) * half + f0);
+  int kv_row = 0;
+#pragma unroll
+  for (int mm = 0; mm < 16; ++mm) {
+    const int r = a.kv_rows[min(row0 + mm, kHsrMaxRows - 1)];
+    if (n == mm) kv_row = r;
+  }
+  auto epi = [&](f32x4 res, float ssq) {
+    const float rstd = 1.0f / sqrtf(ssq / (float)H + a.eps);
+    const float b[4] = {bf16lo_to_f32(bw.x), bf16hi_to_f32(bw.x),
+                        bf16lo_to_f32(bw.y), bf16hi_to_f32(bw.y)};
+    const bool is_v = hd >= a.Hq + a.Hkv;
+    float o[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float y = fmaf(res[i], rstd, b[i]);
+      const float partner = lane_xor<32>(y, lane);      // the other half of the rotary pair
+      o[i] = y;
+      if (!is_v) o[i] = hi ? fmaf(partner, sn[i], y * cs[i]) : fmaf(-partner, sn[i], y * cs[i]);
+    }
+    if (!m_ok) return;
+    const u32x2 ow = {pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+    const int feat = hi * half + f0;
+    if (hd < a.Hq) {
+      *(u32x2 *)((bf16_t *)a.q_out + ((int64_t)m * a.Hq + hd) * d + feat) = ow;
+    } else {
+      const int c = is_v ? hd - a.Hq - a.Hkv : hd - a.Hq;
+      bf16_t *base = (bf16_t *)(is_v ? a.v_cache : a.k_cache);
+      *(u32x2 *)(base + (int64_t)kv_row * a.stride_tok + (int64_t)c * a.stride_head + feat) = ow;
+    }
+  };
+  skinny_gemm<true>((const bf16_t *)a.w, H, wrow, xload, (const bf16_t *)a.gamma, row0, a.M, smem, epi);
+}
+
+// ---------------------------------------------------------------------------------------------
+// One activation row: a wavefront owns one output feature (FC) or one rotary pair of a head (QKV), as
+// in the kernels of whole slices.  It issues the loads of its weight row(s) KS slices at a time, then
+// fetches the activation row (shared by all wavefronts through L2), multiplies and reduces across its
+// lanes on the vector ALU.
+// ---------------------------------------------------------------------------------------------
+template <int KS>             // slices in flight: at least K / 512 (K = 2H), or 16
+__global__ void __launch_bounds__(256)
+hsr_fc_any_gemv_kernel(HsrFcArgs a) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  const int lane = threadIdx.x & 63;
+  const int nfeat = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int H = a.H;
+  if (nfeat >= H) return;
+  const int K = 2 * H;
+  const __amdgpu_buffer_rsrc_t rs = weight_rows((const bf16_t *)a.w + (int64_t)__builtin_amdgcn_readfirstlane(nfeat) * K);
+  const int tok = min(max(a.token_ids[0], 0), a.vocab - 1);
+  const bf16_t *E = (const bf16_t *)a.embed + (int64_t)tok * H;
+  const bf16_t *Hp = (const bf16_t *)a.h_prev;
+  float acc = 0.f;
+  for (int s0 = 0; s0 < K; s0 += KS * kSlice) {
+    u32x4 wv[KS], xv[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int k = s0 + kSlice * s + 8 * lane;
+      wv[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, k < K ? (unsigned int)k * 2u : kPastEnd, 0, 2);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // all of the row on its way before anything else
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {     // columns below H meet the embedding, the rest the hidden state
+      const int k = min(s0 + kSlice * s + 8 * lane, K - 8);
+      xv[s] = *(const u32x4 *)(k < H ? E + k : Hp + (k - H));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if (s0 + kSlice * s + 8 * lane >= K) xv[s] = (u32x4){0u, 0u, 0u, 0u};
+      const unsigned int w4[4] = {wv[s].x, wv[s].y, wv[s].z, wv[s].w};
+      const unsigned int x4[4] = {xv[s].x, xv[s].y, xv[s].z, xv[s].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w4[e]), __builtin_bit_cast(bf16x2, x4[e]),
+                                              acc, false);
+    }
+  }
+  acc = wave_sum_valu(acc);
+  if (lane == 0) {
+    const float b = a.bias != nullptr ? bf16_to_f32(((const bf16_t *)a.bias)[nfeat]) : 0.f;
+    ((bf16_t *)a.z)[nfeat] = f32_to_bf16(acc + b);
+  }
+}
+
+template <int KS>             // slices in flight: at least H / 512, or 8
+__global__ void __launch_bounds__(256)
+draft_qkv_any_gemv_kernel(DraftQkvArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int half = a.d >> 1;
+  const int pair = blockIdx.x * 4 + (threadIdx.x >> 6);      // (head, feature of the first half)
+  const int n_heads = a.Hq + 2 * a.Hkv;
+  if (pair >= n_heads * half) return;
+  const int hd = pair / half, f = pair - hd * half;
+  const int H = a.H;
+  const int64_t row0 = (int64_t)__builtin_amdgcn_readfirstlane(hd * a.d + f);
+  const __amdgpu_buffer_rsrc_t rs = weight_rows((const bf16_t *)a.w + row0 * H);
+  const unsigned int pair_off = (unsigned int)half * (unsigned int)H * 2u;
+  u32x4 w0[KS], w1[KS];
+  auto issue = [&](int k0) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int k = k0 + kSlice * s + 8 * lane;
+      const unsigned int off = k < H ? (unsigned int)k * 2u : kPastEnd;
+      w0[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 2);
+      w1[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, pair_off, 2);
+    }
+  };
+  issue(0);
+  // epilogue operands ahead of the arithmetic
+  const bool is_v = hd >= a.Hq + a.Hkv;
+  float b0 = 0.f, b1 = 0.f;
+  if (a.bias != nullptr) {
+    b0 = bf16_to_f32(((const bf16_t *)a.bias)[hd * a.d + f]);
+    b1 = bf16_to_f32(((const bf16_t *)a.bias)[hd * a.d + f + half]);
+  }
+  const float cs = a.rope_cos[f], sn = a.rope_sin[f];
+  const bf16_t *Z = (const bf16_t *)a.z, *G = (const bf16_t *)a.gamma;
+  float s0 = 0.f, s1 = 0.f, ssq = 0.f;
+  for (int k0 = 0; k0 < H; k0 += KS * kSlice) {
+    if (k0 > 0) issue(k0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int k = min(k0 + kSlice * s + 8 * lane, H - 8);
+      float xf[8], gf[8], a0[8], a1[8];
+      u32x4 x = *(const u32x4 *)(Z + k);
+      if (k0 + kSlice * s + 8 * lane >= H) x = (u32x4){0u, 0u, 0u, 0u};
+      Elem<bf16_t>::unpack(x, xf);
+      Elem<bf16_t>::unpack(*(const u32x4 *)(G + k), gf);
+      Elem<bf16_t>::unpack(w0[s], a0);
+      Elem<bf16_t>::unpack(w1[s], a1);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float u = xf[e] * gf[e];
+        ssq = fmaf(xf[e], xf[e], ssq);
+        s0 = fmaf(a0[e], u, s0);
+        s1 = fmaf(a1[e], u, s1);
+      }
+    }
+  }
+  s0 = wave_sum_valu(s0); s1 = wave_sum_valu(s1); ssq = wave_sum_valu(ssq);
+  if (lane != 0) return;
+  const float rstd = __builtin_amdgcn_rsqf(ssq / (float)H + a.eps);
+  const float y0 = fmaf(s0, rstd, b0), y1 = fmaf(s1, rstd, b1);
+  float o0 = y0, o1 = y1;
+  if (!is_v) {
+    o0 = y0 * cs - y1 * sn;
+    o1 = y1 * cs + y0 * sn;
+  }
+  bf16_t *dst;
+  if (hd < a.Hq) {
+    dst = (bf16_t *)a.q_out + (int64_t)hd * a.d;
+  } else {
+    const int c = is_v ? hd - a.Hq - a.Hkv : hd - a.Hq;
+    dst = (bf16_t *)(is_v ? a.v_cache : a.k_cache) + (int64_t)a.kv_rows[0] * a.stride_tok +
+          (int64_t)c * a.stride_head;
+  }
+  dst[f] = f32_to_bf16(o0);
+  dst[f + half] = f32_to_bf16(o1);
+}
+
+template <auto kKern, class Args>
+hipError_t launch_skinny(int nw, dim3 grid, const Args &a, hipStream_t st) {
+  // more than 64 KB of dynamic LDS has to be allowed once per kernel
+  static const hipError_t attr = hipFuncSetAttribute((const void *)kKern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     skinny_lds_bytes(kMaxWaves));
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kKern, grid, dim3(nw * 64), skinny_lds_bytes(nw), st, a);
+  return hipGetLastError();
+}
+
+// Wavefronts for rows of K elements: as few rounds of slices as eight wavefronts allow, dealt evenly.
+int skinny_waves(int K) {
+  const int slices = (K + kSlice - 1) / kSlice;
+  const int rounds = (slices + kMaxWaves - 1) / kMaxWaves;
+  return (slices + rounds - 1) / rounds;
+}
+
+}  // namespace
+
+hipError_t launch_hsr_fc_any(const HsrFcArgs &a, hipStream_t st) {
+  const int K = 2 * a.H, slices = (K + kSlice - 1) / kSlice;
+  if (a.M == 1) {               // one row: a wavefront per output feature
+    const dim3 grid((a.H + 3) / 4);
+    if (slices <= 4) hipLaunchKernelGGL(hsr_fc_any_gemv_kernel<4>, grid, dim3(256), 0, st, a);
+    else if (slices <= 8) hipLaunchKernelGGL(hsr_fc_any_gemv_kernel<8>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(hsr_fc_any_gemv_kernel<16>, grid, dim3(256), 0, st, a);
+    return hipGetLastError();
+  }
+  return launch_skinny<hsr_fc_any_kernel>(skinny_waves(K), dim3((a.H + 15) / 16, (a.M + 15) / 16), a, st);
+}
+
+hipError_t launch_draft_qkv_any(const DraftQkvArgs &a, hipStream_t st) {
+  const int n_heads = a.Hq + 2 * a.Hkv, slices = (a.H + kSlice - 1) / kSlice;
+  if (a.M == 1) {               // one row: a wavefront per rotary pair
+    const dim3 grid((n_heads * (a.d / 2) + 3) / 4);
+    if (slices <= 4) hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<4>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<8>, grid, dim3(256), 0, st, a);
+    return hipGetLastError();
+  }
+  return launch_skinny<draft_qkv_any_kernel>(skinny_waves(a.H), dim3(n_heads * (a.d / 16), (a.M + 15) / 16), a, st);
+}
+
+}  // namespace sparrow

@@ -1,0 +1,87 @@
+"""The draft's input side in bf16 for hidden sizes around the 512-element slice of a wavefront (8 to
+8,200, short last slices) and row counts around the 16-row block, against plain fp64 products."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sp():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2602_15318_amd as sp_
+    return sp_
+
+
+def _bf(g, *shape, std=1.0):
+    import torch
+    return (torch.randn(*shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+
+
+def _close(got, ref, abs_sum, what):
+    # one rounding of the result to bf16 (at most 2^-8 of it), and of every product term at most 2^-16
+    # (activation times gamma as two bf16 terms) plus its share of the fp32 sums: 2^-15 of the sum of
+    # the terms' magnitudes covers both
+    bound = 1.01 * 2.0 ** -8 * ref.abs() + 2.0 ** -15 * abs_sum
+    excess = (got.double() - ref).abs() - bound
+    assert float(excess.max()) <= 0, f"{what}: over the bound by {float(excess.max()):.3e}"
+
+
+@pytest.mark.parametrize("H", [8, 72, 512, 520, 1000, 1280, 2560, 3584, 4104, 5120, 8200])
+@pytest.mark.parametrize("M", [1, 2, 16, 17, 64])
+def test_hsr_fc(sp, H, M):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(H + M)
+    embed, h, w, b = _bf(g, 50, H), _bf(g, M, H), _bf(g, H, 2 * H, std=H ** -0.5), _bf(g, H)
+    tok = torch.randint(0, 50, (M,), generator=g, device="cuda", dtype=torch.int32)
+    x = torch.cat([embed[tok.long()], h], dim=1).double()
+    for bias in (b, None):
+        z = sp.hsr_fc(embed, tok, h, w, bias)
+        add = 0.0 if bias is None else bias.double()
+        _close(z, x @ w.double().t() + add, x.abs() @ w.double().abs().t() + abs(add), f"H={H} M={M}")
+
+
+@pytest.mark.parametrize("H,Hq,Hkv,d", [(8, 2, 1, 64), (72, 6, 2, 128), (512, 4, 2, 64), (1000, 8, 2, 128), (2560, 40, 8, 64),
+                                        (3072, 28, 4, 128), (4104, 8, 1, 64), (5120, 40, 8, 128), (8200, 4, 4, 64)])
+@pytest.mark.parametrize("M", [1, 2, 16, 17, 64])
+def test_draft_qkv_append(sp, H, Hq, Hkv, d, M):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(H + M)
+    F = (Hq + 2 * Hkv) * d
+    z, gam, w, b = _bf(g, M, H, std=1.5), _bf(g, H), _bf(g, F, H, std=H ** -0.5), _bf(g, F)
+    ang = torch.rand(M, d // 2, generator=g, device="cuda", dtype=torch.float64) * 6.0
+    kc, vc = torch.zeros(80, Hkv, d, dtype=torch.bfloat16, device="cuda"), torch.zeros(80, Hkv, d, dtype=torch.bfloat16, device="cuda")
+    rows = np.random.default_rng(M).permutation(80)[:M].astype(np.int32)
+    q = sp.draft_qkv_append(z, gam, 1e-6, w, b, ang.cos().float(), ang.sin().float(), rows, Hq, kc, vc)
+    x = z.double()
+    u = x * torch.rsqrt((x * x).mean(dim=1, keepdim=True) + 1e-6) * gam.double()
+    f = (u @ w.double().t() + b.double()).view(M, -1, d)
+    s = (u.abs() @ w.double().abs().t() + b.double().abs()).view(M, -1, d)
+    c, sn = ang.cos().float().double()[:, None], ang.sin().float().double()[:, None]
+    lo, hi, slo, shi = f[..., :d // 2], f[..., d // 2:], s[..., :d // 2], s[..., d // 2:]
+    rot = torch.cat([lo * c - hi * sn, hi * c + lo * sn], dim=2)
+    srot = torch.cat([slo + shi, slo + shi], dim=2)
+    at = torch.from_numpy(rows).long().cuda()
+    _close(q, rot[:, :Hq], srot[:, :Hq], f"q H={H} M={M}")
+    _close(kc[at], rot[:, Hq:Hq + Hkv], srot[:, Hq:Hq + Hkv], f"k H={H} M={M}")
+    _close(vc[at], f[:, Hq + Hkv:], s[:, Hq + Hkv:], f"v H={H} M={M}")
+    rest = np.setdiff1d(np.arange(80), rows)
+    assert not kc[rest].any() and not vc[rest].any()
+
+
+@pytest.mark.parametrize("M", [1, 3])
+def test_infinite_weights_give_infinities(sp, M):
+    """A weight of infinity beside non-zero activations: its features are infinite, the others finite."""
+    import torch
+    H, Hq, Hkv, d = 520, 4, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    z, w = _bf(g, M, H).abs() + 0.5, _bf(g, (Hq + 2 * Hkv) * d, H, std=0.05)
+    v_feat = (Hq + Hkv) * d + 5
+    w[v_feat, 513] = float("inf")
+    gam, one = torch.ones(H, dtype=torch.bfloat16, device="cuda"), torch.ones(M, d // 2, device="cuda")
+    kc, vc = (torch.zeros(M, Hkv, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    sp.draft_qkv_append(z, gam, 1e-6, w, None, one, one, np.arange(M), Hq, kc, vc)
+    assert torch.isposinf(vc[:, 0, 5]).all()
+    vc[:, 0, 5] = 0
+    assert torch.isfinite(vc).all() and torch.isfinite(kc).all()

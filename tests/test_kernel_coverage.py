@@ -19,7 +19,7 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
                               "test_gpu_parity_tree.py", "test_gpu_parity_hsr.py",
                               "test_gpu_parity_commit.py", "test_gpu_graph_and_passes.py")
 
-V64, LM = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py"
+V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
 
 COVERAGE = {
     # ---- verification attention, matrix cores (bf16): <head_dim, steps in flight, row tiles>
@@ -75,7 +75,6 @@ COVERAGE = {
     "tree_select_kernel": (T, "test_tree_expand_and_select", ""),
     # ---- draft input and post-accept commit
     "hsr_fc_generic_kernel<float>": (H, "test_hsr_fc", "f32-4-1-64-256"),
-    "hsr_fc_generic_kernel<unsigned short>": (H, "test_hsr_fc", "bf16-4-2-64-512"),
     "hsr_fc_mfma_kernel<7, 2>": (H, "test_hsr_fc", "bf16-28-4-128-3584"),
     "hsr_fc_mfma_kernel<8, 2>": (H, "test_hsr_fc", "bf16-32-8-128-4096"),
     "hsr_fc_gemv_kernel<14>": (H, "test_hsr_fc", "bf16-28-4-128-3584, one row"),
@@ -83,9 +82,16 @@ COVERAGE = {
     "draft_qkv_gemv_kernel<7>": (H, "test_draft_qkv_append", "bf16-28-4-128-3584, one row"),
     "draft_qkv_gemv_kernel<8>": (H, "test_draft_qkv_append", "bf16-32-8-128-4096, one row"),
     "draft_qkv_generic_kernel<float>": (H, "test_draft_qkv_append", "f32-4-1-64-256"),
-    "draft_qkv_generic_kernel<unsigned short>": (H, "test_draft_qkv_append", "bf16-4-2-64-512"),
     "draft_qkv_mfma_kernel<7, 1>": (H, "test_draft_qkv_append", "bf16-28-4-128-3584"),
     "draft_qkv_mfma_kernel<8, 1>": (H, "test_draft_qkv_append", "bf16-32-8-128-4096"),
+    # hidden sizes other than 3,584 and 4,096; one row: <slices of a weight row in flight>
+    "hsr_fc_any_kernel": (HW, "test_hsr_fc", "two rows and more"),
+    "draft_qkv_any_kernel": (HW, "test_draft_qkv_append", "two rows and more"),
+    "hsr_fc_any_gemv_kernel<4>": (HW, "test_hsr_fc", "hidden up to 1,024"),
+    "hsr_fc_any_gemv_kernel<8>": (HW, "test_hsr_fc", "hidden 1,280"),
+    "hsr_fc_any_gemv_kernel<16>": (HW, "test_hsr_fc", "hidden 2,560 and more"),
+    "draft_qkv_any_gemv_kernel<4>": (HW, "test_draft_qkv_append", "hidden up to 1,000"),
+    "draft_qkv_any_gemv_kernel<8>": (HW, "test_draft_qkv_append", "hidden 2,560 and more"),
     "kv_commit_kernel": (C, "test_kv_commit_bit_exact", ""),
     # ---- measurement aid (no part of the method, nothing to compare): run, input left alone
     "stream_read_kernel<2>": (G, "test_stream_read_shapes_run", ""),
