@@ -18,5 +18,6 @@ def __getattr__(name):
     # missing library raises ImportError there: there is no fallback path.
     if name in __all__:
         from . import binding
-        return getattr(binding, name)
+        value = globals()[name] = getattr(binding, name)      # (found without this function from now on)
+        return value
     raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
