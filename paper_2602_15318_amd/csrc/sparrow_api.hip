@@ -98,6 +98,16 @@ int plan_chunk(const sparrow_attn_desc *d, int32_t n_q, int64_t total_tokens, bo
   return (int)chunk;
 }
 
+// Sequences of at most this many rows are verified in one piece each (no combine pass).  One workgroup
+// then walks the sequence alone, a 64-token step in ~0.8 us, so the line rises with the number of
+// workgroups that run side by side.  In one piece / in splits, us a call: chain of 5 over 100 tokens
+// (4 workgroups) 5.3 / 7.1, over 300 8.4 / 7.7; 4 trees of 30 nodes (32) over 200 13.0 / 14.6, over 400
+// 16.0 / 14.7; 16 chains of 8 (64) over 500 12.6 / 13.5, over 800 16.4 / 15.9.
+int direct_rows(const sparrow_attn_desc *d, int32_t B, int32_t n_q) {
+  const int workgroups = B * d->n_kv_heads * verify_mfma_row_blocks(n_q * (d->n_q_heads / d->n_kv_heads));
+  return std::min(512, 128 + 6 * workgroups);
+}
+
 // The matrix-core kernel addresses a sequence's K/V rows by 32-bit byte offsets; judged on the
 // call's total token count so that the workspace query and the call always agree.
 bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
@@ -509,7 +519,15 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
       tab = tab_g; chunk = chunk_g; need = need_g;
     }
   }
-  const int n_slots = tab.cu_split[B];
+  // Short sequences in one piece: the partial pass then writes the result and the combine pass is left
+  // out.  Only when both passes are asked for at once; the scratch asked for stays that of the split
+  // plan.
+  bool direct = false;
+  if (mfma && passes == 3) {
+    int longest = 0;
+    for (int b = 0; b < B; ++b) longest = std::max(longest, cu_seqlens[b + 1] - cu_seqlens[b]);
+    direct = longest <= direct_rows(desc, B, n_q);
+  }
   if (static_ws) {
     if (need > (size_t)SPARROW_STATIC_WS_BYTES)
       return fail(SPARROW_ERR_UNSUPPORTED,
@@ -524,15 +542,22 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
                 workspace_bytes, workspace ? "" : " (NULL)");
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
     return fail(SPARROW_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
+  size_t bytes_o, bytes_ml;
+  verify_ws_layout(desc, tab.cu_split[B], n_q, mfma, &bytes_o, &bytes_ml);
+  if (direct)
+    for (int b = 0; b <= B; ++b) tab.cu_split[b] = b;
+  if (direct) {
+    chunk = 0;
+    for (int b = 0; b < B; ++b) chunk = std::max(chunk, split_len(cu_seqlens[b + 1] - cu_seqlens[b], 1));
+  }
   VerifyArgs a;
+  a.direct = direct;
   a.q = q; a.k = k; a.v = v; a.parent = parent;
   a.parent_stride = parent ? desc->parent_stride : 0;
   a.B = B; a.n_q = n_q; a.Hq = desc->n_q_heads; a.Hkv = desc->n_kv_heads; a.d = desc->head_dim;
-  a.chunk = chunk; a.n_slots = n_slots;
+  a.chunk = chunk; a.n_slots = tab.cu_split[B];
   a.scale_log2 = scale_log2_of(desc);
   a.stride_tok = desc->kv_stride_token; a.stride_head = desc->kv_stride_head;
-  size_t bytes_o, bytes_ml;
-  verify_ws_layout(desc, n_slots, n_q, mfma, &bytes_o, &bytes_ml);
   a.part_o = (float *)workspace;
   a.part_ml = (float *)((char *)workspace + bytes_o);
   a.out = out; a.lse = lse;
@@ -542,7 +567,7 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
                         : launch_verify_partial_generic(desc->dtype, a, tab, st);
     if (e != hipSuccess) return fail(SPARROW_ERR_DEVICE, "verify partial launch: %s", hipGetErrorString(e));
   }
-  if (passes & 2) {
+  if ((passes & 2) && !direct) {
     hipError_t e = mfma ? launch_verify_combine_mfma(a, tab, st) : launch_verify_combine(desc->dtype, a, tab, st);
     if (e != hipSuccess) return fail(SPARROW_ERR_DEVICE, "verify combine launch: %s", hipGetErrorString(e));
   }

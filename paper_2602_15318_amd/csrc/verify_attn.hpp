@@ -23,6 +23,7 @@ struct VerifyArgs {
   int32_t chunk;          // longest split of the call, in tokens (the kernels derive each
                           // sequence's own split length from SeqTable)
   int32_t n_slots;        // cu_split[B]
+  int32_t direct;         // matrix-core path: one split per sequence, the partial pass writes out and lse
   float scale_log2;       // softmax scale * log2(e)
   int64_t stride_tok, stride_head;
   // plain-ALU path: part_o [n_slots, n_q, Hq, d], part_ml [n_slots, n_q, Hq, 2];

@@ -94,7 +94,7 @@ template <int kD> constexpr bool kWideState = kD == 64;
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
 template <int kD, int kPrefetch, int kQT>
 __global__ void __launch_bounds__(256 * kStreams)
-verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, int flat) {
+verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, int flat, int direct) {
   constexpr int kSub = 128 / kD;                           // 32-token tiles per stream per step
   constexpr int kRowBytes = 2 * kD;                        // one K or V row of a head
   constexpr int kChunks = kD / 8;                          // 16-byte chunks of a row
@@ -469,6 +469,21 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
       const float l_tot = l_mine * a0 + l1 * a1;
       const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;
       const float s0 = a0 * inv_l, s1 = a1 * inv_l;
+      if (direct) {
+        // the split is the whole sequence: the merged streams are the result (the rows and columns
+        // of a lane as in the combine pass)
+        if (row_ok[qt]) {
+          const int64_t orow = ((int64_t)b * a.n_q + i_row[qt]) * a.Hq + h[qt];
+          bf16_t *out = (bf16_t *)a.out + orow * kD + 4 * c4;
+#pragma unroll
+          for (int mt = 0; mt < kMT; ++mt) {
+            const f32x4 r = o_acc[qt][mt] * s0 + mo[(w * kMT + mt) * 64 + lane] * s1;
+            *reinterpret_cast<u32x2 *>(out + 16 * mt) = (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
+          }
+          if (a.lse != nullptr && c4 == 0) a.lse[orow] = (m_new + fast_log2(l_tot)) * kLn2;
+        }
+        continue;
+      }
       if (kWide) {
         // fp32 partials: [unit][wavefront][d-tile][lane] x 4 floats
         f32x4 *po = reinterpret_cast<f32x4 *>(a.part_o) + (unit * 4 + w) * (kMT * 64) + lane;
@@ -649,19 +664,20 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
   constexpr int kSub = 128 / kD;
   constexpr int kLdsBytes = kStreams * 2 * 2 * kSub * kTile * kD * 2;
   static_assert(kLdsBytes <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
+  const int direct = a.direct;
   const int steps = (a.chunk / kTile + kStreams * kSub - 1) / (kStreams * kSub);   // of a full split
   const int tiles = (R + kRowsPerWG - 1) / kRowsPerWG;
   const int qt = (tiles + rbs - 1) / rbs;
   if (qt == 3)      // a second tile in flight does not fit the registers (and the step is compute-bound)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 3>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 3>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2 && steps <= 10)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (steps <= 3)       // (a second step in flight pays from 4 steps on: -0.15 us at the 7 steps of a 26k chain)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   return hipGetLastError();
 }
 
