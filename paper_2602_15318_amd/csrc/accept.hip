@@ -1,6 +1,6 @@
 // Greedy acceptance, plain-ALU lm_head pass and the finalize pass.
 //
-// Step 1 (this file: any dtype; accept_mfma.hip: bf16 on the matrix cores): logits of the
+// Step 1 (this file: hidden sizes beyond the matrix-core kernels of accept_mfma.hip): logits of the
 // B*(n_q+1) verified rows against the whole vocabulary, never written out: every wavefront keeps,
 // per row, the best (value, lowest index) of the vocabulary range it owns and writes one
 // candidate per row.  Step 2: reduce the candidates to the target's greedy token per row

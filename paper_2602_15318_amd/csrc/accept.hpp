@@ -49,7 +49,7 @@ hipError_t launch_accept_sample(const SampleArgs &a, hipStream_t st);
 int accept_num_candidates(int dtype, int M, int H, int V);
 bool lm_head_mfma_supported(int dtype, int M, int H, int V);
 hipError_t launch_lm_head_generic(int dtype, const AcceptArgs &a, hipStream_t st);
-hipError_t launch_lm_head_mfma(const AcceptArgs &a, hipStream_t st);
+hipError_t launch_lm_head_mfma(int dtype, const AcceptArgs &a, hipStream_t st);
 hipError_t launch_accept_finalize(const AcceptArgs &a, hipStream_t st);
 
 }  // namespace sparrow

@@ -1,4 +1,4 @@
-// Greedy acceptance, matrix-core lm_head pass: bf16, gfx950.
+// Greedy acceptance, matrix-core lm_head pass: bf16 and fp32, gfx950.
 //
 // logits[r, v] = sum_x hidden[r, x] * W[v, x] for the B*(n_q+1) verified rows r against the whole
 // vocabulary; 1.09 GB of weights for Qwen2.5-VL-7B, read exactly once per pass, so the pass is bound
@@ -7,6 +7,7 @@
 // vocabulary rows it has seen for its column; one candidate per (workgroup, row) is written at the
 // end and reduced by the finalize kernel.
 #include <algorithm>
+#include <type_traits>
 
 #include "accept.hpp"
 #include "common.hpp"
@@ -225,10 +226,10 @@ hipError_t launch_ksplit(const AcceptArgs &a, int row0, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Tiled kernel for more than 32 hidden rows (draft trees, batches): one pass over W whatever the
-// number of rows up to 256, two row blocks side by side above.
+// Tiled kernel for more than 32 hidden rows (draft trees, batches) and for fp32: one pass over W
+// whatever the number of rows up to 256 (fp32: 128), row blocks side by side above.
 //
-// A persistent workgroup of 4 wavefronts owns tiles of 128 vocabulary rows x BM hidden rows and walks
+// A persistent workgroup of 4 wavefronts owns tiles of VT vocabulary rows x BM hidden rows and walks
 // the hidden size in steps of BK; the wavefronts form a WV x WM grid.  Both operands of a step travel
 // memory -> registers (requested one step ahead) -> LDS (rows of 2 BK bytes, 16-byte chunks
 // XOR-swizzled as in the attention kernel) -> MFMA operands.  The LDS tile is single-buffered: two or
@@ -240,34 +241,37 @@ hipError_t launch_ksplit(const AcceptArgs &a, int row0, hipStream_t st) {
 // is the bound; at 256 rows LDS and matrix cores are, and steps of 64 keep two workgroups on a
 // compute unit.  152,064 x 3584 with the finalize pass, against passes of 64 rows by pairs of k-split
 // workgroups: 33 rows 182 (229) us, 64 rows 185 (225), 128 rows 233 (430), 248 rows 355 (834).
-constexpr int kGmV = 128;                 // vocabulary rows of a tile
+// fp32 (v_mfma_f32_16x16x4: fp32 products and sums at 157 TFLOP/s), against the plain-ALU kernel:
+// 152,064 x 3584 at 9 rows 346 (1678) us = 6.3 TB/s, at 64 rows 658 (7436), at 248 rows 2620 (29300) =
+// 103 TFLOP/s; 32,000 x 1024 at 9 rows 32 (138).
 constexpr int kGmWaves = 4;
 
-template <int BK> __device__ __forceinline__ int gm_swz(int row) {
-  return BK == 128 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
+template <int kRow> __device__ __forceinline__ int gm_swz(int row) {
+  return kRow == 256 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
 }
 
-template <int BM, int WV, int BK>
+template <class T, int VT, int BM, int WV, int kRow>      // kRow: bytes of a row that a step covers
 __global__ void __launch_bounds__(kGmWaves * 64, 2)
 lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   constexpr int WM = kGmWaves / WV;
-  constexpr int NV = kGmV / WV / 16, NM = BM / WM / 16;      // 16-row tiles of a wavefront
-  constexpr int kRow = BK * 2, kChunks = BK / 8;             // bytes and 16-byte chunks of a row of a step
+  constexpr int NV = VT / WV / 16, NM = BM / WM / 16;      // 16-row tiles of a wavefront
+  constexpr bool kF32 = std::is_same<T, float>::value;
+  constexpr int kPer = Elem<T>::kPer16B, kChunks = kRow / 16, BK = kChunks * kPer;
   constexpr int kLdRows = kGmWaves * 64 / kChunks;                      // rows that one load of the workgroup covers
-  constexpr int kLdV = kGmV / kLdRows, kLdM = BM / kLdRows;  // loads of a thread per step
+  constexpr int kLdV = VT / kLdRows, kLdM = BM / kLdRows;  // loads of a thread per step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wv = w / WM, wm = w % WM;
   const int n = lane & 15, c4 = lane >> 4;
   const int H = a.H, V = a.V;
-  const unsigned int row_bytes = (unsigned int)H * 2u;
+  const unsigned int row_bytes = (unsigned int)H * (unsigned int)sizeof(T);
   // workgroups of one vocabulary stream (the row blocks) sit 8 indices apart: one XCD, one time
   const int mb = ((int)blockIdx.x >> 3) % blocks_m;
   const int stream = ((int)blockIdx.x >> 3) / blocks_m * 8 + ((int)blockIdx.x & 7);
   const int n_streams = (int)gridDim.x / blocks_m;
   const int row0 = mb * BM;
-  const int n_vt = (V + kGmV - 1) / kGmV;
+  const int n_vt = (V + VT - 1) / VT;
   const int n_tiles = n_vt > stream ? (n_vt - stream + n_streams - 1) / n_streams : 0;
   const int nk = (H + BK - 1) / BK;
   const int n_steps = n_tiles * nk;
@@ -281,13 +285,13 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   u32x4 sg[kLdV + kLdM];
   int is_tile = 0, is_k = 0;                                 // the step the next issue() fetches
   auto issue = [&]() {
-    const int v0 = (stream + min(is_tile, max(n_tiles - 1, 0)) * n_streams) * kGmV;
-    const int rows = min(kGmV, max(V - v0, 0));
+    const int v0 = (stream + min(is_tile, max(n_tiles - 1, 0)) * n_streams) * VT;
+    const int rows = min(VT, max(V - v0, 0));
     const __amdgpu_buffer_rsrc_t rs_v = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const unsigned char *)a.lm_head + (int64_t)min(v0, V - 1) * row_bytes), (short)0,
         (int)(rows * row_bytes), 0x00027000);
-    const int k = is_k * BK + ld_ch * 8;
-    const unsigned int off = k < H ? ld_off + (unsigned int)is_k * (BK * 2) : 0x80000000u;
+    const int k = is_k * BK + ld_ch * kPer;
+    const unsigned int off = k < H ? ld_off + (unsigned int)(is_k * kRow) : 0x80000000u;
 #pragma unroll
     for (int j = 0; j < kLdV; ++j)
       sg[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_v, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 2);
@@ -296,7 +300,7 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
       sg[kLdV + j] = __builtin_amdgcn_raw_buffer_load_b128(rs_m, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 0);
     if (++is_k == nk) { is_k = 0; ++is_tile; }
   };
-  const int st_off = ld_row * kRow + ((ld_ch ^ gm_swz<BK>(ld_row)) << 4);
+  const int st_off = ld_row * kRow + ((ld_ch ^ gm_swz<kRow>(ld_row)) << 4);
   auto stash = [&]() {
     unsigned char *p = smem + st_off;
 #pragma unroll
@@ -314,7 +318,7 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   for (int j = 0; j < NM; ++j) { best[j] = -INFINITY; best_i[j] = 0x7fffffff; }
   const int m_wave = row0 + wm * (NM * 16);                  // first hidden row of the wavefront
   const bool live = m_wave < a.M;                            // a wavefront of padding rows only loads
-  const int rd_row = n * kRow, rd_swz = gm_swz<BK>(n);
+  const int rd_row = n * kRow, rd_swz = gm_swz<kRow>(n);
 
   int cp_tile = 0, cp_k = 0;
   // One step: the operands of this step out of buffer `buf`, then (their latency covered) the next
@@ -322,24 +326,49 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   auto compute = [&]() {
     if (live) {
       const unsigned char *pv = smem + wv * (NV * 16 * kRow) + rd_row;
-      const unsigned char *pm = smem + (kGmV + wm * (NM * 16)) * kRow + rd_row;
-#pragma unroll
-      for (int ks = 0; ks < BK / 32; ++ks) {
-        const int ch = ((4 * ks + c4) ^ rd_swz) << 4;
-        bf16x8 av[NV], bm[NM];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) av[i] = *reinterpret_cast<const bf16x8 *>(pv + i * 16 * kRow + ch);
-#pragma unroll
-        for (int j = 0; j < NM; ++j) bm[j] = *reinterpret_cast<const bf16x8 *>(pm + j * 16 * kRow + ch);
+      const unsigned char *pm = smem + (VT + wm * (NM * 16)) * kRow + rd_row;
+// fp32: the step's products go to accumulators of their own and are added to the tile's, so that a
+      // logit takes H / BK roundings at its full size and not H / 4
+      f32x4 part[kF32 ? NV : 1][kF32 ? NM : 1];
+      if (kF32)
 #pragma unroll
         for (int i = 0; i < NV; ++i)
 #pragma unroll
-          for (int j = 0; j < NM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bm[j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < NM; ++j) part[kF32 ? i : 0][kF32 ? j : 0] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < kRow / 64; ++ks) {
+        const int ch = ((4 * ks + c4) ^ rd_swz) << 4;
+        u32x4 av[NV], bm[NM];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) av[i] = *reinterpret_cast<const u32x4 *>(pv + i * 16 * kRow + ch);
+#pragma unroll
+        for (int j = 0; j < NM; ++j) bm[j] = *reinterpret_cast<const u32x4 *>(pm + j * 16 * kRow + ch);
+        if constexpr (kF32) {
+          // element e of the four lanes' chunks is one k-step of 4 (the same columns on both sides)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+#pragma unroll
+              for (int j = 0; j < NM; ++j)
+                part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av[i][e]), __uint_as_float(bm[j][e]), part[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int j = 0; j < NM; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[i]), __builtin_bit_cast(bf16x8, bm[j]), acc[i][j], 0, 0, 0);
+        }
       }
+      if (kF32)
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int j = 0; j < NM; ++j) acc[i][j] += part[kF32 ? i : 0][kF32 ? j : 0];
     }
     if (++cp_k == nk) {                                      // tile finished
       if (live) {
-        const int v0 = (stream + cp_tile * n_streams) * kGmV + wv * (NV * 16) + 4 * c4;
+        const int v0 = (stream + cp_tile * n_streams) * VT + wv * (NV * 16) + 4 * c4;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
           const int vbase = v0 + 16 * i;
@@ -402,21 +431,34 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   }
 }
 
-template <int BM, int WV, int BK>
-hipError_t launch_tiled(const AcceptArgs &a, hipStream_t st) {
-  constexpr int lds = (kGmV + BM) * BK * 2;
+template <class T, int VT, int BM, int WV, int kRow>
+hipError_t launch_tiled_vt(const AcceptArgs &a, hipStream_t st) {
+  constexpr int lds = (VT + BM) * kRow;
   static_assert(lds <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
-  hipLaunchKernelGGL((lm_head_tiled_kernel<BM, WV, BK>), dim3(a.n_cand), dim3(kGmWaves * 64), lds, st, a, (a.M + BM - 1) / BM);
+  hipLaunchKernelGGL((lm_head_tiled_kernel<T, VT, BM, WV, kRow>), dim3(a.n_cand), dim3(kGmWaves * 64), lds, st, a, (a.M + BM - 1) / BM);
   return hipGetLastError();
 }
 
-// Workgroups of the tiled kernel: two per compute unit (three at 64 rows, where registers and LDS
-// allow it), fewer if there are fewer tiles; a multiple of 8 per row block.
-int tiled_grid(int M, int V) {
-  const int blocks_m = (M + 255) / 256;
-  const int tiles = (V + kGmV - 1) / kGmV;
-  return std::min(kNumCU * (M > 64 ? 2 : 3), (tiles + 7) / 8 * 8 * blocks_m);
+// Rows of a vocabulary tile: 128, or 64 where tiles of 128 would leave compute units without one
+// (8,640 x 3456 at 248 rows, 68 tiles of 128: 75 us with tiles of 64; fp32 at 9 rows 56 us).
+int tiled_rows(int M, int V, int bm) { return (V + 127) / 128 * ((M + bm - 1) / bm) < kNumCU ? 64 : 128; }
+
+template <class T, int BM, int WV, int kRow>
+hipError_t launch_tiled(const AcceptArgs &a, hipStream_t st) {
+  return tiled_rows(a.M, a.V, BM) == 64 ? launch_tiled_vt<T, 64, BM, WV, kRow>(a, st) : launch_tiled_vt<T, 128, BM, WV, kRow>(a, st);
 }
+
+// Workgroups of the tiled kernel for row blocks of bm: two per compute unit (three at 64 rows, four
+// below, where registers and LDS allow it), fewer if there are fewer tiles; a multiple of 8 per row
+// block.
+int tiled_grid(int M, int V, int bm) {
+  const int blocks_m = (M + bm - 1) / bm, vt = tiled_rows(M, V, bm);
+  const int tiles = (V + vt - 1) / vt;
+  const int per_block = kNumCU * (bm > 64 ? 2 : bm > 32 ? 3 : 4) / (8 * blocks_m) * 8;
+  return std::min(per_block, (tiles + 7) / 8 * 8) * blocks_m;
+}
+int f32_block(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128; }
+
 // Up to here the k-split kernel, whose hidden rows sit in registers: at 32 rows 169 us against 182.
 constexpr int kKsMaxRows = 32;
 
@@ -424,17 +466,29 @@ constexpr int kKsMaxRows = 32;
 
 bool lm_head_mfma_supported(int dtype, int M, int H, int V) {
   (void)M; (void)V;
+  if (dtype == SPARROW_F32) return H % 4 == 0 && H <= (1 << 20);
   return dtype == SPARROW_BF16 && H % 8 == 0 && H <= 2 * kKsWaves * kKsSlice;     // two slices per wavefront
 }
 
-int accept_num_candidates(int, int M, int H, int V) { return M > kKsMaxRows ? tiled_grid(M, V) : ksplit_grid(H, V); }
+int accept_num_candidates(int dtype, int M, int H, int V) {
+  if (dtype == SPARROW_F32) return tiled_grid(M, V, f32_block(M));
+  return M > kKsMaxRows ? tiled_grid(M, V, M > 128 ? 256 : M > 64 ? 128 : 64) : ksplit_grid(H, V);
+}
 
 // Up to 32 rows: one pass over W per 32 rows, or 16.  Above 4,096 the hidden rows of a wavefront's two
 // slices fill its registers at 16 rows: passes of 16.
-hipError_t launch_lm_head_mfma(const AcceptArgs &a, hipStream_t st) {
-  if (a.M > 128) return launch_tiled<256, 1, 64>(a, st);
-  if (a.M > 64) return launch_tiled<128, 2, 128>(a, st);
-  if (a.M > kKsMaxRows) return launch_tiled<64, 2, 128>(a, st);
+hipError_t launch_lm_head_mfma(int dtype, const AcceptArgs &a, hipStream_t st) {
+  if (dtype == SPARROW_F32) {
+    switch (f32_block(a.M)) {
+      case 16: return launch_tiled<float, 16, 4, 256>(a, st);
+      case 32: return launch_tiled<float, 32, 4, 256>(a, st);
+      case 64: return launch_tiled<float, 64, 2, 256>(a, st);
+      default: return launch_tiled<float, 128, 2, 128>(a, st);
+    }
+  }
+  if (a.M > 128) return launch_tiled<bf16_t, 256, 1, 128>(a, st);
+  if (a.M > 64) return launch_tiled<bf16_t, 128, 2, 256>(a, st);
+  if (a.M > kKsMaxRows) return launch_tiled<bf16_t, 64, 2, 256>(a, st);
   const bool wide = a.H > kKsWaves * kKsSlice;
   for (int row0 = 0; row0 < a.M;) {
     const int left = a.M - row0;

@@ -683,7 +683,7 @@ static int accept_body(int32_t dtype, const void *hidden_rows, const void *lm_he
   a.bonus_id = bonus_id;
   a.logits = sample ? (float *)((char *)workspace + base) : nullptr;
   hipStream_t st = (hipStream_t)hip_stream;
-  hipError_t e = mfma ? launch_lm_head_mfma(a, st) : launch_lm_head_generic(dtype, a, st);
+  hipError_t e = mfma ? launch_lm_head_mfma(dtype, a, st) : launch_lm_head_generic(dtype, a, st);
   if (e != hipSuccess) return fail(SPARROW_ERR_DEVICE, "lm_head launch: %s", hipGetErrorString(e));
   if (!sample) {
     e = launch_accept_finalize(a, st);
@@ -819,7 +819,7 @@ int sparrow_draft_topk(int32_t dtype, const void *hidden_rows, const void *lm_he
   a.cand_idx = (int32_t *)(ws + round_up((size_t)M * n_cand * sizeof(float), 256));
   a.logits = (float *)(ws + base);
   hipStream_t st = (hipStream_t)hip_stream;
-  hipError_t e = mfma ? launch_lm_head_mfma(a, st) : launch_lm_head_generic(dtype, a, st);
+  hipError_t e = mfma ? launch_lm_head_mfma(dtype, a, st) : launch_lm_head_generic(dtype, a, st);
   if (e != hipSuccess) return fail(SPARROW_ERR_DEVICE, "lm_head launch: %s", hipGetErrorString(e));
   TopkArgs t;
   t.logits = a.logits; t.stats = (float *)(ws + base + lb);      // written by the chunk kernel

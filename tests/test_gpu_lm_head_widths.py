@@ -15,11 +15,12 @@ def sp():
     return sp_
 
 
-def _check(sp, H, V, M, seed):
+def _check(sp, H, V, M, seed, dtype="bfloat16"):
     import torch
+    dt = getattr(torch, dtype)
     g = torch.Generator(device="cuda").manual_seed(seed)
-    W = (torch.randn(V, H, generator=g, device="cuda") * H ** -0.5).to(torch.bfloat16)
-    hid = (torch.randn(M, H, generator=g, device="cuda") * 2.0).to(torch.bfloat16)
+    W = (torch.randn(V, H, generator=g, device="cuda") * H ** -0.5).to(dt)
+    hid = (torch.randn(M, H, generator=g, device="cuda") * 2.0).to(dt)
     logits = hid.double() @ W.double().t()
     # fp32 sums of H products: a random walk of H roundings of 2^-24, far below 64 * 2^-24 of the
     # largest possible partial sum |hid| . |W|
@@ -61,8 +62,22 @@ def test_many_rows(sp, H, V, M):
     _check(sp, H, V, M, H + V + M)
 
 
+@pytest.mark.parametrize("H", [4, 68, 260, 1028, 3584])
+@pytest.mark.parametrize("M,V", [(1, 5003), (16, 15), (17, 777), (33, 4096), (64, 130), (65, 2049), (300, 1000), (512, 129)])
+def test_fp32(sp, H, V, M):
+    _check(sp, H, V, M, H + V + M, "float32")
+
+
+@pytest.mark.parametrize("M,dtype", [(9, "float32"), (20, "float32"), (50, "float32"), (100, "float32"), (100, "bfloat16"),
+                                     (200, "bfloat16")])
+def test_tiles_of_128_vocabulary_rows(sp, M, dtype):
+    """Vocabularies that give every compute unit a tile of 128 rows."""
+    _check(sp, 264, 33001, M, M, dtype)
+
+
 def test_wider_than_the_matrix_core_kernels(sp):
     _check(sp, 8704, 300, 3, 1)
+    _check(sp, (1 << 20) + 4, 20, 2, 1, "float32")
 
 
 @pytest.mark.parametrize("H", [520, 5120])
