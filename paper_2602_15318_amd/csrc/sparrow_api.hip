@@ -81,13 +81,14 @@ float scale_log2_of(const sparrow_attn_desc *d) {
 // pure overhead traffic, so no more splits than it takes to occupy the chip.
 int plan_chunk(const sparrow_attn_desc *d, int32_t n_q, int64_t total_tokens, bool mfma) {
   const int R = n_q * (d->n_q_heads / d->n_kv_heads);
-  const int rbs = mfma ? verify_mfma_row_blocks(R) : (R + 15) / 16;
+  const int rbs = mfma ? verify_mfma_row_blocks(d->dtype, R) : (R + 15) / 16;
   int slots;
   if (mfma) {
     // The row blocks of one (split, KV head) run side by side on one XCD (they share the K/V
     // stream through its L2), one workgroup per compute unit: whole groups per XCD only.
     const int groups_per_xcd = (kNumCU / kNumXCD) / rbs > 0 ? (kNumCU / kNumXCD) / rbs : 1;
     slots = groups_per_xcd * kNumXCD / d->n_kv_heads;
+    if (d->dtype == SPARROW_F32) slots *= 2;               // two workgroups of 4 wavefronts per compute unit
   } else {
     slots = kNumCU / (d->n_kv_heads * rbs);
   }
@@ -102,9 +103,11 @@ int plan_chunk(const sparrow_attn_desc *d, int32_t n_q, int64_t total_tokens, bo
 // then walks the sequence alone, a 64-token step in ~0.8 us, so the line rises with the number of
 // workgroups that run side by side.  In one piece / in splits, us a call: chain of 5 over 100 tokens
 // (4 workgroups) 5.3 / 7.1, over 300 8.4 / 7.7; 4 trees of 30 nodes (32) over 200 13.0 / 14.6, over 400
-// 16.0 / 14.7; 16 chains of 8 (64) over 500 12.6 / 13.5, over 800 16.4 / 15.9.
+// 16.0 / 14.7; 16 chains of 8 (64) over 500 12.6 / 13.5, over 800 16.4 / 15.9.  fp32 steps are longer:
+// only what the plan gives one split anyway (over 100 rows 13.6 / 11.4).
 int direct_rows(const sparrow_attn_desc *d, int32_t B, int32_t n_q) {
-  const int workgroups = B * d->n_kv_heads * verify_mfma_row_blocks(n_q * (d->n_q_heads / d->n_kv_heads));
+  if (d->dtype == SPARROW_F32) return 64;
+  const int workgroups = B * d->n_kv_heads * verify_mfma_row_blocks(d->dtype, n_q * (d->n_q_heads / d->n_kv_heads));
   return std::min(512, 128 + 6 * workgroups);
 }
 
@@ -113,7 +116,7 @@ int direct_rows(const sparrow_attn_desc *d, int32_t B, int32_t n_q) {
 bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
   return verify_partial_mfma_supported(d->dtype, d->head_dim) &&
          d->kv_stride_token < (1ll << 24) &&
-         total_tokens * d->kv_stride_token * 2 < (1ll << 31);
+         total_tokens * d->kv_stride_token * (d->dtype == SPARROW_BF16 ? 2 : 4) < (1ll << 31);
 }
 
 // Splits per sequence in proportion to its length (at least one), within the budget of about one
@@ -155,13 +158,17 @@ int plan_splits(const sparrow_attn_desc *d, const int32_t *cu_seqlens, int32_t B
   return chunk;
 }
 
+// Shapes whose plain-ALU kernels remain the way out where the scratch at hand is too small for partials
+// padded to 64 rows.
+bool small_units_elsewhere(const sparrow_attn_desc *d) { return d->head_dim == 64 || d->dtype == SPARROW_F32; }
+
 // Workspace split: partial outputs first, then (max, sum) pairs, each rounded up to 256 bytes.
 void verify_ws_layout(const sparrow_attn_desc *d, int64_t slots, int32_t n_q, bool mfma,
                       size_t *bytes_o, size_t *bytes_ml) {
   if (mfma) {
     const int R = n_q * (d->n_q_heads / d->n_kv_heads);
     const size_t units = (size_t)slots * d->n_kv_heads * ((R + 63) / 64);
-    *bytes_o = round_up(units * verify_mfma_unit_floats_o() * sizeof(float), 256);
+    *bytes_o = round_up(units * verify_mfma_unit_floats_o(d->dtype, d->head_dim) * sizeof(float), 256);
     *bytes_ml = round_up(units * verify_mfma_unit_floats_ml() * sizeof(float), 256);
   } else {
     const size_t rows = (size_t)slots * n_q * d->n_q_heads;
@@ -464,7 +471,7 @@ size_t sparrow_verify_attn_workspace(const sparrow_attn_desc *desc, int32_t B, i
   };
   const bool mfma = use_mfma_verify(desc, total_tokens);
   size_t need = bytes(mfma);
-  if (mfma && desc->head_dim == 64) need = std::max(need, bytes(false));   // either kernel's partials fit
+  if (mfma && small_units_elsewhere(desc)) need = std::max(need, bytes(false));   // either kernel's partials fit
   return need;
 }
 
@@ -506,10 +513,10 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
   SeqTable tab;
   int chunk = plan_splits(desc, cu_seqlens, B, n_q, total, mfma, &tab);
   size_t need = verify_ws_bytes(desc, tab.cu_split[B], n_q, mfma);
-  // Heads of 64 go to the plain-ALU kernels where only their partials fit the scratch at hand: those
+  // Heads of 64 and fp32 go to the plain-ALU kernels where only their partials fit the scratch at hand: those
   // have no padding to 64 rows (64 sequences of one row over 64 KV heads: 1 MB against 37 MB).  The
   // static scratch also refuses what it cannot hold for them, so its limit is one rule per shape.
-  if (mfma && desc->head_dim == 64) {
+  if (mfma && small_units_elsewhere(desc)) {
     SeqTable tab_g;
     const int chunk_g = plan_splits(desc, cu_seqlens, B, n_q, total, false, &tab_g);
     const size_t need_g = verify_ws_bytes(desc, tab_g.cu_split[B], n_q, false);
@@ -563,12 +570,12 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
   a.out = out; a.lse = lse;
   hipStream_t st = (hipStream_t)hip_stream;
   if (passes & 1) {
-    hipError_t e = mfma ? launch_verify_partial_mfma(a, tab, st)
+    hipError_t e = mfma ? launch_verify_partial_mfma(desc->dtype, a, tab, st)
                         : launch_verify_partial_generic(desc->dtype, a, tab, st);
     if (e != hipSuccess) return fail(SPARROW_ERR_DEVICE, "verify partial launch: %s", hipGetErrorString(e));
   }
   if ((passes & 2) && !direct) {
-    hipError_t e = mfma ? launch_verify_combine_mfma(a, tab, st) : launch_verify_combine(desc->dtype, a, tab, st);
+    hipError_t e = mfma ? launch_verify_combine_mfma(desc->dtype, a, tab, st) : launch_verify_combine(desc->dtype, a, tab, st);
     if (e != hipSuccess) return fail(SPARROW_ERR_DEVICE, "verify combine launch: %s", hipGetErrorString(e));
   }
   return SPARROW_OK;

@@ -52,16 +52,19 @@ __device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int B, int slot)
 // Partial pass, plain-ALU version: any supported dtype / head_dim.
 hipError_t launch_verify_partial_generic(int dtype, const VerifyArgs &a, const SeqTable &tab,
                                          hipStream_t st);
-// Partial pass, matrix-core version: bf16, head_dim 64 or 128.
+// Partial pass, matrix-core versions (fp32 has a kernel of its own).
 bool verify_partial_mfma_supported(int dtype, int head_dim);
-hipError_t launch_verify_partial_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
+hipError_t launch_verify_partial_mfma(int dtype, const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
+hipError_t launch_verify_partial_f32(const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
+int verify_f32_row_blocks(int R);
 // Workgroups per (split, KV head) for R = n_q * (Hq / Hkv) rows.
-int verify_mfma_row_blocks(int R);
+int verify_mfma_row_blocks(int dtype, int R);
 // Its partials use a tiled layout of their own: workspace floats per (split, KV head, block of 64
 // rows) unit, and the matching combine pass.
-int64_t verify_mfma_unit_floats_o();
+constexpr int kMlFloats = 3;              // per row of a partial: max, sum, output scale
+int64_t verify_mfma_unit_floats_o(int dtype, int head_dim);
 int64_t verify_mfma_unit_floats_ml();
-hipError_t launch_verify_combine_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
+hipError_t launch_verify_combine_mfma(int dtype, const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
 // Second pass: merge the per-split partials of every (row, head).
 hipError_t launch_verify_combine(int dtype, const VerifyArgs &a, const SeqTable &tab,
                                  hipStream_t st);

@@ -6,7 +6,8 @@
 // produces, for one (split, KV head, block of 16 rows), the online-softmax partial
 //     m = max_t s_t,   l = sum_t 2^(s_t - m),   o = sum_t 2^(s_t - m) v_t
 // with s_t = scale * log2(e) * <q, k_t>; the combine pass merges the splits.  All arithmetic is
-// fp32, so this version also serves the fp32 configuration (tolerance 1e-5).
+// fp32, addressing 64-bit: it serves calls whose K/V span 2 GiB, and heads of 64 and fp32 where the
+// scratch is too small for the matrix-core kernels' partials.
 #include "common.hpp"
 #include "verify_attn.hpp"
 

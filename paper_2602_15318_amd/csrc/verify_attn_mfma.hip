@@ -29,7 +29,6 @@ namespace {
 
 constexpr int kTile = 32;                 // tokens per tile
 constexpr int kRowsPerWG = 64;
-constexpr int kMlFloats = 3;              // per row of a partial: max, sum, output scale
 constexpr int kStreams = 2;
 constexpr float kSlack = 8.0f;            // log2 units a score may exceed a row's reference point
 
@@ -543,7 +542,7 @@ __device__ __forceinline__ f32x4 partial_values(const f32x4 &w) { return w; }
 // kCombWaves = 16 for the decode-time case (one sequence cut into ~64 splits); 8 or 4 when no
 // sequence of the call has more than 32 or 16 splits (draft trees, batches), where 16 wavefronts
 // per output tile would mostly find nothing to merge.
-template <int kD, int kCombWaves>
+template <class T, int kD, int kCombWaves>
 __global__ void __launch_bounds__(64 * kCombWaves)
 verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
   __shared__ f32x4 xo[kCombWaves][64];
@@ -562,7 +561,7 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
   const int n = lane & 15, c4 = lane >> 4;
   const int R = a.n_q * g;
   if (rb * kRowsPerWG + 16 * wq >= R) return;    // tile without rows (uniform)
-  constexpr bool kWide = kWideState<kD>;
+  constexpr bool kWide = kWideState<kD> || std::is_same<T, float>::value;    // fp32 partials
   typedef typename std::conditional<kWide, f32x4, u32x2>::type part_t;      // 4 values of a lane
   const part_t *po = reinterpret_cast<const part_t *>(a.part_o);
   float m_run = kNegBig, l_run = 0.f;
@@ -615,9 +614,11 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
       const int i_row = rho / g, h = c * g + rho % g;
       const int64_t orow = ((int64_t)b * a.n_q + i_row) * a.Hq + h;
       const float inv = 1.0f / l;
-      bf16_t *out = (bf16_t *)a.out + orow * kD + 16 * mt + 4 * c4;
-      u32x2 w0 = {pack_bf16x2(r[0] * inv, r[1] * inv), pack_bf16x2(r[2] * inv, r[3] * inv)};
-      *reinterpret_cast<u32x2 *>(out) = w0;
+      T *out = (T *)a.out + orow * kD + 16 * mt + 4 * c4;
+      if constexpr (std::is_same<T, float>::value)
+        *reinterpret_cast<f32x4 *>(out) = r * inv;
+      else
+        *reinterpret_cast<u32x2 *>(out) = (u32x2){pack_bf16x2(r[0] * inv, r[1] * inv), pack_bf16x2(r[2] * inv, r[3] * inv)};
       if (a.lse != nullptr && mt == 0 && c4 == 0) a.lse[orow] = (m + fast_log2(l)) * kLn2;
     }
   }
@@ -630,16 +631,18 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
 // reads bound them), 16.3 us here, launched call by call, with the same error against 64 bits (1.7e-3:
 // the output's own rounding).
 bool verify_partial_mfma_supported(int dtype, int head_dim) {
-  return dtype == SPARROW_BF16 && (head_dim == 128 || head_dim == 64);
+  return (dtype == SPARROW_BF16 || dtype == SPARROW_F32) && (head_dim == 128 || head_dim == 64);
 }
 
-// Floats of workspace per (split, KV head, row block) unit of the tiled partial layout.
-int64_t verify_mfma_unit_floats_o() { return 4096; }    // 16 KB: 64 rows of 128 halves or of 64 floats
+// Floats of workspace per (split, KV head, row block) unit of the tiled partial layout: 64 rows of 128
+// halves, or of floats.
+int64_t verify_mfma_unit_floats_o(int dtype, int head_dim) { return dtype == SPARROW_F32 ? 64 * head_dim : 4096; }
 int64_t verify_mfma_unit_floats_ml() { return kRowsPerWG * kMlFloats; }
 
 // Row blocks (workgroups per split and KV head) for R rows: blocks of three 64-row tiles unless
 // blocks of two leave fewer empty tiles (7 tiles: 2+2+2+1 beats 3+3+1, measured).
-int verify_mfma_row_blocks(int R) {
+int verify_mfma_row_blocks(int dtype, int R) {
+  if (dtype == SPARROW_F32) return verify_f32_row_blocks(R);
   const int tiles = (R + kRowsPerWG - 1) / kRowsPerWG;
   const int rbs3 = (tiles + 2) / 3, rbs2 = (tiles + 1) / 2;
   return rbs3 * 3 - tiles <= rbs2 * 2 - tiles ? rbs3 : rbs2;
@@ -648,7 +651,7 @@ int verify_mfma_row_blocks(int R) {
 template <int kD>
 static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
   const int R = a.n_q * (a.Hq / a.Hkv);
-  const int rbs = verify_mfma_row_blocks(R);
+  const int rbs = verify_mfma_row_blocks(SPARROW_BF16, R);
   PieceTable pt;
   int max_ns = 0;
   for (int b = 0; b < SPARROW_MAX_BATCH; ++b) {
@@ -681,11 +684,12 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_verify_partial_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
+hipError_t launch_verify_partial_mfma(int dtype, const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
+  if (dtype == SPARROW_F32) return launch_verify_partial_f32(a, tab, st);
   return a.d == 128 ? launch_partial<128>(a, tab, st) : launch_partial<64>(a, tab, st);
 }
 
-template <int kD>
+template <class T, int kD>
 static hipError_t launch_combine(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
   const int R = a.n_q * (a.Hq / a.Hkv);
   const int rbs = (R + kRowsPerWG - 1) / kRowsPerWG;
@@ -693,16 +697,17 @@ static hipError_t launch_combine(const VerifyArgs &a, const SeqTable &tab, hipSt
   int max_ns = 0;
   for (int b = 0; b < a.B; ++b) max_ns = std::max(max_ns, tab.cu_split[b + 1] - tab.cu_split[b]);
   if (max_ns > 32)
-    hipLaunchKernelGGL((verify_combine_tiled_kernel<kD, 16>), grid, dim3(64 * 16), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+    hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 16>), grid, dim3(64 * 16), 0, st, a, tab, rbs, a.Hq / a.Hkv);
   else if (max_ns > 16)
-    hipLaunchKernelGGL((verify_combine_tiled_kernel<kD, 8>), grid, dim3(64 * 8), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+    hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 8>), grid, dim3(64 * 8), 0, st, a, tab, rbs, a.Hq / a.Hkv);
   else
-    hipLaunchKernelGGL((verify_combine_tiled_kernel<kD, 4>), grid, dim3(64 * 4), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+    hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 4>), grid, dim3(64 * 4), 0, st, a, tab, rbs, a.Hq / a.Hkv);
   return hipGetLastError();
 }
 
-hipError_t launch_verify_combine_mfma(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
-  return a.d == 128 ? launch_combine<128>(a, tab, st) : launch_combine<64>(a, tab, st);
+hipError_t launch_verify_combine_mfma(int dtype, const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
+  if (dtype == SPARROW_F32) return a.d == 128 ? launch_combine<float, 128>(a, tab, st) : launch_combine<float, 64>(a, tab, st);
+  return a.d == 128 ? launch_combine<bf16_t, 128>(a, tab, st) : launch_combine<bf16_t, 64>(a, tab, st);
 }
 
 }  // namespace sparrow

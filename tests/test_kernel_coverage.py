@@ -19,31 +19,43 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
                               "test_gpu_parity_tree.py", "test_gpu_parity_hsr.py",
                               "test_gpu_parity_commit.py", "test_gpu_graph_and_passes.py")
 
+VF = "test_gpu_verify_f32.py"
 V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
 
 COVERAGE = {
-    # ---- verification attention, matrix cores (bf16): <head_dim, steps in flight, row tiles>
+    # ---- verification attention, matrix cores, bf16: <head_dim, steps in flight, row tiles>
     "verify_partial_mfma_kernel<128, 1, 1>": (A, "test_c5_bf16_26k_chain8_layer", "C5 layer, C2; chains up to 64 rows per KV head"),
     "verify_partial_mfma_kernel<128, 2, 1>": (A, "test_c4_bf16_ragged_batch8", "splits longer than 10 steps: ragged batch"),
     "verify_partial_mfma_kernel<128, 1, 2>": (A, "test_paper_sized_trees_at_26k_context", "16-node tree: one block of 128 rows, short splits"),
     "verify_partial_mfma_kernel<128, 2, 2>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree and the 30-node tree: blocks of 128 rows"),
     "verify_partial_mfma_kernel<128, 1, 3>": (A, "test_paper_sized_trees_at_26k_context", "48-, 44- and 25-node trees: blocks of 192 rows"),
-    "verify_combine_tiled_kernel<128, 16>": (A, "test_c5_bf16_26k_chain8_layer", "more than 32 splits per sequence"),
-    "verify_combine_tiled_kernel<128, 8>": (A, "test_paper_sized_trees_at_26k_context", "17 to 32 splits (30-, 48-node trees)"),
-    "verify_combine_tiled_kernel<128, 4>": (A, "test_c3_bf16_26k_tree60", "at most 16 splits (C3, C4, batches)"),
+    "verify_combine_tiled_kernel<unsigned short, 128, 16>": (A, "test_c5_bf16_26k_chain8_layer", "more than 32 splits per sequence"),
+    "verify_combine_tiled_kernel<unsigned short, 128, 8>": (A, "test_paper_sized_trees_at_26k_context", "17 to 32 splits (30-, 48-node trees)"),
+    "verify_combine_tiled_kernel<unsigned short, 128, 4>": (A, "test_c3_bf16_26k_tree60", "at most 16 splits (C3, C4, batches)"),
     "verify_partial_mfma_kernel<64, 1, 1>": (V64, "test_rows_and_contexts", "up to 64 rows, short contexts"),
     "verify_partial_mfma_kernel<64, 2, 1>": (V64, "test_batches_and_long_contexts", "26k chain, ragged batch"),
     "verify_partial_mfma_kernel<64, 1, 2>": (V64, "test_rows_and_contexts", "70, 240 and 480 rows"),
     "verify_partial_mfma_kernel<64, 2, 2>": (V64, "test_batches_and_long_contexts", "tree of 19 nodes at 26k"),
     "verify_partial_mfma_kernel<64, 1, 3>": (V64, "test_rows_and_contexts", "175 rows"),
-    "verify_combine_tiled_kernel<64, 16>": (V64, "test_batches_and_long_contexts", "26k chain: 64 splits"),
-    "verify_combine_tiled_kernel<64, 8>": (V64, "test_batches_and_long_contexts", "17 to 32 splits"),
-    "verify_combine_tiled_kernel<64, 4>": (V64, "test_rows_and_contexts", "short contexts"),
+    "verify_combine_tiled_kernel<unsigned short, 64, 16>": (V64, "test_batches_and_long_contexts", "26k chain: 64 splits"),
+    "verify_combine_tiled_kernel<unsigned short, 64, 8>": (V64, "test_batches_and_long_contexts", "17 to 32 splits"),
+    "verify_combine_tiled_kernel<unsigned short, 64, 4>": (V64, "test_rows_and_contexts", "short contexts"),
+    # fp32: <head_dim, row tiles>, <storage type, head_dim, wavefronts>
+    "verify_partial_f32_kernel<64, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
+    "verify_partial_f32_kernel<64, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
+    "verify_combine_tiled_kernel<float, 64, 16>": (VF, "test_batches_and_long_contexts", ""),
+    "verify_combine_tiled_kernel<float, 64, 8>": (VF, "test_rows_and_contexts", ""),
+    "verify_combine_tiled_kernel<float, 64, 4>": (VF, "test_rows_and_contexts", ""),
+    "verify_partial_f32_kernel<128, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
+    "verify_partial_f32_kernel<128, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
+    "verify_combine_tiled_kernel<float, 128, 16>": (VF, "test_batches_and_long_contexts", ""),
+    "verify_combine_tiled_kernel<float, 128, 8>": (VF, "test_rows_and_contexts", ""),
+    "verify_combine_tiled_kernel<float, 128, 4>": (VF, "test_rows_and_contexts", ""),
     # ---- verification attention, plain ALU: <storage type, head_dim>
-    "verify_partial_generic_kernel<float, 64>": (A, "test_c1_fp32", "C1"),
-    "verify_combine_kernel<float, 64>": (A, "test_c1_fp32", "C1"),
-    "verify_partial_generic_kernel<float, 128>": (A, "test_verify_context_lengths", "f32-8-2-128"),
-    "verify_combine_kernel<float, 128>": (A, "test_verify_context_lengths", "f32-8-2-128"),
+    "verify_partial_generic_kernel<float, 64>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
+    "verify_combine_kernel<float, 64>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
+    "verify_partial_generic_kernel<float, 128>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
+    "verify_combine_kernel<float, 128>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
     "verify_partial_generic_kernel<unsigned short, 64>": (V64, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
     "verify_combine_kernel<unsigned short, 64>": (V64, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
     "verify_partial_generic_kernel<unsigned short, 128>": (A, "test_kv_span_of_2_gib_takes_the_plain_alu_kernels", "K/V span of 2 GiB"),
