@@ -486,9 +486,10 @@ class TreePool:
     def __init__(self, width: int, depth: int, device="cuda"):
         cap = width + max(depth - 1, 0) * width * width
         self.width = width
-        self.tok = torch.zeros(cap, dtype=torch.int32, device=device)
-        self.par = torch.zeros(cap, dtype=torch.int32, device=device)
-        self.score = torch.zeros(cap, dtype=torch.float32, device=device)
+        part = (cap + 63) // 64 * 64
+        pool = torch.zeros(3 * part, dtype=torch.int32, device=device)      # one fill for the three arrays
+        self.tok, self.par = pool[:cap], pool[part:part + cap]
+        self.score = pool[2 * part:2 * part + cap].view(torch.float32)
         self.n = 0
         self.front = None
 

@@ -19,7 +19,7 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
                               "test_gpu_parity_tree.py", "test_gpu_parity_hsr.py",
                               "test_gpu_parity_commit.py", "test_gpu_graph_and_passes.py")
 
-VF = "test_gpu_verify_f32.py"
+VF, TS = "test_gpu_verify_f32.py", "test_gpu_tree_sizes.py"
 V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
 
 COVERAGE = {
@@ -92,7 +92,11 @@ COVERAGE = {
     "accept_sample_kernel": (AS, "test_accept_sample_matches_oracle", "deterministic children"),
     "accept_sample_q_kernel": (ASQ, "test_accept_sample_q_matches_oracle", "sampled draft"),
     # ---- dynamic draft tree
-    "topk_chunk_kernel": (T, "test_draft_topk", ""),
+    # <logits a thread owns>
+    "topk_chunk_kernel<1>": (T, "test_draft_topk", "vocabularies up to 16,384"),
+    "topk_chunk_kernel<4>": (TS, "test_topk_vocabularies", "up to 65,536"),
+    "topk_chunk_kernel<10>": (TS, "test_topk_vocabularies", "up to 163,840"),
+    "topk_chunk_kernel<16>": (TS, "test_topk_vocabularies", "up to 262,144"),
     "topk_merge_kernel": (T, "test_draft_topk", ""),
     "tree_expand_kernel": (T, "test_tree_expand_and_select", ""),
     "tree_select_kernel": (T, "test_tree_expand_and_select", ""),
