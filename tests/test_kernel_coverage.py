@@ -2,8 +2,8 @@
 oracle.  The table below is checked two ways on the CPU: its keys must be exactly the set of
 `__global__` instantiations the library holds (read from the library's host stubs, so a new
 template instance cannot appear without a line here), and every test it names must exist.  That
-each line is true was observed with a kernel trace of every GPU test file
-(profiles/gpu_test_suite_kernel_coverage.txt).
+the lines are true was observed with a kernel trace of every GPU test file for the instantiations
+that profiles/gpu_test_suite_kernel_coverage.txt lists.
 
 instantiation                                   test file : test (parameters)
 """
