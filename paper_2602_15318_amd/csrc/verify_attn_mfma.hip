@@ -83,10 +83,12 @@ struct PieceTable {
 };
 
 // Heads of 64 keep the intermediate state of an attention row in 32 bits (as the plain-ALU kernel
-// does): probabilities enter the output MFMA as the sum of two bf16 terms, row sums are added up on
-// the vector ALU, split partials are stored in fp32.  Heads of 128 round probabilities to bf16 and
-// partials to fp16.  The second output MFMA of a tile is hidden: with 64-wide heads a token brings
-// half the bytes and the same number of scores, and the kernel waits for memory or for the softmax.
+// does): probabilities enter the output MFMA as three bf16 terms that add up to their 24 bits, row
+// sums are added up on the vector ALU, split partials are stored in fp32.  Heads of 128 round
+// probabilities to bf16 and partials to fp16.  The second and third output MFMA of a tile are mostly
+// hidden: with 64-wide heads a token brings half the bytes and the same number of scores, and the kernel
+// waits for memory or for the softmax.  Against two terms (16 bits of a probability): four ragged
+// sequences of 6,001, 16/4 heads, chain of 8, 14.0 -> 14.5 us a call; 60-node tree at 26k 36.4 -> 39 to 41.
 template <int kD> constexpr bool kWideState = kD == 64;
 
 // kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
@@ -289,7 +291,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 
   // One step of one stream: 32*kSub tokens against the wavefront's 16 rows, one joint softmax
   // update (a single running-max / rescale for the whole step).
-  auto compute = [&](int st, int buf, auto na_tag) {
+  auto compute = [&](int st, int buf, auto na_tag) __attribute__((always_inline)) {
     constexpr int NA = decltype(na_tag)::value;   // live row tiles (the leading ones)
     const unsigned char *Ks = lds_at(strm, buf, 0);
     const unsigned char *Vs = lds_at(strm, buf, 1);
@@ -320,7 +322,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     const bool edge = tb + kSub * kTile > min(t1, L);   // uniform: split end or draft rows in reach
     if (kQT > 1) __builtin_amdgcn_sched_barrier(0);     // keep the V^T reads below the softmax
     bf16x8 pb[NA][kSub];
-    bf16x8 pl[kWide ? NA : 1][kSub];                    // kWide: what pb leaves of the probability
+    bf16x8 pm[kWide ? NA : 1][kSub], pl[kWide ? NA : 1][kSub];   // kWide: what pb leaves of the probability
 #pragma unroll
     for (int qt = 0; qt < NA; ++qt) {
       float sc[4 * kSlabs];
@@ -368,12 +370,15 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
           const float p = fast_exp2(fmaf(sc[8 * u + e], a.scale_log2, -m_run[qt]));
           if (!kMfmaRowSum) psum += p;
           if (kWide) {
-            // p = hi + lo: hi the leading 8 bits (cut off, so that lo has p's sign), lo the next 8.
-            // Where hi is not zero lo is at least 2^-126, far below p, so that an infinite V gives
-            // an infinity here and no 0 * inf.
+            // p = hi + mid + lo: the leading 8 bits (cut off, so that the rest has p's sign), the
+            // next 8, the last 8.  Where hi is not zero the others are at least 2^-126 (the median:
+            // rest < hi), far below p, so that an infinite V gives an infinity here and no 0 * inf.
             const float hi = __uint_as_float(__float_as_uint(p) & 0xffff0000u);
+            const float rest = __builtin_amdgcn_fmed3f(p - hi, 0x1p-126f, hi);
+            const float mid = __uint_as_float(__float_as_uint(rest) & 0xffff0000u);
             pb[qt][u][e] = (__bf16)hi;
-            pl[qt][u][e] = (__bf16)fmaxf(p - hi, fminf(hi, 0x1p-126f));
+            pm[qt][u][e] = (__bf16)mid;
+            pl[qt][u][e] = (__bf16)__builtin_amdgcn_fmed3f(rest - mid, 0x1p-126f, mid);
           } else {
             pb[qt][u][e] = (__bf16)p;
           }
@@ -400,7 +405,10 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 #pragma unroll
         for (int qt = 0; qt < NA; ++qt) {
           o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pb[qt][u], o_acc[qt][mt], 0, 0, 0);
-          if (kWide) o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pl[qt][u], o_acc[qt][mt], 0, 0, 0);
+          if (kWide) {
+            o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pm[qt][u], o_acc[qt][mt], 0, 0, 0);
+            o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pl[qt][u], o_acc[qt][mt], 0, 0, 0);
+          }
         }
       }
     }
@@ -410,7 +418,8 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   // A wavefront with a partly filled set of row tiles computes all of them (the empty ones on a zero
   // query): a second, one-tile instance of the step in the same kernel costs more registers than
   // the kernel has.
-  auto run = [&](int st, int buf) {
+  // (always_inline: as a call it would keep the wavefront's state in scratch memory)
+  auto run = [&](int st, int buf) __attribute__((always_inline)) {
     if (n_act > 0) compute(st, buf, std::integral_constant<int, kQT>{});
   };
 
@@ -628,7 +637,7 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
 
 // Both head sizes of the boundary.  Measured at d = 64 (16/4 heads, 4 ragged sequences of 6,001 on
 // average, chain of 8, 23.5 MB a call): 107 us with the plain-ALU kernels (fp32 multiply-adds and LDS
-// reads bound them), 16.3 us here, launched call by call, with the same error against 64 bits (1.7e-3:
+// reads bound them), 14.5 us here, launched call by call, with the same error against 64 bits (1.7e-3:
 // the output's own rounding).
 bool verify_partial_mfma_supported(int dtype, int head_dim) {
   return (dtype == SPARROW_BF16 || dtype == SPARROW_F32) && (head_dim == 128 || head_dim == 64);

@@ -25,7 +25,7 @@ def _cfg(Hq, Hkv):
 
 def _check(out, lse, ref, ref_lse, what):
     # the output's bf16 rounding (8 significant bits: half a unit is at most 2^-8 of the value) is all that is larger than fp32 sums: 2e-5 of the
-    # row's largest value covers those and the 2^-16 a probability loses as two bf16 terms
+    # row's largest value covers those
     bound = 2.0 ** -8 * np.abs(ref) + 2e-5 * np.abs(ref).max()
     assert np.all(np.abs(out - ref) <= 1.01 * bound), what
     assert np.abs(lse - ref_lse).max() <= 2e-5, f"{what}: lse"      # row sums stay in fp32
@@ -65,6 +65,26 @@ def test_an_infinite_value_row_stays_infinite(sp, oracle):
     hit[:, 4:8, 7] = True
     assert np.all(np.isposinf(out[hit])) and np.all(np.isfinite(out[~hit]))
     assert np.all(np.abs(out - ref)[~hit] <= 1.01 * (2.0 ** -8 * np.abs(ref) + 2e-5 * np.abs(ref).max())[~hit])
+
+
+def test_probabilities_keep_32_bits(sp):
+    """Three tokens whose weighted values cancel down to 2^-18 of their sizes: what is left shows the
+    probabilities' low bits.  Their own fp32 error (score, exponential) is a few units of 2^-24."""
+    import torch
+    Hkv, d = 16, 64
+    g = torch.Generator().manual_seed(11)
+    q, k = (torch.randn(n, Hkv, d, generator=g).bfloat16() for n in (1, 3))
+    p = torch.softmax(torch.einsum("hd,thd->ht", q[0].double(), k.double()) / 8.0, dim=1)       # [Hkv, 3]
+    v = torch.zeros(3, Hkv, d, dtype=torch.bfloat16)
+    v[0] = (1 + torch.rand(Hkv, d, generator=g)).bfloat16()
+    for i in (1, 2):
+        left = sum(p[:, j, None] * v[j].double() for j in range(i))
+        v[i] = (-left / p[:, i, None]).bfloat16()
+    ref = sum(p[:, j, None] * v[j].double() for j in range(3))
+    size = sum(p[:, j, None] * v[j].double().abs() for j in range(3))
+    out, _ = sp.verify_attn(q.cuda(), k.cuda(), v.cuda(), np.array([0, 3], dtype=np.int32), None, 1)
+    # each term within 2^-21 of its size, and the output's rounding
+    assert torch.all((out[0].cpu().double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -20 * size)
 
 
 def test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels(sp, oracle):
