@@ -15,14 +15,14 @@
 //   - the partial sums of the wavefronts meet in LDS and wavefront 0 runs the epilogue.
 // For the QKV step the tile's 16 weight rows are features f..f+7 and f+d/2..f+d/2+7 of one head,
 // so both halves of every rotary pair sit in the same tile (lanes l and l^32 of the result);
-// RMSNorm is folded in: the activations enter the B operand multiplied by gamma, as the sum of two
-// bf16 terms (the product needs up to 16 bits), and the row's 1/rms (from the squares each wavefront
+// RMSNorm is folded in: the activations enter the B operand multiplied by gamma, exactly, as the sum of two
+// bf16 terms (the product has up to 16 bits), and the row's 1/rms (from the squares each wavefront
 // sees in its own slices) scales the result.
 // One activation row runs a wavefront per output feature or rotary pair instead.
 //
 // Measured (FC + QKV, one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64, six
-// rows 141 + 67 -> 9.3 + 9.9 us, one row 56 + 22 -> 7.3 + 6.8; hidden 5,120, 40/8 heads of 128, 16 rows
-// 823 + 447 -> 31.6 + 31.1 us; hidden 1,024, 16/4 heads of 64, six rows 36 + 21 -> 4.8 + 6.4.
+// rows 141 + 67 -> 9.3 + 10.2 us, one row 56 + 22 -> 7.3 + 6.8; hidden 5,120, 40/8 heads of 128, 16 rows
+// 823 + 447 -> 31.6 + 32.5 us; hidden 1,024, 16/4 heads of 64, six rows 36 + 21 -> 4.8 + 6.5.
 #include "common.hpp"
 #include "hsr_input.hpp"
 
@@ -83,9 +83,9 @@ __device__ __forceinline__ void skinny_gemm(const bf16_t *W, int K, WRow wrow, X
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // activations times gamma, in place: xr the leading 8 bits of the products (cut off), gr the next 8.
-  // The fused multiply-add leaves gr the product's sign and, by 2^-22 of the product, never zero: an
-  // infinite weight then gives an infinity, and no 0 * inf or inf - inf.
+  // activations times gamma, in place: xr the leading 8 bits of the products (cut off), gr the other 8:
+  // the whole product.  Where the other 8 are zero gr is 2^-40 of the product, with its sign (elsewhere
+  // that share is rounded off): an infinite weight then gives an infinity, and no 0 * inf or inf - inf.
   auto convert = [&]() {
 #pragma unroll
     for (int ks = 0; ks < kPart; ++ks) {
@@ -98,7 +98,8 @@ __device__ __forceinline__ void skinny_gemm(const bf16_t *W, int K, WRow wrow, X
         ssq = fmaf(xf[e], xf[e], ssq);
         const float u = xf[e] * gf[e];
         hb[e] = __float_as_uint(u) & 0xffff0000u;
-        lo[e] = fmaf(__uint_as_float(hb[e]), -(1.0f - 0x1p-22f), u);
+        const float hi = __uint_as_float(hb[e]);
+        lo[e] = fmaf(hi, 0x1p-40f, u - hi);
       }
       xr[ks] = (u32x4){(hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3], (hb[4] >> 16) | hb[5], (hb[6] >> 16) | hb[7]};
       gr[kNorm ? ks : 0] = (u32x4){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]),

@@ -20,9 +20,8 @@ def _bf(g, *shape, std=1.0):
 
 
 def _close(got, ref, abs_sum, what):
-    # one rounding of the result to bf16 (at most 2^-8 of it), and of every product term at most 2^-16
-    # (activation times gamma as two bf16 terms) plus its share of the fp32 sums: 2^-15 of the sum of
-    # the terms' magnitudes covers both
+    # one rounding of the result to bf16 (at most 2^-8 of it) and the fp32 sums: 2^-15 of the sum of the
+    # terms' magnitudes covers them
     bound = 1.01 * 2.0 ** -8 * ref.abs() + 2.0 ** -15 * abs_sum
     excess = (got.double() - ref).abs() - bound
     assert float(excess.max()) <= 0, f"{what}: over the bound by {float(excess.max()):.3e}"
@@ -68,6 +67,25 @@ def test_draft_qkv_append(sp, H, Hq, Hkv, d, M):
     _close(vc[at], f[:, Hq + Hkv:], s[:, Hq + Hkv:], f"v H={H} M={M}")
     rest = np.setdiff1d(np.arange(80), rows)
     assert not kc[rest].any() and not vc[rest].any()
+
+
+@pytest.mark.parametrize("M", [1, 2, 17])
+def test_normalised_activations_enter_exactly(sp, M):
+    """An activation times its gamma has 16 bits.  Three products that cancel exactly leave nothing:
+    (1 + 2^-7)^2 - (1 + 2^-6) - 2^-14.  (At most 2^-38: the second bf16 term of a product is never zero.)"""
+    import torch
+    H, Hq, Hkv, d = 1032, 4, 2, 64
+    rng = np.random.default_rng(5)
+    z, gam = torch.ones(M, H, dtype=torch.bfloat16), torch.ones(H, dtype=torch.bfloat16)
+    z[:, 1::3] = gam[1::3] = 1 + 2.0 ** -7
+    w = torch.zeros((Hq + 2 * Hkv) * d, H, dtype=torch.bfloat16)
+    for f in range(w.shape[0]):
+        c = 3 * rng.integers(0, H // 3, size=3) + np.array([0, 1, 2])
+        w[f, c] = torch.tensor([-(1 + 2.0 ** -6), 1.0, -2.0 ** -14], dtype=torch.bfloat16)
+    one = torch.ones(M, d // 2, device="cuda")
+    kc, vc = (torch.ones(M, Hkv, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    q = sp.draft_qkv_append(z.cuda(), gam.cuda(), 1e-6, w.cuda(), None, one, one, np.arange(M), Hq, kc, vc)
+    assert max(float(t.abs().max()) for t in (q, kc, vc)) <= 2.0 ** -38
 
 
 @pytest.mark.parametrize("M", [1, 3])
