@@ -78,7 +78,7 @@ verify_partial_f32_kernel(VerifyArgs a, SeqTable tab, int rbs) {
   const unsigned int row_bytes = (unsigned int)a.stride_tok * 4u;
 
   // loader: thread -> rows tid / kChunks + kLdRows j, 16-byte chunk tid % kChunks; rows past the end of
-  // the split are clamped to its last token (loaded, never used)
+  // the split are clamped to its last token (their probability is zero)
   const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
   u32x4 stage[2 * kLd];
   auto issue = [&](int t) {
@@ -91,7 +91,15 @@ verify_partial_f32_kernel(VerifyArgs a, SeqTable tab, int rbs) {
       stage[kLd + j] = __builtin_nontemporal_load((const u32x4 *)(Vg + o));
     }
   };
-  auto stash = [&](int buf) {
+  auto stash = [&](int t, int buf) {
+    // values past the end of the split are zero, as in the plain-ALU kernel: a duplicate of an infinite
+    // last row would give 0 * inf
+    const int left = t1 - (t0 + t * kTile);
+    if (left < kTile) {                                    // uniform over the workgroup
+#pragma unroll
+      for (int j = 0; j < kLd; ++j)
+        if (ld_row + kLdRows * j >= left) stage[kLd + j] = (u32x4){0u, 0u, 0u, 0u};
+    }
     unsigned char *kb = lds + buf * 2 * kTileBytes, *vb = kb + kTileBytes;
 #pragma unroll
     for (int j = 0; j < kLd; ++j) {
@@ -212,7 +220,7 @@ verify_partial_f32_kernel(VerifyArgs a, SeqTable tab, int rbs) {
   // double buffered: a wavefront may write tile t + 1 while others still read tile t, and reaches tile
   // t + 2's writes only after the barrier of tile t + 1, behind which tile t has been read by all
   for (int t = 0; t < n_tiles; ++t) {
-    stash(t & 1);
+    stash(t, t & 1);
     issue(min(t + 1, n_tiles - 1));
     __syncthreads();
     if (n_act > 0) compute(t, t & 1);

@@ -175,7 +175,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 
   // ---- loader: in step `st` stream `strm` owns tiles (st*kStreams + strm)*kSub .. +kSub, i.e.
   // 32*kSub consecutive tokens; thread -> rows tid/kChunks + kLdRows j, 16-byte chunk tid%kChunks.  Rows past
-  // the end of the split are clamped to its last token (loaded, never used), so every load is
+  // the end of the split are clamped to its last token (their probability is zero), so every load is
   // unconditional and the number of loads in flight is a compile-time constant at every wait.
   const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
   constexpr int kLd = kSub * kTile / kLdRows;         // loads per step (per K and per V)
@@ -192,7 +192,17 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   };
   // row r of the step lands at byte r*kRowBytes + ((chunk ^ swz(r)) * 16); swz depends on r mod 8 only
   const int st_off = ld_row * kRowBytes + ((ld_ch ^ swz<kD>(ld_row)) << 4);
-  auto stash = [&](int buf, const u32x4 *sg) {
+  auto stash = [&](int buf, int st, u32x4 *sg) {
+    if (kWide) {
+      // values past the end of the split are zero, as in the plain-ALU kernel: a duplicate of an
+      // infinite last row would give 0 * inf
+      const int left = t1 - (t0 + (st * kStreams + strm) * kSub * kTile);
+      if (left < kSub * kTile) {                           // uniform over the wavefront
+#pragma unroll
+        for (int j = 0; j < kLd; ++j)
+          if (ld_row + kLdRows * j >= left) sg[kLd + j] = (u32x4){0u, 0u, 0u, 0u};
+      }
+    }
     unsigned char *kb = lds_at(strm, buf, 0), *vb = lds_at(strm, buf, 1);
 #pragma unroll
     for (int j = 0; j < kLd; ++j) {
@@ -431,7 +441,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     for (int p = 0; p < kPrefetch; ++p) {
       const int st = base + p;
       const int buf = st & 1;
-      stash(buf, stage[p]);
+      stash(buf, st, stage[p]);
       issue(st + kPrefetch, stage[p]);
       __syncthreads();
       if ((st * kStreams + strm) * kSub < n_tiles) run(st, buf);
@@ -443,7 +453,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     const int st = base + p;
     if (st < n_steps) {                    // uniform over the workgroup
       const int buf = st & 1;
-      stash(buf, stage[p]);
+      stash(buf, st, stage[p]);
       __syncthreads();
       if ((st * kStreams + strm) * kSub < n_tiles) run(st, buf);
     }
@@ -598,8 +608,10 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
 #pragma unroll
     for (int u = 0; u < kCombInFlight; ++u) {
       // weight of the split: its share of the softmax denominator (its output is normalised)
-      const float wgt = (sb + kCombWaves * u < s1) ? fast_exp2(ms[u] - mx) * ls[u] : 0.f;
+      const bool in = sb + kCombWaves * u < s1;
+      const float wgt = in ? fast_exp2(ms[u] - mx) * ls[u] : 0.f;
       l_run += wgt;
+      if (kWide && !in) pa[u] = part_t{};          // (uniform; a duplicate of an infinite partial: no 0 * inf)
       o += partial_values(pa[u]) * (wgt * cs[u]);
     }
   }

@@ -50,6 +50,20 @@ def test_batches_and_long_contexts(sp, oracle, Hq, Hkv, d, lengths, n_q, nodes):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L", [30, 97, 700, 3000])
+def test_an_infinite_value_in_the_last_row_stays_infinite(sp, d, L):
+    """The rows that fill up the last tile bring no 0 * inf."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(L)
+    q, k, v = (torch.randn(n, h, d, generator=g, device="cuda") for n, h in ((1, 8), (L + 1, 2), (L + 1, 2)))
+    v[L, 1, 7] = float("inf")
+    out, _ = sp.verify_attn(q, k, v, np.array([0, L + 1], dtype=np.int32), None, 1)
+    assert torch.isposinf(out[0, 4:, 7]).all()
+    out[0, 4:, 7] = 0
+    assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels(sp, oracle, d):
     import torch
     c = _case(64, 64, d, tuple(200 + 5 * i % 50 for i in range(64)), 1, 0)

@@ -87,6 +87,20 @@ def test_probabilities_keep_32_bits(sp):
     assert torch.all((out[0].cpu().double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -20 * size)
 
 
+@pytest.mark.parametrize("L", [30, 97, 700, 3000])
+def test_an_infinite_value_in_the_last_row_stays_infinite(sp, L):
+    """The last draft row, which only itself attends: its infinity reaches its own output and not, through
+    the rows that fill up the last tile, as 0 * inf."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(L)
+    q, k, v = (torch.randn(n, h, 64, generator=g, device="cuda").bfloat16() for n, h in ((1, 8), (L + 1, 2), (L + 1, 2)))
+    v[L, 1, 7] = float("inf")
+    out, _ = sp.verify_attn(q, k, v, np.array([0, L + 1], dtype=np.int32), None, 1)
+    assert torch.isposinf(out[0, 4:, 7]).all()
+    out[0, 4:, 7] = 0
+    assert torch.isfinite(out).all()
+
+
 def test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels(sp, oracle):
     """64 sequences of one row over 64 KV heads: the matrix-core partials (64-row units) are far larger
     than the plain-ALU ones.  The static scratch and a caller's small workspace still serve the call."""
