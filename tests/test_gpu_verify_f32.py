@@ -50,6 +50,21 @@ def test_batches_and_long_contexts(sp, oracle, Hq, Hkv, d, lengths, n_q, nodes):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L", [63, 126, 1500])
+def test_output_sums_are_short_chains(sp, d, L):
+    """Equal probabilities (a zero query): the output is the mean of the values and its error that of the
+    sums over the tokens.  A rounding at the sum's size is 2.6e-8 of it (0.3 * 2^-23 over the mantissa), a chain
+    of n additions from zero sqrt(n / 2) of them: 16 tokens at a time, a chain over those (at most 16) and some
+    six roundings where pieces are merged stay at sqrt(8 + 8 + 6) * 2.6e-8; one chain over 64 is at 1.5e-7."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(L)
+    k, v = (torch.randn(L + 1, 16, d, generator=g, device="cuda") for _ in range(2))
+    out, _ = sp.verify_attn(torch.zeros(1, 16, d, device="cuda"), k, v, np.array([0, L + 1], dtype=np.int32), None, 1)
+    ref = v.double().mean(dim=0)
+    assert float((out[0].double() - ref).norm() / ref.norm()) <= 1.25e-7
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("L", [30, 97, 700, 3000])
 def test_an_infinite_value_in_the_last_row_stays_infinite(sp, d, L):
     """The rows that fill up the last tile bring no 0 * inf."""
