@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/sparrow.h"
+#include "common.hpp"
 
 namespace sparrow {
 
@@ -47,6 +48,14 @@ __device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int B, int slot)
   int b = 0;
   while (b + 1 < B && tab.cu_split[b + 1] <= slot) ++b;
   return b;
+}
+
+// Natural-log sum-exp of a row: reference point m (log2 units) and sum l.  kWide: rounded once at its full
+// size.  (m may lie below the row's maximum; log2(l) is then larger than in the plain-ALU kernels and so are
+// the roundings of the other form.  Root mean square error over 6,000 fp32 tokens, 60 rows, heads of 128:
+// 4.9e-7 against 4.65e-7 there, 4.6e-7 in this form.)
+template <bool kWide> __device__ __forceinline__ float lse_of(float m, float l) {
+  return kWide ? fmaf(m, kLn2, fast_log2(l) * kLn2) : (m + fast_log2(l)) * kLn2;
 }
 
 // Partial pass, plain-ALU version: any supported dtype / head_dim.

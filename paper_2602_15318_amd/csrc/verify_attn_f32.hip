@@ -250,7 +250,7 @@ verify_partial_f32_kernel(VerifyArgs a, SeqTable tab, int rbs) {
       float *out = (float *)a.out + orow * kD + 4 * c4;
 #pragma unroll
       for (int mt = 0; mt < kMT; ++mt) *reinterpret_cast<f32x4 *>(out + 16 * mt) = o_acc[qt][mt] * inv_l;
-      if (a.lse != nullptr && c4 == 0) a.lse[orow] = (m_run[qt] + fast_log2(l_tot)) * kLn2;
+      if (a.lse != nullptr && c4 == 0) a.lse[orow] = lse_of<true>(m_run[qt], l_tot);
       continue;
     }
     const int64_t unit = ((int64_t)slot * a.Hkv + c) * rbs64 + rb * kQT + qt;

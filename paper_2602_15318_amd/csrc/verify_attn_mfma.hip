@@ -498,7 +498,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
             const f32x4 r = o_acc[qt][mt] * s0 + mo[(w * kMT + mt) * 64 + lane] * s1;
             *reinterpret_cast<u32x2 *>(out + 16 * mt) = (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
           }
-          if (a.lse != nullptr && c4 == 0) a.lse[orow] = (m_new + fast_log2(l_tot)) * kLn2;
+          if (a.lse != nullptr && c4 == 0) a.lse[orow] = lse_of<kWide>(m_new, l_tot);
         }
         continue;
       }
@@ -640,7 +640,7 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
         *reinterpret_cast<f32x4 *>(out) = r * inv;
       else
         *reinterpret_cast<u32x2 *>(out) = (u32x2){pack_bf16x2(r[0] * inv, r[1] * inv), pack_bf16x2(r[2] * inv, r[3] * inv)};
-      if (a.lse != nullptr && mt == 0 && c4 == 0) a.lse[orow] = (m + fast_log2(l)) * kLn2;
+      if (a.lse != nullptr && mt == 0 && c4 == 0) a.lse[orow] = lse_of<kWide>(m, l);
     }
   }
 }

@@ -64,6 +64,24 @@ def test_output_sums_are_short_chains(sp, d, L):
     assert float((out[0].double() - ref).norm() / ref.norm()) <= 1.25e-7
 
 
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_log_sum_exp_is_rounded_once_at_its_size(sp, dtype):
+    """Root mean square error of values near 7.9: the last rounding 0.29 * 2^-21 = 1.4e-7, scores and row sums
+    2.3e-7; a second rounding at 11.4 (log2 units), 0.29 * 2^-20 * ln 2, would make 3.3e-7 of it."""
+    import torch
+    L, n, Hq, Hkv, d = 1500, 60, 16, 4, 64
+    g = torch.Generator(device="cuda").manual_seed(2)
+    q, k, v = (torch.randn(t, h, d, generator=g, device="cuda").to(getattr(torch, dtype)) for t, h in ((n, Hq), (L + n, Hkv), (L + n, Hkv)))
+    _, lse = sp.verify_attn(q, k, v, np.array([0, L + n], dtype=np.int32), None, n)
+    hidden = torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1)
+    for h in range(Hq):
+        s = q[:, h].double() @ k[:, h // 4].double().t().contiguous() / 8.0
+        s[:, L:][hidden] = -float("inf")
+        err = lse[:, h].double() - torch.logsumexp(s, dim=1)
+        lse[:, h] = err.float()
+    assert float(lse.double().pow(2).mean().sqrt()) <= 3.0e-7
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("L", [30, 97, 700, 3000])
 def test_an_infinite_value_in_the_last_row_stays_infinite(sp, d, L):
