@@ -38,8 +38,12 @@ constexpr int kKsWaves = 8;               // most wavefronts of a workgroup
 //
 // NB = blocks of 16 hidden rows handled in one pass over W (1 or 2); the vocabulary group is
 // kKsGroup / NB tiles so that the partial logits in LDS stay at 4 KB per wavefront.
-// Measured: 152,064 x 3584 at 9 rows 167 us with the finalize pass (6.5 TB/s); 64,003 x 2048 at 9
-// rows 49 us, 32 rows 55 us; 151,936 x 2560 120 us.
+// A matrix instruction rounds its sums at the size they have reached, so a chain over a whole slice loses
+// more than the products deserve: pairs of instructions (64 products) start from zero and are added up in
+// fp64, and so are the wavefronts' shares.  Error of a logit 0.55e-7 of its size whatever H is (chains
+// over the slice in fp32: 0.65e-7 at H = 256, 1.35e-7 at 5,120; a plain-ALU sum 0.55 to 0.9e-7).
+// Measured: 152,064 x 3584 at 9 rows 165 us with the finalize pass (6.6 TB/s); 64,003 x 2048 at 9
+// rows 49 us, 32 rows 54 us; 151,936 x 2560 118 us.
 template <int SPW, int NB>
 __global__ void __launch_bounds__(kKsWaves * 64)
 lm_head_ksplit_kernel(AcceptArgs a, int row0) {
@@ -116,12 +120,11 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) { best[nb] = -INFINITY; best_i[nb] = 0x7fffffff; }
   for (int t = 0; t < n_tiles; ++t) {
-    f32x4 acc[NB][2];
+    double acc[NB][4];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      acc[nb][0] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      acc[nb][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    }
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[nb][i] = 0.0;
 #pragma unroll
     for (int sl = 0; sl < SPW; ++sl) {
 #pragma unroll
@@ -130,13 +133,17 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0) {
       issue(sl + 1 < SPW ? t : t + 1, sl + 1 < SPW ? sl + 1 : 0);
 #pragma unroll
       for (int ks = 0; ks < 16; ks += 2) {
+        if (NB > 1 && ks % 8 == 0) __builtin_amdgcn_sched_barrier(0);     // operands read further ahead spill registers
         const int ch0 = 4 * ks + c4, ch1 = ch0 + 4;
         const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch0 & ~15) | ((ch0 & 15) ^ n)) << 4));
         const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch1 & ~15) | ((ch1 & 15) ^ n)) << 4));
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          acc[nb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, hreg[nb][sl][ks], acc[nb][0], 0, 0, 0);
-          acc[nb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, hreg[nb][sl][ks + 1], acc[nb][1], 0, 0, 0);
+          f32x4 p = {0.f, 0.f, 0.f, 0.f};
+          p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, hreg[nb][sl][ks], p, 0, 0, 0);
+          p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, hreg[nb][sl][ks + 1], p, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[nb][i] += (double)p[i];
         }
       }
     }
@@ -144,7 +151,8 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0) {
     // the tile's partial logits go to LDS at once ([row block][wavefront][tile of the group]: G * NB
     // = 4 slots per wavefront whatever NB), not into registers held for the whole group
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) red[((nb * nw + w) * G + g) * 64 + lane] = acc[nb][0] + acc[nb][1];
+    for (int nb = 0; nb < NB; ++nb)
+      red[((nb * nw + w) * G + g) * 64 + lane] = (f32x4){(float)acc[nb][0], (float)acc[nb][1], (float)acc[nb][2], (float)acc[nb][3]};
     if (g == G - 1 || t == n_tiles - 1) {     // uniform over the workgroup
       // sum the group's partial logits over the wavefronts; the tiles of the group (the last group
       // may hold fewer than G) are dealt to the wavefronts
@@ -153,8 +161,13 @@ lm_head_ksplit_kernel(AcceptArgs a, int row0) {
         const int vbase = tile_row0(t - g + tg) + 4 * c4;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          f32x4 sum = red[((nb * nw + 0) * G + tg) * 64 + lane];
-          for (int ww = 1; ww < nw; ++ww) sum += red[((nb * nw + ww) * G + tg) * 64 + lane];
+          double sum64[4] = {0.0, 0.0, 0.0, 0.0};
+          for (int ww = 0; ww < nw; ++ww) {
+            const f32x4 part = red[((nb * nw + ww) * G + tg) * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum64[i] += (double)part[i];
+          }
+          const f32x4 sum = {(float)sum64[0], (float)sum64[1], (float)sum64[2], (float)sum64[3]};
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (vbase + i < V && sum[i] > best[nb]) { best[nb] = sum[i]; best_i[nb] = vbase + i; }

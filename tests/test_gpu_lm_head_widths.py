@@ -75,6 +75,29 @@ def test_tiles_of_128_vocabulary_rows(sp, M, dtype):
     _check(sp, 264, 33001, M, M, dtype)
 
 
+@pytest.mark.parametrize("H", [256, 520, 1000, 2568, 3584, 5120])
+@pytest.mark.parametrize("M", [1, 17])
+@pytest.mark.parametrize("dtype,limit", [("bfloat16", 0.62e-7)])
+def test_logits_carry_the_error_of_short_sums_only(sp, H, M, dtype, limit):
+    """The 2-norm error of the logits against 64 bits does not grow with the width.  A matrix instruction
+    rounds its sums at the size they have reached (about four times per 32 bf16 products, once per fp32
+    product, 0.3 * 2^-23 each): two bf16 instructions or four fp32 ones from zero are at 0.5e-7 and 0.77e-7
+    of the logit's size, the final rounding and that of the wavefronts' shares at 0.25e-7 each."""
+    import torch
+    import paper_2602_15318_amd.binding as bd
+    V, k, dt = 2049, 2, getattr(torch, dtype)
+    g = torch.Generator(device="cuda").manual_seed(H + M)
+    W = (torch.randn(V, H, generator=g, device="cuda") * 0.02).to(dt)
+    hid = torch.randn(M, H, generator=g, device="cuda").to(dt)
+    code = bd._dtype_code(W)
+    ws = torch.zeros(bd.lib.sparrow_draft_topk_workspace(code, M, H, V, k), dtype=torch.uint8, device="cuda")
+    sp.draft_topk(hid, W, k, workspace=ws)
+    at = bd.lib.sparrow_accept_workspace(code, 1, M - 1, H, V)          # the logits lie behind the candidates
+    logits = ws[at:at + 4 * M * V].view(torch.float32).view(M, V).double()
+    ref = hid.double() @ W.double().t()
+    assert float((logits - ref).norm() / ref.norm()) <= limit
+
+
 def test_wider_than_the_matrix_core_kernels(sp):
     _check(sp, 8704, 300, 3, 1)
     _check(sp, (1 << 20) + 4, 20, 2, 1, "float32")
