@@ -242,35 +242,42 @@ hipError_t launch_ksplit(const AcceptArgs &a, int row0, hipStream_t st) {
 // Tiled kernel for more than 32 hidden rows (draft trees, batches) and for fp32: one pass over W
 // whatever the number of rows up to 256 (fp32: 128), row blocks side by side above.
 //
-// A persistent workgroup of 4 wavefronts owns tiles of VT vocabulary rows x BM hidden rows and walks
-// the hidden size in steps of BK; the wavefronts form a WV x WM grid.  Both operands of a step travel
-// memory -> registers (requested one step ahead) -> LDS (rows of 2 BK bytes, 16-byte chunks
-// XOR-swizzled as in the attention kernel) -> MFMA operands.  The LDS tile is single-buffered: two or
-// three workgroups share a compute unit, and one's MFMAs run under the other's loads and LDS traffic
-// (one workgroup of 8 wavefronts with two buffers and up to 4 steps in flight, whose phases do not
-// overlap: 401 us at 248 rows against 355).  Rows past V or M and columns past H come back as zeros
-// from the bounds check of the buffer loads, so no size has to be a multiple of anything.
-// Steps of 128 (256 contiguous bytes of a weight row) serve up to 128 rows, where the weight stream
-// is the bound; at 256 rows LDS and matrix cores are, and steps of 64 keep two workgroups on a
-// compute unit.  152,064 x 3584 with the finalize pass, against passes of 64 rows by pairs of k-split
-// workgroups: 33 rows 182 (229) us, 64 rows 185 (225), 128 rows 233 (430), 248 rows 355 (834).
-// fp32 (v_mfma_f32_16x16x4: fp32 products and sums at 157 TFLOP/s), against the plain-ALU kernel:
-// 152,064 x 3584 at 9 rows 346 (1678) us = 6.3 TB/s, at 64 rows 658 (7436), at 248 rows 2620 (29300) =
-// 103 TFLOP/s; 32,000 x 1024 at 9 rows 32 (138).
-constexpr int kGmWaves = 4;
-
+// A persistent workgroup of 4 or 8 wavefronts owns tiles of VT vocabulary rows x BM hidden rows and walks
+// the hidden size in steps of kRow bytes of a row; the wavefronts form a WV x WM grid.  Both operands of a
+// step travel memory -> registers (requested one step ahead) -> LDS (16-byte chunks XOR-swizzled as in the
+// attention kernel) -> MFMA operands.  Where several workgroups share a compute unit the LDS tile is
+// single-buffered and one's MFMAs run under the other's loads and LDS traffic; a workgroup of 8
+// wavefronts has two tiles and one barrier per step (248 rows 515 -> 488 us).  Rows past V or M and columns
+// past H come back as zeros from the bounds check of the buffer loads, so no size has to be a multiple of
+// anything.
+// Sums: a matrix instruction rounds at the size its sums have reached (about four times per 32 bf16
+// products, once per fp32 product), so chains of two bf16 instructions or four fp32 ones start from zero
+// and are added up in fp64.  Error of a logit, against one fp32 chain over H (bf16) or over a step (fp32)
+// and against the plain-ALU kernels: bf16 0.5e-7 of its size at every width (0.86e-7 at H = 256, 3.7e-7 at
+// 3,584, 4.5e-7 at 5,120; 0.55 to 1.05e-7), fp32 0.8e-7 (1.2 to 2.7e-7; 0.78 to 1.9e-7).  The sums take
+// 8 registers per 16 x 16 tile and the additions two vector instructions per value: wavefront tiles are
+// 64 x 64 at most, and 256 rows take one workgroup of 8 wavefronts per compute unit.
+// 152,064 x 3584 with the finalize pass, us (with one fp32 chain; before this kernel, passes of 64 rows by
+// pairs of k-split workgroups): 64 rows 188 (183; 209), 128 rows 275 (232; 413), 248 rows 445
+// (350; 826).  Tiles of 128 rows for 248: 533 to 561; of 64: 590; one chain after the other instead of
+// the chains of a row of tiles side by side: 488.
+// fp32 (v_mfma_f32_16x16x4: fp32 products at 157 TFLOP/s; in brackets the plain-ALU kernel): 9 rows 335 (1678), 64 rows 735 (7324),
+// 248 rows 3124 (29370); 32,000 x 1024 at 9 rows 32 (137).
 template <int kRow> __device__ __forceinline__ int gm_swz(int row) {
   return kRow == 256 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
 }
 
-template <class T, int VT, int BM, int WV, int kRow>      // kRow: bytes of a row that a step covers
-__global__ void __launch_bounds__(kGmWaves * 64, 2)
+// LDS tiles: two where one workgroup of 8 wavefronts has the compute unit to itself
+constexpr int tiled_buffers(int waves) { return waves == 8 ? 2 : 1; }
+
+template <class T, int VT, int BM, int kWaves, int WV, int kRow>      // kRow: bytes of a row that a step covers
+__global__ void __launch_bounds__(kWaves * 64, 2)
 lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
-  constexpr int WM = kGmWaves / WV;
+  constexpr int WM = kWaves / WV;
   constexpr int NV = VT / WV / 16, NM = BM / WM / 16;      // 16-row tiles of a wavefront
   constexpr bool kF32 = std::is_same<T, float>::value;
   constexpr int kPer = Elem<T>::kPer16B, kChunks = kRow / 16, BK = kChunks * kPer;
-  constexpr int kLdRows = kGmWaves * 64 / kChunks;                      // rows that one load of the workgroup covers
+  constexpr int kLdRows = kWaves * 64 / kChunks;           // rows that one load of the workgroup covers
   constexpr int kLdV = VT / kLdRows, kLdM = BM / kLdRows;  // loads of a thread per step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -289,7 +296,7 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   const int nk = (H + BK - 1) / BK;
   const int n_steps = n_tiles * nk;
 
-  // loader: thread -> rows tid/8 + 64 j, 16-byte chunk tid%8 of the step's 128 bytes of a row
+  // loader: thread -> rows tid / kChunks + kLdRows j, 16-byte chunk tid % kChunks of the step's part of a row
   const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
   const unsigned int ld_off = (unsigned int)ld_row * row_bytes + (unsigned int)ld_ch * 16u;
   const __amdgpu_buffer_rsrc_t rs_m = __builtin_amdgcn_make_buffer_rsrc(
@@ -314,17 +321,20 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
     if (++is_k == nk) { is_k = 0; ++is_tile; }
   };
   const int st_off = ld_row * kRow + ((ld_ch ^ gm_swz<kRow>(ld_row)) << 4);
-  auto stash = [&]() {
-    unsigned char *p = smem + st_off;
+  constexpr int kTileBytes = (VT + BM) * kRow;
+  auto stash = [&](int buf) {
+    unsigned char *p = smem + buf * kTileBytes + st_off;
 #pragma unroll
     for (int j = 0; j < kLdV + kLdM; ++j) *reinterpret_cast<u32x4 *>(p + kLdRows * j * kRow) = sg[j];
   };
 
-  f32x4 acc[NV][NM];
+  double acc[NV][NM][4];
 #pragma unroll
   for (int i = 0; i < NV; ++i)
 #pragma unroll
-    for (int j = 0; j < NM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NM; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0;
   float best[NM];
   int best_i[NM];
 #pragma unroll
@@ -334,50 +344,45 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   const int rd_row = n * kRow, rd_swz = gm_swz<kRow>(n);
 
   int cp_tile = 0, cp_k = 0;
-  // One step: the operands of this step out of buffer `buf`, then (their latency covered) the next
-  // step's tiles out of the staging registers into the other buffer, then the MFMAs.
-  auto compute = [&]() {
+  // One step: operands out of LDS, chains of kChain 16-byte chunks from zero (64 bf16 products, 16 fp32
+  // ones), each added to the tile's running sums in fp64
+  constexpr int kChain = kF32 ? 1 : 2;
+  auto compute = [&](int buf) {
     if (live) {
-      const unsigned char *pv = smem + wv * (NV * 16 * kRow) + rd_row;
-      const unsigned char *pm = smem + (VT + wm * (NM * 16)) * kRow + rd_row;
-// fp32: the step's products go to accumulators of their own and are added to the tile's, so that a
-      // logit takes H / BK roundings at its full size and not H / 4
-      f32x4 part[kF32 ? NV : 1][kF32 ? NM : 1];
-      if (kF32)
+      const unsigned char *pv = smem + buf * kTileBytes + wv * (NV * 16 * kRow) + rd_row;
+      const unsigned char *pm = smem + buf * kTileBytes + (VT + wm * (NM * 16)) * kRow + rd_row;
 #pragma unroll
-        for (int i = 0; i < NV; ++i)
+      for (int ks = 0; ks < kRow / 64; ks += kChain) {
+        u32x4 bm[kChain][NM];
+        int ch[kChain];
 #pragma unroll
-          for (int j = 0; j < NM; ++j) part[kF32 ? i : 0][kF32 ? j : 0] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int x = 0; x < kChain; ++x) {
+          ch[x] = ((4 * (ks + x) + c4) ^ rd_swz) << 4;
 #pragma unroll
-      for (int ks = 0; ks < kRow / 64; ++ks) {
-        const int ch = ((4 * ks + c4) ^ rd_swz) << 4;
-        u32x4 av[NV], bm[NM];
+          for (int j = 0; j < NM; ++j) bm[x][j] = *reinterpret_cast<const u32x4 *>(pm + j * 16 * kRow + ch[x]);
+        }
 #pragma unroll
-        for (int i = 0; i < NV; ++i) av[i] = *reinterpret_cast<const u32x4 *>(pv + i * 16 * kRow + ch);
+        for (int i = 0; i < NV; ++i) {
+          u32x4 av[kChain];
 #pragma unroll
-        for (int j = 0; j < NM; ++j) bm[j] = *reinterpret_cast<const u32x4 *>(pm + j * 16 * kRow + ch);
-        if constexpr (kF32) {
-          // element e of the four lanes' chunks is one k-step of 4 (the same columns on both sides)
+          for (int x = 0; x < kChain; ++x) av[x] = *reinterpret_cast<const u32x4 *>(pv + i * 16 * kRow + ch[x]);
+          f32x4 p[NM];
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
+          for (int x = 0; x < (kF32 ? 4 : kChain); ++x)
 #pragma unroll
-            for (int i = 0; i < NV; ++i)
+            for (int j = 0; j < NM; ++j) {
+              if (x == 0) p[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+              if constexpr (kF32)       // element x of the four lanes' chunks is one k-step of 4 (the same columns on both sides)
+                p[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av[0][x]), __uint_as_float(bm[0][j][x]), p[j], 0, 0, 0);
+              else
+                p[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[x]), __builtin_bit_cast(bf16x8, bm[x][j]), p[j], 0, 0, 0);
+            }
 #pragma unroll
-              for (int j = 0; j < NM; ++j)
-                part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av[i][e]), __uint_as_float(bm[j][e]), part[i][j], 0, 0, 0);
-        } else {
+          for (int j = 0; j < NM; ++j)
 #pragma unroll
-          for (int i = 0; i < NV; ++i)
-#pragma unroll
-            for (int j = 0; j < NM; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[i]), __builtin_bit_cast(bf16x8, bm[j]), acc[i][j], 0, 0, 0);
+            for (int e = 0; e < 4; ++e) acc[i][j][e] += (double)p[j][e];
         }
       }
-      if (kF32)
-#pragma unroll
-        for (int i = 0; i < NV; ++i)
-#pragma unroll
-          for (int j = 0; j < NM; ++j) acc[i][j] += part[kF32 ? i : 0][kF32 ? j : 0];
     }
     if (++cp_k == nk) {                                      // tile finished
       if (live) {
@@ -390,11 +395,11 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
             const int row = m_wave + 16 * j + n;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const float lg = acc[i][j][e];
+              const float lg = (float)acc[i][j][e];
               if (vbase + e < V && lg > best[j]) { best[j] = lg; best_i[j] = vbase + e; }   // ascending: lowest wins
               if (a.logits != nullptr && vbase + e < V && row < a.M) a.logits[(int64_t)row * V + vbase + e] = lg;
+              acc[i][j][e] = 0.0;
             }
-            acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
           }
         }
       }
@@ -404,12 +409,26 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   };
 
   issue();
-  for (int s = 0; s < n_steps; ++s) {
-    stash();
-    __syncthreads();
+  if constexpr (tiled_buffers(kWaves) == 2) {
+    // one barrier per step: tile s + 1 goes into the buffer that every wavefront has read before the
+    // barrier of step s - 1
+    stash(0);
     issue();
-    compute();
     __syncthreads();
+    for (int s = 0; s < n_steps; ++s) {
+      stash((s + 1) & 1);
+      issue();
+      compute(s & 1);
+      __syncthreads();
+    }
+  } else {
+    for (int s = 0; s < n_steps; ++s) {
+      stash(0);
+      __syncthreads();
+      issue();
+      compute(0);
+      __syncthreads();
+    }
   }
 
   // one candidate per (workgroup, row): the four lanes of a column, then the WV wavefronts of a row
@@ -429,7 +448,7 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
     if (c4 == 0) { cv[wv * BM + wm * (NM * 16) + 16 * j + n] = bv; ci[wv * BM + wm * (NM * 16) + 16 * j + n] = bi; }
   }
   __syncthreads();
-  for (int r = tid; r < blocks_m * BM && r < a.M; r += kGmWaves * 64) {
+  for (int r = tid; r < blocks_m * BM && r < a.M; r += kWaves * 64) {
     float bv = -INFINITY;                                    // rows of the other block: a neutral candidate
     int bi = 0x7fffffff;
     if (r >= row0 && r < row0 + BM) {
@@ -444,11 +463,15 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   }
 }
 
-template <class T, int VT, int BM, int WV, int kRow>
+template <class T, int VT, int BM, int kWaves, int WV, int kRow>
 hipError_t launch_tiled_vt(const AcceptArgs &a, hipStream_t st) {
-  constexpr int lds = (VT + BM) * kRow;
-  static_assert(lds <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
-  hipLaunchKernelGGL((lm_head_tiled_kernel<T, VT, BM, WV, kRow>), dim3(a.n_cand), dim3(kGmWaves * 64), lds, st, a, (a.M + BM - 1) / BM);
+  constexpr int lds = tiled_buffers(kWaves) * (VT + BM) * kRow;
+  if (lds > 64 * 1024) {      // has to be allowed once per kernel
+    static const hipError_t attr = hipFuncSetAttribute((const void *)lm_head_tiled_kernel<T, VT, BM, kWaves, WV, kRow>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return attr;
+  }
+  hipLaunchKernelGGL((lm_head_tiled_kernel<T, VT, BM, kWaves, WV, kRow>), dim3(a.n_cand), dim3(kWaves * 64), lds, st, a, (a.M + BM - 1) / BM);
   return hipGetLastError();
 }
 
@@ -456,18 +479,18 @@ hipError_t launch_tiled_vt(const AcceptArgs &a, hipStream_t st) {
 // (8,640 x 3456 at 248 rows, 68 tiles of 128: 75 us with tiles of 64; fp32 at 9 rows 56 us).
 int tiled_rows(int M, int V, int bm) { return (V + 127) / 128 * ((M + bm - 1) / bm) < kNumCU ? 64 : 128; }
 
-template <class T, int BM, int WV, int kRow>
+template <class T, int BM, int kWaves, int WV, int kRow>
 hipError_t launch_tiled(const AcceptArgs &a, hipStream_t st) {
-  return tiled_rows(a.M, a.V, BM) == 64 ? launch_tiled_vt<T, 64, BM, WV, kRow>(a, st) : launch_tiled_vt<T, 128, BM, WV, kRow>(a, st);
+  return tiled_rows(a.M, a.V, BM) == 64 ? launch_tiled_vt<T, 64, BM, kWaves, WV, kRow>(a, st) : launch_tiled_vt<T, 128, BM, kWaves, WV, kRow>(a, st);
 }
 
-// Workgroups of the tiled kernel for row blocks of bm: two per compute unit (three at 64 rows, four
-// below, where registers and LDS allow it), fewer if there are fewer tiles; a multiple of 8 per row
-// block.
+// Workgroups of the tiled kernel for row blocks of bm: as many per compute unit as registers allow (one of
+// 8 wavefronts at 256 rows, two of 4 at 128, three at 64, four below), fewer if there are fewer tiles; a
+// multiple of 8 per row block.
 int tiled_grid(int M, int V, int bm) {
   const int blocks_m = (M + bm - 1) / bm, vt = tiled_rows(M, V, bm);
   const int tiles = (V + vt - 1) / vt;
-  const int per_block = kNumCU * (bm > 64 ? 2 : bm > 32 ? 3 : 4) / (8 * blocks_m) * 8;
+  const int per_block = kNumCU * (bm > 128 ? 1 : bm > 64 ? 2 : bm > 32 ? 3 : 4) / (8 * blocks_m) * 8;
   return std::min(per_block, (tiles + 7) / 8 * 8) * blocks_m;
 }
 int f32_block(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128; }
@@ -493,15 +516,15 @@ int accept_num_candidates(int dtype, int M, int H, int V) {
 hipError_t launch_lm_head_mfma(int dtype, const AcceptArgs &a, hipStream_t st) {
   if (dtype == SPARROW_F32) {
     switch (f32_block(a.M)) {
-      case 16: return launch_tiled<float, 16, 4, 256>(a, st);
-      case 32: return launch_tiled<float, 32, 4, 256>(a, st);
-      case 64: return launch_tiled<float, 64, 2, 256>(a, st);
-      default: return launch_tiled<float, 128, 2, 128>(a, st);
+      case 16: return launch_tiled<float, 16, 4, 4, 256>(a, st);
+      case 32: return launch_tiled<float, 32, 4, 4, 256>(a, st);
+      case 64: return launch_tiled<float, 64, 4, 2, 128>(a, st);
+      default: return launch_tiled<float, 128, 4, 2, 128>(a, st);
     }
   }
-  if (a.M > 128) return launch_tiled<bf16_t, 256, 1, 128>(a, st);
-  if (a.M > 64) return launch_tiled<bf16_t, 128, 2, 256>(a, st);
-  if (a.M > kKsMaxRows) return launch_tiled<bf16_t, 64, 2, 256>(a, st);
+  if (a.M > 128) return launch_tiled<bf16_t, 256, 8, 2, 128>(a, st);
+  if (a.M > 64) return launch_tiled<bf16_t, 128, 4, 2, 128>(a, st);
+  if (a.M > kKsMaxRows) return launch_tiled<bf16_t, 64, 4, 2, 128>(a, st);
   const bool wide = a.H > kKsWaves * kKsSlice;
   for (int row0 = 0; row0 < a.M;) {
     const int left = a.M - row0;

@@ -76,8 +76,8 @@ def test_tiles_of_128_vocabulary_rows(sp, M, dtype):
 
 
 @pytest.mark.parametrize("H", [256, 520, 1000, 2568, 3584, 5120])
-@pytest.mark.parametrize("M", [1, 17])
-@pytest.mark.parametrize("dtype,limit", [("bfloat16", 0.62e-7)])
+@pytest.mark.parametrize("M", [1, 17, 33, 65, 129, 300])
+@pytest.mark.parametrize("dtype,limit", [("bfloat16", 0.62e-7), ("float32", 0.9e-7)])
 def test_logits_carry_the_error_of_short_sums_only(sp, H, M, dtype, limit):
     """The 2-norm error of the logits against 64 bits does not grow with the width.  A matrix instruction
     rounds its sums at the size they have reached (about four times per 32 bf16 products, once per fp32

@@ -72,21 +72,21 @@ COVERAGE = {
     "lm_head_ksplit_kernel<1, 1>": (AC, "test_c5_full_vocab_accept", "at most 16 rows"),
     "lm_head_ksplit_kernel<1, 2>": (AC, "test_accept_shapes", "bf16-1024-9000-4-7: 17-32 rows"),
     "lm_head_ksplit_kernel<2, 1>": (LM, "test_hidden_sizes", "hidden above 4,096"),
-    # <storage type, vocabulary rows and hidden rows of a tile, wavefronts along the vocabulary, bytes of a row per step>
-    "lm_head_tiled_kernel<float, 64, 16, 4, 256>": (LM, "test_fp32", "fp32, up to 16 rows"),
-    "lm_head_tiled_kernel<float, 128, 16, 4, 256>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 16 rows"),
-    "lm_head_tiled_kernel<float, 64, 32, 4, 256>": (LM, "test_fp32", "fp32, up to 32 rows"),
-    "lm_head_tiled_kernel<float, 128, 32, 4, 256>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 32 rows"),
-    "lm_head_tiled_kernel<float, 64, 64, 2, 256>": (LM, "test_fp32", "fp32, up to 64 rows"),
-    "lm_head_tiled_kernel<float, 128, 64, 2, 256>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 64 rows"),
-    "lm_head_tiled_kernel<float, 64, 128, 2, 128>": (LM, "test_fp32", "fp32, up to 128 rows"),
-    "lm_head_tiled_kernel<float, 128, 128, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 128 rows"),
-    "lm_head_tiled_kernel<unsigned short, 64, 64, 2, 256>": (LM, "test_hidden_sizes", "bf16, up to 64 rows"),
-    "lm_head_tiled_kernel<unsigned short, 128, 64, 2, 256>": (LM, "test_whole_vocabularies", "bf16, up to 64 rows"),
-    "lm_head_tiled_kernel<unsigned short, 64, 128, 2, 256>": (LM, "test_many_rows", "bf16, up to 128 rows"),
-    "lm_head_tiled_kernel<unsigned short, 128, 128, 2, 256>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 128 rows"),
-    "lm_head_tiled_kernel<unsigned short, 64, 256, 1, 128>": (LM, "test_many_rows", "bf16, up to 256 rows"),
-    "lm_head_tiled_kernel<unsigned short, 128, 256, 1, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 256 rows"),
+    # <storage type, vocabulary rows and hidden rows of a tile, wavefronts, of these along the vocabulary, bytes of a row per step>
+    "lm_head_tiled_kernel<float, 64, 16, 4, 4, 256>": (LM, "test_fp32", "fp32, up to 16 rows"),
+    "lm_head_tiled_kernel<float, 128, 16, 4, 4, 256>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 16 rows"),
+    "lm_head_tiled_kernel<float, 64, 32, 4, 4, 256>": (LM, "test_fp32", "fp32, up to 32 rows"),
+    "lm_head_tiled_kernel<float, 128, 32, 4, 4, 256>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 32 rows"),
+    "lm_head_tiled_kernel<float, 64, 64, 4, 2, 128>": (LM, "test_fp32", "fp32, up to 64 rows"),
+    "lm_head_tiled_kernel<float, 128, 64, 4, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 64 rows"),
+    "lm_head_tiled_kernel<float, 64, 128, 4, 2, 128>": (LM, "test_fp32", "fp32, up to 128 rows"),
+    "lm_head_tiled_kernel<float, 128, 128, 4, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 128 rows"),
+    "lm_head_tiled_kernel<unsigned short, 64, 64, 4, 2, 128>": (LM, "test_hidden_sizes", "bf16, up to 64 rows"),
+    "lm_head_tiled_kernel<unsigned short, 128, 64, 4, 2, 128>": (LM, "test_whole_vocabularies", "bf16, up to 64 rows"),
+    "lm_head_tiled_kernel<unsigned short, 64, 128, 4, 2, 128>": (LM, "test_many_rows", "bf16, up to 128 rows"),
+    "lm_head_tiled_kernel<unsigned short, 128, 128, 4, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 128 rows"),
+    "lm_head_tiled_kernel<unsigned short, 64, 256, 8, 2, 128>": (LM, "test_many_rows", "bf16, up to 256 rows"),
+    "lm_head_tiled_kernel<unsigned short, 128, 256, 8, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 256 rows"),
     "accept_finalize_kernel": (AC, "test_accept_shapes", "every greedy case"),
     "logit_stats_kernel": (AS, "test_accept_sample_matches_oracle", "every stochastic case"),
     "accept_sample_kernel": (AS, "test_accept_sample_matches_oracle", "deterministic children"),
