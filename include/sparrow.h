@@ -199,7 +199,8 @@ int sparrow_verify_attn_static(const sparrow_attn_desc *desc, const void *q, con
  *  accept_len  dev int32 out [B]        in [0, tree depth]
  *  accept_path dev int32 out [B*n_q]    accepted node indices root-first, -1 padded
  *  bonus_id    dev int32 out [B]        target token at the last accepted row
- *  workspace   dev, at least sparrow_accept_workspace() bytes (per-tile argmax candidates)
+ *  workspace   dev, at least sparrow_accept_workspace() bytes (per-tile argmax candidates); the query
+ *              never falls as B or n_q grow, so the largest batch's serves every smaller one
  *  Limits: B*(n_q+1) <= SPARROW_MAX_ACCEPT_ROWS logit rows (the weights are streamed once per 64
  *  rows).  n_q = 0 is allowed (plain greedy decode of row 0).
  * sparrow_accept_trees: the same with one draft tree per sequence (a batch of requests that each

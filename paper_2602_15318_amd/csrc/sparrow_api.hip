@@ -602,12 +602,23 @@ static int accept_candidates(int32_t dtype, int M, int H, int V) {
   return generic_num_candidates(V);
 }
 
+// Bytes of the argmax candidates of M rows.
+static size_t accept_cand_bytes(int32_t dtype, int M, int hidden, int vocab) {
+  const size_t n = (size_t)M * accept_candidates(dtype, M, hidden, vocab);
+  return round_up(n * sizeof(float), 256) + round_up(n * sizeof(int32_t), 256);
+}
+
+// The candidates per row fall where a wider row block takes over: the query is the largest need of any
+// row count up to M, so that a workspace sized for the largest batch serves every smaller one.  Within a
+// row block the need grows with the rows, but for blocks side by side, which share the compute units.
 size_t sparrow_accept_workspace(int32_t dtype, int32_t B, int32_t n_q, int32_t hidden,
                                 int32_t vocab) {
   if (B <= 0 || n_q < 0 || hidden <= 0 || vocab <= 0) return 0;
   const int M = B * (n_q + 1);
-  const size_t n = (size_t)M * accept_candidates(dtype, M, hidden, vocab);
-  return round_up(n * sizeof(float), 256) + round_up(n * sizeof(int32_t), 256);
+  size_t need = accept_cand_bytes(dtype, M, hidden, vocab);
+  for (int m = (std::min(M, kAcceptMaxRows) - 1) / 16 * 16; m > 0; m -= 16)
+    need = std::max(need, accept_cand_bytes(dtype, m, hidden, vocab));
+  return need;
 }
 
 // Shared body of the greedy and the stochastic acceptance.  sample == nullptr: greedy.

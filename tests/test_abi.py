@@ -254,3 +254,16 @@ def test_debug_validators_on_host_arrays(lib):
     for bad in ([0, 4, 10, 1, 3], [0, 4, 4, 1, 3], [4, 0, 9, 1, 3], [0, 4, 9, 1, 4], [-1, 4, 9, 1, 3]):
         assert call(np.array(bad, dtype=np.int32)) == INVALID, bad
     assert call(tix, x=np.array([0, 3, 3], dtype=np.int32)) == INVALID               # empty text domain
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("hidden,vocab", [(256, 32000), (512, 40), (520, 5003), (1024, 152064), (3584, 152064), (5120, 64003), (8704, 300)])
+def test_acceptance_workspaces_never_shrink_with_more_rows(lib, dtype, hidden, vocab):
+    """A workspace sized for the largest batch serves every smaller one: the row blocks of the lm_head kernels
+    change at 16, 32, 64, 128 and 256 rows, and with them the candidates per row."""
+    for query in (lambda m: lib.sparrow_accept_workspace(dtype, m, 0, hidden, vocab),
+                  lambda m: lib.sparrow_accept_workspace(dtype, 1, m - 1, hidden, vocab),
+                  lambda m: lib.sparrow_accept_sample_workspace(dtype, m, 0, hidden, vocab),
+                  lambda m: lib.sparrow_draft_topk_workspace(dtype, m, hidden, vocab, 8)):
+        sizes = [query(m) for m in range(1, 513)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:]))
