@@ -55,6 +55,13 @@ def test_batches_and_long_contexts(sp, oracle, lengths, n_q, nodes):
     _run(sp, oracle, 28, 4, lengths, n_q, nodes)
 
 
+@pytest.mark.parametrize("Hq,Hkv,lengths,nodes", [(28, 4, (26112,), 60), (32, 8, tuple(4129 + 300 * (i % 3 - 1) for i in range(12)), 30)])
+def test_two_row_tiles_over_long_pieces(sp, oracle, Hq, Hkv, lengths, nodes):
+    """More than ten steps per piece at blocks of 128 rows: two steps in flight, the number of steps odd (13 at 26k)
+    and mixed."""
+    _run(sp, oracle, Hq, Hkv, lengths, 0, nodes)
+
+
 def test_an_infinite_value_row_stays_infinite(sp, oracle):
     """One infinite V element: that output column is infinite, the others are as they were."""
     c = wl.verify_case(_cfg(16, 4), seed=5, layouts=(((wl.TEXT, 700),),), n_q=4, parent=None)

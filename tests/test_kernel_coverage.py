@@ -2,8 +2,8 @@
 oracle.  The table below is checked two ways on the CPU: its keys must be exactly the set of
 `__global__` instantiations the library holds (read from the library's host stubs, so a new
 template instance cannot appear without a line here), and every test it names must exist.  That
-the lines are true was observed with a kernel trace of every GPU test file for the instantiations
-that profiles/gpu_test_suite_kernel_coverage.txt lists.
+every instantiation runs in the test file named for it was observed with a kernel trace of all GPU test
+files (profiles/gpu_test_suite_kernel_coverage.txt).
 
 instantiation                                   test file : test (parameters)
 """
@@ -21,11 +21,12 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
 
 VF, TS = "test_gpu_verify_f32.py", "test_gpu_tree_sizes.py"
 V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
+VP = "test_gpu_verify_plain_alu.py"
 
 COVERAGE = {
     # ---- verification attention, matrix cores, bf16: <head_dim, steps in flight, row tiles>
     "verify_partial_mfma_kernel<128, 1, 1>": (A, "test_c5_bf16_26k_chain8_layer", "C5 layer, C2; chains up to 64 rows per KV head"),
-    "verify_partial_mfma_kernel<128, 2, 1>": (A, "test_c4_bf16_ragged_batch8", "splits longer than 10 steps: ragged batch"),
+    "verify_partial_mfma_kernel<128, 2, 1>": (A, "test_c4_bf16_ragged_batch8", "splits of four steps and more: ragged batch"),
     "verify_partial_mfma_kernel<128, 1, 2>": (A, "test_paper_sized_trees_at_26k_context", "16-node tree: one block of 128 rows, short splits"),
     "verify_partial_mfma_kernel<128, 2, 2>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree and the 30-node tree: blocks of 128 rows"),
     "verify_partial_mfma_kernel<128, 1, 3>": (A, "test_paper_sized_trees_at_26k_context", "48-, 44- and 25-node trees: blocks of 192 rows"),
@@ -35,7 +36,7 @@ COVERAGE = {
     "verify_partial_mfma_kernel<64, 1, 1>": (V64, "test_rows_and_contexts", "up to 64 rows, short contexts"),
     "verify_partial_mfma_kernel<64, 2, 1>": (V64, "test_batches_and_long_contexts", "26k chain, ragged batch"),
     "verify_partial_mfma_kernel<64, 1, 2>": (V64, "test_rows_and_contexts", "70, 240 and 480 rows"),
-    "verify_partial_mfma_kernel<64, 2, 2>": (V64, "test_batches_and_long_contexts", "tree of 19 nodes at 26k"),
+    "verify_partial_mfma_kernel<64, 2, 2>": (V64, "test_two_row_tiles_over_long_pieces", "60 nodes at 26k, 12 trees of 30 at 4k"),
     "verify_partial_mfma_kernel<64, 1, 3>": (V64, "test_rows_and_contexts", "175 rows"),
     "verify_combine_tiled_kernel<unsigned short, 64, 16>": (V64, "test_batches_and_long_contexts", "26k chain: 64 splits"),
     "verify_combine_tiled_kernel<unsigned short, 64, 8>": (V64, "test_batches_and_long_contexts", "17 to 32 splits"),
@@ -52,12 +53,12 @@ COVERAGE = {
     "verify_combine_tiled_kernel<float, 128, 8>": (VF, "test_rows_and_contexts", ""),
     "verify_combine_tiled_kernel<float, 128, 4>": (VF, "test_rows_and_contexts", ""),
     # ---- verification attention, plain ALU: <storage type, head_dim>
-    "verify_partial_generic_kernel<float, 64>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
-    "verify_combine_kernel<float, 64>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
-    "verify_partial_generic_kernel<float, 128>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
-    "verify_combine_kernel<float, 128>": (VF, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
-    "verify_partial_generic_kernel<unsigned short, 64>": (V64, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
-    "verify_combine_kernel<unsigned short, 64>": (V64, "test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels", "static scratch"),
+    "verify_partial_generic_kernel<float, 64>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
+    "verify_combine_kernel<float, 64>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
+    "verify_partial_generic_kernel<float, 128>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
+    "verify_combine_kernel<float, 128>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
+    "verify_partial_generic_kernel<unsigned short, 64>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
+    "verify_combine_kernel<unsigned short, 64>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
     "verify_partial_generic_kernel<unsigned short, 128>": (A, "test_kv_span_of_2_gib_takes_the_plain_alu_kernels", "K/V span of 2 GiB"),
     "verify_combine_kernel<unsigned short, 128>": (A, "test_kv_span_of_2_gib_takes_the_plain_alu_kernels", "K/V span of 2 GiB"),
     # ---- draft window attention: <storage type, head_dim>
