@@ -135,7 +135,11 @@ int sparrow_draft_window_attn(const sparrow_attn_desc *desc, const void *q, cons
  *  out        dev [B*n_q, Hq, d]
  *  lse        dev float [B*n_q, Hq] or NULL
  *  workspace  dev, at least sparrow_verify_attn_workspace() bytes, 256-byte aligned; holds the
- *             per-split partial results in a format internal to the library
+ *             per-split partial results in a format internal to the library.  The query holds for its
+ *             B, n_q and total_tokens; it may fall as n_q grows (other numbers of splits), so a
+ *             workspace for several shapes is sized by the largest of their queries.  With less
+ *             than the query fp32 and heads of 64 still run if the plain-ALU kernels' partials fit
+ *             (5 to 13 times slower on long contexts); otherwise SPARROW_ERR_WORKSPACE
  *  total_tokens = cu_seqlens[B] - cu_seqlens[0], the rows of the call's sequences
  *  B = 0 or n_q = 0: SPARROW_OK and nothing is enqueued.
  */
@@ -201,8 +205,9 @@ int sparrow_verify_attn_static(const sparrow_attn_desc *desc, const void *q, con
  *  bonus_id    dev int32 out [B]        target token at the last accepted row
  *  workspace   dev, at least sparrow_accept_workspace() bytes (per-tile argmax candidates); the query
  *              never falls as B or n_q grow, so the largest batch's serves every smaller one
- *  Limits: B*(n_q+1) <= SPARROW_MAX_ACCEPT_ROWS logit rows (the weights are streamed once per 64
- *  rows).  n_q = 0 is allowed (plain greedy decode of row 0).
+ *  Limits: B*(n_q+1) <= SPARROW_MAX_ACCEPT_ROWS logit rows.  The weights are streamed from memory once
+ *  per 256 rows (fp32: per 128; bf16 with hidden > 4,096 and 17 to 32 rows: twice; bf16 with hidden >
+ *  8,192: once per 8 rows, without the matrix cores).  n_q = 0 is allowed (plain greedy decode of row 0).
  * sparrow_accept_trees: the same with one draft tree per sequence (a batch of requests that each
  *  grew a dynamic tree): parent dev int32 [B, parent_stride], parent_stride >= n_q (0 = the shared
  *  [n_q] form of sparrow_accept).

@@ -1,6 +1,7 @@
 // Greedy acceptance, plain-ALU lm_head pass and the finalize pass.
 //
-// Step 1 (this file: hidden sizes beyond the matrix-core kernels of accept_mfma.hip): logits of the
+// Step 1 (this file: hidden sizes beyond the matrix-core kernels of accept_mfma.hip, bf16 above 8,192 and fp32
+// above 2^20, which the entry points accept as they always did): logits of the
 // B*(n_q+1) verified rows against the whole vocabulary, never written out: every wavefront keeps,
 // per row, the best (value, lowest index) of the vocabulary range it owns and writes one
 // candidate per row.  Step 2: reduce the candidates to the target's greedy token per row

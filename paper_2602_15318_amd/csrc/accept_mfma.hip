@@ -495,7 +495,9 @@ int tiled_grid(int M, int V, int bm) {
 }
 int f32_block(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128; }
 
-// Up to here the k-split kernel, whose hidden rows sit in registers: at 32 rows 169 us against 182.
+// Up to here the k-split kernel, whose hidden rows sit in registers: at 32 rows of 3,584 173 us against 186.
+// (Above 4,096 columns 17 to 32 rows then take two passes over W: 24 rows of 5,120 456 us, where the tiled
+// kernel needs 270 for 64.  The line is the same there so far.)
 constexpr int kKsMaxRows = 32;
 
 }  // namespace
@@ -511,8 +513,8 @@ int accept_num_candidates(int dtype, int M, int H, int V) {
   return M > kKsMaxRows ? tiled_grid(M, V, M > 128 ? 256 : M > 64 ? 128 : 64) : ksplit_grid(H, V);
 }
 
-// Up to 32 rows: one pass over W per 32 rows, or 16.  Above 4,096 the hidden rows of a wavefront's two
-// slices fill its registers at 16 rows: passes of 16.
+// Up to 32 rows: one pass over W, two of 16 rows above 4,096 columns, where the hidden rows of a wavefront's
+// two slices fill its registers at 16 rows.
 hipError_t launch_lm_head_mfma(int dtype, const AcceptArgs &a, hipStream_t st) {
   if (dtype == SPARROW_F32) {
     switch (f32_block(a.M)) {

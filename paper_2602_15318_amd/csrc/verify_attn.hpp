@@ -29,9 +29,10 @@ struct VerifyArgs {
   int64_t stride_tok, stride_head;
   // plain-ALU path: part_o [n_slots, n_q, Hq, d], part_ml [n_slots, n_q, Hq, 2];
   // matrix-core path: tiled per (split, KV head, row block), see verify_attn_mfma.hip
-  float *part_o;          // partial outputs (plain-ALU path: unnormalised fp32; matrix-core
-                          // path: normalised fp16)
-  float *part_ml;         // running max (log2 domain), partial sum
+  float *part_o;          // partial outputs (plain-ALU path: unnormalised fp32; matrix-core path:
+                          // normalised, fp32, or fp16 for bf16 heads of 128)
+  float *part_ml;         // reference point (log2 domain) and partial sum; matrix-core path: and
+                          // the scale of fp16 outputs
   void *out;              // [B*n_q, Hq, d]
   float *lse;             // [B*n_q, Hq] or nullptr
 };
