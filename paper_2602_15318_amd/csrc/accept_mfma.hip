@@ -46,7 +46,8 @@ constexpr int kKsWaves = 8;               // most wavefronts of a workgroup
 // rows 49 us, 32 rows 54 us; 151,936 x 2560 118 us.
 template <int SPW, int NB>
 __global__ void __launch_bounds__(kKsWaves * 64)
-lm_head_ksplit_kernel(AcceptArgs a, int row0) {
+lm_head_ksplit_kernel(AcceptArgs a, int first_row) {
+  const int row0 = first_row + 16 * NB * (int)blockIdx.y;     // row blocks side by side
   const int wg = (int)blockIdx.x, n_wg = (int)gridDim.x;      // streams of vocabulary tiles
   constexpr int G = kKsGroup / NB;          // vocabulary tiles per group
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -219,22 +220,28 @@ int ksplit_waves(int H) {
 }
 int ksplit_lds(int nw) { return nw * (16384 + kKsGroup * 64 * 16); }
 
-// Workgroups of a pass = candidates per row: as many as fit the compute units (160 KB of LDS, eight
-// wavefronts each), and no more than there are vocabulary tiles.
-int ksplit_grid(int H, int V) {
+// Workgroups of a row block = candidates per row: as many as fit the compute units (160 KB of LDS, eight
+// wavefronts each), shared by the row blocks, and no more than there are vocabulary tiles.
+int ksplit_slots(int H) {
   const int nw = ksplit_waves(H);
-  const int per_cu = std::min(160 * 1024 / ksplit_lds(nw), kKsWaves / nw);
-  const int tiles = (V + 15) / 16;
-  return std::min(kNumCU * per_cu, tiles);
+  return kNumCU * std::min(160 * 1024 / ksplit_lds(nw), kKsWaves / nw);
 }
+// (a multiple of 8 where several blocks stream the same tiles: one XCD, whose L2 serves all but the first)
+int ksplit_grid(int H, int V, int blocks) {
+  return std::min(blocks > 1 ? std::max(ksplit_slots(H) / blocks / 8 * 8, 8) : ksplit_slots(H), (V + 15) / 16);
+}
+// Hidden rows of a workgroup: 32, or 16 above 4,096 columns, where the hidden rows of a wavefront's two slices
+// fill its registers.
+bool ksplit_wide(int H) { return H > kKsWaves * kKsSlice; }
+int ksplit_blocks(int M, int H) { const int rows = ksplit_wide(H) ? 16 : 32; return (M + rows - 1) / rows; }
 
 template <int SPW, int NB>
-hipError_t launch_ksplit(const AcceptArgs &a, int row0, hipStream_t st) {
+hipError_t launch_ksplit(const AcceptArgs &a, int row0, int blocks, hipStream_t st) {
   static const hipError_t attr = hipFuncSetAttribute((const void *)lm_head_ksplit_kernel<SPW, NB>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, ksplit_lds(kKsWaves));
   if (attr != hipSuccess) return attr;
   const int nw = ksplit_waves(a.H);
-  hipLaunchKernelGGL((lm_head_ksplit_kernel<SPW, NB>), dim3(a.n_cand), dim3(nw * 64), ksplit_lds(nw), st, a, row0);
+  hipLaunchKernelGGL((lm_head_ksplit_kernel<SPW, NB>), dim3(a.n_cand, blocks), dim3(nw * 64), ksplit_lds(nw), st, a, row0);
   return hipGetLastError();
 }
 
@@ -500,6 +507,19 @@ int f32_block(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128; 
 // kernel needs 270 for 64.  The line is the same there so far.)
 constexpr int kKsMaxRows = 32;
 
+// Above that line the k-split kernel, all its row blocks side by side, where the vocabulary is too small to fill
+// the chip with tiles of the whole hidden size: the tiled kernel then lasts 0.8 us per 64 columns, one step after
+// the other, a k-split workgroup 4 us per 16-row tile (6 with two slices per wavefront), whatever the width.
+// k-split / tiled / pairs of k-split workgroups before, us with the finalize pass: 1,000 x 3,584, 64 rows 18 / 46 /
+// 21, 256 rows 20 / 61 / 75; 8,640 x 3,584, 64 rows 30 / 50 / 32; 16,000 x 4,096, 64 rows 45 / 61 / 45, 128 rows
+// 66 / 70 / 85; 1,000 x 8,192, 64 rows 27 / 78 / 570 (plain ALU); 32,000 x 2,048, 64 rows 50 / 41 / 146.
+bool ksplit_small(int M, int H, int V) {
+  if (M <= kKsMaxRows || H > 2 * kKsWaves * kKsSlice) return false;
+  const int blocks = ksplit_blocks(M, H), grid = ksplit_grid(H, V, blocks);
+  const int rounds = ((V + 15) / 16 + grid - 1) / grid * ((blocks * grid + ksplit_slots(H) - 1) / ksplit_slots(H));
+  return (ksplit_wide(H) ? 6 : 4) * rounds + 8 < 6 + H / 80;
+}
+
 }  // namespace
 
 bool lm_head_mfma_supported(int dtype, int M, int H, int V) {
@@ -510,7 +530,8 @@ bool lm_head_mfma_supported(int dtype, int M, int H, int V) {
 
 int accept_num_candidates(int dtype, int M, int H, int V) {
   if (dtype == SPARROW_F32) return tiled_grid(M, V, f32_block(M));
-  return M > kKsMaxRows ? tiled_grid(M, V, M > 128 ? 256 : M > 64 ? 128 : 64) : ksplit_grid(H, V);
+  if (ksplit_small(M, H, V)) return ksplit_grid(H, V, ksplit_blocks(M, H));
+  return M > kKsMaxRows ? tiled_grid(M, V, M > 128 ? 256 : M > 64 ? 128 : 64) : ksplit_grid(H, V, 1);
 }
 
 // Up to 32 rows: one pass over W, two of 16 rows above 4,096 columns, where the hidden rows of a wavefront's
@@ -524,16 +545,20 @@ hipError_t launch_lm_head_mfma(int dtype, const AcceptArgs &a, hipStream_t st) {
       default: return launch_tiled<float, 128, 4, 2, 128>(a, st);
     }
   }
+  const bool wide = ksplit_wide(a.H);
+  if (ksplit_small(a.M, a.H, a.V)) {
+    const int blocks = ksplit_blocks(a.M, a.H);
+    return wide ? launch_ksplit<2, 1>(a, 0, blocks, st) : launch_ksplit<1, 2>(a, 0, blocks, st);
+  }
   if (a.M > 128) return launch_tiled<bf16_t, 256, 8, 2, 128>(a, st);
   if (a.M > 64) return launch_tiled<bf16_t, 128, 4, 2, 128>(a, st);
   if (a.M > kKsMaxRows) return launch_tiled<bf16_t, 64, 4, 2, 128>(a, st);
-  const bool wide = a.H > kKsWaves * kKsSlice;
   for (int row0 = 0; row0 < a.M;) {
     const int left = a.M - row0;
     hipError_t e;
-    if (wide) { e = launch_ksplit<2, 1>(a, row0, st); row0 += 16; }
-    else if (left > 16) { e = launch_ksplit<1, 2>(a, row0, st); row0 += 32; }
-    else { e = launch_ksplit<1, 1>(a, row0, st); row0 += 16; }
+    if (wide) { e = launch_ksplit<2, 1>(a, row0, 1, st); row0 += 16; }
+    else if (left > 16) { e = launch_ksplit<1, 2>(a, row0, 1, st); row0 += 32; }
+    else { e = launch_ksplit<1, 1>(a, row0, 1, st); row0 += 16; }
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

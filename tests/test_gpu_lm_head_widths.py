@@ -98,6 +98,14 @@ def test_logits_carry_the_error_of_short_sums_only(sp, H, M, dtype, limit):
     assert float((logits - ref).norm() / ref.norm()) <= limit
 
 
+@pytest.mark.parametrize("H", [2048, 4104, 8192])
+@pytest.mark.parametrize("M", [33, 64, 65, 200, 512])
+@pytest.mark.parametrize("V", [7, 1000, 3001])
+def test_row_blocks_side_by_side(sp, H, M, V):
+    """Small vocabularies above 32 rows: the k-split kernel with up to 32 row blocks in one launch."""
+    _check(sp, H, V, M, H + V + M)
+
+
 def test_wider_than_the_matrix_core_kernels(sp):
     _check(sp, 8704, 300, 3, 1)
     _check(sp, (1 << 20) + 4, 20, 2, 1, "float32")
