@@ -9,7 +9,7 @@
 //                       the row's statistics;
 //   tree_expand_kernel  one workgroup: appends the candidates of a level to the pool with their
 //                       cumulative scores and ranks them for the next frontier;
-//   tree_select_kernel  one wavefront: finds the score of the `total`-th best entry bit by bit, keeps
+//   tree_select_kernel  (and _small_, up to 128 entries) one wavefront: finds the score of the `total`-th best entry bit by bit, keeps
 //                       what reaches it, renumbers in pool order (population counts of ballots).
 // "Better" is always: higher value, then lower index -- the order of the oracle.
 #include "common.hpp"
@@ -187,10 +187,65 @@ tree_expand_kernel(ExpandArgs a) {
   }
 }
 
-// Entry 64 r + l of the pool sits in register r of lane l.  The score of the keep-th best is found bit by
-// bit on order-preserving integer keys (the number of entries that reach a candidate: one ballot per
-// register); entries above it are kept, and of those equal to it the first in pool order.  No barrier and
-// no rank counting: 689 entries 10 to 15 us, against 24 to 30 for a workgroup that ranked by counting.
+// Order-preserving integer key of a score (+ 0: the two zeros are one score).
+__device__ __forceinline__ unsigned int score_key(float score) {
+  const unsigned int u = __float_as_uint(score + 0.0f);
+  return (u & 0x80000000u) ? ~u : u | 0x80000000u;
+}
+
+// Pools of up to 128 entries, two per lane: every entry's rank is counted, the others' keys read across the
+// lanes; a kept entry's new number and its parent's are population counts of the ballots of kept ones.  One
+// memory round trip, no LDS: 72 entries 3.8 us, against 5.7 to 7.1 with the kernel for larger pools and 5.1
+// with a workgroup that ranked by counting (8 entries 2.8, 3.7 to 5.0 and 2.9).
+constexpr int kSelectSmall = 128;
+__global__ void __launch_bounds__(64)
+tree_select_small_kernel(SelectArgs a) {
+  const int lane = threadIdx.x, n = a.n_pool, keep = min(a.total, n);
+  unsigned int key[2];
+  unsigned long long order[2];          // key, then the lower index: no two entries are equal
+  int par[2], tok[2], rank[2] = {0, 0};
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = 64 * u + lane;
+    key[u] = i < n ? score_key(a.pool_score[i]) : 0u;
+    order[u] = (unsigned long long)key[u] << 32 | (0xffffffffu - (unsigned int)i);
+    par[u] = i < n ? a.pool_par[i] : -1;
+    tok[u] = i < n ? a.pool_tok[i] : 0;
+  }
+#pragma unroll
+  for (int v = 0; v < 2; ++v)
+    for (int j0 = 0; j0 < min(n - 64 * v, 64); j0 += 8)   // (entries past the pool rank behind all others)
+#pragma unroll
+      for (int j = j0; j < j0 + 8; ++j) {
+        const unsigned int kj = (unsigned int)__builtin_amdgcn_readlane((int)key[v], j);
+        const unsigned long long oj = (unsigned long long)kj << 32 | (0xffffffffu - (unsigned int)(64 * v + j));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) rank[u] += oj > order[u] ? 1 : 0;
+      }
+  unsigned long long kept[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) kept[u] = __builtin_amdgcn_ballot_w64(64 * u + lane < n && rank[u] < keep);
+  auto new_id = [&](int i) {            // -1: not kept
+    const unsigned long long m = kept[i >> 6], bit = 1ull << (i & 63);
+    return (m & bit) == 0ull ? -1 : (i >= 64 ? __popcll(kept[0]) : 0) + __popcll(m & (bit - 1ull));
+  };
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = 64 * u + lane;
+    if (i >= n) continue;
+    const int id = new_id(i);
+    if (id < 0) continue;
+    a.parent[id] = (par[u] >= 0 && par[u] < n) ? new_id(par[u]) : -1;
+    a.ids[id] = tok[u];
+    a.pool_index[id] = i;
+  }
+}
+
+// Larger pools.  Entry 64 r + l of the pool sits in register r of lane l.  The score of the keep-th best is
+// found bit by bit on order-preserving integer keys (the number of entries that reach a candidate: one ballot
+// per register); entries above it are kept, and of those equal to it the first in pool order.  No barrier and
+// no rank counting: 200 entries 8 us, 689 entries 9.4 to 12, against 9.5 and 30 for a workgroup that ranked by
+// counting.
 __global__ void __launch_bounds__(64)
 tree_select_kernel(SelectArgs a) {
   constexpr int kRegs = kTreeMaxPool / 64;
@@ -201,11 +256,7 @@ tree_select_kernel(SelectArgs a) {
 #pragma unroll
   for (int r = 0; r < kRegs; ++r) {
     key[r] = 0u;
-    if (r < regs && 64 * r + lane < n) {
-      // (+ 0: the two zeros are one score)
-      const unsigned int u = __float_as_uint(a.pool_score[64 * r + lane] + 0.0f);
-      key[r] = (u & 0x80000000u) ? ~u : u | 0x80000000u;
-    }
+    if (r < regs && 64 * r + lane < n) key[r] = score_key(a.pool_score[64 * r + lane]);
   }
   auto reach = [&](unsigned int t) {
     int cnt = 0;
@@ -271,7 +322,8 @@ hipError_t launch_tree_expand(const ExpandArgs &a, hipStream_t st) {
 }
 
 hipError_t launch_tree_select(const SelectArgs &a, hipStream_t st) {
-  hipLaunchKernelGGL(tree_select_kernel, dim3(1), dim3(64), 0, st, a);
+  if (a.n_pool <= kSelectSmall) hipLaunchKernelGGL(tree_select_small_kernel, dim3(1), dim3(64), 0, st, a);
+  else hipLaunchKernelGGL(tree_select_kernel, dim3(1), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
