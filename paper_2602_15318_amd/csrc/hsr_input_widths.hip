@@ -18,7 +18,8 @@
 // RMSNorm is folded in: the activations enter the B operand multiplied by gamma, exactly, as the sum of two
 // bf16 terms (the product has up to 16 bits), and the row's 1/rms (from the squares each wavefront
 // sees in its own slices) scales the result.
-// One activation row runs a wavefront per output feature or rotary pair instead.
+// One activation row (QKV: also two of up to 1,024 columns) runs a wavefront per output feature or rotary
+// pair instead.
 //
 // Measured (FC + QKV, one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64, six
 // rows 141 + 67 -> 9.3 + 10.2 us, one row 56 + 22 -> 7.3 + 6.8; hidden 5,120, 40/8 heads of 128, 16 rows
@@ -311,7 +312,7 @@ hsr_fc_any_gemv_kernel(HsrFcArgs a) {
 template <int KS>             // slices in flight: at least H / 512, or 8
 __global__ void __launch_bounds__(256)
 draft_qkv_any_gemv_kernel(DraftQkvArgs a) {
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, m = blockIdx.y;         // activation row
   const int half = a.d >> 1;
   const int pair = blockIdx.x * 4 + (threadIdx.x >> 6);      // (head, feature of the first half)
   const int n_heads = a.Hq + 2 * a.Hkv;
@@ -339,8 +340,8 @@ draft_qkv_any_gemv_kernel(DraftQkvArgs a) {
     b0 = bf16_to_f32(((const bf16_t *)a.bias)[hd * a.d + f]);
     b1 = bf16_to_f32(((const bf16_t *)a.bias)[hd * a.d + f + half]);
   }
-  const float cs = a.rope_cos[f], sn = a.rope_sin[f];
-  const bf16_t *Z = (const bf16_t *)a.z, *G = (const bf16_t *)a.gamma;
+  const float cs = a.rope_cos[m * half + f], sn = a.rope_sin[m * half + f];
+  const bf16_t *Z = (const bf16_t *)a.z + (int64_t)m * H, *G = (const bf16_t *)a.gamma;
   float s0 = 0.f, s1 = 0.f, ssq = 0.f;
   for (int k0 = 0; k0 < H; k0 += KS * kSlice) {
     if (k0 > 0) issue(k0);
@@ -374,10 +375,10 @@ draft_qkv_any_gemv_kernel(DraftQkvArgs a) {
   }
   bf16_t *dst;
   if (hd < a.Hq) {
-    dst = (bf16_t *)a.q_out + (int64_t)hd * a.d;
+    dst = (bf16_t *)a.q_out + ((int64_t)m * a.Hq + hd) * a.d;
   } else {
     const int c = is_v ? hd - a.Hq - a.Hkv : hd - a.Hq;
-    dst = (bf16_t *)(is_v ? a.v_cache : a.k_cache) + (int64_t)a.kv_rows[0] * a.stride_tok +
+    dst = (bf16_t *)(is_v ? a.v_cache : a.k_cache) + (int64_t)a.kv_rows[m] * a.stride_tok +
           (int64_t)c * a.stride_head;
   }
   dst[f] = f32_to_bf16(o0);
@@ -417,9 +418,12 @@ hipError_t launch_hsr_fc_any(const HsrFcArgs &a, hipStream_t st) {
 
 hipError_t launch_draft_qkv_any(const DraftQkvArgs &a, hipStream_t st) {
   const int n_heads = a.Hq + 2 * a.Hkv, slices = (a.H + kSlice - 1) / kSlice;
-  if (a.M == 1) {               // one row: a wavefront per rotary pair
-    const dim3 grid((n_heads * (a.d / 2) + 3) / 4);
-    if (slices <= 4) hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<4>, grid, dim3(256), 0, st, a);
+  // One row: a wavefront per rotary pair.  Two rows as well up to 1,024 columns, where both rows' weights come
+  // from the caches and the staged kernel's latency shows (256 columns 6.0 us; 4.6 with a plain-ALU kernel).
+  if (a.M == 1 || (a.M == 2 && a.H <= 1024)) {
+    const dim3 grid((n_heads * (a.d / 2) + 3) / 4, a.M);
+    if (slices <= 1) hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<1>, grid, dim3(256), 0, st, a);
+    else if (slices <= 4) hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<4>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<8>, grid, dim3(256), 0, st, a);
     return hipGetLastError();
   }

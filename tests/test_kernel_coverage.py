@@ -115,11 +115,12 @@ COVERAGE = {
     "draft_qkv_mfma_kernel<8, 1>": (H, "test_draft_qkv_append", "bf16-32-8-128-4096"),
     # hidden sizes other than 3,584 and 4,096; one row: <slices of a weight row in flight>
     "hsr_fc_any_kernel": (HW, "test_hsr_fc", "two rows and more"),
-    "draft_qkv_any_kernel": (HW, "test_draft_qkv_append", "two rows and more"),
+    "draft_qkv_any_kernel": (HW, "test_draft_qkv_append", "two rows and more (three up to 1,024 columns)"),
     "hsr_fc_any_gemv_kernel<4>": (HW, "test_hsr_fc", "hidden up to 1,024"),
     "hsr_fc_any_gemv_kernel<8>": (HW, "test_hsr_fc", "hidden 1,280"),
     "hsr_fc_any_gemv_kernel<16>": (HW, "test_hsr_fc", "hidden 2,560 and more"),
-    "draft_qkv_any_gemv_kernel<4>": (HW, "test_draft_qkv_append", "hidden up to 1,000"),
+    "draft_qkv_any_gemv_kernel<1>": (HW, "test_draft_qkv_append", "hidden up to 512"),
+    "draft_qkv_any_gemv_kernel<4>": (HW, "test_draft_qkv_append", "hidden 1,000, one and two rows"),
     "draft_qkv_any_gemv_kernel<8>": (HW, "test_draft_qkv_append", "hidden 2,560 and more"),
     "kv_commit_kernel": (C, "test_kv_commit_bit_exact", ""),
     # ---- measurement aid (no part of the method, nothing to compare): run, input left alone
