@@ -9,8 +9,9 @@
 //                       the row's statistics;
 //   tree_expand_kernel  one workgroup: appends the candidates of a level to the pool with their
 //                       cumulative scores and ranks them for the next frontier;
-//   tree_select_kernel  (and _small_, up to 128 entries) one wavefront: finds the score of the `total`-th best entry bit by bit, keeps
-//                       what reaches it, renumbers in pool order (population counts of ballots).
+//   tree_select_kernel  one wavefront: finds the score of the `total`-th best entry bit by bit, keeps
+//                       what reaches it, renumbers in pool order (population counts of ballots);
+//                       tree_select_small_kernel ranks pools of up to 128 entries by counting.
 // "Better" is always: higher value, then lower index -- the order of the oracle.
 #include "common.hpp"
 #include "draft_tree.hpp"
@@ -196,7 +197,7 @@ __device__ __forceinline__ unsigned int score_key(float score) {
 // Pools of up to 128 entries, two per lane: every entry's rank is counted, the others' keys read across the
 // lanes; a kept entry's new number and its parent's are population counts of the ballots of kept ones.  One
 // memory round trip, no LDS: 72 entries 3.8 us, against 5.7 to 7.1 with the kernel for larger pools and 5.1
-// with a workgroup that ranked by counting (8 entries 2.8, 3.7 to 5.0 and 2.9).
+// with a workgroup that ranked by counting (8 entries 2.0, 3.7 to 5.0 and 2.9).
 constexpr int kSelectSmall = 128;
 __global__ void __launch_bounds__(64)
 tree_select_small_kernel(SelectArgs a) {
