@@ -91,9 +91,18 @@ struct PieceTable {
 // sequences of 6,001, 16/4 heads, chain of 8, 14.0 -> 14.5 us a call; 60-node tree at 26k 36.4 -> 39 to 41.
 template <int kD> constexpr bool kWideState = kD == 64;
 
+// kPing (two row tiles over long splits) runs its two streams half a step apart: while one stream's
+// wavefronts issue the MFMAs of a step (scores of the next tile, output of this one), the other stream's, which
+// share the SIMDs with them, are in their softmax.  In step, the phases of all wavefronts add up: matrix
+// cores, vector ALU and LDS were busy 27, 31 and 42 per cent of the time.  The LDS reads of V^T, the LDS
+// writes and the requests of later tiles are issued between the MFMAs; independent sums alternate.
+// 60-node tree over 26,112 tokens 45.4 -> 41.0 us a call (with the combine pass) in an unbroken row of calls, 40.2
+// -> 37.0 to 39.4 in short ones at a higher clock; two of 64 nodes over 30,000 (64/8 heads) 157 -> 138 (910 TFLOP/s).  Three row tiles and the fp32 state of heads of 64 do not leave the
+// registers for it (the latter 42 -> 67 us with spills); which calls take it: ping_pong_pays below.
+
 // kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
-template <int kD, int kPrefetch, int kQT>
+template <int kD, int kPrefetch, int kQT, bool kPing>
 __global__ void __launch_bounds__(256 * kStreams)
 verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, int flat, int direct) {
   constexpr int kSub = 128 / kD;                           // 32-token tiles per stream per step
@@ -179,41 +188,40 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   // unconditional and the number of loads in flight is a compile-time constant at every wait.
   const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
   constexpr int kLd = kSub * kTile / kLdRows;         // loads per step (per K and per V)
-  u32x4 stage[kPrefetch][2 * kLd];
-  auto issue = [&](int st, u32x4 *sg) {
-    const int tb = t0 + (st * kStreams + strm) * kSub * kTile;
+  const unsigned int ld_first = (unsigned int)(t0 + ld_row) * row_bytes + (unsigned int)ld_ch * 16u;
+  const unsigned int ld_last = (unsigned int)(t1 - 1) * row_bytes + (unsigned int)ld_ch * 16u;
+  auto issue1 = [&](const unsigned char *src, int st, int j, u32x4 *sg) __attribute__((always_inline)) {
+    const unsigned int to = (unsigned int)((st * kStreams + strm) * kSub * kTile + kLdRows * j) * row_bytes;
+    sg[j] = __builtin_nontemporal_load((const u32x4 *)(src + min(ld_first + to, ld_last)));
+  };
+  auto issue = [&](const unsigned char *src, int st, u32x4 *sg) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kLd; ++j) {
-      const int r = min(tb + ld_row + kLdRows * j, t1 - 1);
-      const unsigned int o = (unsigned int)r * row_bytes + (unsigned int)ld_ch * 16u;
-      sg[j] = __builtin_nontemporal_load((const u32x4 *)(Kg + o));
-      sg[kLd + j] = __builtin_nontemporal_load((const u32x4 *)(Vg + o));
-    }
+    for (int j = 0; j < kLd; ++j) issue1(src, st, j, sg);
   };
   // row r of the step lands at byte r*kRowBytes + ((chunk ^ swz(r)) * 16); swz depends on r mod 8 only
   const int st_off = ld_row * kRowBytes + ((ld_ch ^ swz<kD>(ld_row)) << 4);
-  auto stash = [&](int buf, int st, u32x4 *sg) {
-    if (kWide) {
+  auto stash1 = [&](int buf, int kv, int st, int j, u32x4 *sg) __attribute__((always_inline)) {
+    if ((kWide || kPing) && kv == 1) {
       // values past the end of the split are zero, as in the plain-ALU kernel: a duplicate of an
       // infinite last row would give 0 * inf
       const int left = t1 - (t0 + (st * kStreams + strm) * kSub * kTile);
-      if (left < kSub * kTile) {                           // uniform over the wavefront
-#pragma unroll
-        for (int j = 0; j < kLd; ++j)
-          if (ld_row + kLdRows * j >= left) sg[kLd + j] = (u32x4){0u, 0u, 0u, 0u};
-      }
+      if (left < kSub * kTile && ld_row + kLdRows * j >= left) sg[j] = (u32x4){0u, 0u, 0u, 0u};
     }
-    unsigned char *kb = lds_at(strm, buf, 0), *vb = lds_at(strm, buf, 1);
-#pragma unroll
-    for (int j = 0; j < kLd; ++j) {
-      *reinterpret_cast<u32x4 *>(kb + st_off + kLdRows * j * kRowBytes) = sg[j];
-      *reinterpret_cast<u32x4 *>(vb + st_off + kLdRows * j * kRowBytes) = sg[kLd + j];
-    }
+    *reinterpret_cast<u32x4 *>(lds_at(strm, buf, kv) + st_off + kLdRows * j * kRowBytes) = sg[j];
   };
+  auto stash = [&](int buf, int kv, int st, u32x4 *sg) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kLd; ++j) stash1(buf, kv, st, j, sg);
+  };
+  // kPing: K runs one step ahead of V, so K of the second step is asked for with the first
+  u32x4 kst[kPrefetch][kLd], vst[kPrefetch][kLd];
+  u32x4 k_next[kLd];
 
   // ---- first step, then Q^T (B operand of the score MFMA: lane (n, c4) holds
   // Q[row][32*ks + 8*c4 .. +8]), then the rest of the look-ahead.
-  issue(0, stage[0]);
+  issue(Kg, 0, kst[0]);
+  issue(Vg, 0, vst[0]);
+  if (kPing) issue(Kg, 1, k_next);
   __builtin_amdgcn_sched_barrier(0);      // the first step is on its way before anything else is worked out
 
   const int g = a.Hq / a.Hkv;
@@ -249,7 +257,10 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     // skew between the two streams).
     if (kPrefetch > 1) __syncthreads();
 #pragma unroll
-    for (int p = 1; p < kPrefetch; ++p) issue(p, stage[p]);
+    for (int p = 1; p < kPrefetch; ++p) {
+      issue(Vg, p, vst[p]);
+      issue(Kg, kPing ? p + 1 : p, kst[p]);
+    }
     // Loads retire in order: Q (and the first step before it) have landed once at most the
     // loads issued after Q are outstanding (other counters untouched).
     constexpr int kAfterQ = (kPrefetch - 1) * 2 * kLd;
@@ -299,47 +310,34 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     for (int mt = 0; mt < kMT; ++mt) o_acc[qt][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
 
-  // One step of one stream: 32*kSub tokens against the wavefront's 16 rows, one joint softmax
-  // update (a single running-max / rescale for the whole step).
-  auto compute = [&](int st, int buf, auto na_tag) __attribute__((always_inline)) {
-    constexpr int NA = decltype(na_tag)::value;   // live row tiles (the leading ones)
+  f32x4 s[kQT][kSlabs];                           // scores of a step, S^T
+  bf16x8 pb[kQT][kSub];                           // its probabilities, P^T
+  bf16x8 pm[kWide ? kQT : 1][kSub], pl[kWide ? kQT : 1][kSub];   // kWide: what pb leaves of the probability
+  bf16x8 ka[kSlabs][kKS];                         // K operands of a step
+  auto read_k = [&](int buf, int j) __attribute__((always_inline)) {
     const unsigned char *Ks = lds_at(strm, buf, 0);
-    const unsigned char *Vs = lds_at(strm, buf, 1);
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks)
+      ka[j][ks] = lds_read_b128(Ks + j * 16 * kRowBytes + k_off + (((4 * ks + c4) ^ k_swz) << 4));
+  };
+  auto scores = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int qt = 0; qt < kQT; ++qt) s[qt][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks)
+#pragma unroll
+      for (int qt = 0; qt < kQT; ++qt)
+        s[qt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[j][ks], qreg[qt][ks], s[qt][j], 0, 0, 0);
+  };
+  // One joint softmax update of a step (a single running-max / rescale for its 32*kSub tokens).
+  auto softmax = [&](int st) __attribute__((always_inline)) {
     const int tb = t0 + (st * kStreams + strm) * kSub * kTile;
-    f32x4 s[NA][kSlabs];
-    // Tree instances raise the wavefront's priority for their MFMA phases: the other wavefront of
-    // the SIMD is then in its softmax, and the matrix pipe stays fed (-3 % on the 60-node tree).
-    constexpr bool kPrio = kQT > 1;
-    if (kPrio) __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int j = 0; j < kSlabs; ++j) {
-      bf16x8 ka[kKS];
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks)
-        ka[ks] = lds_read_b128(Ks + j * 16 * kRowBytes + k_off + (((4 * ks + c4) ^ k_swz) << 4));
-#pragma unroll
-      for (int qt = 0; qt < NA; ++qt) s[qt][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks)
-#pragma unroll
-        for (int qt = 0; qt < NA; ++qt)
-          s[qt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks], qreg[qt][ks], s[qt][j], 0, 0, 0);
-    }
     // mask, online softmax (per lane = per query row).  Scores stay unscaled until the exponent:
     // exp2(s * scale_log2 - m) is one fused multiply-add per score (scale_log2 > 0, so the
     // maximum can be taken before scaling).
-    if (kPrio) __builtin_amdgcn_s_setprio(0);
     const bool edge = tb + kSub * kTile > min(t1, L);   // uniform: split end or draft rows in reach
-    if (kQT > 1) __builtin_amdgcn_sched_barrier(0);     // keep the V^T reads below the softmax
-    bf16x8 pb[NA][kSub];
-    bf16x8 pm[kWide ? NA : 1][kSub], pl[kWide ? NA : 1][kSub];   // kWide: what pb leaves of the probability
 #pragma unroll
-    for (int qt = 0; qt < NA; ++qt) {
-      float sc[4 * kSlabs];
-#pragma unroll
-      for (int j = 0; j < kSlabs; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sc[4 * j + i] = s[qt][j][i];
+    for (int qt = 0; qt < kQT; ++qt) {
       if (edge) {
         // (an opaque copy of the step's first token: without it the compiler works the token
         // numbers, their distances to L and the shift counts out on EVERY step, ahead of the
@@ -353,12 +351,12 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
             const int tok = tb_e + 16 * j + 4 * c4 + i;
             const int dj = tok - L;
             const bool vis = (dj < 0) | (((anc[qt] >> (dj & 63)) & 1ull) != 0ull);
-            sc[4 * j + i] = ((tok < t1) & vis) ? sc[4 * j + i] : -INFINITY;
+            s[qt][j][i] = ((tok < t1) & vis) ? s[qt][j][i] : -INFINITY;
           }
       }
-      float mx = sc[0];
+      float mx = s[qt][0][0];
 #pragma unroll
-      for (int e = 1; e < 4 * kSlabs; ++e) mx = fmaxf(mx, sc[e]);
+      for (int e = 1; e < 4 * kSlabs; ++e) mx = fmaxf(mx, s[qt][e >> 2][e & 3]);
       mx *= a.scale_log2;
       // The reference point m of a row moves only when some score of the wavefront's tile lies
       // more than kSlack above it (exponentials then stay below 2^kSlack, far from overflow, and
@@ -377,7 +375,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         float psum = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float p = fast_exp2(fmaf(sc[8 * u + e], a.scale_log2, -m_run[qt]));
+          const float p = fast_exp2(fmaf(s[qt][2 * u + (e >> 2)][e & 3], a.scale_log2, -m_run[qt]));
           if (!kMfmaRowSum) psum += p;
           if (kWide) {
             // p = hi + mid + lo: the leading 8 bits (cut off, so that the rest has p's sign), the
@@ -393,27 +391,35 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
             pb[qt][u][e] = (__bf16)p;
           }
         }
-        // row sums on the matrix cores: every row of ones . P^T is the sum over the 32 tokens
-        // (kMfmaRowSum off: per-lane sums on the vector ALU, merged across the four lanes at the end)
-        if (kMfmaRowSum)
-          l_acc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[qt][u], l_acc[qt], 0, 0, 0);
-        else
-          l_acc[qt][0] += psum;
+        if (!kMfmaRowSum) l_acc[qt][0] += psum;   // (merged across the four lanes at the end)
       }
     }
-    if (kQT > 1) __builtin_amdgcn_sched_barrier(0);
-    if (kPrio) __builtin_amdgcn_s_setprio(1);
+  };
+  auto read_v = [&](const unsigned char *Vs, int mt, int u) __attribute__((always_inline)) {   // V^T operand
+    const unsigned char *at = Vs + v_off + (((2 * mt + v_chb) ^ v_swz) << 4);
+    const bf16x4 va = lds_read_tr(at + (2 * u) * 16 * kRowBytes);
+    const bf16x4 vb = lds_read_tr(at + (2 * u + 1) * 16 * kRowBytes);
+    return (bf16x8)__builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  // row sums on the matrix cores: every row of ones . P^T is the sum over the 32 tokens
+  auto row_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int qt = 0; qt < kQT; ++qt)
+#pragma unroll
+      for (int u = 0; u < kSub; ++u)
+        l_acc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[qt][u], l_acc[qt], 0, 0, 0);
+  };
+  auto output = [&](int buf) __attribute__((always_inline)) {
+    const unsigned char *Vs = lds_at(strm, buf, 1);
+    if (kMfmaRowSum) row_sums();
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt) {
-      const int ch = ((2 * mt + v_chb) ^ v_swz) << 4;
       if (kQT > 1 && mt == 4) __builtin_amdgcn_sched_barrier(0);    // at most 4 d-tiles of V^T in flight
 #pragma unroll
       for (int u = 0; u < kSub; ++u) {
-        const bf16x4 va = lds_read_tr(Vs + (2 * u) * 16 * kRowBytes + v_off + ch);
-        const bf16x4 vb = lds_read_tr(Vs + (2 * u + 1) * 16 * kRowBytes + v_off + ch);
-        const bf16x8 vt = __builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7);
+        const bf16x8 vt = read_v(Vs, mt, u);
 #pragma unroll
-        for (int qt = 0; qt < NA; ++qt) {
+        for (int qt = 0; qt < kQT; ++qt) {
           o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pb[qt][u], o_acc[qt][mt], 0, 0, 0);
           if (kWide) {
             o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pm[qt][u], o_acc[qt][mt], 0, 0, 0);
@@ -422,40 +428,136 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         }
       }
     }
-    if (kPrio) __builtin_amdgcn_s_setprio(0);
   };
 
   // A wavefront with a partly filled set of row tiles computes all of them (the empty ones on a zero
   // query): a second, one-tile instance of the step in the same kernel costs more registers than
   // the kernel has.
-  // (always_inline: as a call it would keep the wavefront's state in scratch memory)
-  auto run = [&](int st, int buf) __attribute__((always_inline)) {
-    if (n_act > 0) compute(st, buf, std::integral_constant<int, kQT>{});
-  };
-
-  // ---- main loop, unrolled by the prefetch depth so that the staging registers are static.
-  // Look-ahead loads past the end of the split are clamped duplicates of its last rows.
-  int base = 0;
-  for (; base + kPrefetch <= n_steps; base += kPrefetch) {
+  // Steps of this stream that hold tokens (none for a wavefront without rows)
+  const int my_steps = n_act > 0 ? (n_tiles - strm * kSub + kStreams * kSub - 1) / (kStreams * kSub) : 0;
+  if constexpr (kPing) {
+    // Step st of a stream: vector phase (K operands of step st + 1 out of LDS, softmax of st), barrier,
+    // matrix phase (scores of st + 1, output of st; V of st + 1 and K of st + 2 into LDS, their successors
+    // requested), barrier.  Steps past the stream's last tile run on masked scores and zero values.
+    static_assert(!kWide && kSub == 1 && kPrefetch == 2, "the instance that runs this");
+    stash(0, 0, 0, kst[0]);
+    stash(0, 1, 0, vst[0]);
+    stash(1, 0, 1, k_next);
+    issue(Vg, 2, vst[0]);
+    issue(Kg, 3, kst[0]);
+    __syncthreads();
+    if (strm == 1) __syncthreads();                        // half a step behind
+    if (n_act > 0) {
 #pragma unroll
-    for (int p = 0; p < kPrefetch; ++p) {
-      const int st = base + p;
-      const int buf = st & 1;
-      stash(buf, st, stage[p]);
-      issue(st + kPrefetch, stage[p]);
-      __syncthreads();
-      if ((st * kStreams + strm) * kSub < n_tiles) run(st, buf);
+      for (int j = 0; j < kSlabs; ++j) { read_k(0, j); scores(j); }
     }
-  }
-  // remainder (n_steps % kPrefetch trips): everything it needs is already in flight
+    __syncthreads();
+    auto fetch1 = [&](int st, int p, int x) __attribute__((always_inline)) {   // p = st & 1; x: V's loads, then K's
+      if (x < kLd) {
+        stash1(p ^ 1, 1, st + 1, x, vst[p ^ 1]);
+        issue1(Vg, st + 3, x, vst[p ^ 1]);
+      } else {
+        stash1(p, 0, st + 2, x - kLd, kst[p ^ 1]);
+        issue1(Kg, st + 4, x - kLd, kst[p ^ 1]);
+      }
+    };
+    auto step = [&](int st, auto parity) __attribute__((always_inline)) {
+      constexpr int p = decltype(parity)::value;           // st & 1
 #pragma unroll
-  for (int p = 0; p < kPrefetch - 1; ++p) {
-    const int st = base + p;
-    if (st < n_steps) {                    // uniform over the workgroup
-      const int buf = st & 1;
-      stash(buf, st, stage[p]);
+      for (int j = 0; j < kSlabs; ++j) read_k(p ^ 1, j);
+      softmax(st);
       __syncthreads();
-      if ((st * kStreams + strm) * kSub < n_tiles) run(st, buf);
+      __builtin_amdgcn_s_setprio(1);
+      const unsigned char *Vs = lds_at(strm, p, 1);
+      bf16x8 vt[kMT];
+#pragma unroll
+      for (int qt = 0; qt < kQT; ++qt)
+#pragma unroll
+        for (int j = 0; j < kSlabs; ++j) s[qt][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < kMT; ++i) {                    // four independent sums alternate
+        const int j = i % kSlabs, ks = i / kSlabs;
+        vt[i] = read_v(Vs, i, 0);
+#pragma unroll
+        for (int qt = 0; qt < kQT; ++qt)
+          s[qt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[j][ks], qreg[qt][ks], s[qt][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int mt = 0; mt < kMT; ++mt) {
+#pragma unroll
+        for (int qt = 0; qt < kQT; ++qt)
+          o_acc[qt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[mt], pb[qt][0], o_acc[qt][mt], 0, 0, 0);
+        if (mt < 2 * kLd) fetch1(st, p, mt);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      row_sums();
+      __builtin_amdgcn_s_setprio(0);
+      __syncthreads();
+    };
+    auto idle_step = [&](int st, auto parity) __attribute__((always_inline)) {   // a wavefront without rows only loads
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < 2 * kLd; ++x) fetch1(st, decltype(parity)::value, x);
+      __syncthreads();
+    };
+    // (Pairs of steps and a remainder, not one loop with two exits, and a loop of its own for idle wavefronts: the
+    // compiler then knows which loads are under way at every wait.)
+    auto all_steps = [&](auto &one) __attribute__((always_inline)) {
+      int st = 0;
+      for (; st + 2 <= n_steps; st += 2) {
+        one(st, std::integral_constant<int, 0>{});
+        one(st + 1, std::integral_constant<int, 1>{});
+      }
+      if (st < n_steps) one(st, std::integral_constant<int, 0>{});
+    };
+    if (n_act > 0) all_steps(step);
+    else all_steps(idle_step);
+    if (strm == 0) __syncthreads();
+  } else {
+    auto run = [&](int st, int buf) __attribute__((always_inline)) {
+      if (st >= my_steps) return;
+      // Instances for several row tiles raise the wavefront's priority for their MFMA phases: the other
+      // wavefront of the SIMD is then in its softmax, and the matrix pipe stays fed (-3 % on the 60-node tree).
+      constexpr bool kPrio = kQT > 1;
+      if (kPrio) __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int j = 0; j < kSlabs; ++j) { read_k(buf, j); scores(j); }
+      if (kPrio) __builtin_amdgcn_s_setprio(0);
+      if (kPrio) __builtin_amdgcn_sched_barrier(0);        // keep the V^T reads below the softmax
+      softmax(st);
+      if (kPrio) __builtin_amdgcn_sched_barrier(0);
+      if (kPrio) __builtin_amdgcn_s_setprio(1);
+      output(buf);
+      if (kPrio) __builtin_amdgcn_s_setprio(0);
+    };
+    // ---- main loop, unrolled by the prefetch depth so that the staging registers are static.
+    // Look-ahead loads past the end of the split are clamped duplicates of its last rows.
+    int base = 0;
+    for (; base + kPrefetch <= n_steps; base += kPrefetch) {
+#pragma unroll
+      for (int p = 0; p < kPrefetch; ++p) {
+        const int st = base + p;
+        const int buf = st & 1;
+        stash(buf, 0, st, kst[p]);
+        stash(buf, 1, st, vst[p]);
+        issue(Kg, st + kPrefetch, kst[p]);
+        issue(Vg, st + kPrefetch, vst[p]);
+        __syncthreads();
+        run(st, buf);
+      }
+    }
+    // remainder (n_steps % kPrefetch trips): everything it needs is already in flight
+#pragma unroll
+    for (int p = 0; p < kPrefetch - 1; ++p) {
+      const int st = base + p;
+      if (st < n_steps) {                    // uniform over the workgroup
+        const int buf = st & 1;
+        stash(buf, 0, st, kst[p]);
+        stash(buf, 1, st, vst[p]);
+        __syncthreads();
+        run(st, buf);
+      }
     }
   }
 
@@ -669,6 +771,14 @@ int verify_mfma_row_blocks(int dtype, int R) {
   return rbs3 * 3 - tiles <= rbs2 * 2 - tiles ? rbs3 : rbs2;
 }
 
+// The two streams half a step apart: from eleven steps on (shorter splits lose 3 to 10 per cent to the longer
+// start), where the calls are bound by the compute units: several row blocks share a stream.  One block of 128
+// rows runs at 4 TB/s and gains only where a head's rows follow each other in memory (12 ragged sequences
+// of 4,099, trees of 30, us: rows of one head side by side 57.3 -> 53.2, token by token 55.1 -> 55.4 to 58.6).
+static bool ping_pong_pays(const VerifyArgs &a, int steps, int rbs) {
+  return a.d == 128 && steps > 10 && (rbs > 1 || a.stride_tok <= 2 * a.d);
+}
+
 template <int kD>
 static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
   const int R = a.n_q * (a.Hq / a.Hkv);
@@ -693,15 +803,17 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
   const int tiles = (R + kRowsPerWG - 1) / kRowsPerWG;
   const int qt = (tiles + rbs - 1) / rbs;
   if (qt == 3)      // a second tile in flight does not fit the registers (and the step is compute-bound)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 3>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 3, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2 && steps <= 10)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+  else if (qt == 2 && kD == 128 && ping_pong_pays(a, steps, rbs))
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<128, 2, 2, true>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (steps <= 3)       // (a second step in flight pays from 4 steps on: -0.15 us at the 7 steps of a 26k chain)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 1>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 1, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   return hipGetLastError();
 }
 

@@ -21,23 +21,24 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
 
 VF, TS = "test_gpu_verify_f32.py", "test_gpu_tree_sizes.py"
 V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
-VP = "test_gpu_verify_plain_alu.py"
+VP, VL = "test_gpu_verify_plain_alu.py", "test_gpu_verify_long_trees.py"
 
 COVERAGE = {
-    # ---- verification attention, matrix cores, bf16: <head_dim, steps in flight, row tiles>
-    "verify_partial_mfma_kernel<128, 1, 1>": (A, "test_c5_bf16_26k_chain8_layer", "C5 layer, C2; chains up to 64 rows per KV head"),
-    "verify_partial_mfma_kernel<128, 2, 1>": (A, "test_c4_bf16_ragged_batch8", "splits of four steps and more: ragged batch"),
-    "verify_partial_mfma_kernel<128, 1, 2>": (A, "test_paper_sized_trees_at_26k_context", "16-node tree: one block of 128 rows, short splits"),
-    "verify_partial_mfma_kernel<128, 2, 2>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree and the 30-node tree: blocks of 128 rows"),
-    "verify_partial_mfma_kernel<128, 1, 3>": (A, "test_paper_sized_trees_at_26k_context", "48-, 44- and 25-node trees: blocks of 192 rows"),
+    # ---- verification attention, matrix cores, bf16: <head_dim, steps in flight, row tiles, streams half a step apart>
+    "verify_partial_mfma_kernel<128, 1, 1, false>": (A, "test_c5_bf16_26k_chain8_layer", "C5 layer, C2; chains up to 64 rows per KV head"),
+    "verify_partial_mfma_kernel<128, 2, 1, false>": (A, "test_c4_bf16_ragged_batch8", "splits of four steps and more: ragged batch"),
+    "verify_partial_mfma_kernel<128, 1, 2, false>": (A, "test_paper_sized_trees_at_26k_context", "16-node tree: one block of 128 rows, short splits"),
+    "verify_partial_mfma_kernel<128, 2, 2, true>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree and the 30-node tree: blocks of 128 rows"),
+    "verify_partial_mfma_kernel<128, 2, 2, false>": (VL, "test_split_ends", "token-major K/V, one block of 128 rows"),
+    "verify_partial_mfma_kernel<128, 1, 3, false>": (A, "test_paper_sized_trees_at_26k_context", "48-, 44- and 25-node trees: blocks of 192 rows"),
     "verify_combine_tiled_kernel<unsigned short, 128, 16>": (A, "test_c5_bf16_26k_chain8_layer", "more than 32 splits per sequence"),
     "verify_combine_tiled_kernel<unsigned short, 128, 8>": (A, "test_paper_sized_trees_at_26k_context", "17 to 32 splits (30-, 48-node trees)"),
     "verify_combine_tiled_kernel<unsigned short, 128, 4>": (A, "test_c3_bf16_26k_tree60", "at most 16 splits (C3, C4, batches)"),
-    "verify_partial_mfma_kernel<64, 1, 1>": (V64, "test_rows_and_contexts", "up to 64 rows, short contexts"),
-    "verify_partial_mfma_kernel<64, 2, 1>": (V64, "test_batches_and_long_contexts", "26k chain, ragged batch"),
-    "verify_partial_mfma_kernel<64, 1, 2>": (V64, "test_rows_and_contexts", "70, 240 and 480 rows"),
-    "verify_partial_mfma_kernel<64, 2, 2>": (V64, "test_two_row_tiles_over_long_pieces", "60 nodes at 26k, 12 trees of 30 at 4k"),
-    "verify_partial_mfma_kernel<64, 1, 3>": (V64, "test_rows_and_contexts", "175 rows"),
+    "verify_partial_mfma_kernel<64, 1, 1, false>": (V64, "test_rows_and_contexts", "up to 64 rows, short contexts"),
+    "verify_partial_mfma_kernel<64, 2, 1, false>": (V64, "test_batches_and_long_contexts", "26k chain, ragged batch"),
+    "verify_partial_mfma_kernel<64, 1, 2, false>": (V64, "test_rows_and_contexts", "70, 240 and 480 rows"),
+    "verify_partial_mfma_kernel<64, 2, 2, false>": (V64, "test_two_row_tiles_over_long_pieces", "60 nodes at 26k, 12 trees of 30 at 4k"),
+    "verify_partial_mfma_kernel<64, 1, 3, false>": (V64, "test_rows_and_contexts", "175 rows"),
     "verify_combine_tiled_kernel<unsigned short, 64, 16>": (V64, "test_batches_and_long_contexts", "26k chain: 64 splits"),
     "verify_combine_tiled_kernel<unsigned short, 64, 8>": (V64, "test_batches_and_long_contexts", "17 to 32 splits"),
     "verify_combine_tiled_kernel<unsigned short, 64, 4>": (V64, "test_rows_and_contexts", "short contexts"),
