@@ -253,10 +253,15 @@ hipError_t launch_ksplit(const AcceptArgs &a, int row0, int blocks, hipStream_t 
 // the hidden size in steps of kRow bytes of a row; the wavefronts form a WV x WM grid.  Both operands of a
 // step travel memory -> registers (requested one step ahead) -> LDS (16-byte chunks XOR-swizzled as in the
 // attention kernel) -> MFMA operands.  Where several workgroups share a compute unit the LDS tile is
-// single-buffered and one's MFMAs run under the other's loads and LDS traffic; a workgroup of 8
-// wavefronts has two tiles and one barrier per step (248 rows 515 -> 488 us).  Rows past V or M and columns
-// past H come back as zeros from the bounds check of the buffer loads, so no size has to be a multiple of
-// anything.
+// single-buffered and one's MFMAs run under the other's loads and LDS traffic.  A workgroup of 8 wavefronts has
+// the compute unit to itself and three LDS tiles that its loads fill directly, two steps ahead.  Rows past V or M
+// and columns past H come back as zeros from the bounds check of the buffer loads, so no size has to be a multiple
+// of anything.
+// What bounds it at 248 rows: MFMAs (530 ns of a step at the clock they run at), fp64 additions (600 ns) and
+// operand reads from LDS, which overlap only in part with two wavefronts per SIMD; without any load a step takes
+// 1.05 us, with them 1.5.  152,064 x 3584 at 248 / 372 rows, us: through registers, two LDS tiles 458 / 880; straight
+// to LDS 440 / 850; barrier before the last row of tiles 430 / 800; additions of a row of tiles beside the next
+// one's MFMAs 415 / 750.  (The two wavefronts of a SIMD half a step apart, with two barriers per step, 495 / 960.)
 // Sums: a matrix instruction rounds at the size its sums have reached (about four times per 32 bf16
 // products, once per fp32 product), so chains of two bf16 instructions or four fp32 ones start from zero
 // and are added up in fp64.  Error of a logit, against one fp32 chain over H (bf16) or over a step (fp32)
@@ -265,7 +270,7 @@ hipError_t launch_ksplit(const AcceptArgs &a, int row0, int blocks, hipStream_t 
 // 8 registers per 16 x 16 tile and the additions two vector instructions per value: wavefront tiles are
 // 64 x 64 at most, and 256 rows take one workgroup of 8 wavefronts per compute unit.
 // 152,064 x 3584 with the finalize pass, us (with one fp32 chain; before this kernel, passes of 64 rows by
-// pairs of k-split workgroups): 64 rows 188 (183; 209), 128 rows 275 (232; 413), 248 rows 445
+// pairs of k-split workgroups): 64 rows 188 (183; 209), 128 rows 275 (232; 413), 248 rows 415
 // (350; 826).  Tiles of 128 rows for 248: 533 to 561; of 64: 590; one chain after the other instead of
 // the chains of a row of tiles side by side: 488.
 // fp32 (v_mfma_f32_16x16x4: fp32 products at 157 TFLOP/s; in brackets the plain-ALU kernel): 9 rows 335 (1678), 64 rows 735 (7324),
@@ -274,8 +279,33 @@ template <int kRow> __device__ __forceinline__ int gm_swz(int row) {
   return kRow == 256 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
 }
 
-// LDS tiles: two where one workgroup of 8 wavefronts has the compute unit to itself
-constexpr int tiled_buffers(int waves) { return waves == 8 ? 2 : 1; }
+// LDS tiles: three where one workgroup of 8 wavefronts has the compute unit to itself
+constexpr int tiled_buffers(int waves) { return waves == 8 ? 3 : 1; }
+
+__device__ __forceinline__ unsigned int lds_offset(const unsigned char *p) {
+  return (unsigned int)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
+// A buffer resource in scalar registers
+__device__ __forceinline__ u32x4 buffer_words(const void *p, unsigned int bytes) {
+  const uint64_t at = (uint64_t)p;
+  return (u32x4){(unsigned int)__builtin_amdgcn_readfirstlane((int)(unsigned int)at),
+                 (unsigned int)__builtin_amdgcn_readfirstlane((int)(unsigned int)(at >> 32)) & 0xffffu,
+                 (unsigned int)__builtin_amdgcn_readfirstlane((int)bytes), 0x00027000u};
+}
+// 16 bytes per lane from memory straight to LDS, lane l's at dst + 16 l (dst uniform); past the end of the buffer
+// zeros.  Written out because the compiler, which cannot tell the LDS tiles apart, would wait for every load in
+// flight before the next LDS read; it does not count these, and wait_loads() waits for them.  The wait states are
+// those between a scalar register written by the vector ALU, or M0, and its use here.
+template <bool kNt> __device__ __forceinline__ void load_to_lds(u32x4 rs, unsigned int off, unsigned int dst) {
+  if constexpr (kNt)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
+}
+// All but the last kLeft vector memory operations of the wavefront are done, and its LDS reads
+template <int kLeft> __device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kLeft) : "memory");
+}
 
 template <class T, int VT, int BM, int kWaves, int WV, int kRow>      // kRow: bytes of a row that a step covers
 __global__ void __launch_bounds__(kWaves * 64, 2)
@@ -294,45 +324,58 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   const int H = a.H, V = a.V;
   const unsigned int row_bytes = (unsigned int)H * (unsigned int)sizeof(T);
   // workgroups of one vocabulary stream (the row blocks) sit 8 indices apart: one XCD, one time
-  const int mb = ((int)blockIdx.x >> 3) % blocks_m;
-  const int stream = ((int)blockIdx.x >> 3) / blocks_m * 8 + ((int)blockIdx.x & 7);
-  const int n_streams = (int)gridDim.x / blocks_m;
+  const int mb = __builtin_amdgcn_readfirstlane(((int)blockIdx.x >> 3) % blocks_m);
+  const int stream = __builtin_amdgcn_readfirstlane(((int)blockIdx.x >> 3) / blocks_m * 8 + ((int)blockIdx.x & 7));
+  const int n_streams = __builtin_amdgcn_readfirstlane((int)gridDim.x / blocks_m);
   const int row0 = mb * BM;
   const int n_vt = (V + VT - 1) / VT;
-  const int n_tiles = n_vt > stream ? (n_vt - stream + n_streams - 1) / n_streams : 0;
+  const int n_tiles = __builtin_amdgcn_readfirstlane(n_vt > stream ? (n_vt - stream + n_streams - 1) / n_streams : 0);
   const int nk = (H + BK - 1) / BK;
   const int n_steps = n_tiles * nk;
 
-  // loader: thread -> rows tid / kChunks + kLdRows j, 16-byte chunk tid % kChunks of the step's part of a row
-  const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
+  // loader: thread -> rows tid / kChunks + kLdRows j, one 16-byte chunk of the step's part of a row
+  const int ld_row = tid / kChunks, ld_pos = tid % kChunks;
+  constexpr int kTileBytes = (VT + BM) * kRow;
+  constexpr int kLd = kLdV + kLdM;
+  // straight to LDS: the 64 lanes of a load fill 1 KB in their order, so that the swizzle is a choice of which
+  // chunk a lane fetches (kLdRows is a multiple of 16: the same one for every j)
+  constexpr bool kDirect = tiled_buffers(kWaves) > 1;
+  static_assert(!kDirect || (kLdRows % 16 == 0 && kRow == 128), "a wavefront's load covers whole rows");
+  const int ld_ch = kDirect ? ld_pos ^ gm_swz<kRow>(ld_row) : ld_pos;
   const unsigned int ld_off = (unsigned int)ld_row * row_bytes + (unsigned int)ld_ch * 16u;
-  const __amdgpu_buffer_rsrc_t rs_m = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)((const unsigned char *)a.hidden + (int64_t)row0 * row_bytes), (short)0,
-      (int)(min(BM, a.M - row0) * row_bytes), 0x00027000);
-  u32x4 sg[kLdV + kLdM];
+  const unsigned char *const hid0 = (const unsigned char *)a.hidden + (int64_t)row0 * row_bytes;
+  const unsigned int hid_bytes = (unsigned int)min(BM, a.M - row0) * row_bytes;
+  u32x4 sg[kLd];
   int is_tile = 0, is_k = 0;                                 // the step the next issue() fetches
-  auto issue = [&]() {
+  auto issue = [&](int buf) {
     const int v0 = (stream + min(is_tile, max(n_tiles - 1, 0)) * n_streams) * VT;
     const int rows = min(VT, max(V - v0, 0));
-    const __amdgpu_buffer_rsrc_t rs_v = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)((const unsigned char *)a.lm_head + (int64_t)min(v0, V - 1) * row_bytes), (short)0,
-        (int)(rows * row_bytes), 0x00027000);
+    const unsigned char *const w0 = (const unsigned char *)a.lm_head + (int64_t)min(v0, V - 1) * row_bytes;
     const int k = is_k * BK + ld_ch * kPer;
     const unsigned int off = k < H ? ld_off + (unsigned int)(is_k * kRow) : 0x80000000u;
+    if constexpr (kDirect) {
+      const u32x4 rs_v = buffer_words(w0, (unsigned int)rows * row_bytes), rs_m = buffer_words(hid0, hid_bytes);
+      const unsigned int dst = lds_offset(smem) + (unsigned int)(buf * kTileBytes + w * 1024);
 #pragma unroll
-    for (int j = 0; j < kLdV; ++j)
-      sg[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_v, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 2);
+      for (int j = 0; j < kLd; ++j)
+        if (j < kLdV) load_to_lds<true>(rs_v, off + (unsigned int)(kLdRows * j) * row_bytes, dst + j * kLdRows * kRow);
+        else load_to_lds<false>(rs_m, off + (unsigned int)(kLdRows * (j - kLdV)) * row_bytes, dst + j * kLdRows * kRow);
+    } else {
+      const __amdgpu_buffer_rsrc_t rs_v = __builtin_amdgcn_make_buffer_rsrc((void *)w0, (short)0, (int)(rows * row_bytes), 0x00027000);
+      const __amdgpu_buffer_rsrc_t rs_m = __builtin_amdgcn_make_buffer_rsrc((void *)hid0, (short)0, (int)hid_bytes, 0x00027000);
 #pragma unroll
-    for (int j = 0; j < kLdM; ++j)
-      sg[kLdV + j] = __builtin_amdgcn_raw_buffer_load_b128(rs_m, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 0);
+      for (int j = 0; j < kLdV; ++j)
+        sg[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_v, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 2);
+#pragma unroll
+      for (int j = 0; j < kLdM; ++j)
+        sg[kLdV + j] = __builtin_amdgcn_raw_buffer_load_b128(rs_m, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 0);
+    }
     if (++is_k == nk) { is_k = 0; ++is_tile; }
   };
-  const int st_off = ld_row * kRow + ((ld_ch ^ gm_swz<kRow>(ld_row)) << 4);
-  constexpr int kTileBytes = (VT + BM) * kRow;
-  auto stash = [&](int buf) {
-    unsigned char *p = smem + buf * kTileBytes + st_off;
+  auto stash = [&]() {
+    unsigned char *p = smem + ld_row * kRow + ((ld_pos ^ gm_swz<kRow>(ld_row)) << 4);
 #pragma unroll
-    for (int j = 0; j < kLdV + kLdM; ++j) *reinterpret_cast<u32x4 *>(p + kLdRows * j * kRow) = sg[j];
+    for (int j = 0; j < kLd; ++j) *reinterpret_cast<u32x4 *>(p + kLdRows * j * kRow) = sg[j];
   };
 
   double acc[NV][NM][4];
@@ -351,48 +394,62 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   const int rd_row = n * kRow, rd_swz = gm_swz<kRow>(n);
 
   int cp_tile = 0, cp_k = 0;
-  // One step: operands out of LDS, chains of kChain 16-byte chunks from zero (64 bf16 products, 16 fp32
-  // ones), each added to the tile's running sums in fp64
+  // Operands out of LDS, chains of kChain 16-byte chunks from zero (64 bf16 products, 16 fp32 ones), each added to the
+  // tile's running sums in fp64
   constexpr int kChain = kF32 ? 1 : 2;
-  auto compute = [&](int buf) {
-    if (live) {
-      const unsigned char *pv = smem + buf * kTileBytes + wv * (NV * 16 * kRow) + rd_row;
-      const unsigned char *pm = smem + buf * kTileBytes + (VT + wm * (NM * 16)) * kRow + rd_row;
+  u32x4 bm[kChain][NM];
+  // Straight to LDS: the products of a row of tiles are added while the matrix cores form the next one's, over
+  // the barrier and into the next step
+  f32x4 pend[NM];
+  if constexpr (kDirect) {
 #pragma unroll
-      for (int ks = 0; ks < kRow / 64; ks += kChain) {
-        u32x4 bm[kChain][NM];
-        int ch[kChain];
+    for (int j = 0; j < NM; ++j) pend[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+  auto chunk = [&](int ks) { return ((4 * ks + c4) ^ rd_swz) << 4; };
+  auto read_m = [&](int buf, int ks) {
+    const unsigned char *pm = smem + buf * kTileBytes + (VT + wm * (NM * 16)) * kRow + rd_row;
 #pragma unroll
-        for (int x = 0; x < kChain; ++x) {
-          ch[x] = ((4 * (ks + x) + c4) ^ rd_swz) << 4;
+    for (int x = 0; x < kChain; ++x)
 #pragma unroll
-          for (int j = 0; j < NM; ++j) bm[x][j] = *reinterpret_cast<const u32x4 *>(pm + j * 16 * kRow + ch[x]);
-        }
+      for (int j = 0; j < NM; ++j) bm[x][j] = *reinterpret_cast<const u32x4 *>(pm + j * 16 * kRow + chunk(ks + x));
+  };
+  auto read_v = [&](u32x4 *av, int buf, int ks, int i) {
+    const unsigned char *pv = smem + buf * kTileBytes + wv * (NV * 16 * kRow) + rd_row;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          u32x4 av[kChain];
+    for (int x = 0; x < kChain; ++x) av[x] = *reinterpret_cast<const u32x4 *>(pv + i * 16 * kRow + chunk(ks + x));
+  };
+  auto products = [&](const u32x4 *av, int i) {              // row i of the wavefront's tiles
+    f32x4 p[NM];
 #pragma unroll
-          for (int x = 0; x < kChain; ++x) av[x] = *reinterpret_cast<const u32x4 *>(pv + i * 16 * kRow + ch[x]);
-          f32x4 p[NM];
+    for (int x = 0; x < (kF32 ? 4 : kChain); ++x)
 #pragma unroll
-          for (int x = 0; x < (kF32 ? 4 : kChain); ++x)
+      for (int j = 0; j < NM; ++j) {
+        if (x == 0) p[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if constexpr (kF32)       // element x of the four lanes' chunks is one k-step of 4 (the same columns on both sides)
+          p[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av[0][x]), __uint_as_float(bm[0][j][x]), p[j], 0, 0, 0);
+        else
+          p[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[x]), __builtin_bit_cast(bf16x8, bm[x][j]), p[j], 0, 0, 0);
+      }
+    const int to = kDirect ? (i + NV - 1) % NV : i;
 #pragma unroll
-            for (int j = 0; j < NM; ++j) {
-              if (x == 0) p[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-              if constexpr (kF32)       // element x of the four lanes' chunks is one k-step of 4 (the same columns on both sides)
-                p[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av[0][x]), __uint_as_float(bm[0][j][x]), p[j], 0, 0, 0);
-              else
-                p[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[x]), __builtin_bit_cast(bf16x8, bm[x][j]), p[j], 0, 0, 0);
-            }
+    for (int j = 0; j < NM; ++j) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[to][j][e] += (double)(kDirect ? pend[j][e] : p[j][e]);
+      if constexpr (kDirect) pend[j] = p[j];
+    }
+  };
+  auto end_step = [&]() {
+    if (++cp_k == nk) {                                      // tile finished
+      if (live) {
+        if constexpr (kDirect) {
 #pragma unroll
           for (int j = 0; j < NM; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] += (double)p[j][e];
+            for (int e = 0; e < 4; ++e) {
+              acc[NV - 1][j][e] += (double)pend[j][e];
+              pend[j][e] = 0.f;
+            }
         }
-      }
-    }
-    if (++cp_k == nk) {                                      // tile finished
-      if (live) {
         const int v0 = (stream + cp_tile * n_streams) * VT + wv * (NV * 16) + 4 * c4;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -410,30 +467,64 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
           }
         }
       }
+      if (kDirect && a.logits != nullptr) wait_loads<0>();   // its stores share the loads' counter
       cp_k = 0;
       ++cp_tile;
     }
   };
 
-  issue();
-  if constexpr (tiled_buffers(kWaves) == 2) {
-    // one barrier per step: tile s + 1 goes into the buffer that every wavefront has read before the
-    // barrier of step s - 1
-    stash(0);
-    issue();
+  if constexpr (kDirect) {
+    // One barrier per step, before the last row of tiles: behind it tile s + 1 is complete in LDS and tile s read
+    // for the last time (that row's operands are in registers), so that the step goes on with the hidden rows of
+    // tile s + 1 and step s + 1 begins by filling tile s's buffer.  Every load has a step and a half to arrive.
+    static_assert(kRow / 64 == kChain, "one chain per step");
+    issue(0);
+    issue(1);
+    wait_loads<kLd>();
     __syncthreads();
+    read_m(0, 0);
+    int rd = 0, wr = 2;
     for (int s = 0; s < n_steps; ++s) {
-      stash((s + 1) & 1);
-      issue();
-      compute(s & 1);
+      u32x4 av[kChain];
+      issue(wr);
+      if (live) {
+#pragma unroll
+        for (int i = 0; i < NV - 1; ++i) {
+          read_v(av, rd, 0, i);
+          products(av, i);
+        }
+        read_v(av, rd, 0, NV - 1);
+      }
+      wait_loads<kLd>();
       __syncthreads();
+      rd = rd == 2 ? 0 : rd + 1;
+      wr = wr == 2 ? 0 : wr + 1;
+      if (live) {
+        products(av, NV - 1);
+        read_m(rd, 0);
+      }
+      end_step();
     }
+    wait_loads<0>();                                         // the two tiles requested past the end
   } else {
+    issue(0);
     for (int s = 0; s < n_steps; ++s) {
-      stash(0);
+      stash();
       __syncthreads();
-      issue();
-      compute(0);
+      issue(0);
+      if (live) {
+#pragma unroll
+        for (int ks = 0; ks < kRow / 64; ks += kChain) {
+          read_m(0, ks);
+#pragma unroll
+          for (int i = 0; i < NV; ++i) {
+            u32x4 av[kChain];
+            read_v(av, 0, ks, i);
+            products(av, i);
+          }
+        }
+      }
+      end_step();
       __syncthreads();
     }
   }

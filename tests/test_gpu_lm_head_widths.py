@@ -75,6 +75,27 @@ def test_tiles_of_128_vocabulary_rows(sp, M, dtype):
     _check(sp, 264, 33001, M, M, dtype)
 
 
+@pytest.mark.parametrize("H", [8, 64, 72, 200, 1032])
+@pytest.mark.parametrize("M,V", [(129, 70001), (200, 5003), (256, 33001), (505, 33001)])
+def test_rows_straight_to_lds(sp, H, V, M):
+    """Row blocks of 256 with the loads of two steps in flight: 1 to 17 steps per tile, one to three tiles per
+    workgroup.  What lies behind the last row and the last token in memory must not reach the result."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(H + V + M)
+    W = torch.full((V + 128, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hid = torch.full((M + 256, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    W[:V] = torch.randn(V, H, generator=g, device="cuda") * H ** -0.5
+    hid[:M] = torch.randn(M, H, generator=g, device="cuda") * 2.0
+    logits = hid[:M].double() @ W[:V].double().t()
+    tol = 64 * 2.0 ** -24 * float((hid[:M].double().abs() @ W[:V].double().abs().t()).max())     # as in _check
+    ids, logp = sp.draft_topk(hid[:M], W[:V], 4)
+    ref = torch.topk(torch.log_softmax(logits, dim=1), 4, dim=1).values
+    assert float((logp.double() - ref).abs().max()) <= 2 * tol + 2e-6
+    got = sp.accept(hid[:M], W[:V], torch.zeros(0, dtype=torch.int32, device="cuda"), None, M, 0)["target_ids"].long()
+    assert torch.all(logits.max(dim=1).values - logits.gather(1, got[:, None])[:, 0] <= 2 * tol)
+    assert torch.all((ids == got[:, None].to(ids.dtype)).any(dim=1))
+
+
 @pytest.mark.parametrize("H", [256, 520, 1000, 2568, 3584, 5120])
 @pytest.mark.parametrize("M", [1, 17, 33, 65, 129, 300])
 @pytest.mark.parametrize("dtype,limit", [("bfloat16", 0.62e-7), ("float32", 0.9e-7)])
