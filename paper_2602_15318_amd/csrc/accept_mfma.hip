@@ -46,8 +46,8 @@ constexpr int kKsWaves = 8;               // most wavefronts of a workgroup
 // rows 49 us, 32 rows 54 us; 151,936 x 2560 118 us.
 template <int SPW, int NB>
 __global__ void __launch_bounds__(kKsWaves * 64)
-lm_head_ksplit_kernel(AcceptArgs a, int first_row) {
-  const int row0 = first_row + 16 * NB * (int)blockIdx.y;     // row blocks side by side
+lm_head_ksplit_kernel(AcceptArgs a) {
+  const int row0 = 16 * NB * (int)blockIdx.y;     // row blocks side by side
   const int wg = (int)blockIdx.x, n_wg = (int)gridDim.x;      // streams of vocabulary tiles
   constexpr int G = kKsGroup / NB;          // vocabulary tiles per group
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -233,15 +233,16 @@ int ksplit_grid(int H, int V, int blocks) {
 // Hidden rows of a workgroup: 32, or 16 above 4,096 columns, where the hidden rows of a wavefront's two slices
 // fill its registers.
 bool ksplit_wide(int H) { return H > kKsWaves * kKsSlice; }
-int ksplit_blocks(int M, int H) { const int rows = ksplit_wide(H) ? 16 : 32; return (M + rows - 1) / rows; }
+int ksplit_rows(int H) { return ksplit_wide(H) ? 16 : 32; }
+int ksplit_blocks(int M, int H) { return (M + ksplit_rows(H) - 1) / ksplit_rows(H); }
 
 template <int SPW, int NB>
-hipError_t launch_ksplit(const AcceptArgs &a, int row0, int blocks, hipStream_t st) {
+hipError_t launch_ksplit(const AcceptArgs &a, int blocks, hipStream_t st) {
   static const hipError_t attr = hipFuncSetAttribute((const void *)lm_head_ksplit_kernel<SPW, NB>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, ksplit_lds(kKsWaves));
   if (attr != hipSuccess) return attr;
   const int nw = ksplit_waves(a.H);
-  hipLaunchKernelGGL((lm_head_ksplit_kernel<SPW, NB>), dim3(a.n_cand, blocks), dim3(nw * 64), ksplit_lds(nw), st, a, row0);
+  hipLaunchKernelGGL((lm_head_ksplit_kernel<SPW, NB>), dim3(a.n_cand, blocks), dim3(nw * 64), ksplit_lds(nw), st, a);
   return hipGetLastError();
 }
 
@@ -308,7 +309,7 @@ template <int kLeft> __device__ __forceinline__ void wait_loads() {
 }
 
 template <class T, int VT, int BM, int kWaves, int WV, int kRow>      // kRow: bytes of a row that a step covers
-__global__ void __launch_bounds__(kWaves * 64, 2)
+__global__ void __launch_bounds__(kWaves * 64, kWaves == 8 && BM <= 64 ? 4 : 2)
 lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   constexpr int WM = kWaves / WV;
   constexpr int NV = VT / WV / 16, NM = BM / WM / 16;      // 16-row tiles of a wavefront
@@ -573,31 +574,40 @@ hipError_t launch_tiled_vt(const AcceptArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Rows of a vocabulary tile: 128, or 64 where tiles of 128 would leave compute units without one
-// (8,640 x 3456 at 248 rows, 68 tiles of 128: 75 us with tiles of 64; fp32 at 9 rows 56 us).
-int tiled_rows(int M, int V, int bm) { return (V + 127) / 128 * ((M + bm - 1) / bm) < kNumCU ? 64 : 128; }
+// Workgroups of the tiled kernel on a compute unit, as registers and LDS tiles allow.  bf16: one of 8 wavefronts,
+// two up to 64 rows; fp32: workgroups of 4, two at 128 rows, three at 64, four below.
+int tiled_per_cu(bool f32, int bm) { return f32 ? (bm > 64 ? 2 : bm > 32 ? 3 : 4) : bm > 64 ? 1 : 2; }
+
+// Rows of a vocabulary tile: 128, or 64.  bf16: 64 where all tiles of 64 then fit the chip at once; a second round
+// of them takes longer than one of 128 (2,560 x 32,000 at 100 rows 57 us against 43, 5,120 x 32,000 at 200 rows 147
+// against 118; 2,048 x 16,384 at 100 rows, 256 tiles of 64, 26).  fp32: where tiles of 128 would leave compute units
+// without one (9 rows 56 us).
+int tiled_rows(bool f32, int M, int V, int bm) {
+  const int blocks_m = (M + bm - 1) / bm;
+  if (f32) return (V + 127) / 128 * blocks_m < kNumCU ? 64 : 128;
+  return (V + 63) / 64 * blocks_m <= kNumCU * tiled_per_cu(f32, bm) ? 64 : 128;
+}
 
 template <class T, int BM, int kWaves, int WV, int kRow>
 hipError_t launch_tiled(const AcceptArgs &a, hipStream_t st) {
-  return tiled_rows(a.M, a.V, BM) == 64 ? launch_tiled_vt<T, 64, BM, kWaves, WV, kRow>(a, st) : launch_tiled_vt<T, 128, BM, kWaves, WV, kRow>(a, st);
+  return tiled_rows(std::is_same<T, float>::value, a.M, a.V, BM) == 64 ? launch_tiled_vt<T, 64, BM, kWaves, WV, kRow>(a, st) : launch_tiled_vt<T, 128, BM, kWaves, WV, kRow>(a, st);
 }
 
-// Workgroups of the tiled kernel for row blocks of bm: as many per compute unit as registers allow (one of
-// 8 wavefronts at 256 rows, two of 4 at 128, three at 64, four below), fewer if there are fewer tiles; a
-// multiple of 8 per row block.
-int tiled_grid(int M, int V, int bm) {
-  const int blocks_m = (M + bm - 1) / bm, vt = tiled_rows(M, V, bm);
+// Workgroups for row blocks of bm: as many as the chip holds, fewer if there are fewer tiles; a multiple of 8 per
+// row block.
+int tiled_grid(bool f32, int M, int V, int bm) {
+  const int blocks_m = (M + bm - 1) / bm, vt = tiled_rows(f32, M, V, bm);
   const int tiles = (V + vt - 1) / vt;
-  const int per_block = kNumCU * (bm > 128 ? 1 : bm > 64 ? 2 : bm > 32 ? 3 : 4) / (8 * blocks_m) * 8;
+  const int per_block = kNumCU * tiled_per_cu(f32, bm) / (8 * blocks_m) * 8;
   return std::min(per_block, (tiles + 7) / 8 * 8) * blocks_m;
 }
 int f32_block(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128; }
 
-// Up to here the k-split kernel, whose hidden rows sit in registers: at 32 rows of 3,584 173 us against 186.
-// (Above 4,096 columns 17 to 32 rows then take two passes over W: 24 rows of 5,120 456 us, where the tiled
-// kernel needs 270 for 64.  The line is the same there so far.)
-constexpr int kKsMaxRows = 32;
-
+// Up to here the k-split kernel, whose hidden rows sit in registers: one row block.  Against the tiled kernel at 32
+// rows, us: 152,064 x 3584 171 / 167, 64,003 x 2048 53 / 57, 40,003 x 1024 26.7 / 23.5, 32,000 x 2560 38 / 34: either
+// way by width and vocabulary up to 4,096 columns; above, where 17 rows need a second pass over W, 32,000 x 5120
+// 112 / 60.
+//
 // Above that line the k-split kernel, all its row blocks side by side, where the vocabulary is too small to fill
 // the chip with tiles of the whole hidden size: the tiled kernel then lasts 0.8 us per 64 columns, one step after
 // the other, a k-split workgroup 4 us per 16-row tile (6 with two slices per wavefront), whatever the width.
@@ -605,7 +615,7 @@ constexpr int kKsMaxRows = 32;
 // 21, 256 rows 20 / 61 / 75; 8,640 x 3,584, 64 rows 30 / 50 / 32; 16,000 x 4,096, 64 rows 45 / 61 / 45, 128 rows
 // 66 / 70 / 85; 1,000 x 8,192, 64 rows 27 / 78 / 570 (plain ALU); 32,000 x 2,048, 64 rows 50 / 41 / 146.
 bool ksplit_small(int M, int H, int V) {
-  if (M <= kKsMaxRows || H > 2 * kKsWaves * kKsSlice) return false;
+  if (M <= ksplit_rows(H) || H > 2 * kKsWaves * kKsSlice) return false;
   const int blocks = ksplit_blocks(M, H), grid = ksplit_grid(H, V, blocks);
   const int rounds = ((V + 15) / 16 + grid - 1) / grid * ((blocks * grid + ksplit_slots(H) - 1) / ksplit_slots(H));
   return (ksplit_wide(H) ? 6 : 4) * rounds + 8 < 6 + H / 80;
@@ -620,13 +630,11 @@ bool lm_head_mfma_supported(int dtype, int M, int H, int V) {
 }
 
 int accept_num_candidates(int dtype, int M, int H, int V) {
-  if (dtype == SPARROW_F32) return tiled_grid(M, V, f32_block(M));
+  if (dtype == SPARROW_F32) return tiled_grid(true, M, V, f32_block(M));
   if (ksplit_small(M, H, V)) return ksplit_grid(H, V, ksplit_blocks(M, H));
-  return M > kKsMaxRows ? tiled_grid(M, V, M > 128 ? 256 : M > 64 ? 128 : 64) : ksplit_grid(H, V, 1);
+  return M > ksplit_rows(H) ? tiled_grid(false, M, V, M > 128 ? 256 : M > 64 ? 128 : 64) : ksplit_grid(H, V, 1);
 }
 
-// Up to 32 rows: one pass over W, two of 16 rows above 4,096 columns, where the hidden rows of a wavefront's
-// two slices fill its registers at 16 rows.
 hipError_t launch_lm_head_mfma(int dtype, const AcceptArgs &a, hipStream_t st) {
   if (dtype == SPARROW_F32) {
     switch (f32_block(a.M)) {
@@ -639,20 +647,13 @@ hipError_t launch_lm_head_mfma(int dtype, const AcceptArgs &a, hipStream_t st) {
   const bool wide = ksplit_wide(a.H);
   if (ksplit_small(a.M, a.H, a.V)) {
     const int blocks = ksplit_blocks(a.M, a.H);
-    return wide ? launch_ksplit<2, 1>(a, 0, blocks, st) : launch_ksplit<1, 2>(a, 0, blocks, st);
+    return wide ? launch_ksplit<2, 1>(a, blocks, st) : launch_ksplit<1, 2>(a, blocks, st);
   }
   if (a.M > 128) return launch_tiled<bf16_t, 256, 8, 2, 128>(a, st);
-  if (a.M > 64) return launch_tiled<bf16_t, 128, 4, 2, 128>(a, st);
-  if (a.M > kKsMaxRows) return launch_tiled<bf16_t, 64, 4, 2, 128>(a, st);
-  for (int row0 = 0; row0 < a.M;) {
-    const int left = a.M - row0;
-    hipError_t e;
-    if (wide) { e = launch_ksplit<2, 1>(a, row0, 1, st); row0 += 16; }
-    else if (left > 16) { e = launch_ksplit<1, 2>(a, row0, 1, st); row0 += 32; }
-    else { e = launch_ksplit<1, 1>(a, row0, 1, st); row0 += 16; }
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  if (a.M > 64) return launch_tiled<bf16_t, 128, 8, 2, 128>(a, st);
+  if (a.M > ksplit_rows(a.H)) return launch_tiled<bf16_t, 64, 8, 2, 128>(a, st);
+  if (wide) return launch_ksplit<2, 1>(a, 1, st);
+  return a.M > 16 ? launch_ksplit<1, 2>(a, 1, st) : launch_ksplit<1, 1>(a, 1, st);
 }
 
 }  // namespace sparrow

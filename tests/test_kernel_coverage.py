@@ -83,10 +83,10 @@ COVERAGE = {
     "lm_head_tiled_kernel<float, 128, 64, 4, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 64 rows"),
     "lm_head_tiled_kernel<float, 64, 128, 4, 2, 128>": (LM, "test_fp32", "fp32, up to 128 rows"),
     "lm_head_tiled_kernel<float, 128, 128, 4, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "fp32, up to 128 rows"),
-    "lm_head_tiled_kernel<unsigned short, 64, 64, 4, 2, 128>": (LM, "test_hidden_sizes", "bf16, up to 64 rows"),
-    "lm_head_tiled_kernel<unsigned short, 128, 64, 4, 2, 128>": (LM, "test_whole_vocabularies", "bf16, up to 64 rows"),
-    "lm_head_tiled_kernel<unsigned short, 64, 128, 4, 2, 128>": (LM, "test_many_rows", "bf16, up to 128 rows"),
-    "lm_head_tiled_kernel<unsigned short, 128, 128, 4, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 128 rows"),
+    "lm_head_tiled_kernel<unsigned short, 64, 64, 8, 2, 128>": (LM, "test_hidden_sizes", "bf16, up to 64 rows"),
+    "lm_head_tiled_kernel<unsigned short, 128, 64, 8, 2, 128>": (LM, "test_whole_vocabularies", "bf16, up to 64 rows"),
+    "lm_head_tiled_kernel<unsigned short, 64, 128, 8, 2, 128>": (LM, "test_many_rows", "bf16, up to 128 rows"),
+    "lm_head_tiled_kernel<unsigned short, 128, 128, 8, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 128 rows"),
     "lm_head_tiled_kernel<unsigned short, 64, 256, 8, 2, 128>": (LM, "test_many_rows", "bf16, up to 256 rows"),
     "lm_head_tiled_kernel<unsigned short, 128, 256, 8, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 256 rows"),
     "accept_finalize_kernel": (AC, "test_accept_shapes", "every greedy case"),
