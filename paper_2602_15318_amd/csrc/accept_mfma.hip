@@ -250,19 +250,19 @@ hipError_t launch_ksplit(const AcceptArgs &a, int blocks, hipStream_t st) {
 // Tiled kernel for more than 32 hidden rows (draft trees, batches) and for fp32: one pass over W
 // whatever the number of rows up to 256 (fp32: 128), row blocks side by side above.
 //
-// A persistent workgroup of 4 or 8 wavefronts owns tiles of VT vocabulary rows x BM hidden rows and walks
+// A persistent workgroup of 4 (fp32) or 8 (bf16) wavefronts owns tiles of VT vocabulary rows x BM hidden rows and walks
 // the hidden size in steps of kRow bytes of a row; the wavefronts form a WV x WM grid.  Both operands of a
 // step travel memory -> registers (requested one step ahead) -> LDS (16-byte chunks XOR-swizzled as in the
-// attention kernel) -> MFMA operands.  Where several workgroups share a compute unit the LDS tile is
-// single-buffered and one's MFMAs run under the other's loads and LDS traffic.  A workgroup of 8 wavefronts has
-// the compute unit to itself and three LDS tiles that its loads fill directly, two steps ahead.  Rows past V or M
+// attention kernel) -> MFMA operands; the workgroups that share a compute unit have one LDS tile each and one's
+// MFMAs run under the other's loads and LDS traffic.  A workgroup of 8 wavefronts has three LDS tiles that its loads
+// fill directly, two steps ahead.  Rows past V or M
 // and columns past H come back as zeros from the bounds check of the buffer loads, so no size has to be a multiple
 // of anything.
 // What bounds it at 248 rows: MFMAs (530 ns of a step at the clock they run at), fp64 additions (600 ns) and
 // operand reads from LDS, which overlap only in part with two wavefronts per SIMD; without any load a step takes
 // 1.05 us, with them 1.5.  152,064 x 3584 at 248 / 372 rows, us: through registers, two LDS tiles 458 / 880; straight
 // to LDS 440 / 850; barrier before the last row of tiles 430 / 800; additions of a row of tiles beside the next
-// one's MFMAs 415 / 750.  (The two wavefronts of a SIMD half a step apart, with two barriers per step, 495 / 960.)
+// one's MFMAs 415 / 750.  At 40 / 96 / 124 rows, 4 wavefronts through registers, 179 / 270 / 276; as here 168 / 228 / 253.  (The two wavefronts of a SIMD half a step apart, with two barriers per step, 495 / 960.)
 // Sums: a matrix instruction rounds at the size its sums have reached (about four times per 32 bf16
 // products, once per fp32 product), so chains of two bf16 instructions or four fp32 ones start from zero
 // and are added up in fp64.  Error of a logit, against one fp32 chain over H (bf16) or over a step (fp32)
@@ -270,17 +270,14 @@ hipError_t launch_ksplit(const AcceptArgs &a, int blocks, hipStream_t st) {
 // 3,584, 4.5e-7 at 5,120; 0.55 to 1.05e-7), fp32 0.8e-7 (1.2 to 2.7e-7; 0.78 to 1.9e-7).  The sums take
 // 8 registers per 16 x 16 tile and the additions two vector instructions per value: wavefront tiles are
 // 64 x 64 at most, and 256 rows take one workgroup of 8 wavefronts per compute unit.
-// 152,064 x 3584 with the finalize pass, us (with one fp32 chain; before this kernel, passes of 64 rows by
-// pairs of k-split workgroups): 64 rows 188 (183; 209), 128 rows 275 (232; 413), 248 rows 415
-// (350; 826).  Tiles of 128 rows for 248: 533 to 561; of 64: 590; one chain after the other instead of
-// the chains of a row of tiles side by side: 488.
+// 152,064 x 3584 with the finalize pass, us: 62 rows 178, 124 rows 253, 248 rows 415.
 // fp32 (v_mfma_f32_16x16x4: fp32 products at 157 TFLOP/s; in brackets the plain-ALU kernel): 9 rows 335 (1678), 64 rows 735 (7324),
 // 248 rows 3124 (29370); 32,000 x 1024 at 9 rows 32 (137).
 template <int kRow> __device__ __forceinline__ int gm_swz(int row) {
   return kRow == 256 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
 }
 
-// LDS tiles: three where one workgroup of 8 wavefronts has the compute unit to itself
+// LDS tiles: three for a workgroup of 8 wavefronts (147 KB at 256 rows, two workgroups of 72 KB at 64)
 constexpr int tiled_buffers(int waves) { return waves == 8 ? 3 : 1; }
 
 __device__ __forceinline__ unsigned int lds_offset(const unsigned char *p) {
@@ -611,9 +608,9 @@ int f32_block(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128; 
 // Above that line the k-split kernel, all its row blocks side by side, where the vocabulary is too small to fill
 // the chip with tiles of the whole hidden size: the tiled kernel then lasts 0.8 us per 64 columns, one step after
 // the other, a k-split workgroup 4 us per 16-row tile (6 with two slices per wavefront), whatever the width.
-// k-split / tiled / pairs of k-split workgroups before, us with the finalize pass: 1,000 x 3,584, 64 rows 18 / 46 /
-// 21, 256 rows 20 / 61 / 75; 8,640 x 3,584, 64 rows 30 / 50 / 32; 16,000 x 4,096, 64 rows 45 / 61 / 45, 128 rows
-// 66 / 70 / 85; 1,000 x 8,192, 64 rows 27 / 78 / 570 (plain ALU); 32,000 x 2,048, 64 rows 50 / 41 / 146.
+// k-split / tiled, us with the finalize pass: 1,009 x 736 at 74 rows 9.1 / 13.7; 4,658 x 4,152 at 62 rows 25 / 39;
+// 2,078 x 5,416 at 64 rows 21 / 48; 1,330 x 3,840 at 357 rows 32 / 58; 5,193 x 7,416 at 102 rows 62 / 81.  Where the
+// two estimates are close they miss by up to a fifth (14,716 x 1,904 at 48 rows 27 / 22).
 bool ksplit_small(int M, int H, int V) {
   if (M <= ksplit_rows(H) || H > 2 * kKsWaves * kKsSlice) return false;
   const int blocks = ksplit_blocks(M, H), grid = ksplit_grid(H, V, blocks);
