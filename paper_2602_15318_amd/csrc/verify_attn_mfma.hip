@@ -91,14 +91,15 @@ struct PieceTable {
 // sequences of 6,001, 16/4 heads, chain of 8, 14.0 -> 14.5 us a call; 60-node tree at 26k 36.4 -> 39 to 41.
 template <int kD> constexpr bool kWideState = kD == 64;
 
-// kPing (two row tiles over long splits) runs its two streams half a step apart: while one stream's
+// kPing (two row tiles, several row blocks, long splits) runs its two streams half a step apart: while one stream's
 // wavefronts issue the MFMAs of a step (scores of the next tile, output of this one), the other stream's, which
 // share the SIMDs with them, are in their softmax.  In step, the phases of all wavefronts add up: matrix
 // cores, vector ALU and LDS were busy 27, 31 and 42 per cent of the time.  The LDS reads of V^T, the LDS
 // writes and the requests of later tiles are issued between the MFMAs; independent sums alternate.
-// 60-node tree over 26,112 tokens 45.4 -> 41.0 us a call (with the combine pass) in an unbroken row of calls, 40.2
-// -> 37.0 to 39.4 in short ones at a higher clock; two of 64 nodes over 30,000 (64/8 heads) 157 -> 138 (910 TFLOP/s).  Three row tiles and the fp32 state of heads of 64 do not leave the
-// registers for it (the latter 42 -> 67 us with spills); which calls take it: ping_pong_pays below.
+// In step / half a step apart, us a call with the combine pass, in an unbroken row of calls: 60-node tree over 26,112
+// tokens (28/4 heads) 38.5 / 35.8, two of 64 nodes over 30,000 (64/8 heads) 147 / 135 (930 TFLOP/s).  Three row tiles
+// and the fp32 state of heads of 64 do not leave the registers for it (the latter 42 -> 67 us with spills); which
+// calls take it: half_step_pays below.
 
 // kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
@@ -771,13 +772,12 @@ int verify_mfma_row_blocks(int dtype, int R) {
   return rbs3 * 3 - tiles <= rbs2 * 2 - tiles ? rbs3 : rbs2;
 }
 
-// The two streams half a step apart: from eleven steps on (shorter splits lose 3 to 10 per cent to the longer
-// start), where the calls are bound by the compute units: several row blocks share a stream.  One block of 128
-// rows runs at 4 TB/s and gains only where a head's rows follow each other in memory (12 ragged sequences
-// of 4,099, trees of 30, us: rows of one head side by side 57.3 -> 53.2, token by token 55.1 -> 55.4 to 58.6).
-static bool ping_pong_pays(const VerifyArgs &a, int steps, int rbs) {
-  return a.d == 128 && steps > 10 && (rbs > 1 || a.stride_tok <= 2 * a.d);
-}
+// The two streams half a step apart: where several row blocks share a stream, from 14 steps on.  Time in step / half a
+// step apart, median and range over drawn calls (8 to 64 nodes, 1 to 12 sequences, all layouts of K and V):
+//   several blocks, 11 to 13 steps 0.99 (0.93 to 1.03), 14 to 18 steps 1.02 (0.95 to 1.06), more 1.04 (1.00 to 1.10):
+//   the longer start and end of a split have to be earned back;
+//   one block of 128 rows 0.97 (0.90 to 1.11): half of the matrix work per byte of K and V, which then set the pace.
+static bool half_step_pays(int steps, int rbs) { return rbs > 1 && steps >= 14; }
 
 template <int kD>
 static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
@@ -806,7 +806,7 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
     hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 3, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2 && steps <= 10)
     hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
-  else if (qt == 2 && kD == 128 && ping_pong_pays(a, steps, rbs))
+  else if (qt == 2 && kD == 128 && half_step_pays(steps, rbs))
     hipLaunchKernelGGL((verify_partial_mfma_kernel<128, 2, 2, true>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2)
     hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);

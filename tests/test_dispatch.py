@@ -1,0 +1,50 @@
+"""The kernels that calls are sent to, and how their work is cut, on the CPU (launch_recorder.py)."""
+import pytest
+
+from launch_recorder import record
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("recorder")
+    return lambda calls: record(calls, tmp)
+
+
+def verify(Hq, Hkv, n_q, lens, layout="token", own=False, d=128):
+    return dict(call="verify", Hq=Hq, Hkv=Hkv, d=d, n_q=n_q, lens=list(lens), layout=layout, own=own)
+
+
+IN_STEP, HALF_STEP = "verify_partial_mfma_kernel<128, 2, 2, false>", "verify_partial_mfma_kernel<128, 2, 2, true>"
+
+
+@pytest.mark.parametrize("layout", ["token", "head", "pair"])
+def test_streams_half_a_step_apart_only_where_they_are_faster(launches, layout):
+    """Several blocks of 128 rows over splits of 14 steps of 64 tokens and more.  One block loses 1 to 9 per cent by it
+    with every layout of K and V, shorter splits 1 to 4."""
+    cases = [((28, 4, 16), 64, 704, IN_STEP), ((28, 4, 16), 64, 1920, IN_STEP), ((32, 8, 30), 32, 1472, IN_STEP),
+             ((28, 4, 30), 32, 704, IN_STEP), ((28, 4, 30), 32, 832, IN_STEP), ((28, 4, 30), 32, 864, HALF_STEP),
+             ((28, 4, 60), 16, 832, IN_STEP), ((28, 4, 60), 16, 864, HALF_STEP), ((28, 4, 60), 16, 1664, HALF_STEP),
+             ((28, 4, 60), 16, 640, "verify_partial_mfma_kernel<128, 1, 2, false>")]
+    got = launches([verify(*heads, [splits * piece], layout) for heads, splits, piece, _ in cases])
+    for (heads, splits, piece, kernel), run in zip(cases, got):
+        assert (run[0]["splits"], run[0]["pieces"]) == ([splits], [piece]), (heads, run[0])
+        assert run[0]["kernel"] == kernel, (heads, splits, piece)
+
+
+def test_long_tree_cases(launches):
+    """test_gpu_verify_long_trees.py runs the instances, splits and grids that it names."""
+    from test_gpu_verify_long_trees import BATCHES, ONE_SEQUENCE
+    got = launches([verify(*heads, [splits * piece - short]) for heads, splits, piece, short in ONE_SEQUENCE])
+    for (heads, splits, piece, short), run in zip(ONE_SEQUENCE, got):
+        assert (run[0]["splits"], run[0]["pieces"]) == ([splits], [piece]), (heads, short, run[0])
+        assert short < piece
+        half = heads[0] // heads[1] * heads[2] > 128 and piece > 832
+        assert run[0]["kernel"] == (HALF_STEP if half else IN_STEP), (heads, piece, short)
+    kinds = set()
+    for layout in ("token", "head", "pair"):
+        got = launches([verify(*heads, lens, layout, own=True) for heads, lens, _, _ in BATCHES])
+        for (heads, lens, splits, flat), run in zip(BATCHES, got):
+            assert (run[0]["splits"], run[0]["flat"]) == (list(splits), flat), (heads, lens, run[0])
+            last = [n - (s - 1) * p for n, s, p in zip(lens, splits, run[0]["pieces"])]
+            kinds.add((run[0]["kernel"], flat, min(last) <= 0))
+    assert kinds >= {(HALF_STEP, False, False), (HALF_STEP, True, False), (HALF_STEP, True, True), (IN_STEP, True, False)}

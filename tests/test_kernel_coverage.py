@@ -28,8 +28,8 @@ COVERAGE = {
     "verify_partial_mfma_kernel<128, 1, 1, false>": (A, "test_c5_bf16_26k_chain8_layer", "C5 layer, C2; chains up to 64 rows per KV head"),
     "verify_partial_mfma_kernel<128, 2, 1, false>": (A, "test_c4_bf16_ragged_batch8", "splits of four steps and more: ragged batch"),
     "verify_partial_mfma_kernel<128, 1, 2, false>": (A, "test_paper_sized_trees_at_26k_context", "16-node tree: one block of 128 rows, short splits"),
-    "verify_partial_mfma_kernel<128, 2, 2, true>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree and the 30-node tree: blocks of 128 rows"),
-    "verify_partial_mfma_kernel<128, 2, 2, false>": (VL, "test_split_ends", "token-major K/V, one block of 128 rows"),
+    "verify_partial_mfma_kernel<128, 2, 2, true>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree: several blocks of 128 rows, long splits"),
+    "verify_partial_mfma_kernel<128, 2, 2, false>": (VL, "test_split_ends", "one block of 128 rows over long splits; several over shorter ones"),
     "verify_partial_mfma_kernel<128, 1, 3, false>": (A, "test_paper_sized_trees_at_26k_context", "48-, 44- and 25-node trees: blocks of 192 rows"),
     "verify_combine_tiled_kernel<unsigned short, 128, 16>": (A, "test_c5_bf16_26k_chain8_layer", "more than 32 splits per sequence"),
     "verify_combine_tiled_kernel<unsigned short, 128, 8>": (A, "test_paper_sized_trees_at_26k_context", "17 to 32 splits (30-, 48-node trees)"),
