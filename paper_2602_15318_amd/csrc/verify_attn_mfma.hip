@@ -202,15 +202,24 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   // row r of the step lands at byte r*kRowBytes + ((chunk ^ swz(r)) * 16); swz depends on r mod 8 only
   const int st_off = ld_row * kRowBytes + ((ld_ch ^ swz<kD>(ld_row)) << 4);
   auto stash1 = [&](int buf, int kv, int st, int j, u32x4 *sg) __attribute__((always_inline)) {
-    if ((kWide || kPing) && kv == 1) {
-      // values past the end of the split are zero, as in the plain-ALU kernel: a duplicate of an
-      // infinite last row would give 0 * inf
+    if (kPing && kv == 1) {                                // values past the end of the split: zero
       const int left = t1 - (t0 + (st * kStreams + strm) * kSub * kTile);
       if (left < kSub * kTile && ld_row + kLdRows * j >= left) sg[j] = (u32x4){0u, 0u, 0u, 0u};
     }
     *reinterpret_cast<u32x4 *>(lds_at(strm, buf, kv) + st_off + kLdRows * j * kRowBytes) = sg[j];
   };
   auto stash = [&](int buf, int kv, int st, u32x4 *sg) __attribute__((always_inline)) {
+    if (kWide && kv == 1) {
+      // values past the end of the split are zero, as in the plain-ALU kernel: a duplicate of an
+      // infinite last row would give 0 * inf.  One test per step, uniform over the wavefront (tested load by
+      // load: 0.2 us a call)
+      const int left = t1 - (t0 + (st * kStreams + strm) * kSub * kTile);
+      if (left < kSub * kTile) {
+#pragma unroll
+        for (int j = 0; j < kLd; ++j)
+          if (ld_row + kLdRows * j >= left) sg[j] = (u32x4){0u, 0u, 0u, 0u};
+      }
+    }
 #pragma unroll
     for (int j = 0; j < kLd; ++j) stash1(buf, kv, st, j, sg);
   };
@@ -339,6 +348,9 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     const bool edge = tb + kSub * kTile > min(t1, L);   // uniform: split end or draft rows in reach
 #pragma unroll
     for (int qt = 0; qt < kQT; ++qt) {
+      float sc[4 * kSlabs];       // (as elements of s the maxima cost an instruction more per score)
+#pragma unroll
+      for (int e = 0; e < 4 * kSlabs; ++e) sc[e] = s[qt][e >> 2][e & 3];
       if (edge) {
         // (an opaque copy of the step's first token: without it the compiler works the token
         // numbers, their distances to L and the shift counts out on EVERY step, ahead of the
@@ -352,12 +364,12 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
             const int tok = tb_e + 16 * j + 4 * c4 + i;
             const int dj = tok - L;
             const bool vis = (dj < 0) | (((anc[qt] >> (dj & 63)) & 1ull) != 0ull);
-            s[qt][j][i] = ((tok < t1) & vis) ? s[qt][j][i] : -INFINITY;
+            sc[4 * j + i] = ((tok < t1) & vis) ? sc[4 * j + i] : -INFINITY;
           }
       }
-      float mx = s[qt][0][0];
+      float mx = sc[0];
 #pragma unroll
-      for (int e = 1; e < 4 * kSlabs; ++e) mx = fmaxf(mx, s[qt][e >> 2][e & 3]);
+      for (int e = 1; e < 4 * kSlabs; ++e) mx = fmaxf(mx, sc[e]);
       mx *= a.scale_log2;
       // The reference point m of a row moves only when some score of the wavefront's tile lies
       // more than kSlack above it (exponentials then stay below 2^kSlack, far from overflow, and
@@ -376,7 +388,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         float psum = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float p = fast_exp2(fmaf(s[qt][2 * u + (e >> 2)][e & 3], a.scale_log2, -m_run[qt]));
+          const float p = fast_exp2(fmaf(sc[8 * u + e], a.scale_log2, -m_run[qt]));
           if (!kMfmaRowSum) psum += p;
           if (kWide) {
             // p = hi + mid + lo: the leading 8 bits (cut off, so that the rest has p's sign), the
