@@ -48,3 +48,19 @@ def test_long_tree_cases(launches):
             last = [n - (s - 1) * p for n, s, p in zip(lens, splits, run[0]["pieces"])]
             kinds.add((run[0]["kernel"], flat, min(last) <= 0))
     assert kinds >= {(HALF_STEP, False, False), (HALF_STEP, True, False), (HALF_STEP, True, True), (IN_STEP, True, False)}
+
+
+def test_lm_head_cases_straight_to_lds(launches):
+    """test_gpu_lm_head_widths.py runs every instance that loads straight to LDS: each row block with one tile per
+    workgroup and, where its tiles have 128 rows, with several; and these instances from 17 rows up above 4,096 columns."""
+    from test_gpu_lm_head_widths import STRAIGHT_TO_LDS, STRAIGHT_TO_LDS_WIDE
+    cases = [(H, M, V, vt) for H in (8, 1032) for M, V, vt in STRAIGHT_TO_LDS] + STRAIGHT_TO_LDS_WIDE
+    seen = {}
+    for call in ("accept", "topk"):
+        got = launches([dict(call=call, dtype="bf16", M=M, H=H, V=V) for H, M, V, _ in cases])
+        for (H, M, V, vt), run in zip(cases, got):
+            rows = 64 if M <= 64 else 128 if M <= 128 else 256
+            assert run[0]["kernel"] == f"lm_head_tiled_kernel<unsigned short, {vt}, {rows}, 8, 2, 128>", (call, H, M, V)
+            workgroups = run[0]["grid"][0] // -(-M // rows)
+            seen.setdefault((vt, rows), set()).add(-(-V // vt) > workgroups)
+    assert seen == {(64, r): {False} for r in (64, 128, 256)} | {(128, r): {False, True} for r in (64, 128, 256)}

@@ -75,11 +75,21 @@ def test_tiles_of_128_vocabulary_rows(sp, M, dtype):
     _check(sp, 264, 33001, M, M, dtype)
 
 
-@pytest.mark.parametrize("H", [8, 64, 72, 200, 1032])
-@pytest.mark.parametrize("M,V", [(129, 70001), (200, 5003), (256, 33001), (505, 33001)])
+# Rows, vocabulary, vocabulary rows of a tile: row blocks of 64, 128 and 256 rows, full and not, one tile per workgroup and
+# several.  test_dispatch.py holds the instances and the tiles per workgroup against the library.
+STRAIGHT_TO_LDS = [(33, 140001, 128), (64, 140001, 128), (50, 30011, 64), (65, 33001, 128), (100, 70001, 128),
+                   (128, 33001, 128), (128, 9001, 64), (129, 70001, 128), (200, 5003, 64), (256, 33001, 128), (505, 33001, 128)]
+# Width, rows, vocabulary, vocabulary rows of a tile: above 4,096 columns from 17 rows on
+STRAIGHT_TO_LDS_WIDE = [(4104, 17, 33001, 128), (5120, 20, 32000, 64), (5120, 24, 70001, 128), (8192, 32, 33001, 128),
+                        (4104, 33, 70001, 128), (8192, 50, 20011, 64), (5120, 64, 33001, 128), (4104, 65, 12001, 64),
+                        (5120, 100, 33001, 128), (8192, 128, 20011, 128), (5120, 129, 20001, 128), (4104, 300, 33001, 128)]
+
+
+@pytest.mark.parametrize("H,M,V", [(H, M, V) for H in (8, 64, 72, 200, 1032) for M, V, _ in STRAIGHT_TO_LDS]
+                         + [(H, M, V) for H, M, V, _ in STRAIGHT_TO_LDS_WIDE])
 def test_rows_straight_to_lds(sp, H, V, M):
-    """Row blocks of 256 with the loads of two steps in flight: 1 to 17 steps per tile, one to three tiles per
-    workgroup.  What lies behind the last row and the last token in memory must not reach the result."""
+    """Loads of two steps in flight: 1 to 128 steps per tile, one to three tiles per workgroup.  What lies behind the
+    last row and the last token in memory must not reach the result."""
     import torch
     g = torch.Generator(device="cuda").manual_seed(H + V + M)
     W = torch.full((V + 128, H), float("nan"), dtype=torch.bfloat16, device="cuda")
