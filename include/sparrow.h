@@ -206,8 +206,8 @@ int sparrow_verify_attn_static(const sparrow_attn_desc *desc, const void *q, con
  *  workspace   dev, at least sparrow_accept_workspace() bytes (per-tile argmax candidates); the query
  *              never falls as B or n_q grow, so the largest batch's serves every smaller one
  *  Limits: B*(n_q+1) <= SPARROW_MAX_ACCEPT_ROWS logit rows.  The weights are streamed from memory once
- *  per 256 rows (fp32: per 128; bf16 with hidden > 4,096 and 17 to 32 rows: twice; bf16 with hidden >
- *  8,192: once per 8 rows, without the matrix cores).  n_q = 0 is allowed (plain greedy decode of row 0).
+ *  per 256 rows (fp32: per 128; bf16 with hidden > 8,192: once per 8 rows, without the matrix cores).
+ *  n_q = 0 is allowed (plain greedy decode of row 0).
  * sparrow_accept_trees: the same with one draft tree per sequence (a batch of requests that each
  *  grew a dynamic tree): parent dev int32 [B, parent_stride], parent_stride >= n_q (0 = the shared
  *  [n_q] form of sparrow_accept).

@@ -247,22 +247,30 @@ hipError_t launch_ksplit(const AcceptArgs &a, int blocks, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Tiled kernel for more than 32 hidden rows (draft trees, batches) and for fp32: one pass over W
-// whatever the number of rows up to 256 (fp32: 128), row blocks side by side above.
+// Tiled kernel for the rows that the k-split kernel does not take (bf16: more than 32, more than 16 above 4,096
+// columns) and for fp32: one pass over W whatever the number of rows up to 256 (fp32: 128), row blocks side by
+// side above.
 //
-// A persistent workgroup of 4 (fp32) or 8 (bf16) wavefronts owns tiles of VT vocabulary rows x BM hidden rows and walks
-// the hidden size in steps of kRow bytes of a row; the wavefronts form a WV x WM grid.  Both operands of a
-// step travel memory -> registers (requested one step ahead) -> LDS (16-byte chunks XOR-swizzled as in the
-// attention kernel) -> MFMA operands; the workgroups that share a compute unit have one LDS tile each and one's
-// MFMAs run under the other's loads and LDS traffic.  A workgroup of 8 wavefronts has three LDS tiles that its loads
-// fill directly, two steps ahead.  Rows past V or M
-// and columns past H come back as zeros from the bounds check of the buffer loads, so no size has to be a multiple
-// of anything.
+// A persistent workgroup owns tiles of VT vocabulary rows x BM hidden rows and walks the hidden size in steps of
+// kRow bytes of a row; its wavefronts form a WV x WM grid.  16-byte chunks lie XOR-swizzled in LDS as in the
+// attention kernel.  fp32: 4 wavefronts; both operands of a step travel memory -> registers (requested one step
+// ahead) -> LDS -> MFMA operands; the workgroups that share a compute unit have one LDS tile each and one's MFMAs
+// run under the other's loads and LDS traffic.  bf16: 8 wavefronts; the loads fill three LDS tiles directly, two
+// steps ahead.  Rows past V or M and columns past H come back as zeros from the bounds check of the buffer loads,
+// so no size has to be a multiple of anything.
 // What bounds it at 248 rows: MFMAs (530 ns of a step at the clock they run at), fp64 additions (600 ns) and
 // operand reads from LDS, which overlap only in part with two wavefronts per SIMD; without any load a step takes
-// 1.05 us, with them 1.5.  152,064 x 3584 at 248 / 372 rows, us: through registers, two LDS tiles 458 / 880; straight
-// to LDS 440 / 850; barrier before the last row of tiles 430 / 800; additions of a row of tiles beside the next
-// one's MFMAs 415 / 750.  At 40 / 96 / 124 rows, 4 wavefronts through registers, 179 / 270 / 276; as here 168 / 228 / 253.  (The two wavefronts of a SIMD half a step apart, with two barriers per step, 495 / 960.)
+// 1.05 us, with them 1.5.  152,064 x 3584 at 248 / 372 rows, us, step by step: through registers, two LDS tiles
+// 458 / 880; straight to LDS 440 / 850; barrier before the last row of tiles 430 / 800; additions of a row of tiles
+// beside the next one's MFMAs 415 / 750.  (The two wavefronts of a SIMD half a step apart, with two barriers per
+// step, 495 / 960.)
+// bf16 tiles, 4 wavefronts through registers (256 rows: 8, two LDS tiles) / as here, time ratio over drawn sizes,
+// median and range: 64 x 64 1.07 (0.97 to 1.59), 128 x 64 1.02 (0.93 to 1.16), 64 x 128 1.23 (1.10 to 1.63), 128 x
+// 128 1.11 (0.99 to 1.24), 64 x 256 1.02 (0.94 to 1.14), 128 x 256 1.11 (0.99 to 1.46), the gains of other tile
+// heights included; with the logits stored 1.02, 1.00, 1.09, 1.03, 1.01, 1.06 (0.93 to 1.49).  128 x 64 is slower
+// where all tiles fit the chip at once and rows are short (33 rows of 584 x 45,097 22.9 / 24.6 us), 64 x 256 with
+// more than 400 rows of 3,000 columns and more (429 rows of 4,560 x 5,977 87.5 / 92.5), 128 x 128 where the store of
+// the logits has no second workgroup to hide behind (103 rows of 2,720 x 65,136 125 / 134).
 // Sums: a matrix instruction rounds at the size its sums have reached (about four times per 32 bf16
 // products, once per fp32 product), so chains of two bf16 instructions or four fp32 ones start from zero
 // and are added up in fp64.  Error of a logit, against one fp32 chain over H (bf16) or over a step (fp32)
@@ -270,14 +278,15 @@ hipError_t launch_ksplit(const AcceptArgs &a, int blocks, hipStream_t st) {
 // 3,584, 4.5e-7 at 5,120; 0.55 to 1.05e-7), fp32 0.8e-7 (1.2 to 2.7e-7; 0.78 to 1.9e-7).  The sums take
 // 8 registers per 16 x 16 tile and the additions two vector instructions per value: wavefront tiles are
 // 64 x 64 at most, and 256 rows take one workgroup of 8 wavefronts per compute unit.
-// 152,064 x 3584 with the finalize pass, us: 62 rows 178, 124 rows 253, 248 rows 415.
-// fp32 (v_mfma_f32_16x16x4: fp32 products at 157 TFLOP/s; in brackets the plain-ALU kernel): 9 rows 335 (1678), 64 rows 735 (7324),
-// 248 rows 3124 (29370); 32,000 x 1024 at 9 rows 32 (137).
+// 152,064 x 3584 with the finalize pass, us (through registers): 40 rows 178 (188), 62 rows 186 (191), 96 rows 230
+// (276), 124 rows 253 (281), 248 rows 399 (446), 372 rows 746 (874).
+// fp32 (v_mfma_f32_16x16x4: fp32 products at 157 TFLOP/s; in brackets the plain-ALU kernel): 9 rows 335 (1678), 64
+// rows 735 (7324), 248 rows 3124 (29370); 32,000 x 1024 at 9 rows 32 (137).
 template <int kRow> __device__ __forceinline__ int gm_swz(int row) {
   return kRow == 256 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
 }
 
-// LDS tiles: three for a workgroup of 8 wavefronts (147 KB at 256 rows, two workgroups of 72 KB at 64)
+// LDS tiles: three for a workgroup of 8 wavefronts (144 KiB at 128 x 256, two workgroups of 72 KiB at 128 x 64)
 constexpr int tiled_buffers(int waves) { return waves == 8 ? 3 : 1; }
 
 __device__ __forceinline__ unsigned int lds_offset(const unsigned char *p) {
@@ -296,9 +305,11 @@ __device__ __forceinline__ u32x4 buffer_words(const void *p, unsigned int bytes)
 // those between a scalar register written by the vector ALU, or M0, and its use here.
 template <bool kNt> __device__ __forceinline__ void load_to_lds(u32x4 rs, unsigned int off, unsigned int dst) {
   if constexpr (kNt)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                 ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
 }
 // All but the last kLeft vector memory operations of the wavefront are done, and its LDS reads
 template <int kLeft> __device__ __forceinline__ void wait_loads() {
@@ -359,8 +370,10 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
         if (j < kLdV) load_to_lds<true>(rs_v, off + (unsigned int)(kLdRows * j) * row_bytes, dst + j * kLdRows * kRow);
         else load_to_lds<false>(rs_m, off + (unsigned int)(kLdRows * (j - kLdV)) * row_bytes, dst + j * kLdRows * kRow);
     } else {
-      const __amdgpu_buffer_rsrc_t rs_v = __builtin_amdgcn_make_buffer_rsrc((void *)w0, (short)0, (int)(rows * row_bytes), 0x00027000);
-      const __amdgpu_buffer_rsrc_t rs_m = __builtin_amdgcn_make_buffer_rsrc((void *)hid0, (short)0, (int)hid_bytes, 0x00027000);
+      const __amdgpu_buffer_rsrc_t rs_v =
+          __builtin_amdgcn_make_buffer_rsrc((void *)w0, (short)0, (int)(rows * row_bytes), 0x00027000);
+      const __amdgpu_buffer_rsrc_t rs_m =
+          __builtin_amdgcn_make_buffer_rsrc((void *)hid0, (short)0, (int)hid_bytes, 0x00027000);
 #pragma unroll
       for (int j = 0; j < kLdV; ++j)
         sg[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_v, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 2);
@@ -423,10 +436,11 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
 #pragma unroll
       for (int j = 0; j < NM; ++j) {
         if (x == 0) p[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if constexpr (kF32)       // element x of the four lanes' chunks is one k-step of 4 (the same columns on both sides)
+        if constexpr (kF32)       // element x of the four lanes' chunks is one k-step of 4 (same columns on both sides)
           p[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av[0][x]), __uint_as_float(bm[0][j][x]), p[j], 0, 0, 0);
         else
-          p[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[x]), __builtin_bit_cast(bf16x8, bm[x][j]), p[j], 0, 0, 0);
+          p[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[x]),
+                                                         __builtin_bit_cast(bf16x8, bm[x][j]), p[j], 0, 0, 0);
       }
     const int to = kDirect ? (i + NV - 1) % NV : i;
 #pragma unroll
@@ -567,7 +581,8 @@ hipError_t launch_tiled_vt(const AcceptArgs &a, hipStream_t st) {
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
   }
-  hipLaunchKernelGGL((lm_head_tiled_kernel<T, VT, BM, kWaves, WV, kRow>), dim3(a.n_cand), dim3(kWaves * 64), lds, st, a, (a.M + BM - 1) / BM);
+  hipLaunchKernelGGL((lm_head_tiled_kernel<T, VT, BM, kWaves, WV, kRow>), dim3(a.n_cand), dim3(kWaves * 64), lds, st, a,
+                     (a.M + BM - 1) / BM);
   return hipGetLastError();
 }
 
@@ -587,7 +602,9 @@ int tiled_rows(bool f32, int M, int V, int bm) {
 
 template <class T, int BM, int kWaves, int WV, int kRow>
 hipError_t launch_tiled(const AcceptArgs &a, hipStream_t st) {
-  return tiled_rows(std::is_same<T, float>::value, a.M, a.V, BM) == 64 ? launch_tiled_vt<T, 64, BM, kWaves, WV, kRow>(a, st) : launch_tiled_vt<T, 128, BM, kWaves, WV, kRow>(a, st);
+  return tiled_rows(std::is_same<T, float>::value, a.M, a.V, BM) == 64
+             ? launch_tiled_vt<T, 64, BM, kWaves, WV, kRow>(a, st)
+             : launch_tiled_vt<T, 128, BM, kWaves, WV, kRow>(a, st);
 }
 
 // Workgroups for row blocks of bm: as many as the chip holds, fewer if there are fewer tiles; a multiple of 8 per
@@ -606,11 +623,13 @@ int f32_block(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128; 
 // 112 / 60.
 //
 // Above that line the k-split kernel, all its row blocks side by side, where the vocabulary is too small to fill
-// the chip with tiles of the whole hidden size: the tiled kernel then lasts 0.8 us per 64 columns, one step after
-// the other, a k-split workgroup 4 us per 16-row tile (6 with two slices per wavefront), whatever the width.
-// k-split / tiled, us with the finalize pass: 1,009 x 736 at 74 rows 9.1 / 13.7; 4,658 x 4,152 at 62 rows 25 / 39;
-// 2,078 x 5,416 at 64 rows 21 / 48; 1,330 x 3,840 at 357 rows 32 / 58; 5,193 x 7,416 at 102 rows 62 / 81.  Where the
-// two estimates are close they miss by up to a fifth (14,716 x 1,904 at 48 rows 27 / 22).
+// the chip with tiles of the whole hidden size: the tiled kernel then lasts some 0.6 us per 64 columns, one step
+// after the other, a k-split workgroup 4 us per 16-row tile (6 with two slices per wavefront), whatever the width.
+// The rule's 0.8 us are those of the tiled kernel through registers: it estimates today's a third too high, the
+// k-split kernel 5 per cent.  180 drawn shapes that it gives to the k-split kernel, k-split / tiled in us with the
+// finalize pass: 1,221 x 6,280 at 155 rows 26 / 91, 1,476 x 8,120 at 62 rows 23 / 66, 11,134 x 3,080 at 56 rows 31 /
+// 33; 1.49 times as fast in the median, and for ten of them slower, by up to a sixth, where the two estimates are
+// close (6,229 x 768 at 43 rows 14.8 / 12.3, 14,547 x 7,464 at 34 rows 82 / 72).
 bool ksplit_small(int M, int H, int V) {
   if (M <= ksplit_rows(H) || H > 2 * kKsWaves * kKsSlice) return false;
   const int blocks = ksplit_blocks(M, H), grid = ksplit_grid(H, V, blocks);

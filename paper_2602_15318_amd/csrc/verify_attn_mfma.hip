@@ -1,9 +1,9 @@
 // Verification attention, matrix-core partial pass: bf16, head_dim 128 or 64, gfx950.
 //
-// One workgroup (8 wavefronts) owns one (context split, KV head, block of 64 rows); a row is a
+// One workgroup (8 wavefronts) owns one (context split, KV head, block of 64, 128 or 192 rows); a row is a
 // (draft row, query head of the group) pair, so all rows of a block share the K/V stream.
 // The workgroup runs two token streams (wavefronts 0-3 and 4-7) that take alternate 32-token
-// tiles; within a stream wavefront w owns rows 16w..16w+15 of the block, so rows are never merged
+// tiles; within a stream wavefront w owns rows 16w..16w+15 of each 64 of the block, so rows are never merged
 // between wavefronts and the two streams are merged once, through LDS, at the end.
 // K/V tiles travel HBM -> registers (coalesced 16-byte loads, several tiles in flight) -> LDS
 // (XOR-swizzled 16-byte chunks, double buffered per stream) and are read by the four wavefronts
@@ -189,6 +189,8 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   // unconditional and the number of loads in flight is a compile-time constant at every wait.
   const int ld_row = tid / kChunks, ld_ch = tid % kChunks;
   constexpr int kLd = kSub * kTile / kLdRows;         // loads per step (per K and per V)
+  // (A request far past the end of the split may wrap around 2^32 where rows are megabytes apart: it still lies
+  // between the sequence's first row and ld_last, and no step of the split reads what it brings.)
   const unsigned int ld_first = (unsigned int)(t0 + ld_row) * row_bytes + (unsigned int)ld_ch * 16u;
   const unsigned int ld_last = (unsigned int)(t1 - 1) * row_bytes + (unsigned int)ld_ch * 16u;
   auto issue1 = [&](const unsigned char *src, int st, int j, u32x4 *sg) __attribute__((always_inline)) {
