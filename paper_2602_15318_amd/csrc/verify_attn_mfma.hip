@@ -96,10 +96,10 @@ template <int kD> constexpr bool kWideState = kD == 64;
 // share the SIMDs with them, are in their softmax.  In step, the phases of all wavefronts add up: matrix
 // cores, vector ALU and LDS were busy 27, 31 and 42 per cent of the time.  The LDS reads of V^T, the LDS
 // writes and the requests of later tiles are issued between the MFMAs; independent sums alternate.
-// In step / half a step apart, us a call with the combine pass, in an unbroken row of calls: 60-node tree over 26,112
-// tokens (28/4 heads) 38.5 / 35.8, two of 64 nodes over 30,000 (64/8 heads) 147 / 135 (930 TFLOP/s).  Three row tiles
-// and the fp32 state of heads of 64 do not leave the registers for it (the latter 42 -> 67 us with spills); which
-// calls take it: half_step_pays below.
+// In step / half a step apart, us a call with the combine pass, in an unbroken row of calls, on two cards: 60-node
+// tree over 26,112 tokens (28/4 heads) 38.5 / 35.8 and 40.2 / 39.4, two of 64 nodes over 30,000 (64/8 heads) 147 /
+// 135 (930 TFLOP/s) and 158 / 144.  Three row tiles and the fp32 state of heads of 64 do not leave the registers
+// for it (the latter 42 -> 67 us with spills); which calls take it: half_step_pays below.
 
 // kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
@@ -787,10 +787,12 @@ int verify_mfma_row_blocks(int dtype, int R) {
 }
 
 // The two streams half a step apart: where several row blocks share a stream, from 14 steps on.  Time in step / half a
-// step apart, median and range over drawn calls (8 to 64 nodes, 1 to 12 sequences, all layouts of K and V):
-//   several blocks, 11 to 13 steps 0.99 (0.93 to 1.03), 14 to 18 steps 1.02 (0.95 to 1.06), more 1.04 (1.00 to 1.10):
-//   the longer start and end of a split have to be earned back;
-//   one block of 128 rows 0.97 (0.90 to 1.11): half of the matrix work per byte of K and V, which then set the pace.
+// step apart, medians on two cards and the whole range, over drawn calls (8 to 64 nodes, 1 to 12 sequences, all
+// layouts of K and V):
+//   several blocks, 11 to 13 steps 0.99 and 0.98 (0.89 to 1.04), 14 to 18 steps 1.02 and 1.01 (0.92 to 1.08), more
+//   1.04 and 1.03 (0.92 to 1.10): the longer start and end of a split have to be earned back;
+//   one block of 128 rows 0.97 and 0.97 (0.85 to 1.11): half of the matrix work per byte of K and V, which then set
+//   the pace.
 static bool half_step_pays(int steps, int rbs) { return rbs > 1 && steps >= 14; }
 
 template <int kD>
