@@ -586,14 +586,15 @@ hipError_t launch_tiled_vt(const AcceptArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Workgroups of the tiled kernel on a compute unit, as registers and LDS tiles allow.  bf16: one of 8 wavefronts,
-// two up to 64 rows; fp32: workgroups of 4, two at 128 rows, three at 64, four below.
+// Workgroups of the tiled kernel on a compute unit.  bf16: one of 8 wavefronts, two up to 64 rows, as registers and
+// LDS tiles allow (64 x 128 with 102 registers and 72 KiB would fit twice and runs once, as 128 x 128 does); fp32:
+// workgroups of 4, two at 128 rows, three at 64, four below.
 int tiled_per_cu(bool f32, int bm) { return f32 ? (bm > 64 ? 2 : bm > 32 ? 3 : 4) : bm > 64 ? 1 : 2; }
 
 // Rows of a vocabulary tile: 128, or 64.  bf16: 64 where all tiles of 64 then fit the chip at once; a second round
-// of them takes longer than one of 128 (2,560 x 32,000 at 100 rows 57 us against 43, 5,120 x 32,000 at 200 rows 147
-// against 118; 2,048 x 16,384 at 100 rows, 256 tiles of 64, 26).  fp32: where tiles of 128 would leave compute units
-// without one (9 rows 56 us).
+// of them takes longer than one of 128 (2,560 x 32,000 at 100 rows, one workgroup per compute unit either way, 57 us
+// against 43, 5,120 x 32,000 at 200 rows 147 against 118; 2,048 x 16,384 at 100 rows, 256 tiles of 64, 26).  fp32:
+// where tiles of 128 would leave compute units without one (9 rows 56 us).
 int tiled_rows(bool f32, int M, int V, int bm) {
   const int blocks_m = (M + bm - 1) / bm;
   if (f32) return (V + 127) / 128 * blocks_m < kNumCU ? 64 : 128;

@@ -114,10 +114,10 @@ def _depths(parent, n_q):
 
 
 @pytest.mark.parametrize("dtype,H,V,B,nodes", [
-    ("bf16", 3584, 8192, 8, 30),      # 8 requests x 30-node trees: 248 logit rows, four 64-row passes
-    ("bf16", 4096, 4096, 3, 25),      # 78 rows: one paired pass and one 16-row pass
-    ("bf16", 1024, 5000, 5, 12),      # 65 rows on the fallback matrix-core kernel
-    ("f32", 256, 1000, 7, 9),         # 70 rows on the plain-ALU kernel
+    ("bf16", 3584, 8192, 8, 30),      # 8 requests x 30-node trees: 248 logit rows, one tiled block
+    ("bf16", 4096, 4096, 3, 25),      # 78 rows: three k-split blocks side by side
+    ("bf16", 1024, 5000, 5, 12),      # 65 rows: three k-split blocks, two wavefronts each
+    ("f32", 256, 1000, 7, 9),         # 70 rows in fp32
     ("bf16", 3584, 2048, 8, 63),      # 512 rows, the most one call takes
 ])
 def test_accept_one_tree_per_sequence_and_many_rows(sp, oracle, dtype, H, V, B, nodes):

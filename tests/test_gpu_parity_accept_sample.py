@@ -72,10 +72,10 @@ CASES = [
     ("bf16", 512, 777, 2, 8, False, 1.0, 0.5),
     ("bf16", 512, 4096, 2, 12, True, 0.5, 0.7),
     ("bf16", 3584, 4096, 1, 8, False, 1.0, 0.6),       # k-split lm_head
-    ("bf16", 3584, 2048, 2, 20, True, 1.0, 0.6),       # 42 rows: two passes of the k-split kernel
-    ("bf16", 1024, 3000, 1, 8, False, 2.0, 0.5),       # fallback matrix-core lm_head
+    ("bf16", 3584, 2048, 2, 20, True, 1.0, 0.6),       # 42 rows: two k-split blocks side by side
+    ("bf16", 1024, 3000, 1, 8, False, 2.0, 0.5),       # two slices of the hidden size
     ("bf16", 4096, 4096, 1, 8, False, 1.0, 0.6),       # k-split lm_head, eight wavefronts
-    ("bf16", 4096, 2048, 2, 20, True, 1.0, 0.6),       # 42 rows: its paired-workgroup pass
+    ("bf16", 4096, 2048, 2, 20, True, 1.0, 0.6),       # 42 rows of eight wavefronts
 ]
 
 
@@ -103,7 +103,7 @@ def test_accept_sample_matches_oracle(sp, oracle, dtype, H, V, B, n_q, tree, T, 
 
 
 def test_accept_sample_one_tree_per_sequence(sp, oracle):
-    """parent [B, n_q]: every sequence walks its own tree (70 logit rows: two passes of lm_head)."""
+    """parent [B, n_q]: every sequence walks its own tree (70 logit rows: three k-split blocks of lm_head)."""
     dtype, H, V, B, nodes, T = "bf16", 3584, 2048, 5, 13, 1.0
     trees = np.stack([wl.pruned_tree(300 + i, nodes, (3, 2, 2, 1, 1, 1)) for i in range(B)])
     n_q = trees.shape[1]
