@@ -129,6 +129,25 @@ def test_logits_carry_the_error_of_short_sums_only(sp, H, M, dtype, limit):
     assert float((logits - ref).norm() / ref.norm()) <= limit
 
 
+@pytest.mark.parametrize("M,V,dtype", [(M, V, "bfloat16") for M in (3, 20, 40, 100, 140) for V in (33001, 33002, 33003)]
+                         + [(40, 2050, "bfloat16"), (140, 6827, "bfloat16"), (5, 2051, "float32"), (70, 130, "float32")])
+def test_stored_logits_of_odd_vocabularies(sp, M, V, dtype):
+    """Four logits by one store, the last of a row by fewer: every logit of every row, one slice of a weight row."""
+    import torch
+    import paper_2602_15318_amd.binding as bd
+    H, k, dt = 264, 2, getattr(torch, dtype)
+    g = torch.Generator(device="cuda").manual_seed(V + M)
+    W = (torch.randn(V, H, generator=g, device="cuda") * H ** -0.5).to(dt)
+    hid = (torch.randn(M, H, generator=g, device="cuda") * 2.0).to(dt)
+    code = bd._dtype_code(W)
+    ws = torch.full((bd.lib.sparrow_draft_topk_workspace(code, M, H, V, k),), 0xff, dtype=torch.uint8, device="cuda")
+    sp.draft_topk(hid, W, k, workspace=ws)
+    at = bd.lib.sparrow_accept_workspace(code, 1, M - 1, H, V)          # the logits lie behind the candidates
+    logits = ws[at:at + 4 * M * V].view(torch.float32).view(M, V).double()
+    tol = 64 * 2.0 ** -24 * float((hid.double().abs() @ W.double().abs().t()).max())     # as in _check
+    assert float((logits - hid.double() @ W.double().t()).abs().max()) <= tol
+
+
 @pytest.mark.parametrize("H", [2048, 4104, 8192])
 @pytest.mark.parametrize("M", [33, 64, 65, 200, 512])
 @pytest.mark.parametrize("V", [7, 1000, 3001])
