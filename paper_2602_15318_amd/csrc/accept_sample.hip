@@ -1,6 +1,6 @@
 // Stochastic (temperature > 0) tree acceptance on the logits stored by the lm_head pass.
 //
-//   logit_stats_kernel   the whole chip reads the M x V logits once (grid M x 64 chunks): per
+//   logit_stats_kernel   the whole chip reads the M x V logits once (64 chunks per row): per
 //                        chunk the max and the sum of exponentials of logits / T, and per block of
 //                        256 tokens the sum of exponentials relative to the chunk's max;
 //   accept_sample_kernel one workgroup per sequence walks the tree: at the current node it merges
@@ -52,33 +52,43 @@ __device__ __forceinline__ float uniform_of(const SampleArgs &a, int b, int j) {
   return (float)(w >> 8) * (1.0f / 16777216.0f);
 }
 
-// A wavefront owns whole blocks of 256 tokens (blocks b0 + w, b0 + w + 4, ... of the chunk), a lane
-// four consecutive tokens of each: the chunk is read once, 16 bytes per lane, and stays in
-// registers for the maximum and for the sums.
-constexpr int kStatBlocksPerWave = kBonusMaxBlocks / kStatChunks / (kStatThreads / 64);   // 16
+// A chunk's blocks of 256 tokens are dealt to kWaves wavefronts, 1 or 4, a lane owns four consecutive tokens of each: the
+// chunk is read once, 16 bytes per lane, all loads in flight together, and stays in registers for the maximum and for
+// the sums.  One wavefront exchanges nothing through LDS, and the wavefronts of a workgroup serve four chunks.  Four / one
+// wavefront, us: 315 rows of 6,828 31.0 / 9.9 (a chunk is one block at most, three wavefronts in four had none), 156 of
+// 16,724 18.2 / 7.4, 180 of 152,064 31.7 / 23.5, 36 of 64,003 7.9 / 5.0, 30 of 56,772 5.6 / 4.5; with long chunks of few
+// rows the chip is short of wavefronts: 24 of 152,064 6.9 / 7.4, 16 of 122,762 5.7 / 6.1.
+constexpr int kStatAhead = 16;
+constexpr int kStatWaves = kStatThreads / 64;
+typedef f32x4 __attribute__((aligned(4))) f32x4u;       // rows of odd vocabularies start at any multiple of 4 bytes
 
+int stat_blocks_per_chunk(int V) {
+  const int n_blk = (V + kBonusBlock - 1) / kBonusBlock;
+  return (n_blk + kStatChunks - 1) / kStatChunks;
+}
+
+template <int kWaves>
 __global__ void __launch_bounds__(kStatThreads)
 logit_stats_kernel(SampleArgs a) {
-  __shared__ float red[kStatThreads / 64];
-  constexpr int kWaves = kStatThreads / 64;
-  const int c = blockIdx.x, r = blockIdx.y;
+  __shared__ float red[kStatWaves];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = kWaves == 1 ? 0 : wave;                             // wavefront within the chunk
+  const int c = kWaves == 1 ? blockIdx.x * kStatWaves + wave : blockIdx.x, r = blockIdx.y;
   const int n_blk = (a.V + kBonusBlock - 1) / kBonusBlock;
   const int bpc = (n_blk + kStatChunks - 1) / kStatChunks;          // blocks per chunk
   const int b0 = min(n_blk, c * bpc), b1 = min(n_blk, b0 + bpc);
   const float *lg = a.logits + (int64_t)r * a.V;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  // scaled logits of this lane: x[k][i] = token (b0 + w + 4 k) * 256 + 4 lane + i, kNegBig past V
-  float x[kStatBlocksPerWave][4];
-  const bool row_aligned = (((int64_t)r * a.V) & 3) == 0;           // 16-byte loads possible
+  // scaled logits of this lane: x[k][i] = token (b0 + w + kWaves k) * 256 + 4 lane + i, kNegBig past V
+  float x[kStatAhead][4];
 #pragma unroll
-  for (int k = 0; k < kStatBlocksPerWave; ++k) {
+  for (int k = 0; k < kStatAhead; ++k) {
     const int ib = b0 + w + kWaves * k;
     const int v = ib * kBonusBlock + 4 * lane;
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[k][i] = kNegBig;
     if (ib < b1) {
-      if (row_aligned && v + 3 < a.V) {
-        const f32x4 q = *reinterpret_cast<const f32x4 *>(lg + v);
+      if (v + 3 < a.V) {
+        const f32x4 q = *reinterpret_cast<const f32x4u *>(lg + v);
 #pragma unroll
         for (int i = 0; i < 4; ++i) x[k][i] = q[i] * a.inv_temp_log2;
       } else {
@@ -90,18 +100,23 @@ logit_stats_kernel(SampleArgs a) {
   }
   float m = kNegBig;
 #pragma unroll
-  for (int k = 0; k < kStatBlocksPerWave; ++k)
+  for (int k = 0; k < kStatAhead; ++k)
 #pragma unroll
     for (int i = 0; i < 4; ++i) m = fmaxf(m, x[k][i]);
   m = wave_max_valu(m);
-  if (lane == 0) red[w] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  // block sums relative to the chunk's max
-  float s = 0.f;
+  if constexpr (kWaves > 1) {
+    if (lane == 0) red[w] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    __syncthreads();
+  }
+  // block sums relative to the chunk's max; four running sums whatever the number of wavefronts
+  constexpr int kSums = kStatWaves / kWaves;
+  float s[kSums];
 #pragma unroll
-  for (int k = 0; k < kStatBlocksPerWave; ++k) {
+  for (int k = 0; k < kSums; ++k) s[k] = 0.f;
+#pragma unroll
+  for (int k = 0; k < kStatAhead; ++k) {
     const int ib = b0 + w + kWaves * k;
     if (ib < b1) {                              // uniform over the wavefront
       const int v = ib * kBonusBlock + 4 * lane;
@@ -111,15 +126,16 @@ logit_stats_kernel(SampleArgs a) {
         if (v + i < a.V) t += fast_exp2(x[k][i] - m);
       t = wave_sum_valu(t);
       if (lane == 0) a.blk_sum[(int64_t)r * n_blk + ib] = t;
-      s += t;                                   // the same value in every lane
+      s[k % kSums] += t;                        // the same value in every lane
     }
   }
-  if (lane == 0) red[w] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float *o = a.stats + ((int64_t)r * kStatChunks + c) * 2;
-    o[0] = m;                                   // kNegBig and sum 0 for an empty chunk
-    o[1] = red[0] + red[1] + red[2] + red[3];
+  float *o = a.stats + ((int64_t)r * kStatChunks + c) * 2;         // kNegBig and sum 0 for an empty chunk
+  if constexpr (kWaves == 1) {
+    if (lane == 0) { o[0] = m; o[1] = s[0] + s[1] + s[2] + s[3]; }
+  } else {
+    if (lane == 0) red[w] = s[0];
+    __syncthreads();
+    if (threadIdx.x == 0) { o[0] = m; o[1] = red[0] + red[1] + red[2] + red[3]; }
   }
 }
 
@@ -330,7 +346,6 @@ accept_sample_kernel(SampleArgs a) {
 // any multiple of 4 bytes, are read by the same 16-byte loads (of a type that asks for no more).
 constexpr int kMaxRejections = SPARROW_MAX_NQ;
 constexpr int kAhead = 4;
-typedef f32x4 __attribute__((aligned(4))) f32x4u;
 
 __global__ void __launch_bounds__(kWalkThreads)
 accept_sample_q_kernel(SampleArgs a) {
@@ -533,7 +548,12 @@ accept_sample_q_kernel(SampleArgs a) {
 }  // namespace
 
 hipError_t launch_logit_stats(const SampleArgs &a, hipStream_t st) {
-  hipLaunchKernelGGL(logit_stats_kernel, dim3(kStatChunks, a.M), dim3(kStatThreads), 0, st, a);
+  // (rows and blocks between the measured sizes above; more than 16 blocks do not fit one wavefront's registers)
+  const int bpc = stat_blocks_per_chunk(a.V);
+  if (bpc <= 4 || (bpc <= kStatAhead && a.M >= 32))
+    hipLaunchKernelGGL(logit_stats_kernel<1>, dim3(kStatChunks / kStatWaves, a.M), dim3(kStatThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL(logit_stats_kernel<kStatWaves>, dim3(kStatChunks, a.M), dim3(kStatThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -102,6 +102,14 @@ def test_accept_sample_matches_oracle(sp, oracle, dtype, H, V, B, n_q, tree, T, 
     assert graded >= 2, "fewer than two well-conditioned seeds among 8"
 
 
+# A chunk of the row statistics is a 64th of the row's blocks of 256 tokens: one wavefront's 16 blocks up to 262,144.
+# (A lower temperature above 16,384 tokens, whose flat tails leave no draw well conditioned.)
+@pytest.mark.parametrize("V,T", [(255, 1.0), (257, 1.0), (16384, 1.0), (16385, 0.6), (70003, 0.6), (262144, 0.6), (262145, 0.6),
+                                 (300001, 0.6)])
+def test_vocabularies(sp, oracle, V, T):
+    test_accept_sample_matches_oracle(sp, oracle, "bf16", 64, V, 2, 10, True, T, 0.6)
+
+
 def test_accept_sample_one_tree_per_sequence(sp, oracle):
     """parent [B, n_q]: every sequence walks its own tree (70 logit rows: three k-split blocks of lm_head)."""
     dtype, H, V, B, nodes, T = "bf16", 3584, 2048, 5, 13, 1.0

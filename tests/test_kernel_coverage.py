@@ -90,7 +90,9 @@ COVERAGE = {
     "lm_head_tiled_kernel<unsigned short, 64, 256, 8, 2, 128>": (LM, "test_many_rows", "bf16, up to 256 rows"),
     "lm_head_tiled_kernel<unsigned short, 128, 256, 8, 2, 128>": (LM, "test_tiles_of_128_vocabulary_rows", "bf16, up to 256 rows"),
     "accept_finalize_kernel": (AC, "test_accept_shapes", "every greedy case"),
-    "logit_stats_kernel": (AS, "test_accept_sample_matches_oracle", "every stochastic case"),
+    # <wavefronts of a chunk>
+    "logit_stats_kernel<1>": (AS, "test_accept_sample_matches_oracle", "up to four blocks of 256 tokens a chunk, or 16 and 32 rows"),
+    "logit_stats_kernel<4>": (AS, "test_vocabularies", "longer chunks"),
     "accept_sample_kernel": (AS, "test_accept_sample_matches_oracle", "deterministic children"),
     "accept_sample_q_kernel": (ASQ, "test_accept_sample_q_matches_oracle", "sampled draft"),
     # ---- dynamic draft tree
