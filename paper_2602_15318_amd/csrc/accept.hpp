@@ -38,10 +38,12 @@ struct SampleArgs {
   float *stats;              // [M, kStatChunks, 2]: max and sum of exponentials per chunk
   float *blk_sum;            // [M, ceil(V / 256)]: sum of exponentials per block, relative to the
                              // max of the block's chunk (chunk = ceil(blocks / 64) blocks)
+  void *state;               // sample_state_bytes(B) for a walk that is handed from kernel to kernel, or nullptr
   int32_t *accept_len, *accept_path, *bonus_id;
   int32_t B, n_q, M, V;
   float inv_temp_log2;       // log2(e) / temperature
 };
+size_t sample_state_bytes(int B);
 hipError_t launch_logit_stats(const SampleArgs &a, hipStream_t st);
 hipError_t launch_accept_sample(const SampleArgs &a, hipStream_t st);
 

@@ -3,14 +3,13 @@
 //   logit_stats_kernel   the whole chip reads the M x V logits once (64 chunks per row): per
 //                        chunk the max and the sum of exponentials of logits / T, and per block of
 //                        256 tokens the sum of exponentials relative to the chunk's max;
-//   accept_sample_kernel one workgroup per sequence walks the tree: at the current node it merges
-//                        the row's 64 chunk statistics, evaluates the children's probabilities
-//                        in parallel, lets one thread apply the sequential rejection rule
-//                        (u * S <= p[x] accepts; a rejected token is struck out and its mass leaves
-//                        S), and, when no child is accepted, draws the bonus token from what is
-//                        left by inverse CDF in vocabulary order: a scan over the row's block
-//                        sums (struck-out tokens taken out), then a search inside the one block
-//                        that holds the target -- the only 256 logits of the row it reads.
+//   accept_sample_kernel one workgroup per sequence: merges the 64 chunk statistics of all its rows and fetches what
+//                        decides every node at once, lets one wavefront apply the sequential rejection rule down the
+//                        tree (u * S <= p[x] accepts; a rejected token is struck out and its mass leaves S), and
+//                        draws the bonus token from what is left at the last node by inverse CDF in vocabulary order:
+//                        a scan over the row's block sums (struck-out tokens taken out), then a search inside the
+//                        one block that holds the target -- the only 256 logits of the row it reads;
+//   accept_sample_q_kernel, residual_sums_kernel   the same against a sampled draft, see below.
 // Exponentials are exp2 of logits pre-multiplied by log2(e) / T in fp32; sums across blocks fp64.
 #include "accept.hpp"
 #include "common.hpp"
@@ -139,198 +138,228 @@ logit_stats_kernel(SampleArgs a) {
   }
 }
 
+// Maximum and sum of exponentials of every row of a sequence from the rows' 64 chunk statistics: wavefront w of the
+// workgroup takes rows w, w + 16, ..., all loads in flight together.
+__device__ __forceinline__ void row_statistics(const SampleArgs &a, int64_t row0, float *row_m, float *row_z) {
+  constexpr int kWaves = kWalkThreads / 64, kRows = (SPARROW_MAX_NQ + 1 + kWaves - 1) / kWaves;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const float2 *st = reinterpret_cast<const float2 *>(a.stats) + row0 * kStatChunks + lane;
+  float2 ps[kRows];
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    ps[u] = make_float2(kNegBig, 0.f);
+    if (w + kWaves * u <= a.n_q) ps[u] = st[(w + kWaves * u) * kStatChunks];
+  }
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    if (w + kWaves * u > a.n_q) break;                       // uniform over the wavefront
+    const float m = wave_max_valu(ps[u].x);
+    const float Z = wave_sum_valu(ps[u].y * fast_exp2(ps[u].x - m));
+    if (lane == 0) { row_m[w + kWaves * u] = m; row_z[w + kWaves * u] = Z; }
+  }
+}
+
+// What decides whether a node is accepted, fetched for all nodes at once, lane j of a wavefront for node j (n_q <= 64):
+// the walk then reads registers, where fetched level by level every level paid two memory round trips.  Walk and draw of
+// deterministic children level by level / at once, us: 6 chains of 4 over 56,772 14.8 / 5.6, 6 trees of 29 over 152,064
+// 20.5 / 8.2.  parent = -2: not a node, or its token or parent is out of range (never accepted).
+struct Node {
+  int parent, token;
+  float logit, q, u;                            // of its token in the parent's row; the uniform that decides it
+};
+__device__ __forceinline__ Node fetch_node(const SampleArgs &a, int b, int64_t row0, int j) {
+  Node nd = {-2, -1, 0.f, 0.f, 0.f};
+  if (j < a.n_q) {
+    const int p = a.parent ? a.parent[(int64_t)b * a.parent_stride + j] : j - 1;
+    nd.token = a.draft_ids[(int64_t)b * a.n_q + j];
+    if (p >= -1 && p < a.n_q && nd.token >= 0 && nd.token < a.V) {
+      nd.parent = p;
+      nd.logit = a.logits[(row0 + p + 1) * a.V + nd.token];
+      if (a.draft_q != nullptr) nd.q = a.draft_q[(row0 + p + 1) * a.V + nd.token];
+    }
+    nd.u = uniform_of(a, b, j);
+  }
+  return nd;
+}
+__device__ __forceinline__ float lane_f32(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// The bonus draw's scan, by one wavefront: the block of 256 tokens in which the running sum reaches the target, and the
+// sum of the blocks before it.  Lane l owns n_blk / 64 consecutive blocks; nothing waits for another wavefront (with
+// the scan spread over the workgroup's 16, six barriers took as long as the rest of the kernel).
+// target_of: the target from the sum of all blocks.  block = -1: no live block.
+struct Drawn {
+  int block;
+  double before, target;
+};
+template <class F> __device__ __forceinline__ Drawn find_block(const double *blk_tot, int n_blk, F target_of) {
+  const int lane = threadIdx.x & 63;
+  const int per = (n_blk + 63) / 64, i0 = min(n_blk, lane * per), i1 = min(n_blk, i0 + per);
+  double local = 0.0;
+  int last = -1;                                             // last live block of the lane
+  for (int i = i0; i < i1; ++i) {
+    const double t = blk_tot[i];
+    local += t;
+    if (t > 0.0) last = i;
+  }
+  double incl = local;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  Drawn d;
+  d.target = target_of(__shfl(incl, 63, 64));
+  const unsigned long long hit = __builtin_amdgcn_ballot_w64(local > 0.0 && incl >= d.target);
+  if (hit == 0ull) {               // rounding left the total a hair below the target: the row's last live block, with
+    d.block = last;                // nothing to find in it
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) d.block = max(d.block, __shfl_xor(d.block, o, 64));
+    d.before = -1.0e300;
+    return d;
+  }
+  double run = incl - local;
+  int blk = -1;
+  for (int i = i0; i < i1 && blk < 0; ++i) {
+    const double t = blk_tot[i];
+    if (t > 0.0) {
+      if (run + t >= d.target) blk = i; else run += t;
+    }
+  }
+  if (blk < 0) { blk = last; run = -1.0e300; }               // rounding between the two orders of summation
+  const int owner = __builtin_ctzll(hit);
+  d.block = __shfl(blk, owner, 64);
+  d.before = __shfl(run, owner, 64);
+  return d;
+}
+
+// The token of that block at which the running sum reaches the target, by one wavefront, four tokens of weights e per
+// lane; its last live token if rounding left nothing to find.
+__device__ __forceinline__ int find_token(const Drawn &d, const float *e) {
+  const int lane = threadIdx.x & 63;
+  const float mine = (e[0] + e[1]) + (e[2] + e[3]);
+  float li = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const float up = __shfl_up(li, o, 64);
+    if (lane >= o) li += up;
+  }
+  double run = d.before + (double)(li - mine);
+  int found = -1, lastp = -1;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (e[i] > 0.f) {
+      lastp = d.block * kBonusBlock + 4 * lane + i;
+      run += (double)e[i];
+      if (found < 0 && run >= d.target) found = lastp;
+    }
+  }
+  // first lane that found its element wins (vocabulary order = lane order)
+  const unsigned long long hit = __builtin_amdgcn_ballot_w64(found >= 0);
+  if (hit != 0ull) return __shfl(found, __builtin_ctzll(hit), 64);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) lastp = max(lastp, __shfl_xor(lastp, o, 64));
+  return lastp;
+}
+
 __global__ void __launch_bounds__(kWalkThreads)
 accept_sample_kernel(SampleArgs a) {
-  __shared__ float cand_p[SPARROW_MAX_NQ];      // probability of child j's token, -1 if not a child
-  __shared__ float cand_u[SPARROW_MAX_NQ];      // the uniform that decides child j
-  __shared__ int struck[SPARROW_MAX_NQ];        // tokens rejected at the current node
-  __shared__ int sh_next, sh_nstruck;
-  __shared__ float sh_S, sh_m, sh_Z;
-  __shared__ double wave_tot[kWalkThreads / 64];
-  __shared__ int sh_owner, sh_last, sh_pick, sh_blk;
-  __shared__ double sh_excl;
+  __shared__ float row_m[SPARROW_MAX_NQ + 1], row_z[SPARROW_MAX_NQ + 1];
+  __shared__ int struck[SPARROW_MAX_NQ];        // tokens rejected at the last node
+  __shared__ int sh_cur;
   __shared__ double blk_tot[kBonusMaxBlocks];   // sum of the live exponentials of 256 tokens
-  __shared__ float chunk_m[kStatChunks];        // max of every chunk of the current row
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int n_q = a.n_q, V = a.V;
-  const int32_t *dr = a.draft_ids + (int64_t)b * n_q;
+  const int64_t row0 = (int64_t)b * (n_q + 1);
   int32_t *path = a.accept_path + (int64_t)b * n_q;
-  for (int i = tid; i < n_q; i += kWalkThreads) path[i] = -1;
+  Node nd = {-2, -1, 0.f, 0.f, 0.f};
+  if (w == 0) nd = fetch_node(a, b, row0, lane);
+  row_statistics(a, row0, row_m, row_z);
+  __syncthreads();
   int cur = -1, len = 0;
-  // at most n_q + 1 levels: cur strictly increases along a path
-  for (int level = 0; level <= n_q; ++level) {
-    const int64_t row = (int64_t)b * (n_q + 1) + cur + 1;
-    const float *lg = a.logits + row * V;
-    // ---- row statistics from the 64 chunk partials (wavefront 0)
-    if (w == 0) {
-      const float pm = a.stats[(row * kStatChunks + lane) * 2];
-      const float ps = a.stats[(row * kStatChunks + lane) * 2 + 1];
-      const float m = wave_max(pm);
-      const float Z = wave_sum(ps * fast_exp2(pm - m));
-      chunk_m[lane] = pm;
-      if (lane == 0) { sh_m = m; sh_Z = Z; }
-    }
-    __syncthreads();
-    const float m = sh_m, Z = sh_Z;
-    // ---- children of cur and the probabilities of their tokens
-    if (tid < n_q) {
-      const int pj = a.parent ? a.parent[(int64_t)b * a.parent_stride + tid] : tid - 1;
-      const int x = dr[tid];
-      float p = -1.f;
-      if (pj == cur && x >= 0 && x < V) p = fast_exp2(lg[x] * a.inv_temp_log2 - m) / Z;
-      cand_p[tid] = p;
-      cand_u[tid] = uniform_of(a, b, tid);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      float S = 1.f;
-      int next = -1, ns = 0;
-      for (int j = 0; j < n_q && next < 0; ++j) {
-        const float p = cand_p[j];
-        if (p < 0.f) continue;
-        const int x = dr[j];
-        bool gone = false;
-        for (int k = 0; k < ns; ++k) gone |= struck[k] == x;
-        if (gone || p == 0.f) continue;
-        if (cand_u[j] * S <= p) next = j;
-        else { S -= p; struck[ns++] = x; }
+  float S = 1.f;
+  unsigned long long out = 0ull;                // children rejected at the current node
+  if (w == 0) {                                 // the walk, by one wavefront
+    float p = -1.f;
+    if (nd.parent >= -1) p = fast_exp2(nd.logit * a.inv_temp_log2 - row_m[nd.parent + 1]) / row_z[nd.parent + 1];
+    int mine = -1;
+    bool ended = false;
+    // at most n_q + 1 levels: cur strictly increases along a path
+    for (int level = 0; level <= n_q && !ended; ++level) {
+      unsigned long long kids = __builtin_amdgcn_ballot_w64(nd.parent == cur);
+      int next = -1;
+      S = 1.f;
+      out = 0ull;
+      while (kids != 0ull && next < 0) {
+        const int j = __builtin_ctzll(kids);
+        kids &= kids - 1;
+        const float pj = lane_f32(p, j);
+        const bool gone = (__builtin_amdgcn_ballot_w64(nd.token == __builtin_amdgcn_readlane(nd.token, j)) & out) != 0ull;
+        if (gone || pj == 0.f) continue;
+        if (lane_f32(nd.u, j) * S <= pj) next = j;
+        else { S -= pj; out |= 1ull << j; }
       }
-      sh_next = next; sh_S = S; sh_nstruck = ns;
-      sh_owner = kWalkThreads; sh_last = -1; sh_pick = -1;
-    }
-    __syncthreads();
-    const int next = sh_next;
-    if (next >= 0) {
-      if (tid == 0) path[len] = next;
+      if (next < 0) { ended = true; break; }
+      if (lane == len) mine = next;
       ++len;
       cur = next;
-      __syncthreads();          // cand_p / struck are rewritten at the next level
-      continue;
     }
-    // ---- bonus token: inverse CDF over what is left of the row's distribution.  The sums of
-    // the row's 256-token blocks come from the statistics pass (relative to their chunk's max);
-    // rescaled to the row's max, minus the struck-out tokens, they are scanned in fp64 (fp32
-    // inside a block, whose sum is a small part of the mass), so the draw is decided by the fp32
-    // exponentials alone (~1e-7 of the remaining mass).  Only the block that holds the target
-    // is read from the logits.
-    const int ns = sh_nstruck;
-    const double target = (double)uniform_of(a, b, -1) * (double)sh_S * (double)Z;   // unnormalised units
-    auto weight = [&](int v) {
-      bool gone = false;
-      for (int k = 0; k < ns; ++k) gone |= struck[k] == v;
-      return gone ? 0.f : fast_exp2(lg[v] * a.inv_temp_log2 - m);
-    };
-    // the 4 weights of this lane in block ib (0 past the end of the vocabulary)
-    auto lane_weights = [&](int ib, float *e) {
-      const int v = ib * kBonusBlock + 4 * lane;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) e[i] = (v + i < V) ? weight(v + i) : 0.f;
-    };
-    const int n_blk = (V + kBonusBlock - 1) / kBonusBlock;
-    const int bpc = (n_blk + kStatChunks - 1) / kStatChunks;
-    const float *bs = a.blk_sum + row * n_blk;
-    for (int ib = tid; ib < n_blk; ib += kWalkThreads)
-      blk_tot[ib] = (double)bs[ib] * (double)fast_exp2(chunk_m[ib / bpc] - m);
-    __syncthreads();
-    if (tid == 0) {                  // struck-out tokens leave their blocks
-      for (int k = 0; k < ns; ++k) {
-        const int x = struck[k];
-        const double left = blk_tot[x / kBonusBlock] - (double)fast_exp2(lg[x] * a.inv_temp_log2 - m);
-        blk_tot[x / kBonusBlock] = left > 0.0 ? left : 0.0;
-      }
-    }
-    __syncthreads();
-    // scan over the block sums: thread t owns blocks [t*bp, (t+1)*bp)
-    const int bp = (n_blk + kWalkThreads - 1) / kWalkThreads;
-    double local = 0.0;
-    int last_blk = -1;
-    for (int i = 0; i < bp; ++i) {
-      const int ib = tid * bp + i;
-      if (ib < n_blk) {
-        local += blk_tot[ib];
-        if (blk_tot[ib] > 0.0) last_blk = ib;
-      }
-    }
-    if (last_blk >= 0) atomicMax(&sh_last, last_blk);      // last live block of the row
-    double incl = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const double up = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += up;
-    }
-    if (lane == 63) wave_tot[w] = incl;
-    __syncthreads();
-    double base = 0.0;
-    for (int k = 0; k < w; ++k) base += wave_tot[k];
-    incl += base;
-    if (local > 0.0 && incl >= target) atomicMin(&sh_owner, tid);
-    __syncthreads();
-    if (tid == sh_owner) {           // which of this thread's blocks holds the target
-      double run = incl - local;
-      int blk = -1;
-      for (int i = 0; i < bp && blk < 0; ++i) {
-        const int ib = tid * bp + i;
-        if (ib < n_blk && blk_tot[ib] > 0.0) {
-          if (run + blk_tot[ib] >= target) blk = ib; else run += blk_tot[ib];
-        }
-      }
-      if (blk < 0) {                 // rounding between the two summation orders: last live block
-        for (int i = bp - 1; i >= 0 && blk < 0; --i) {
-          const int ib = tid * bp + i;
-          if (ib < n_blk && blk_tot[ib] > 0.0) blk = ib;
-        }
-        run = -1.0e300;              // nothing in blk reaches the target: its last live token
-      }
-      sh_blk = blk;
-      sh_excl = run;
-    }
-    __syncthreads();
-    if (w == 0 && (sh_owner < kWalkThreads || sh_last >= 0)) {
-      // the block that holds the target; if rounding left the row's total a hair below the
-      // target, the last live block with nothing to find: its last live token is taken
-      const bool owned = sh_owner < kWalkThreads;
-      const int ib = owned ? sh_blk : sh_last;
-      const double excl0 = owned ? sh_excl : -1.0e300;
-      float e[4];
-      lane_weights(ib, e);
-      const float mine = (e[0] + e[1]) + (e[2] + e[3]);
-      float li = mine;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const float up = __shfl_up(li, o, 64);
-        if (lane >= o) li += up;
-      }
-      double run = excl0 + (double)(li - mine);
-      int found = -1, lastp = -1;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (e[i] > 0.f) {
-          lastp = ib * kBonusBlock + 4 * lane + i;
-          run += (double)e[i];
-          if (found < 0 && run >= target) found = lastp;
-        }
-      }
-      // first lane that found its element wins (vocabulary order = lane order)
-      const unsigned long long hit = __builtin_amdgcn_ballot_w64(found >= 0);
-      int pick;
-      if (hit != 0ull) {
-        pick = __shfl(found, __builtin_ctzll(hit), 64);
-      } else {                       // a hair below the target after rounding: last live token
-        pick = lastp;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) pick = max(pick, __shfl_xor(pick, o, 64));
-      }
-      if (lane == 0) sh_pick = pick;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      a.bonus_id[b] = max(sh_pick, 0);
+    if (lane < n_q) path[lane] = mine;
+    if ((out >> lane) & 1ull) struck[__popcll(out & ((1ull << lane) - 1ull))] = nd.token;
+    if (!ended) cur = -2;
+    if (lane == 0) {
+      sh_cur = cur;
       a.accept_len[b] = len;
+      if (!ended) a.bonus_id[b] = 0;            // only with a malformed tree (the walk did not end within n_q + 1 levels)
     }
-    return;
   }
-  // only reachable with a malformed tree (the walk did not end within n_q + 1 levels)
-  if (tid == 0) { a.accept_len[b] = len; a.bonus_id[b] = 0; }
+  __syncthreads();
+  cur = sh_cur;
+  if (cur < -1) return;
+  // ---- bonus token: inverse CDF over what is left of the row's distribution.  The sums of
+  // the row's 256-token blocks come from the statistics pass (relative to their chunk's max);
+  // rescaled to the row's max, minus the struck-out tokens, they are scanned in fp64 (fp32
+  // inside a block, whose sum is a small part of the mass), so the draw is decided by the fp32
+  // exponentials alone (~1e-7 of the remaining mass).  Only the block that holds the target
+  // is read from the logits.
+  const int64_t row = row0 + cur + 1;
+  const float *lg = a.logits + row * V;
+  const float m = row_m[cur + 1], Z = row_z[cur + 1];
+  const int n_blk = (V + kBonusBlock - 1) / kBonusBlock;
+  const int bpc = (n_blk + kStatChunks - 1) / kStatChunks;
+  const float *bs = a.blk_sum + row * n_blk;
+  for (int ib = tid; ib < n_blk; ib += kWalkThreads)
+    blk_tot[ib] = (double)bs[ib] * (double)fast_exp2(a.stats[(row * kStatChunks + ib / bpc) * 2] - m);
+  __syncthreads();
+  if (w != 0) return;
+  const int ns = __popcll(out);
+  const float nd_e = fast_exp2(nd.logit * a.inv_temp_log2 - m);
+  while (out != 0ull) {            // struck-out tokens leave their blocks
+    const int j = __builtin_ctzll(out), x = __builtin_amdgcn_readlane(nd.token, j);
+    out &= out - 1;
+    const double left = blk_tot[x / kBonusBlock] - (double)lane_f32(nd_e, j);
+    blk_tot[x / kBonusBlock] = left > 0.0 ? left : 0.0;      // (every lane stores the same value)
+  }
+  const Drawn d = find_block(blk_tot, n_blk, [&](double) {
+    return (double)uniform_of(a, b, -1) * (double)S * (double)Z;        // unnormalised units
+  });
+  int pick = -1;
+  if (d.block >= 0) {
+    float e[4];                    // 0 past the end of the vocabulary and for struck-out tokens
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int v = d.block * kBonusBlock + 4 * lane + i;
+      e[i] = 0.f;
+      if (v < V) {
+        e[i] = fast_exp2(lg[v] * a.inv_temp_log2 - m);
+        for (int k = 0; k < ns; ++k)
+          if (struck[k] == v) e[i] = 0.f;
+      }
+    }
+    pick = find_token(d, e);
+  }
+  if (lane == 0) a.bonus_id[b] = max(pick, 0);
 }
 
 // Acceptance against a SAMPLED draft: the children of a node were drawn from the draft's
@@ -341,46 +370,109 @@ accept_sample_kernel(SampleArgs a) {
 // from its p, its q and the k sums S_0 .. S_{k-1}, so a rejection costs one pass over the row
 // (logits and q) for the next sum, which also leaves the sums per block of 256 tokens in LDS for
 // the bonus draw: scan over the blocks, then a search inside the block that holds the target.
-// A pass is one workgroup's read of 8 V bytes and bound by its latency: four blocks per wavefront are in
-// flight (64,003 tokens, first child rejected: 50.6 -> 30.2 us a call), and rows of odd vocabularies, which start at
-// any multiple of 4 bytes, are read by the same 16-byte loads (of a type that asks for no more).
+// A pass is one workgroup's read of 8 V bytes and bound by its latency and by the exponentials: four blocks per
+// wavefront are in flight, and rows of odd vocabularies, which start at any multiple of 4 bytes, are read by the same
+// 16-byte loads.
+// kStage = 0: that workgroup does everything.  Where a pass takes it longer than two more launches, three kernels: 1,
+// the walk up to the first residual sum; residual_sums_kernel, that pass by the whole chip; 2, the rest from there
+// (further rejections at the same node, and nodes further down, again by one workgroup).  One kernel that fetched level
+// by level / as here, us of kernels: 4 chains of 8 over 64,003 27.7 / 13.2, 6 of 3 over 152,064 38.4 / 14.4, 6 trees of 25
+// over 16,724 19.3 / 12.3; at 6,828 in one kernel (5 trees of 62) 29.0 / 17.0.
 constexpr int kMaxRejections = SPARROW_MAX_NQ;
 constexpr int kAhead = 4;
 
+struct WalkState {
+  int32_t cur, len;         // node, accepted so far (cur = -2: malformed tree, nothing to draw)
+  int32_t k, j;             // rejections at the node (0 or 1), the first child that is still to be tested
+  float m, Z;               // of the node's row
+};
+// The walk up to the first node that has to know a residual sum, by one wavefront: children are tested against the
+// row's own distribution until one is rejected, or a node has no child left.
+__device__ __forceinline__ WalkState walk_unrejected(const SampleArgs &a, const Node &nd, const float *row_m,
+                                                     const float *row_z, int32_t *path) {
+  const int lane = threadIdx.x & 63, n_q = a.n_q;
+  float p = 0.f, Z = 0.f;
+  if (nd.parent >= -1) {
+    p = fast_exp2(nd.logit * a.inv_temp_log2 - row_m[nd.parent + 1]);
+    Z = row_z[nd.parent + 1];
+  }
+  const bool pass = p > 0.f && nd.u * nd.q * Z <= p;         // as the first child tested at its parent
+  const unsigned long long passes = __builtin_amdgcn_ballot_w64(pass);
+  WalkState s = {-1, 0, 0, n_q, 0.f, 0.f};
+  int mine = -1;
+  bool ended = false;
+  for (int level = 0; level <= n_q; ++level) {
+    // (nodes after their parent only: the others of a malformed tree are never reached)
+    const unsigned long long kids = __builtin_amdgcn_ballot_w64(nd.parent == s.cur && lane > s.cur);
+    const int j = kids != 0ull ? __builtin_ctzll(kids) : n_q;
+    if (j == n_q || ((passes >> j) & 1ull) == 0ull) {
+      s.k = j < n_q;
+      s.j = (kids & (kids - 1)) != 0ull ? j + 1 : n_q;       // n_q: no sibling left to test, the walk goes no further
+      ended = true;
+      break;
+    }
+    if (lane == s.len) mine = j;
+    ++s.len;
+    s.cur = j;
+  }
+  if (lane < n_q) path[lane] = mine;
+  if (ended) { s.m = row_m[s.cur + 1]; s.Z = row_z[s.cur + 1]; }
+  else s.cur = -2;
+  return s;
+}
+
+template <int kStage>
 __global__ void __launch_bounds__(kWalkThreads)
 accept_sample_q_kernel(SampleArgs a) {
-  __shared__ int dr_s[SPARROW_MAX_NQ], par_s[SPARROW_MAX_NQ];
+  __shared__ float row_m[SPARROW_MAX_NQ + 1], row_z[SPARROW_MAX_NQ + 1];
+  __shared__ Node nodes[SPARROW_MAX_NQ];
+  __shared__ WalkState sh_state;
   __shared__ float S_s[kMaxRejections + 1];     // residual sums at the current node
-  __shared__ double blk_tot[kBonusMaxBlocks];   // sums of the current residual per 256 tokens
+  __shared__ double blk_tot[kStage == 1 ? 1 : kBonusMaxBlocks];   // sums of the current residual per 256 tokens
   __shared__ double wave_tot[kWalkThreads / 64];
-  __shared__ float sh_m;
-  __shared__ int sh_owner, sh_last, sh_pick, sh_blk;
-  __shared__ double sh_excl;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int n_q = a.n_q, V = a.V;
+  const int64_t row0 = (int64_t)b * (n_q + 1);
   int32_t *path = a.accept_path + (int64_t)b * n_q;
-  for (int i = tid; i < n_q; i += kWalkThreads) {
-    path[i] = -1;
-    dr_s[i] = a.draft_ids[(int64_t)b * n_q + i];
-    par_s[i] = a.parent ? a.parent[(int64_t)b * a.parent_stride + i] : i - 1;
+  WalkState *const state = reinterpret_cast<WalkState *>(a.state) + b;
+  // nodes and row statistics (in LDS behind the next barrier), in the kernels that test children
+  auto fetch = [&]() {
+    Node nd = {-2, -1, 0.f, 0.f, 0.f};
+    if (w == 0) {
+      nd = fetch_node(a, b, row0, lane);
+      if (lane < n_q) nodes[lane] = nd;
+    }
+    row_statistics(a, row0, row_m, row_z);
+    return nd;
+  };
+  if constexpr (kStage < 2) {
+    const Node nd = fetch();
+    __syncthreads();
+    if (w == 0) {
+      const WalkState s = walk_unrejected(a, nd, row_m, row_z, path);
+      if (lane == 0) { if constexpr (kStage == 1) *state = s; else sh_state = s; }
+    }
+    if constexpr (kStage == 1) return;
+    __syncthreads();
   }
-  __syncthreads();
   const int n_blk = (V + kBonusBlock - 1) / kBonusBlock;
-  int cur = -1, len = 0;
+  WalkState s;
+  if constexpr (kStage == 2) s = *state; else s = sh_state;
+  int cur = s.cur, len = s.len;
+  if (cur < -1) {                                             // malformed tree only
+    if (tid == 0) { a.accept_len[b] = len; a.bonus_id[b] = 0; }
+    return;
+  }
+  bool entered = kStage != 2;                                 // stage 2: the sums that the walk stopped for are there
+  int k = s.k, first = s.j;                                   // rejections at this node so far, next child to test
+  float m = s.m;
+  if (kStage == 2 && first < n_q) (void)fetch();
+  if (tid == 0) S_s[0] = s.Z;
+  __syncthreads();
   for (int level = 0; level <= n_q; ++level) {
-    const int64_t row = (int64_t)b * (n_q + 1) + cur + 1;
+    const int64_t row = row0 + cur + 1;
     const float *lg = a.logits + row * V;
     const float *q = a.draft_q + row * V;
-    if (w == 0) {                                             // row maximum and sum from the chunk partials
-      const float pm = a.stats[(row * kStatChunks + lane) * 2];
-      const float ps = a.stats[(row * kStatChunks + lane) * 2 + 1];
-      const float m = wave_max(pm);
-      const float Z = wave_sum(ps * fast_exp2(pm - m));
-      if (lane == 0) { sh_m = m; S_s[0] = Z; }
-    }
-    __syncthreads();
-    const float m = sh_m;
-    int k = 0;                                                // rejections at this node so far
     // residual of token v after k rejections (unnormalised: p = exp2(..) / S_0)
     auto residual = [&](float lv, float qv, int kk) {
       float r = fast_exp2(lv * a.inv_temp_log2 - m);
@@ -388,7 +480,7 @@ accept_sample_q_kernel(SampleArgs a) {
       return r;
     };
     // one pass over the row: sums of the residual after kk rejections per block of 256 tokens
-    // (into blk_tot) and in total (returned to every thread)
+    // (into blk_tot) and in total (into S_s[kk])
     auto block_sums = [&](int kk) {
       double mine = 0.0;
       for (int ib0 = w; ib0 < n_blk; ib0 += kAhead * (kWalkThreads / 64)) {
@@ -422,130 +514,139 @@ accept_sample_q_kernel(SampleArgs a) {
       }
       if (lane == 0) wave_tot[w] = mine;
       __syncthreads();
-      double tot = 0.0;
-      for (int i = 0; i < kWalkThreads / 64; ++i) tot += wave_tot[i];
-      __syncthreads();                                        // wave_tot is reused by the scan
-      return tot;
+      if (tid == 0 && kk > 0) {
+        double tot = 0.0;
+        for (int i = 0; i < kWalkThreads / 64; ++i) tot += wave_tot[i];
+        S_s[kk] = (float)tot;
+      }
+      __syncthreads();                                        // (wave_tot is reused by the next pass)
     };
-    int next = -1;
-    bool sums_current = false;                                // blk_tot holds the sums of residual k
-    for (int j = cur + 1; j < n_q && next < 0; ++j) {         // uniform: par_s / dr_s are shared
-      if (par_s[j] != cur) continue;
-      const int x = dr_s[j];
-      if (x < 0 || x >= V) continue;
-      const float qx = q[x];
-      const float r = residual(lg[x], qx, k);
-      if (r > 0.f && uniform_of(a, b, j) * qx * S_s[k] <= r) { next = j; break; }
-      if (k == kMaxRejections) continue;                      // (cannot happen: at most n_q children)
-      const double tot = block_sums(k + 1);                   // rejected: the next residual's sum
-      if (tid == 0) S_s[k + 1] = (float)tot;
+    if (!entered) {
+      entered = true;
+      const float *bs = a.blk_sum + row * n_blk;
+      double mine = 0.0;
+      for (int ib = tid; ib < n_blk; ib += kWalkThreads) {
+        const double t = (double)bs[ib];
+        blk_tot[ib] = t;
+        mine += t;
+      }
+      if (first < n_q) {                                      // the total, for the siblings (the draw finds its own)
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) mine += __shfl_xor(mine, o, 64);
+        if (lane == 0) wave_tot[w] = mine;
+        __syncthreads();
+        if (tid == 0 && k > 0) {
+          double tot = 0.0;
+          for (int i = 0; i < kWalkThreads / 64; ++i) tot += wave_tot[i];
+          S_s[k] = (float)tot;
+        }
+      }
       __syncthreads();
-      ++k;
-      sums_current = true;
+    } else {
+      block_sums(k);
     }
-    if (next >= 0) {
-      if (tid == 0) path[len] = next;
+    int next = -1;
+    for (int j = first; j < n_q && next < 0; ++j) {           // uniform: the nodes are shared
+      if (nodes[j].parent != cur) continue;
+      const float r = residual(nodes[j].logit, nodes[j].q, k);
+      if (r > 0.f && nodes[j].u * nodes[j].q * S_s[k] <= r) { next = j; break; }
+      if (k == kMaxRejections) continue;                      // (cannot happen: at most n_q children)
+      block_sums(++k);                                        // rejected: the next residual's sum
+    }
+    if (next < 0) {
+      // ---- bonus token: inverse CDF of the residual after k rejections, in vocabulary order
+      if (w != 0) return;
+      const Drawn d = find_block(blk_tot, n_blk, [&](double total) {
+        return (double)uniform_of(a, b, -1) * (double)(k > 0 ? (float)total : S_s[0]);
+      });
+      int pick = -1;
+      if (d.block >= 0) {
+        float e[4];
+        const int v = d.block * kBonusBlock + 4 * lane;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = v + i < V ? residual(lg[v + i], q[v + i], k) : 0.f;
+        pick = find_token(d, e);
+      }
+      if (lane == 0) {
+        a.bonus_id[b] = max(pick, 0);
+        a.accept_len[b] = len;
+      }
+      return;
+    }
+    // accepted after a rejection at its parent: the nodes below, up to the next one that has to know a sum
+    __syncthreads();                                          // S_s and blk_tot are rewritten at the next node
+    if (tid == 0) path[len] = next;
+    ++len;
+    cur = next;
+    for (k = 0, first = n_q;;) {
+      int j = cur + 1;
+      while (j < n_q && nodes[j].parent != cur) ++j;
+      m = row_m[cur + 1];
+      if (j == n_q) break;                                    // no child: the draw from the row itself
+      const float r = fast_exp2(nodes[j].logit * a.inv_temp_log2 - m);
+      if (!(r > 0.f && nodes[j].u * nodes[j].q * row_z[cur + 1] <= r)) {
+        k = 1;
+        first = j + 1;
+        break;
+      }
+      if (tid == 0) path[len] = j;
       ++len;
-      cur = next;
-      __syncthreads();                                        // S_s is rewritten at the next level
-      continue;
+      cur = j;
     }
-    // ---- bonus token: inverse CDF of the residual after k rejections, in vocabulary order
-    if (!sums_current) (void)block_sums(k);
-    if (tid == 0) { sh_owner = kWalkThreads; sh_last = -1; sh_pick = -1; }
+    if (tid == 0) S_s[0] = row_z[cur + 1];
     __syncthreads();
-    const double target = (double)uniform_of(a, b, -1) * (double)S_s[k];
-    const int bp = (n_blk + kWalkThreads - 1) / kWalkThreads;
-    double local = 0.0;
-    int last_blk = -1;
-    for (int i = 0; i < bp; ++i) {
-      const int ib = tid * bp + i;
-      if (ib < n_blk) {
-        local += blk_tot[ib];
-        if (blk_tot[ib] > 0.0) last_blk = ib;
-      }
-    }
-    if (last_blk >= 0) atomicMax(&sh_last, last_blk);
-    double incl = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const double up = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += up;
-    }
-    if (lane == 63) wave_tot[w] = incl;
-    __syncthreads();
-    double base = 0.0;
-    for (int i = 0; i < w; ++i) base += wave_tot[i];
-    incl += base;
-    if (local > 0.0 && incl >= target) atomicMin(&sh_owner, tid);
-    __syncthreads();
-    if (tid == sh_owner) {                                    // which of this thread's blocks
-      double run = incl - local;
-      int blk = -1;
-      for (int i = 0; i < bp && blk < 0; ++i) {
-        const int ib = tid * bp + i;
-        if (ib < n_blk && blk_tot[ib] > 0.0) {
-          if (run + blk_tot[ib] >= target) blk = ib; else run += blk_tot[ib];
-        }
-      }
-      if (blk < 0) {                                          // rounding between the two orders of summation
-        for (int i = bp - 1; i >= 0 && blk < 0; --i) {
-          const int ib = tid * bp + i;
-          if (ib < n_blk && blk_tot[ib] > 0.0) blk = ib;
-        }
-        run = -1.0e300;
-      }
-      sh_blk = blk;
-      sh_excl = run;
-    }
-    __syncthreads();
-    if (w == 0 && (sh_owner < kWalkThreads || sh_last >= 0)) {
-      const bool owned = sh_owner < kWalkThreads;
-      const int ib = owned ? sh_blk : sh_last;
-      const double excl0 = owned ? sh_excl : -1.0e300;
-      float e[4];
-      const int v = ib * kBonusBlock + 4 * lane;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) e[i] = v + i < V ? residual(lg[v + i], q[v + i], k) : 0.f;
-      const float mine = (e[0] + e[1]) + (e[2] + e[3]);
-      float li = mine;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const float up = __shfl_up(li, o, 64);
-        if (lane >= o) li += up;
-      }
-      double run = excl0 + (double)(li - mine);
-      int found = -1, lastp = -1;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (e[i] > 0.f) {
-          lastp = v + i;
-          run += (double)e[i];
-          if (found < 0 && run >= target) found = lastp;
-        }
-      }
-      const unsigned long long hit = __builtin_amdgcn_ballot_w64(found >= 0);
-      int pick;
-      if (hit != 0ull) {
-        pick = __shfl(found, __builtin_ctzll(hit), 64);
-      } else {                                                // a hair below the target: last live token
-        pick = lastp;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) pick = max(pick, __shfl_xor(pick, o, 64));
-      }
-      if (lane == 0) sh_pick = pick;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      a.bonus_id[b] = max(sh_pick, 0);
-      a.accept_len[b] = len;
-    }
-    return;
   }
   if (tid == 0) { a.accept_len[b] = len; a.bonus_id[b] = 0; }   // malformed tree only
 }
 
+// Sums of the residual at the node where a sequence's walk stopped, per block of 256 tokens, in place of the row's
+// own block sums.  Two blocks per wavefront: 64,003 tokens are 32 workgroups per sequence, and the pass is one round
+// trip for the state and one for the row.
+constexpr int kSumBlocks = 2;
+__global__ void __launch_bounds__(256)
+residual_sums_kernel(SampleArgs a) {
+  const int b = blockIdx.y, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int V = a.V, n_blk = (V + kBonusBlock - 1) / kBonusBlock;
+  const WalkState s = reinterpret_cast<const WalkState *>(a.state)[b];
+  if (s.cur < -1) return;
+  const int64_t row = (int64_t)b * (a.n_q + 1) + s.cur + 1;
+  const float *lg = a.logits + row * V;
+  const float *q = a.draft_q + row * V;
+  float l4[kSumBlocks][4], q4[kSumBlocks][4];
+#pragma unroll
+  for (int u = 0; u < kSumBlocks; ++u) {
+    const int v = (w * kSumBlocks + u) * kBonusBlock + 4 * lane;
+    if (v + 3 < V) {
+      const f32x4 x = *reinterpret_cast<const f32x4u *>(lg + v), y = *reinterpret_cast<const f32x4u *>(q + v);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { l4[u][i] = x[i]; q4[u][i] = y[i]; }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        l4[u][i] = v + i < V ? lg[v + i] : 0.f;
+        q4[u][i] = v + i < V ? q[v + i] : 0.f;
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kSumBlocks; ++u) {
+    const int ib = w * kSumBlocks + u, v = ib * kBonusBlock + 4 * lane;
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (v + i < V) {
+        const float e = fast_exp2(l4[u][i] * a.inv_temp_log2 - s.m);
+        t += s.k > 0 ? fmaxf(e - s.Z * q4[u][i], 0.f) : e;
+      }
+    t = wave_sum_valu(t);
+    if (lane == 0 && ib < n_blk) a.blk_sum[row * n_blk + ib] = t;
+  }
+}
+
 }  // namespace
+
+size_t sample_state_bytes(int B) { return (size_t)B * sizeof(WalkState); }
 
 hipError_t launch_logit_stats(const SampleArgs &a, hipStream_t st) {
   // (rows and blocks between the measured sizes above; more than 16 blocks do not fit one wavefront's registers)
@@ -557,11 +658,21 @@ hipError_t launch_logit_stats(const SampleArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Up to here one workgroup walks a sequence alone: a pass over 16,384 tokens is one round of loads for its 16 wavefronts,
+// and two launches more are 5 us.
+constexpr int kOneWorkgroupVocab = 16384;
+
 hipError_t launch_accept_sample(const SampleArgs &a, hipStream_t st) {
-  if (a.draft_q != nullptr)
-    hipLaunchKernelGGL(accept_sample_q_kernel, dim3(a.B), dim3(kWalkThreads), 0, st, a);
-  else
+  if (a.draft_q == nullptr) {
     hipLaunchKernelGGL(accept_sample_kernel, dim3(a.B), dim3(kWalkThreads), 0, st, a);
+  } else if (a.state != nullptr && a.V > kOneWorkgroupVocab) {
+    const int n_blk = (a.V + kBonusBlock - 1) / kBonusBlock;
+    hipLaunchKernelGGL(accept_sample_q_kernel<1>, dim3(a.B), dim3(kWalkThreads), 0, st, a);
+    hipLaunchKernelGGL(residual_sums_kernel, dim3((n_blk + 4 * kSumBlocks - 1) / (4 * kSumBlocks), a.B), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(accept_sample_q_kernel<2>, dim3(a.B), dim3(kWalkThreads), 0, st, a);
+  } else {
+    hipLaunchKernelGGL(accept_sample_q_kernel<0>, dim3(a.B), dim3(kWalkThreads), 0, st, a);
+  }
   return hipGetLastError();
 }
 

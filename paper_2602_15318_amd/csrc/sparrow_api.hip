@@ -716,6 +716,8 @@ static int accept_body(int32_t dtype, const void *hidden_rows, const void *lm_he
   s.stats = (float *)((char *)workspace + base + logits_bytes);
   s.blk_sum = (float *)((char *)workspace + base + logits_bytes + stats_bytes);
   s.accept_len = accept_len; s.accept_path = accept_path; s.bonus_id = bonus_id;
+  // (sampling has no use for the argmax candidates, which the lm_head pass is done with)
+  s.state = sample_state_bytes(B) <= base ? workspace : nullptr;
   s.B = B; s.n_q = n_q; s.M = M; s.V = vocab;
   s.inv_temp_log2 = 1.4426950408889634f / sample->temperature;
   e = launch_logit_stats(s, st);

@@ -110,6 +110,43 @@ def test_accept_sample_q_matches_oracle(sp, oracle, dtype, H, V, B, n_q, tree, T
     assert len(walked) >= 2, f"all graded walks had the same length {walked}: the cases are too easy"
 
 
+# Above 16,384 tokens the first residual's sums are the whole chip's work, the walk in front of it and the rest of the
+# walk (siblings, nodes below an accepted sibling, the draw) kernels of their own; up to there one workgroup does it all.
+@pytest.mark.parametrize("V", [16384, 16385, 20480, 40003])
+@pytest.mark.parametrize("tree,B,n_q", [("chain", 3, 5), ("tree", 2, 13), ("per-seq", 3, 12)])
+def test_vocabularies(sp, oracle, V, tree, B, n_q):
+    test_accept_sample_q_matches_oracle(sp, oracle, "bf16", 64, V, B, n_q, tree, 1.0, False)
+
+
+def test_residuals_of_siblings_over_a_large_vocabulary(sp, oracle):
+    """Siblings that are rejected one after the other, and accepted after others were: counted on the CPU."""
+    dtype, H, V, B, n_q, T = "bf16", 64, 20011, 4, 24, 1.0
+    parent = np.array([-1] * 6 + [0, 0, 1, 1, 2, 2, 3, 3, 4, 4, 5, 5, 6, 6, 8, 8, 10, 12], dtype=np.int32)
+    cfg = wl.Config("asq", dtype, 4, 1, 64, B, (((wl.TEXT, 8),),) * B, 8, n_q, True, H, V)
+    graded, late, nested = 0, 0, 0
+    for seed in range(16):
+        hidden, W, lg, q, draft = _case(oracle, cfg, seed, B, n_q, parent, V, H, dtype, T)
+        rng = np.random.default_rng(seed + 900)
+        ua = rng.random((B, n_q)).astype(np.float32).astype(np.float64)
+        ub = rng.random(B).astype(np.float32).astype(np.float64)
+        alen, path, bonus, margin = oracle.accept_sample_q(lg, draft, parent, B, n_q, T, q, ua, ub)
+        ok = margin >= MARGIN
+        if not ok.any():
+            continue
+        r = sp.accept_sample_q(dev(hidden, dtype), dev(W, dtype), dev(draft), dev(parent), B, n_q, T, draft_probs=dev(q),
+                               u_accept=dev(ua.astype(np.float32)), u_bonus=dev(ub.astype(np.float32)))
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(r["accept_len"].cpu().numpy()[ok], alen[ok], err_msg=f"seed {seed}")
+        np.testing.assert_array_equal(r["accept_path"].cpu().numpy()[ok], path.reshape(B, n_q)[ok], err_msg=f"seed {seed}")
+        np.testing.assert_array_equal(r["bonus_id"].cpu().numpy()[ok], bonus[ok], err_msg=f"seed {seed}")
+        for b in np.flatnonzero(ok):
+            first = path.reshape(B, n_q)[b][0]
+            late += int(alen[b] > 0 and 0 < first < 6)              # accepted after siblings were rejected
+            nested += int(alen[b] > 1 and 0 < first < 6)            # and the walk went on below it
+        graded += int(ok.sum())
+    assert graded >= 12 and late >= 4 and nested >= 1, (graded, late, nested)
+
+
 def test_generated_uniforms_without_a_draft_distribution(sp, oracle):
     """draft_probs = NULL with library-generated uniforms: the deterministic-children rule of
     sparrow_accept_sample on the Philox stream the oracle generates on its own."""
