@@ -3,6 +3,9 @@
 Function names and argument order follow include/sparrow.h.  Tensors are torch tensors on the
 GPU; the host arrays (cu_seqlens, cu_text) are numpy arrays / sequences of ints.  There is no
 fallback: if the HIP library has not been built, importing this module raises.
+
+The calls of a decoding step go through _native.so (csrc/binding.cpp) where their arguments are plain: it does the
+marshalling below in C++ and returns NotImplemented for everything else.
 """
 from __future__ import annotations
 
@@ -120,6 +123,11 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
+try:
+    from . import _native
+except ImportError as e:
+    raise ImportError("_native.so, the binding's native part, is missing or does not load: build it with "
+                      "`python -m paper_2602_15318_amd.build` (or __graft_entry__.build())") from e
 
 
 def library_path() -> str:
@@ -147,9 +155,8 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported tensor dtype {t.dtype}")
 
 
-# The helpers below run several times per call, and a call's kernels take as little as 5 us: on the
-# 28 verification calls of an 8k context the binding took 14 us a call with ctypes objects for every
-# pointer and a Stream object per call, against 11 us of kernels; 8.8 us this way.
+# The helpers below run several times per call that the native part leaves, and a call's kernels take as little as
+# 5 us: 14 us a call with ctypes objects for every pointer and a Stream object per call, 8.8 to 10 us this way.
 _I32 = np.dtype(np.int32)
 
 
@@ -171,6 +178,9 @@ def _stream_ptr(stream) -> int:
     if stream is not None:
         return stream.cuda_stream
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+_native.setup(_check, _stream_ptr, np.ndarray)
 
 
 def _parent_stride(parent: Optional[torch.Tensor], n_q: int, B: int) -> int:
@@ -209,6 +219,9 @@ def draft_window_attn(q, k, v, cu_seqlens, text_idx, cu_text, window: int, scale
                       out=None, lse=None, want_lse: bool = True, stream=None):
     """sparrow_draft_window_attn.  q [B,Hq,d]; k,v [T,Hkv,d]; text_idx int32 device tensor.
     Returns (out, lse)."""
+    r = _native.draft_window_attn(q, k, v, cu_seqlens, text_idx, cu_text, window, scale, out, lse, want_lse, stream)
+    if r is not NotImplemented:
+        return r
     B = q.shape[0]
     d = _desc(q, k, v, scale)
     cu, ct = _host_i32(cu_seqlens), _host_i32(cu_text)
@@ -236,6 +249,10 @@ def verify_attn(q, k, v, cu_seqlens, parent, n_q: int, scale: float = 0.0, out=N
     """sparrow_verify_attn (sparrow_verify_attn_passes when passes != 3).  q [B*n_q,Hq,d];
     k,v [sum(L_b+n_q),Hkv,d]; parent int32 device tensor [n_q] (one tree for all sequences),
     [B, n_q] (one tree per sequence) or None (chain).  Returns (out, lse)."""
+    if passes == 3:
+        r = _native.verify_attn(q, k, v, cu_seqlens, parent, n_q, scale, out, lse, want_lse, workspace, stream)
+        if r is not NotImplemented:
+            return r
     cu = _host_i32(cu_seqlens)
     B = cu.shape[0] - 1
     d = _desc(q, k, v, scale, _parent_stride(parent, n_q, B))
@@ -280,6 +297,10 @@ def accept(hidden_rows, lm_head, draft_ids, parent, B: int, n_q: int, workspace=
            outputs=None, stream=None):
     """sparrow_accept.  hidden_rows [B*(n_q+1), H]; lm_head [V, H]; draft_ids int32 [B*n_q].
     Returns a dict of int32 device tensors: target_ids, accept_len, accept_path, bonus_id."""
+    if outputs is None:
+        r = _native.accept(hidden_rows, lm_head, draft_ids, parent, B, n_q, workspace, stream)
+        if r is not NotImplemented:
+            return r
     if not hidden_rows.is_contiguous() or not lm_head.is_contiguous():
         raise ValueError("hidden_rows and lm_head must be contiguous")
     if hidden_rows.dtype != lm_head.dtype:
@@ -311,6 +332,9 @@ def accept(hidden_rows, lm_head, draft_ids, parent, B: int, n_q: int, workspace=
 def hsr_fc(embed, token_ids, h_prev, w_fc, b_fc=None, out=None, stream=None):
     """sparrow_hsr_fc: z = FC(embed[token_ids] (+) h_prev).  embed [V,H]; token_ids int32 [M];
     h_prev [M,H]; w_fc [H,2H]; b_fc [H] or None.  Returns z [M,H]."""
+    r = _native.hsr_fc(embed, token_ids, h_prev, w_fc, b_fc, out, stream)
+    if r is not NotImplemented:
+        return r
     M, H = h_prev.shape
     for t in (embed, h_prev, w_fc) + (() if b_fc is None else (b_fc,)):
         if not t.is_contiguous() or t.dtype != h_prev.dtype:
@@ -330,6 +354,10 @@ def draft_qkv_append(z, norm_weight, eps: float, w_qkv, b_qkv, rope_cos, rope_si
                      n_q_heads: int, k_cache, v_cache, q_out=None, stream=None):
     """sparrow_draft_qkv_append.  z [M,H]; w_qkv [(Hq+2Hkv)d, H]; rope_cos/sin float32 [M,d/2];
     kv_rows host int32 [M]; k_cache, v_cache [T,Hkv,d] (written in place).  Returns q [M,Hq,d]."""
+    r = _native.draft_qkv_append(z, norm_weight, eps, w_qkv, b_qkv, rope_cos, rope_sin, kv_rows, n_q_heads, k_cache, v_cache,
+                                 q_out, stream)
+    if r is not NotImplemented:
+        return r
     M, H = z.shape
     Hkv, d = k_cache.shape[1], k_cache.shape[2]
     if k_cache.stride(2) != 1 or v_cache.stride() != k_cache.stride() or v_cache.shape != k_cache.shape:
