@@ -19,11 +19,13 @@
 // bf16 terms (the product has up to 16 bits), and the row's 1/rms (from the squares each wavefront
 // sees in its own slices) scales the result.
 // One activation row (QKV: also two of up to 1,024 columns) runs a wavefront per output feature or rotary
-// pair instead.
+// pair instead (QKV: at every width).
 //
 // Measured (FC + QKV, one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64, six
 // rows 141 + 67 -> 9.3 + 10.2 us, one row 56 + 22 -> 7.3 + 6.8; hidden 5,120, 40/8 heads of 128, 16 rows
 // 823 + 447 -> 31.6 + 32.5 us; hidden 1,024, 16/4 heads of 64, six rows 36 + 21 -> 4.8 + 6.5.
+#include <algorithm>
+
 #include "common.hpp"
 #include "hsr_input.hpp"
 
@@ -46,8 +48,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const bf16_t *firs
 // runs epi(D, sum).  xload(m, k, ok): 8 consecutive bf16 of activation row m at column k (k % 8 == 0),
 // zeros if !ok.  With the norm folded in, the activations of a slice are taken in two halves of 256
 // columns: their two terms fill 64 registers per half beside the 64 of the weights in flight.
+// kFew (norm folded in, at most 8 rows): lanes n and n ^ 8 share row n & 7 and hold one half of a slice's columns each, so
+// that a whole slice takes 64 registers and half the arithmetic.  A matrix instruction's 16 columns then meet weights of
+// one half: columns below 8 are right where they are the first half's, the others where they are the second half's; two
+// sums, added at the end.  The registers left allow a slice's activations to be asked for before its weights and
+// multiplied while those are on their way (behind them, two halves one after the other, the arithmetic and a second round
+// trip came after the last weights).  Before / now, us: 2,560 columns, 40/8 heads of 64, six rows 10.8 / 9.3; 5,120,
+// 40/8 of 128, two rows 31.9 / 23.8, eight 32.4 / 26.2; 1,536, 24/4 of 64, five 7.55 / 7.05; 256, 4/1 of 64, three
+// 6.1 / 5.3.
 // ---------------------------------------------------------------------------------------------
-template <bool kNorm, class WRow, class XLoad, class Epi>
+template <bool kNorm, bool kFew, class WRow, class XLoad, class Epi>
 __device__ __forceinline__ void skinny_gemm(const bf16_t *W, int K, WRow wrow, XLoad xload, const bf16_t *gamma,
                                             int row0, int M, unsigned char *smem, Epi epi) {
   constexpr int kPart = kNorm ? 8 : 16;                      // k-steps of 32 fetched together
@@ -70,15 +80,16 @@ __device__ __forceinline__ void skinny_gemm(const bf16_t *W, int K, WRow wrow, X
     for (int r = 0; r < 16; ++r)
       buf[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, (wrow(r) - first) * K * 2, 2);
   };
-  const int m = row0 + n;
+  static_assert(kNorm || !kFew, "the plain product has no registers to save");
+  const int m = row0 + (kFew ? n & 7 : n);
   const bool m_ok = m < M;
   const __amdgpu_buffer_rsrc_t rs_g = weight_rows(gamma);
   float ssq = 0.f;
   u32x4 xr[kPart], gr[kNorm ? kPart : 1];
-  auto load_x = [&](int k0) {
+  auto load_x = [&](int k0, u32x4 *xr, u32x4 *gr) {
 #pragma unroll
     for (int ks = 0; ks < kPart; ++ks) {
-      const int k = k0 + 32 * ks + 8 * c4;
+      const int k = k0 + 32 * ks + 8 * c4 + (kFew ? 256 * (n >> 3) : 0);
       xr[ks] = xload(m, k, m_ok && k < K);
       if (kNorm) gr[ks] = __builtin_amdgcn_raw_buffer_load_b128(rs_g, k < K ? (unsigned int)k * 2u : kPastEnd, 0, 0);
     }
@@ -126,21 +137,53 @@ __device__ __forceinline__ void skinny_gemm(const bf16_t *W, int K, WRow wrow, X
     }
   };
 
-  issue(w);                               // (nw <= n_slices: every wavefront has a slice)
-  for (int s = w; s < n_slices; s += nw) {
-    load_x(kSlice * s);
-    // lane l of load r holds chunk l of row r; stored at chunk (l & ~15) | ((l & 15) ^ r) so that
-    // the A reads (16 rows, same chunk) spread over all banks
+  // lane l of load r holds chunk l of row r; stored at chunk (l & ~15) | ((l & 15) ^ r) so that
+  // the A reads (16 rows, same chunk) spread over all banks
+  auto stash = [&]() {
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       *reinterpret_cast<u32x4 *>(stg + r * 1024 + (((lane & ~15) | ((lane & 15) ^ r)) << 4)) = buf[r];
-    if (s + nw < n_slices) issue(s + nw);
-    if (kNorm) convert();
-    mul(0);
-    if (kNorm) {
-      load_x(kSlice * s + 256);
+  };
+  if constexpr (kFew) {
+    u32x4 xn[kPart], gn[kPart];
+    load_x(kSlice * w, xr, gr);
+    issue(w);
+    for (int s = w; s < n_slices; s += nw) {
       convert();
-      mul(1);
+      stash();
+      if (s + nw < n_slices) {
+        load_x(kSlice * (s + nw), xn, gn);
+        issue(s + nw);
+      }
+#pragma unroll
+      for (int kh = 0; kh < kPart; ++kh) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {                        // the weights of columns 256 h + 32 kh ...
+          const int ch = 4 * (8 * h + kh) + c4;
+          const bf16x8 a = *reinterpret_cast<const bf16x8 *>(stg + a_base + (((ch & ~15) | ((ch & 15) ^ n)) << 4));
+          acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, xr[kh]), acc[h], 0, 0, 0);
+          acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, gr[kh]), acc[h], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int ks = 0; ks < kPart; ++ks) { xr[ks] = xn[ks]; gr[ks] = gn[ks]; }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[1][e] = lane_xor<8>(acc[1][e], lane);
+    ssq += lane_xor<8>(ssq, lane);
+  } else {
+    issue(w);                             // (nw <= n_slices: every wavefront has a slice)
+    for (int s = w; s < n_slices; s += nw) {
+      load_x(kSlice * s, xr, gr);
+      stash();
+      if (s + nw < n_slices) issue(s + nw);
+      if (kNorm) convert();
+      mul(0);
+      if (kNorm) {
+        load_x(kSlice * s + 256, xr, gr);
+        convert();
+        mul(1);
+      }
     }
   }
   red[w * 64 + lane] = acc[0] + acc[1];
@@ -192,12 +235,13 @@ hsr_fc_any_kernel(HsrFcArgs a) {
                      pack_bf16x2(r[2] + bf16lo_to_f32(bw.y), r[3] + bf16hi_to_f32(bw.y))};
     *(u32x2 *)((bf16_t *)a.z + (int64_t)m * H + f) = o;
   };
-  skinny_gemm<false>((const bf16_t *)a.w, 2 * H, wrow, xload, nullptr, row0, a.M, smem, epi);
+  skinny_gemm<false, false>((const bf16_t *)a.w, 2 * H, wrow, xload, nullptr, row0, a.M, smem, epi);
 }
 
 // ---------------------------------------------------------------------------------------------
 // draft layer input: RMSNorm, QKV, rotary embedding, scatter
 // ---------------------------------------------------------------------------------------------
+template <bool kFew>
 __global__ void __launch_bounds__(kMaxWaves * 64)
 draft_qkv_any_kernel(DraftQkvArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -254,14 +298,13 @@ draft_qkv_any_kernel(DraftQkvArgs a) {
       *(u32x2 *)(base + (int64_t)kv_row * a.stride_tok + (int64_t)c * a.stride_head + feat) = ow;
     }
   };
-  skinny_gemm<true>((const bf16_t *)a.w, H, wrow, xload, (const bf16_t *)a.gamma, row0, a.M, smem, epi);
+  skinny_gemm<true, kFew>((const bf16_t *)a.w, H, wrow, xload, (const bf16_t *)a.gamma, row0, a.M, smem, epi);
 }
 
 // ---------------------------------------------------------------------------------------------
-// One activation row: a wavefront owns one output feature (FC) or one rotary pair of a head (QKV), as
-// in the kernels of whole slices.  It issues the loads of its weight row(s) KS slices at a time, then
-// fetches the activation row (shared by all wavefronts through L2), multiplies and reduces across its
-// lanes on the vector ALU.
+// FC, one activation row: a wavefront owns one output feature, as in the kernel of whole slices.  It issues
+// the loads of its weight row KS slices at a time, then fetches the activation row (shared by all wavefronts
+// through L2), multiplies and reduces across its lanes on the vector ALU.
 // ---------------------------------------------------------------------------------------------
 template <int KS>             // slices in flight: at least K / 512 (K = 2H), or 16
 __global__ void __launch_bounds__(256)
@@ -309,21 +352,54 @@ hsr_fc_any_gemv_kernel(HsrFcArgs a) {
   }
 }
 
+// QKV, one activation row per blockIdx.y: a wavefront owns one rotary pair.  The activations times gamma, as two bf16
+// terms that add up to the whole product (see skinny_gemm), are made once per workgroup and kept in LDS while the weights
+// are on their way: two dot-product instructions per two weights, no unpacking.  They were made by every wavefront, in
+// fp32 with all weights unpacked, 448 vector instructions a wavefront against 112 dot products: FIGURES
+constexpr int kGemvMaxWaves = 16;
+
 template <int KS>             // slices in flight: at least H / 512, or 8
-__global__ void __launch_bounds__(256)
-draft_qkv_any_gemv_kernel(DraftQkvArgs a) {
-  const int lane = threadIdx.x & 63, m = blockIdx.y;         // activation row
+__global__ void __launch_bounds__(kGemvMaxWaves * 64)
+draft_qkv_gemv_kernel(DraftQkvArgs a) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  // (one slice: a lane's own columns, made by every wavefront for itself, without the barrier; 256 columns 3.3 -> 3.1 us)
+  constexpr bool kOwn = KS == 1;
+  __shared__ u32x4 uh[KS * 64], ul[KS * 64];                 // leading and other terms, 8 columns each
+  __shared__ float ssq_lds[kGemvMaxWaves];
+  const int tid = threadIdx.x, lane = tid & 63, m = blockIdx.y;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)blockDim.x >> 6;
   const int half = a.d >> 1;
-  const int pair = blockIdx.x * 4 + (threadIdx.x >> 6);      // (head, feature of the first half)
-  const int n_heads = a.Hq + 2 * a.Hkv;
-  if (pair >= n_heads * half) return;
+  const int n_pairs = (a.Hq + 2 * a.Hkv) * half;
+  const int pair = min((int)blockIdx.x * nw + w, n_pairs - 1);          // (head, feature of the first half)
   const int hd = pair / half, f = pair - hd * half;
   const int H = a.H;
-  const int64_t row0 = (int64_t)__builtin_amdgcn_readfirstlane(hd * a.d + f);
-  const __amdgpu_buffer_rsrc_t rs = weight_rows((const bf16_t *)a.w + row0 * H);
+  const __amdgpu_buffer_rsrc_t rs =
+      weight_rows((const bf16_t *)a.w + (int64_t)__builtin_amdgcn_readfirstlane(hd * a.d + f) * H);
   const unsigned int pair_off = (unsigned int)half * (unsigned int)H * 2u;
-  u32x4 w0[KS], w1[KS];
-  auto issue = [&](int k0) {
+  const __amdgpu_buffer_rsrc_t rs_z = weight_rows((const bf16_t *)a.z + (int64_t)m * H);
+  const __amdgpu_buffer_rsrc_t rs_g = weight_rows((const bf16_t *)a.gamma);
+  // the activations of this thread: 8 columns, twice where KS * 64 threads are more than the workgroup has
+  constexpr int kChunks = KS * 64;
+  float s0 = 0.f, s1 = 0.f, ssq = 0.f;
+  // operands of the end, first of all: in order, they would wait for the weights
+  const bool is_v = hd >= a.Hq + a.Hkv;
+  const __amdgpu_buffer_rsrc_t rs_b = weight_rows((const bf16_t *)a.bias);
+  const unsigned int off_b = a.bias != nullptr ? (unsigned int)(hd * a.d + f) * 2u : kPastEnd;
+  const bf16_t b0 = __builtin_amdgcn_raw_buffer_load_b16(rs_b, off_b, 0, 0);
+  const bf16_t b1 = __builtin_amdgcn_raw_buffer_load_b16(rs_b, off_b, a.bias != nullptr ? a.d : 0, 0);
+  const float cs = a.rope_cos[m * half + f], sn = a.rope_sin[m * half + f];
+  for (int k0 = 0; k0 < H; k0 += KS * kSlice) {
+    if (k0 > 0) __syncthreads();                             // the last slices' terms have been read
+    u32x4 x[2], g[2];
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const int c = kOwn ? lane + 64 * y : tid + y * (int)blockDim.x, k = k0 + 8 * c;
+      const unsigned int off = c < kChunks && k < H ? (unsigned int)k * 2u : kPastEnd;
+      x[y] = __builtin_amdgcn_raw_buffer_load_b128(rs_z, off, 0, 0);
+      g[y] = __builtin_amdgcn_raw_buffer_load_b128(rs_g, off, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);                       // ahead of the weights, whose arrival the terms do not wait for
+    u32x4 w0[KS], w1[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int k = k0 + kSlice * s + 8 * lane;
@@ -331,43 +407,70 @@ draft_qkv_any_gemv_kernel(DraftQkvArgs a) {
       w0[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 2);
       w1[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, pair_off, 2);
     }
-  };
-  issue(0);
-  // epilogue operands ahead of the arithmetic
-  const bool is_v = hd >= a.Hq + a.Hkv;
-  float b0 = 0.f, b1 = 0.f;
-  if (a.bias != nullptr) {
-    b0 = bf16_to_f32(((const bf16_t *)a.bias)[hd * a.d + f]);
-    b1 = bf16_to_f32(((const bf16_t *)a.bias)[hd * a.d + f + half]);
-  }
-  const float cs = a.rope_cos[m * half + f], sn = a.rope_sin[m * half + f];
-  const bf16_t *Z = (const bf16_t *)a.z + (int64_t)m * H, *G = (const bf16_t *)a.gamma;
-  float s0 = 0.f, s1 = 0.f, ssq = 0.f;
-  for (int k0 = 0; k0 < H; k0 += KS * kSlice) {
-    if (k0 > 0) issue(k0);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const int k = min(k0 + kSlice * s + 8 * lane, H - 8);
-      float xf[8], gf[8], a0[8], a1[8];
-      u32x4 x = *(const u32x4 *)(Z + k);
-      if (k0 + kSlice * s + 8 * lane >= H) x = (u32x4){0u, 0u, 0u, 0u};
-      Elem<bf16_t>::unpack(x, xf);
-      Elem<bf16_t>::unpack(*(const u32x4 *)(G + k), gf);
-      Elem<bf16_t>::unpack(w0[s], a0);
-      Elem<bf16_t>::unpack(w1[s], a1);
+    __builtin_amdgcn_sched_barrier(0);
+    u32x4 h_own, l_own;
+    auto terms = [&](const u32x4 &xc, const u32x4 &gc, u32x4 &hi8, u32x4 &lo8) __attribute__((always_inline)) {
+      float xf[8], gf[8], lo[8];
+      unsigned int hb[8];
+      Elem<bf16_t>::unpack(xc, xf);
+      Elem<bf16_t>::unpack(gc, gf);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float u = xf[e] * gf[e];
         ssq = fmaf(xf[e], xf[e], ssq);
-        s0 = fmaf(a0[e], u, s0);
-        s1 = fmaf(a1[e], u, s1);
+        const float u = xf[e] * gf[e];
+        hb[e] = __float_as_uint(u) & 0xffff0000u;
+        const float hi = __uint_as_float(hb[e]);
+        lo[e] = fmaf(hi, 0x1p-40f, u == hi ? 0.f : u - hi);  // (infinite products: both terms)
+      }
+      hi8 = (u32x4){(hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3], (hb[4] >> 16) | hb[5], (hb[6] >> 16) | hb[7]};
+      lo8 = (u32x4){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
+    };
+    if constexpr (kOwn) {
+      terms(x[0], g[0], h_own, l_own);
+    } else {
+      for (int c = tid, y = 0; c < kChunks; c += (int)blockDim.x, ++y) {
+        u32x4 xc = x[0], gc = g[0];
+        if (y == 1) { xc = x[1]; gc = g[1]; }
+        if (y > 1) {                                         // a narrow workgroup's further chunks
+          const int k = k0 + 8 * c;
+          const unsigned int off = k < H ? (unsigned int)k * 2u : kPastEnd;
+          xc = __builtin_amdgcn_raw_buffer_load_b128(rs_z, off, 0, 0);
+          gc = __builtin_amdgcn_raw_buffer_load_b128(rs_g, off, 0, 0);
+        }
+        u32x4 hv, lv;
+        terms(xc, gc, hv, lv);
+        uh[c] = hv;
+        ul[c] = lv;
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const u32x4 hv = kOwn ? h_own : uh[64 * s + lane], lv = kOwn ? l_own : ul[64 * s + lane];
+      const unsigned int h4[4] = {hv.x, hv.y, hv.z, hv.w}, l4[4] = {lv.x, lv.y, lv.z, lv.w};
+      const unsigned int a4[4] = {w0[s].x, w0[s].y, w0[s].z, w0[s].w}, c4[4] = {w1[s].x, w1[s].y, w1[s].z, w1[s].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bf16x2 p0 = __builtin_bit_cast(bf16x2, a4[e]), p1 = __builtin_bit_cast(bf16x2, c4[e]);
+        const bf16x2 h = __builtin_bit_cast(bf16x2, h4[e]), l = __builtin_bit_cast(bf16x2, l4[e]);
+        s0 = __builtin_amdgcn_fdot2_f32_bf16(p0, l, s0, false);
+        s1 = __builtin_amdgcn_fdot2_f32_bf16(p1, l, s1, false);
+        s0 = __builtin_amdgcn_fdot2_f32_bf16(p0, h, s0, false);
+        s1 = __builtin_amdgcn_fdot2_f32_bf16(p1, h, s1, false);
       }
     }
   }
-  s0 = wave_sum_valu(s0); s1 = wave_sum_valu(s1); ssq = wave_sum_valu(ssq);
-  if (lane != 0) return;
+  ssq = wave_sum_valu(ssq);
+  s0 = wave_sum_valu(s0); s1 = wave_sum_valu(s1);
+  if constexpr (!kOwn) {
+    if (lane == 0) ssq_lds[w] = ssq;
+    __syncthreads();
+    ssq = 0.f;
+    for (int ww = 0; ww < nw; ++ww) ssq += ssq_lds[ww];
+  }
+  if (lane != 0 || (int)blockIdx.x * nw + w >= n_pairs) return;
   const float rstd = __builtin_amdgcn_rsqf(ssq / (float)H + a.eps);
-  const float y0 = fmaf(s0, rstd, b0), y1 = fmaf(s1, rstd, b1);
+  const float y0 = fmaf(s0, rstd, bf16_to_f32(b0)), y1 = fmaf(s1, rstd, bf16_to_f32(b1));
   float o0 = y0, o1 = y1;
   if (!is_v) {
     o0 = y0 * cs - y1 * sn;
@@ -421,13 +524,18 @@ hipError_t launch_draft_qkv_any(const DraftQkvArgs &a, hipStream_t st) {
   // One row: a wavefront per rotary pair.  Two rows as well up to 1,024 columns, where both rows' weights come
   // from the caches and the staged kernel's latency shows (256 columns 2.9 us; staged 6.0, plain ALU 4.6).
   if (a.M == 1 || (a.M == 2 && a.H <= 1024)) {
-    const dim3 grid((n_heads * (a.d / 2) + 3) / 4, a.M);
-    if (slices <= 1) hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<1>, grid, dim3(256), 0, st, a);
-    else if (slices <= 4) hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<4>, grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(draft_qkv_any_gemv_kernel<8>, grid, dim3(256), 0, st, a);
+    // as many wavefronts per workgroup as put one workgroup on every compute unit
+    const int pairs = n_heads * (a.d / 2), nw = std::min(std::max((pairs * a.M + 255) / 256, 4), kGemvMaxWaves);
+    const dim3 grid((pairs + nw - 1) / nw, a.M), block(nw * 64);
+    if (slices <= 1) hipLaunchKernelGGL(draft_qkv_gemv_kernel<1>, grid, block, 0, st, a);
+    else if (slices <= 4) hipLaunchKernelGGL(draft_qkv_gemv_kernel<4>, grid, block, 0, st, a);
+    else if (slices <= 7) hipLaunchKernelGGL(draft_qkv_gemv_kernel<7>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(draft_qkv_gemv_kernel<8>, grid, block, 0, st, a);
     return hipGetLastError();
   }
-  return launch_skinny<draft_qkv_any_kernel>(skinny_waves(a.H), dim3(n_heads * (a.d / 16), (a.M + 15) / 16), a, st);
+  const dim3 grid(n_heads * (a.d / 16), (a.M + 15) / 16);
+  return a.M <= 8 ? launch_skinny<draft_qkv_any_kernel<true>>(skinny_waves(a.H), grid, a, st)
+                  : launch_skinny<draft_qkv_any_kernel<false>>(skinny_waves(a.H), grid, a, st);
 }
 
 }  // namespace sparrow

@@ -103,3 +103,33 @@ def test_infinite_weights_give_infinities(sp, M):
     assert torch.isposinf(vc[:, 0, 5]).all()
     vc[:, 0, 5] = 0
     assert torch.isfinite(vc).all() and torch.isfinite(kc).all()
+
+
+# QKV of up to eight rows: two lanes a row; more rows the other way.
+FEW_WIDTHS = [8, 504, 512, 520, 1024, 1032, 2056, 2560, 2568, 4104, 5128]
+
+
+@pytest.mark.parametrize("H,Hq,Hkv,d", [(H, *((6, 3, 64) if i % 2 else (5, 1, 128))) for i, H in enumerate(FEW_WIDTHS)]
+                         + [(2048, 40, 8, 128)])
+@pytest.mark.parametrize("M", [1, 3, 7, 8, 9])
+def test_draft_qkv_of_few_rows(sp, H, Hq, Hkv, d, M):
+    test_draft_qkv_append(sp, H, Hq, Hkv, d, M)
+
+
+@pytest.mark.parametrize("H,Hq,Hkv,d", [(3584, 28, 4, 128), (4096, 6, 2, 64)])
+def test_draft_qkv_of_one_row_at_whole_slices(sp, H, Hq, Hkv, d):
+    test_draft_qkv_append(sp, H, Hq, Hkv, d, 1)
+
+
+@pytest.mark.parametrize("H", [512, 1024, 3584, 4104])
+def test_an_infinite_gamma_gives_infinities(sp, H, M=1):
+    """Both terms of an infinite product are infinite: of one sign, not infinity minus infinity."""
+    import torch
+    Hq, Hkv, d = 4, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(H)
+    z, w = _bf(g, M, H).abs() + 0.5, _bf(g, (Hq + 2 * Hkv) * d, H, std=0.05).abs() + 0.25
+    gam, one = torch.ones(H, dtype=torch.bfloat16, device="cuda"), torch.ones(M, d // 2, device="cuda")
+    gam[H - 3] = float("inf")
+    kc, vc = (torch.zeros(M, Hkv, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    sp.draft_qkv_append(z, gam, 1e-6, w, None, one, one, np.arange(M), Hq, kc, vc)
+    assert torch.isposinf(vc).all()

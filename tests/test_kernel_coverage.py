@@ -115,20 +115,21 @@ COVERAGE = {
     "hsr_fc_mfma_kernel<8, 2>": (H, "test_hsr_fc", "bf16-32-8-128-4096"),
     "hsr_fc_gemv_kernel<14>": (H, "test_hsr_fc", "bf16-28-4-128-3584, one row"),
     "hsr_fc_gemv_kernel<16>": (H, "test_hsr_fc", "bf16-32-8-128-4096, one row"),
-    "draft_qkv_gemv_kernel<7>": (H, "test_draft_qkv_append", "bf16-28-4-128-3584, one row"),
-    "draft_qkv_gemv_kernel<8>": (H, "test_draft_qkv_append", "bf16-32-8-128-4096, one row"),
     "draft_qkv_generic_kernel<float>": (H, "test_draft_qkv_append", "f32-4-1-64-256"),
     "draft_qkv_mfma_kernel<7, 1>": (H, "test_draft_qkv_append", "bf16-28-4-128-3584"),
     "draft_qkv_mfma_kernel<8, 1>": (H, "test_draft_qkv_append", "bf16-32-8-128-4096"),
     # hidden sizes other than 3,584 and 4,096; one row: <slices of a weight row in flight>
     "hsr_fc_any_kernel": (HW, "test_hsr_fc", "two rows and more"),
-    "draft_qkv_any_kernel": (HW, "test_draft_qkv_append", "two rows and more (three up to 1,024 columns)"),
+    # <at most eight rows>
+    "draft_qkv_any_kernel<true>": (HW, "test_draft_qkv_of_few_rows", "two to eight rows (from three up to 1,024 columns)"),
+    "draft_qkv_any_kernel<false>": (HW, "test_draft_qkv_append", "more"),
     "hsr_fc_any_gemv_kernel<4>": (HW, "test_hsr_fc", "hidden up to 1,024"),
     "hsr_fc_any_gemv_kernel<8>": (HW, "test_hsr_fc", "hidden 1,280"),
     "hsr_fc_any_gemv_kernel<16>": (HW, "test_hsr_fc", "hidden 2,560 and more"),
-    "draft_qkv_any_gemv_kernel<1>": (HW, "test_draft_qkv_append", "hidden up to 512"),
-    "draft_qkv_any_gemv_kernel<4>": (HW, "test_draft_qkv_append", "hidden 1,000, one and two rows"),
-    "draft_qkv_any_gemv_kernel<8>": (HW, "test_draft_qkv_append", "hidden 2,560 and more"),
+    "draft_qkv_gemv_kernel<1>": (HW, "test_draft_qkv_append", "one row: hidden up to 512"),
+    "draft_qkv_gemv_kernel<4>": (HW, "test_draft_qkv_append", "hidden 1,000, one and two rows"),
+    "draft_qkv_gemv_kernel<7>": (HW, "test_draft_qkv_of_one_row_at_whole_slices", "hidden 2,056 to 3,584"),
+    "draft_qkv_gemv_kernel<8>": (HW, "test_draft_qkv_append", "hidden 4,104 and more, in two chunks"),
     "kv_commit_kernel": (C, "test_kv_commit_bit_exact", ""),
     # ---- measurement aid (no part of the method, nothing to compare): run, input left alone
     "stream_read_kernel<2>": (G, "test_stream_read_shapes_run", ""),
