@@ -303,33 +303,6 @@ template <int kRow> __device__ __forceinline__ int gm_swz(int row) {
 // LDS tiles: three for a workgroup of 8 wavefronts (144 KiB at 128 x 256, two workgroups of 72 KiB at 128 x 64)
 constexpr int tiled_buffers(int waves) { return waves == 8 ? 3 : 1; }
 
-__device__ __forceinline__ unsigned int lds_offset(const unsigned char *p) {
-  return (unsigned int)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
-}
-// A buffer resource in scalar registers
-__device__ __forceinline__ u32x4 buffer_words(const void *p, unsigned int bytes) {
-  const uint64_t at = (uint64_t)p;
-  return (u32x4){(unsigned int)__builtin_amdgcn_readfirstlane((int)(unsigned int)at),
-                 (unsigned int)__builtin_amdgcn_readfirstlane((int)(unsigned int)(at >> 32)) & 0xffffu,
-                 (unsigned int)__builtin_amdgcn_readfirstlane((int)bytes), 0x00027000u};
-}
-// 16 bytes per lane from memory straight to LDS, lane l's at dst + 16 l (dst uniform); past the end of the buffer
-// zeros.  Written out because the compiler, which cannot tell the LDS tiles apart, would wait for every load in
-// flight before the next LDS read; it does not count these, and wait_loads() waits for them.  The wait states are
-// those between a scalar register written by the vector ALU, or M0, and its use here.
-template <bool kNt> __device__ __forceinline__ void load_to_lds(u32x4 rs, unsigned int off, unsigned int dst) {
-  if constexpr (kNt)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
-                 ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 ::"s"(dst), "v"(off), "s"(rs) : "memory", "m0");
-}
-// All but the last kLeft vector memory operations of the wavefront are done, and its LDS reads
-template <int kLeft> __device__ __forceinline__ void wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kLeft) : "memory");
-}
-
 template <class T, int VT, int BM, int kWaves, int WV, int kRow>      // kRow: bytes of a row that a step covers
 __global__ void __launch_bounds__(kWaves * 64, kWaves == 8 && BM <= 64 ? 4 : 2)
 lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {

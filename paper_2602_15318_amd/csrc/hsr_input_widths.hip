@@ -19,7 +19,7 @@
 // bf16 terms (the product has up to 16 bits), and the row's 1/rms (from the squares each wavefront
 // sees in its own slices) scales the result.
 // One activation row (QKV: also two of up to 1,024 columns) runs a wavefront per output feature or rotary
-// pair instead (QKV: at every width).
+// pair instead (QKV: at every width), two to four rows of FC a wavefront per two features.
 //
 // Measured (FC + QKV, one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64, six
 // rows 141 + 67 -> 9.3 + 10.2 us, one row 56 + 22 -> 7.3 + 6.8; hidden 5,120, 40/8 heads of 128, 16 rows
@@ -352,6 +352,84 @@ hsr_fc_any_gemv_kernel(HsrFcArgs a) {
   }
 }
 
+// FC, two to four activation rows: a wavefront owns two output features.  The activations of KS slices (of the
+// embeddings, then of the hidden states: a slice lies in one of them) go straight to LDS, once per workgroup, ahead of the
+// weights; a weight row's slices are all on their way at once, and every 16 bytes of activations read from LDS meet both
+// features.  The staged kernel brings each wavefront's slices in two or three rounds and leaves compute units without a
+// tile.  Staged / here, us: 2,048 columns, two rows 7.8 / 5.7; 640, two 4.3 / 3.1; 2,560, four 10.0 / 8.8; 5,120, two
+// 28.2 / 23.5, four 28.6 / 25.9; 1,536, four 6.8 / 5.7; 256, three 3.8 / 3.5.  From five rows on LDS reads and dot products
+// catch up with the weights: 2,560, eight rows 10.7 / 12.75, 4,096, seven 16.4 / 21.4; and at 3,584 and 4,096 columns the
+// kernels of whole slices are as fast at two rows and faster at four (12.3 / 14.5).
+constexpr int kFewWaves = 8;
+
+template <int MM, int KS>     // rows (the last ones may be empty), slices in flight
+__global__ void __launch_bounds__(kFewWaves * 64)
+hsr_fc_few_kernel(HsrFcArgs a) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];             // [MM][KS] slices
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
+  const int H = a.H, K = 2 * H, half_slices = (H + kSlice - 1) / kSlice, n_slices = 2 * half_slices;
+  const int f = 2 * min((int)blockIdx.x * nw + w, H / 2 - 1);                      // features f, f + 1
+  const __amdgpu_buffer_rsrc_t rs = weight_rows((const bf16_t *)a.w + (int64_t)f * K);
+  const __amdgpu_buffer_rsrc_t rs_b = weight_rows((const bf16_t *)a.bias);
+  const unsigned int bias =
+      __builtin_amdgcn_raw_buffer_load_b32(rs_b, a.bias != nullptr ? (unsigned int)f * 2u : kPastEnd, 0, 0);
+  const int toks = a.token_ids[min(lane, a.M - 1)];          // lane r: row r
+  float acc[2][MM];
+#pragma unroll
+  for (int r = 0; r < MM; ++r) acc[0][r] = acc[1][r] = 0.f;
+  for (int c0 = 0; c0 < n_slices; c0 += KS) {
+    if (c0 > 0) __syncthreads();                             // the last slices have been read
+    for (int x = w; x < MM * KS; x += nw) {
+      const int r = x / KS, s = c0 + x - r * KS;
+      const bool of_hidden = s >= half_slices;
+      const int at = (s - (of_hidden ? half_slices : 0)) * kSlice + 8 * lane;      // column of its half
+      const int m = min(r, a.M - 1);
+      const int tok = min(max(__builtin_amdgcn_readlane(toks, m), 0), a.vocab - 1);
+      const bf16_t *row = of_hidden ? (const bf16_t *)a.h_prev + (int64_t)m * H : (const bf16_t *)a.embed + (int64_t)tok * H;
+      const bool some = r < a.M && s < n_slices;
+      load_to_lds<false>(buffer_words(row, some ? (unsigned int)H * 2u : 0u), (unsigned int)at * 2u,
+                         lds_offset(smem) + (unsigned int)x * 1024u);
+    }
+    u32x4 w0[KS], w1[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const bool of_hidden = c0 + s >= half_slices;
+      const int at = (c0 + s - (of_hidden ? half_slices : 0)) * kSlice + 8 * lane;
+      const unsigned int off = at < H ? (unsigned int)((of_hidden ? H : 0) + at) * 2u : kPastEnd;
+      w0[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 2);
+      w1[s] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, K * 2, 2);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    wait_loads<2 * KS>();                                    // the activations are in LDS; the weights on their way
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const unsigned int a0[4] = {w0[s].x, w0[s].y, w0[s].z, w0[s].w}, a1[4] = {w1[s].x, w1[s].y, w1[s].z, w1[s].w};
+#pragma unroll
+      for (int r = 0; r < MM; ++r) {
+        const u32x4 xv = *reinterpret_cast<const u32x4 *>(smem + (r * KS + s) * 1024 + lane * 16);
+        const unsigned int x4[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bf16x2 x = __builtin_bit_cast(bf16x2, x4[e]);
+          acc[0][r] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a0[e]), x, acc[0][r], false);
+          acc[1][r] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a1[e]), x, acc[1][r], false);
+        }
+      }
+    }
+  }
+  float z0 = 0.f, z1 = 0.f;                                  // lane r: row r
+#pragma unroll
+  for (int r = 0; r < MM; ++r) {
+    const float y0 = wave_sum_valu(acc[0][r]), y1 = wave_sum_valu(acc[1][r]);
+    if (lane == r) { z0 = y0; z1 = y1; }
+  }
+  if (lane < a.M && (int)blockIdx.x * nw + w < H / 2)
+    *(unsigned int *)((bf16_t *)a.z + (int64_t)lane * H + f) = pack_bf16x2(z0 + bf16lo_to_f32(bias), z1 + bf16hi_to_f32(bias));
+}
+
 // QKV, one activation row per blockIdx.y: a wavefront owns one rotary pair.  The activations times gamma, as two bf16
 // terms that add up to the whole product (see skinny_gemm), are made once per workgroup and kept in LDS while the weights
 // are on their way: two dot-product instructions per two weights, no unpacking.  They were made by every wavefront, in
@@ -498,6 +576,17 @@ hipError_t launch_skinny(int nw, dim3 grid, const Args &a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int MM, int KS>
+hipError_t launch_few(const HsrFcArgs &a, hipStream_t st) {
+  static const hipError_t attr = hipFuncSetAttribute((const void *)hsr_fc_few_kernel<MM, KS>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, MM * KS * 1024);
+  if (attr != hipSuccess) return attr;
+  // as many wavefronts per workgroup as put one workgroup on every compute unit
+  const int pairs = a.H / 2, nw = std::min(std::max((pairs + 255) / 256, 4), kFewWaves);
+  hipLaunchKernelGGL((hsr_fc_few_kernel<MM, KS>), dim3((pairs + nw - 1) / nw), dim3(nw * 64), MM * KS * 1024, st, a);
+  return hipGetLastError();
+}
+
 // Wavefronts for rows of K elements: as few rounds of slices as eight wavefronts allow, dealt evenly.
 int skinny_waves(int K) {
   const int slices = (K + kSlice - 1) / kSlice;
@@ -515,6 +604,10 @@ hipError_t launch_hsr_fc_any(const HsrFcArgs &a, hipStream_t st) {
     else if (slices <= 8) hipLaunchKernelGGL(hsr_fc_any_gemv_kernel<8>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(hsr_fc_any_gemv_kernel<16>, grid, dim3(256), 0, st, a);
     return hipGetLastError();
+  }
+  if (a.M <= 4) {
+    if (slices <= 4) return a.M <= 2 ? launch_few<2, 4>(a, st) : launch_few<4, 4>(a, st);
+    return a.M <= 2 ? launch_few<2, 10>(a, st) : launch_few<4, 10>(a, st);
   }
   return launch_skinny<hsr_fc_any_kernel>(skinny_waves(K), dim3((a.H + 15) / 16, (a.M + 15) / 16), a, st);
 }

@@ -105,8 +105,16 @@ def test_infinite_weights_give_infinities(sp, M):
     assert torch.isfinite(vc).all() and torch.isfinite(kc).all()
 
 
-# QKV of up to eight rows: two lanes a row; more rows the other way.
+# Few rows: FC of two to four rows, two features a wavefront, activations in LDS ten slices at a time (four up to 1,024
+# columns); QKV of up to eight rows, two lanes a row; more rows the other way.  Widths around a slice, both halves of a
+# concatenation in one chunk and in several, workgroups of four to eight wavefronts and a last one with idle ones.
 FEW_WIDTHS = [8, 504, 512, 520, 1024, 1032, 2056, 2560, 2568, 4104, 5128]
+
+
+@pytest.mark.parametrize("H", FEW_WIDTHS)
+@pytest.mark.parametrize("M", [3, 4, 5])
+def test_hsr_fc_of_few_rows(sp, H, M):
+    test_hsr_fc(sp, H, M)
 
 
 @pytest.mark.parametrize("H,Hq,Hkv,d", [(H, *((6, 3, 64) if i % 2 else (5, 1, 128))) for i, H in enumerate(FEW_WIDTHS)]
