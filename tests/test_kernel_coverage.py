@@ -22,6 +22,7 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
 VF, TS = "test_gpu_verify_f32.py", "test_gpu_tree_sizes.py"
 V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
 VP, VL = "test_gpu_verify_plain_alu.py", "test_gpu_verify_long_trees.py"
+DW = "test_gpu_draft_windows.py"
 
 COVERAGE = {
     # ---- verification attention, matrix cores, bf16: <head_dim, steps in flight, row tiles, streams half a step apart>
@@ -63,10 +64,31 @@ COVERAGE = {
     "verify_partial_generic_kernel<unsigned short, 128>": (A, "test_kv_span_of_2_gib_takes_the_plain_alu_kernels", "K/V span of 2 GiB"),
     "verify_combine_kernel<unsigned short, 128>": (A, "test_kv_span_of_2_gib_takes_the_plain_alu_kernels", "K/V span of 2 GiB"),
     # ---- draft window attention: <storage type, head_dim>
-    "draft_window_attn_kernel<float, 64>": (A, "test_c1_fp32", "C1"),
-    "draft_window_attn_kernel<float, 128>": (A, "test_draft_windows_and_layouts", "f32-8-2-128"),
-    "draft_window_attn_kernel<unsigned short, 64>": (A, "test_draft_windows_and_layouts", "bf16-8-2-64"),
-    "draft_window_attn_kernel<unsigned short, 128>": (A, "test_c2_bf16_8k_chain5", "C2 to C5"),
+    # <storage type, head size, workgroups per head, tokens of a round>
+    "draft_window_attn_kernel<float, 64, 1, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 64, 1, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 64, 2, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 64, 2, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 64, 4, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 64, 4, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 128, 1, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 128, 1, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 128, 2, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 128, 2, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 128, 4, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<float, 128, 4, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 64, 1, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 64, 1, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 64, 2, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 64, 2, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 64, 4, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 64, 4, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 128, 1, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 128, 1, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 128, 2, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 128, 2, 8>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 128, 4, 2>": (DW, "test_shares_and_rounds", ""),
+    "draft_window_attn_kernel<unsigned short, 128, 4, 8>": (DW, "test_shares_and_rounds", ""),
     # ---- lm_head + argmax + acceptance
     "lm_head_generic_kernel<float>": (LM, "test_wider_than_the_matrix_core_kernels", "hidden above 2^20"),
     "lm_head_generic_kernel<unsigned short>": (LM, "test_wider_than_the_matrix_core_kernels", "hidden above 8,192"),
