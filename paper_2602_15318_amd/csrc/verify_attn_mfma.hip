@@ -762,6 +762,122 @@ verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
   }
 }
 
+// Batches of at most eight or four splits a sequence bring thousands of output tiles, and the number of wavefronts and of
+// their loads sets the pace, not the chain: 2 wavefronts or 1 (which has no merge), two d-tiles each.  The kernel above
+// with four wavefronts / this one, us a call with the partial pass: 12 trees of 30 nodes over 4,099 tokens, 32/8 heads 54.0 /
+// 49.2, 8 of 20 over 1,500, 64/8 31.8 / 27.3, 16 chains of 8 over 2,000, 28/4 22.2 / 20.7, 12 of 2 over 700, 16/8
+// 14.9 / 12.9, 4 trees of 60 over 8,000, 28/4 50.5 / 47; heads of 64 (fp32 partials) as fast.  One wavefront with one
+// d-tile or four: 20 trees 31.8 and 27.6, 12 chains 13.1 and 14.2.  Two d-tiles with 4 wavefronts, up to 16 splits: 0.97
+// to 1.01 of the speed.
+template <class T, int kD, int kCombWaves>
+__global__ void __launch_bounds__(64 * kCombWaves)
+verify_combine_few_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
+  constexpr int kTiles = 2;                      // d-tiles of a wavefront: the two of a 16-byte pair of fp16 partials
+  __shared__ f32x4 xo[kCombWaves][kTiles][64];
+  __shared__ float xm[kCombWaves][64], xl[kCombWaves][64];
+  const int b = blockIdx.z;
+  const int s0 = tab.cu_split[b], s1 = tab.cu_split[b + 1];
+  // all scalar arguments in one round of loads (see the partial pass)
+  asm volatile("" ::"s"(rbs), "s"(g), "s"(s0), "s"(s1), "s"(a.n_q), "s"(a.Hq), "s"(a.Hkv), "s"(a.part_o),
+               "s"(a.part_ml), "s"(a.out), "s"(a.lse));
+  const int unit_in_seq = blockIdx.x;            // (c * rbs + rb) * 4 + wq
+  const int wq = unit_in_seq & 3, crb = unit_in_seq >> 2;
+  int rb = 0, c = crb;
+  if (rbs > 1) { rb = crb % rbs; c = crb / rbs; }
+  const int mt = blockIdx.y * kTiles;            // first d-tile
+  const int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int n = lane & 15, c4 = lane >> 4;
+  const int R = a.n_q * g;
+  if (rb * kRowsPerWG + 16 * wq >= R) return;    // tile without rows (uniform)
+  constexpr bool kWide = kWideState<kD> || std::is_same<T, float>::value;    // fp32 partials
+  f32x4 o[kTiles];
+  float m_run = kNegBig, l_run = 0.f;
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t) o[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int sb = s0 + ws; sb < s1; sb += kCombWaves * kCombInFlight) {
+    float ms[kCombInFlight], ls[kCombInFlight], cs[kCombInFlight];
+    u32x4 pa[kCombInFlight][kWide ? kTiles : 1];
+#pragma unroll
+    for (int u = 0; u < kCombInFlight; ++u) {
+      const int s = min(sb + kCombWaves * u, s1 - 1);
+      const int64_t unit = ((int64_t)s * a.Hkv + c) * rbs + rb;
+      if constexpr (kWide) {
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t)
+          pa[u][t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.part_o) + ((unit * 4 + wq) * (kD / 16) + mt + t) * 64 + lane);
+      } else {
+        pa[u][0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.part_o) + ((unit * 4 + wq) * (kD / 32) + (mt >> 1)) * 64 + lane);
+      }
+      const float *pml = a.part_ml + (unit * kRowsPerWG + 16 * wq + n) * kMlFloats;
+      ms[u] = __builtin_nontemporal_load(&pml[0]);
+      ls[u] = __builtin_nontemporal_load(&pml[1]);
+      cs[u] = kWide ? 1.f : __builtin_nontemporal_load(&pml[2]);
+    }
+    float mx = m_run;
+#pragma unroll
+    for (int u = 0; u < kCombInFlight; ++u) if (sb + kCombWaves * u < s1) mx = fmaxf(mx, ms[u]);
+    const float alpha = fast_exp2(m_run - mx);
+    m_run = mx;
+    l_run *= alpha;
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) o[t] *= alpha;
+#pragma unroll
+    for (int u = 0; u < kCombInFlight; ++u) {
+      // weight of the split: its share of the softmax denominator (its output is normalised)
+      const bool in = sb + kCombWaves * u < s1;
+      const float wgt = in ? fast_exp2(ms[u] - mx) * ls[u] : 0.f;
+      l_run += wgt;
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t) {
+        f32x4 x;
+        if constexpr (kWide) {
+          if (!in) pa[u][t] = (u32x4){0u, 0u, 0u, 0u};         // (uniform; a duplicate of an infinite partial: no 0 * inf)
+          x = __builtin_bit_cast(f32x4, pa[u][t]);
+        } else {
+          x = t == 0 ? unpack_f16x4(pa[u][0].x, pa[u][0].y) : unpack_f16x4(pa[u][0].z, pa[u][0].w);
+        }
+        o[t] += x * (wgt * cs[u]);
+      }
+    }
+  }
+  float m = m_run, l = l_run;
+  if constexpr (kCombWaves > 1) {
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) xo[ws][t][lane] = o[t];
+    xm[ws][lane] = m_run; xl[ws][lane] = l_run;
+    __syncthreads();
+    if (ws != 0) return;
+    m = xm[0][lane];
+#pragma unroll
+    for (int k = 1; k < kCombWaves; ++k) m = fmaxf(m, xm[k][lane]);
+    l = 0.f;
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) o[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < kCombWaves; ++k) {
+      const float wgt = fast_exp2(xm[k][lane] - m);
+      l = fmaf(xl[k][lane], wgt, l);
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t) o[t] += xo[k][t][lane] * wgt;
+    }
+  }
+  const int rho = rb * kRowsPerWG + 16 * wq + n;
+  if (rho >= R) return;
+  const int i_row = rho / g, h = c * g + rho % g;
+  const int64_t orow = ((int64_t)b * a.n_q + i_row) * a.Hq + h;
+  const float inv = 1.0f / l;
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t) {
+    const f32x4 r = o[t];
+    T *out = (T *)a.out + orow * kD + 16 * (mt + t) + 4 * c4;
+    if constexpr (std::is_same<T, float>::value)
+      *reinterpret_cast<f32x4 *>(out) = r * inv;
+    else
+      *reinterpret_cast<u32x2 *>(out) = (u32x2){pack_bf16x2(r[0] * inv, r[1] * inv), pack_bf16x2(r[2] * inv, r[3] * inv)};
+  }
+  if (a.lse != nullptr && mt == 0 && c4 == 0) a.lse[orow] = lse_of<kWide>(m, l);
+}
+
 }  // namespace
 
 // Both head sizes of the boundary.  Measured at d = 64 (16/4 heads, 4 ragged sequences of 6,001 on
@@ -842,15 +958,19 @@ template <class T, int kD>
 static hipError_t launch_combine(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
   const int R = a.n_q * (a.Hq / a.Hkv);
   const int rbs = (R + kRowsPerWG - 1) / kRowsPerWG;
-  dim3 grid(a.Hkv * rbs * 4, kD / 16, a.B);
+  const dim3 grid(a.Hkv * rbs * 4, kD / 16, a.B), pairs(a.Hkv * rbs * 4, kD / 32, a.B);
   int max_ns = 0;
   for (int b = 0; b < a.B; ++b) max_ns = std::max(max_ns, tab.cu_split[b + 1] - tab.cu_split[b]);
   if (max_ns > 32)
     hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 16>), grid, dim3(64 * 16), 0, st, a, tab, rbs, a.Hq / a.Hkv);
   else if (max_ns > 16)
     hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 8>), grid, dim3(64 * 8), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  else
+  else if (max_ns > 8)
     hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 4>), grid, dim3(64 * 4), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+  else if (max_ns > 4)
+    hipLaunchKernelGGL((verify_combine_few_kernel<T, kD, 2>), pairs, dim3(64 * 2), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+  else
+    hipLaunchKernelGGL((verify_combine_few_kernel<T, kD, 1>), pairs, dim3(64), 0, st, a, tab, rbs, a.Hq / a.Hkv);
   return hipGetLastError();
 }
 

@@ -50,6 +50,19 @@ def test_long_tree_cases(launches):
     assert kinds >= {(HALF_STEP, False, False), (HALF_STEP, True, False), (HALF_STEP, True, True), (IN_STEP, True, False)}
 
 
+def test_combine_of_few_splits(launches):
+    """One wavefront up to four splits a sequence, two up to eight, four, eight and sixteen above;
+    test_gpu_verify_few_splits.py runs the first two at both head sizes."""
+    from test_gpu_verify_few_splits import CASES
+    for d in (64, 128):
+        got = launches([verify(*heads, lens, d=d) for heads, lens, _ in CASES])
+        for (heads, lens, most), run in zip(CASES, got):
+            assert max(run[0]["splits"]) == most, (heads, lens, run[0]["splits"])
+            assert run[1]["kernel"] == f"verify_combine_few_kernel<unsigned short, {d}, {1 if most <= 4 else 2}>", (heads, lens)
+    got = launches([verify(28, 4, 5, [n] * B) for B, n in ((1, 26112), (2, 26112), (4, 26112), (1, 1024))])
+    assert [run[1]["kernel"][-4:] for run in got] == [" 16>", ", 8>", ", 4>", ", 4>"]
+
+
 def test_lm_head_cases_straight_to_lds(launches):
     """test_gpu_lm_head_widths.py runs every instance that loads straight to LDS: each row block with one tile per
     workgroup and, where its tiles have 128 rows, with several; and these instances from 17 rows up above 4,096 columns."""

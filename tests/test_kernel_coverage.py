@@ -22,7 +22,7 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
 VF, TS = "test_gpu_verify_f32.py", "test_gpu_tree_sizes.py"
 V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
 VP, VL = "test_gpu_verify_plain_alu.py", "test_gpu_verify_long_trees.py"
-DW = "test_gpu_draft_windows.py"
+DW, VC = "test_gpu_draft_windows.py", "test_gpu_verify_few_splits.py"
 
 COVERAGE = {
     # ---- verification attention, matrix cores, bf16: <head_dim, steps in flight, row tiles, streams half a step apart>
@@ -55,6 +55,15 @@ COVERAGE = {
     "verify_combine_tiled_kernel<float, 128, 8>": (VF, "test_rows_and_contexts", ""),
     "verify_combine_tiled_kernel<float, 128, 4>": (VF, "test_rows_and_contexts", ""),
     # ---- verification attention, plain ALU: <storage type, head_dim>
+    # at most 8 and 4 splits per sequence
+    "verify_combine_few_kernel<unsigned short, 128, 2>": (VC, "test_few_splits", ""),
+    "verify_combine_few_kernel<unsigned short, 128, 1>": (VC, "test_few_splits", ""),
+    "verify_combine_few_kernel<unsigned short, 64, 2>": (VC, "test_few_splits", ""),
+    "verify_combine_few_kernel<unsigned short, 64, 1>": (VC, "test_few_splits", ""),
+    "verify_combine_few_kernel<float, 128, 2>": (VC, "test_few_splits", ""),
+    "verify_combine_few_kernel<float, 128, 1>": (VC, "test_few_splits", ""),
+    "verify_combine_few_kernel<float, 64, 2>": (VC, "test_few_splits", ""),
+    "verify_combine_few_kernel<float, 64, 1>": (VC, "test_few_splits", ""),
     "verify_partial_generic_kernel<float, 64>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
     "verify_combine_kernel<float, 64>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
     "verify_partial_generic_kernel<float, 128>": (VP, "test_trees_batches_and_splits", "K/V span of 2 GiB"),
