@@ -101,16 +101,27 @@ template <int kD> constexpr bool kWideState = kD == 64;
 // 135 (930 TFLOP/s) and 158 / 144.  Three row tiles and the fp32 state of heads of 64 do not leave the registers
 // for it (the latter 42 -> 67 us with spills); which calls take it: half_step_pays below.
 
+// kTilesOfRows = 0 (heads of 64, at most 32 rows per KV head): two of a stream's four wavefronts would have no row.  All
+// four have rows 0..31 between them twice, and of the two tiles of a step each pair takes one, so that scores and
+// exponentials, which set the pace with two wavefronts, take half as long; four states of a row meet at the end instead
+// of two.  One step in flight: two are slower here (124 registers against 99).  us a call with the combine pass, two
+// wavefronts / all: four ragged sequences of 6,001, 16/4 heads, chain of 8 12.9 / 12.3, eight of 3,000, 32/8, 8 19.6 /
+// 16.7, sixteen of 3,000, 16/4, one row 19.35 / 16.1, six of 9,000, 32/4, 4 20.0 / 16.8, one of 26,000, 14/2, 2 12.9 /
+// 12.2, of 24,004, 16/4, 8 13.5 / 13.0; with two steps in flight 12.9, 17.1, 16.9, 17.4, 12.9, 13.6.
 // kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
-template <int kD, int kPrefetch, int kQT, bool kPing>
+template <int kD, int kPrefetch, int kTilesOfRows, bool kPing>
 __global__ void __launch_bounds__(256 * kStreams)
 verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, int flat, int direct) {
+  constexpr bool kPairs = kTilesOfRows == 0;
+  constexpr int kQT = kPairs ? 1 : kTilesOfRows;
   constexpr int kSub = 128 / kD;                           // 32-token tiles per stream per step
   constexpr int kRowBytes = 2 * kD;                        // one K or V row of a head
   constexpr int kChunks = kD / 8;                          // 16-byte chunks of a row
   constexpr int kLdRows = 256 / kChunks;                   // token rows that one load of a stream covers
-  constexpr int kSlabs = 2 * kSub;                         // 16-token slabs of a step
+  constexpr int kSubW = kPairs ? 1 : kSub;                 // 32-token tiles of a wavefront per step
+  constexpr int kSlabs = 2 * kSubW;                        // 16-token slabs of a wavefront per step
+  static_assert(!kPairs || (kSub == 2 && kQT == 1 && !kPing), "two tiles a step, rows for two wavefronts");
   constexpr int kKS = kD / 32, kMT = kD / 16;              // MFMA k-steps of a score, 16-wide d-tiles
   constexpr bool kWide = kWideState<kD>;
   // [stream][buf][K,V][kSub tiles]; after the main loop the first 34 KB are reused for the merge
@@ -126,6 +137,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   const int strm = wave_id >> 2, w = wave_id & 3;
   const int tid = threadIdx.x & 255, lane = threadIdx.x & 63;
   const int n = lane & 15, c4 = lane >> 4;
+  const int wr = kPairs ? w & 1 : w, u0 = kPairs ? w >> 1 : 0;      // rows 16 wr .. of each 64; first tile of a step
   // Workgroup -> (sequence, KV head, split of the sequence, row block).  Workgroups are handed to
   // the 8 XCDs round-robin by their linear index and gridDim.x is a multiple of 8, so x & 7 is
   // the XCD; the row blocks of one split stream the same K/V and get x values that are equal
@@ -245,9 +257,9 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   int n_act = 0;                                  // row tiles of this wavefront that hold rows
 #pragma unroll
   for (int qt = 0; qt < kQT; ++qt) {
-    const int rho = (rb * kQT + qt) * kRowsPerWG + 16 * w + n;
+    const int rho = (rb * kQT + qt) * kRowsPerWG + 16 * wr + n;
     row_ok[qt] = rho < R;
-    if ((rb * kQT + qt) * kRowsPerWG + 16 * w < R) n_act = qt + 1;
+    if ((rb * kQT + qt) * kRowsPerWG + 16 * wr < R) n_act = qt + 1;
     i_row[qt] = row_ok[qt] ? rho / g : 0;
     h[qt] = row_ok[qt] ? c * g + rho % g : 0;
   }
@@ -323,14 +335,14 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   }
 
   f32x4 s[kQT][kSlabs];                           // scores of a step, S^T
-  bf16x8 pb[kQT][kSub];                           // its probabilities, P^T
-  bf16x8 pm[kWide ? kQT : 1][kSub], pl[kWide ? kQT : 1][kSub];   // kWide: what pb leaves of the probability
+  bf16x8 pb[kQT][kSubW];                          // its probabilities, P^T
+  bf16x8 pm[kWide ? kQT : 1][kSubW], pl[kWide ? kQT : 1][kSubW];   // kWide: what pb leaves of the probability
   bf16x8 ka[kSlabs][kKS];                         // K operands of a step
   auto read_k = [&](int buf, int j) __attribute__((always_inline)) {
     const unsigned char *Ks = lds_at(strm, buf, 0);
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks)
-      ka[j][ks] = lds_read_b128(Ks + j * 16 * kRowBytes + k_off + (((4 * ks + c4) ^ k_swz) << 4));
+      ka[j][ks] = lds_read_b128(Ks + (2 * u0 + j) * 16 * kRowBytes + k_off + (((4 * ks + c4) ^ k_swz) << 4));
   };
   auto scores = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
@@ -343,11 +355,11 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   };
   // One joint softmax update of a step (a single running-max / rescale for its 32*kSub tokens).
   auto softmax = [&](int st) __attribute__((always_inline)) {
-    const int tb = t0 + (st * kStreams + strm) * kSub * kTile;
+    const int tb = t0 + ((st * kStreams + strm) * kSub + u0) * kTile;
     // mask, online softmax (per lane = per query row).  Scores stay unscaled until the exponent:
     // exp2(s * scale_log2 - m) is one fused multiply-add per score (scale_log2 > 0, so the
     // maximum can be taken before scaling).
-    const bool edge = tb + kSub * kTile > min(t1, L);   // uniform: split end or draft rows in reach
+    const bool edge = tb + kSubW * kTile > min(t1, L);   // uniform: split end or draft rows in reach
 #pragma unroll
     for (int qt = 0; qt < kQT; ++qt) {
       float sc[4 * kSlabs];       // (as elements of s the maxima cost an instruction more per score)
@@ -386,7 +398,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         for (int mt = 0; mt < kMT; ++mt) o_acc[qt][mt] *= alpha;
       }
 #pragma unroll
-      for (int u = 0; u < kSub; ++u) {
+      for (int u = 0; u < kSubW; ++u) {
         float psum = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -412,8 +424,8 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   };
   auto read_v = [&](const unsigned char *Vs, int mt, int u) __attribute__((always_inline)) {   // V^T operand
     const unsigned char *at = Vs + v_off + (((2 * mt + v_chb) ^ v_swz) << 4);
-    const bf16x4 va = lds_read_tr(at + (2 * u) * 16 * kRowBytes);
-    const bf16x4 vb = lds_read_tr(at + (2 * u + 1) * 16 * kRowBytes);
+    const bf16x4 va = lds_read_tr(at + (2 * (u0 + u)) * 16 * kRowBytes);
+    const bf16x4 vb = lds_read_tr(at + (2 * (u0 + u) + 1) * 16 * kRowBytes);
     return (bf16x8)__builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7);
   };
   // row sums on the matrix cores: every row of ones . P^T is the sum over the 32 tokens
@@ -421,7 +433,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 #pragma unroll
     for (int qt = 0; qt < kQT; ++qt)
 #pragma unroll
-      for (int u = 0; u < kSub; ++u)
+      for (int u = 0; u < kSubW; ++u)
         l_acc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[qt][u], l_acc[qt], 0, 0, 0);
   };
   auto output = [&](int buf) __attribute__((always_inline)) {
@@ -431,7 +443,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     for (int mt = 0; mt < kMT; ++mt) {
       if (kQT > 1 && mt == 4) __builtin_amdgcn_sched_barrier(0);    // at most 4 d-tiles of V^T in flight
 #pragma unroll
-      for (int u = 0; u < kSub; ++u) {
+      for (int u = 0; u < kSubW; ++u) {
         const bf16x8 vt = read_v(Vs, mt, u);
 #pragma unroll
         for (int qt = 0; qt < kQT; ++qt) {
@@ -449,7 +461,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   // query): a second, one-tile instance of the step in the same kernel costs more registers than
   // the kernel has.
   // Steps of this stream that hold tokens (none for a wavefront without rows)
-  const int my_steps = n_act > 0 ? (n_tiles - strm * kSub + kStreams * kSub - 1) / (kStreams * kSub) : 0;
+  const int my_steps = n_act > 0 ? (n_tiles - strm * kSub - u0 + kStreams * kSub - 1) / (kStreams * kSub) : 0;
   if constexpr (kPing) {
     // Step st of a stream: vector phase (K operands of step st + 1 out of LDS, softmax of st), barrier,
     // matrix phase (scores of st + 1, output of st; V of st + 1 and K of st + 2 into LDS, their successors
@@ -579,6 +591,60 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   // ---- merge the two streams (stream 1 -> LDS -> stream 0) and write the split's partials in
   // register layout: [slot][kv head][row block][wavefront][pair of d-tiles][lane] x 8 halves, so
   // that every store instruction writes 1 KB of contiguous memory.
+  if constexpr (kPairs) {
+    // four wavefronts hold a row (two streams, two tiles of a step): the other three's states meet the first's
+    const int part = strm * 2 + u0;
+    f32x4 *po4 = reinterpret_cast<f32x4 *>(lds) + lane;                        // [part - 1][wr][mt][lane]
+    float *pm4 = reinterpret_cast<float *>(lds + 6 * kMT * 1024) + 2 * lane;   // [part - 1][wr][lane][m, l]
+    const float l_mine = quad_sum(l_acc[0][0]);
+    __syncthreads();
+    if (part > 0) {
+      const int at4 = (part - 1) * 2 + wr;
+#pragma unroll
+      for (int mt = 0; mt < kMT; ++mt) po4[(at4 * kMT + mt) * 64] = o_acc[0][mt];
+      pm4[at4 * 128] = m_run[0];
+      pm4[at4 * 128 + 1] = l_mine;
+    }
+    __syncthreads();
+    if (part > 0 || n_act == 0) return;
+    float m_new = m_run[0];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) m_new = fmaxf(m_new, pm4[(2 * x + wr) * 128]);
+    const float a0 = fast_exp2(m_run[0] - m_new);
+    float l_tot = l_mine * a0;
+#pragma unroll
+    for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] *= a0;
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      const float ax = fast_exp2(pm4[(2 * x + wr) * 128] - m_new);
+      l_tot += pm4[(2 * x + wr) * 128 + 1] * ax;
+#pragma unroll
+      for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] += po4[((2 * x + wr) * kMT + mt) * 64] * ax;
+    }
+    const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    if (direct) {
+      if (!row_ok[0]) return;
+      const int64_t orow = ((int64_t)b * a.n_q + i_row[0]) * a.Hq + h[0];
+      bf16_t *out = (bf16_t *)a.out + orow * kD + 4 * c4;
+#pragma unroll
+      for (int mt = 0; mt < kMT; ++mt) {
+        const f32x4 r = o_acc[0][mt] * inv_l;
+        *reinterpret_cast<u32x2 *>(out + 16 * mt) = (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
+      }
+      if (a.lse != nullptr && c4 == 0) a.lse[orow] = lse_of<kWide>(m_new, l_tot);
+      return;
+    }
+    const int64_t unit = ((int64_t)slot * a.Hkv + c) * rbs64 + rb;
+    f32x4 *po = reinterpret_cast<f32x4 *>(a.part_o) + (unit * 4 + wr) * (kMT * 64) + lane;
+#pragma unroll
+    for (int mt = 0; mt < kMT; ++mt) __builtin_nontemporal_store(o_acc[0][mt] * inv_l, &po[mt * 64]);
+    if (c4 == 0) {
+      float *pml = a.part_ml + (unit * kRowsPerWG + 16 * wr + n) * kMlFloats;
+      __builtin_nontemporal_store(m_new, &pml[0]);
+      __builtin_nontemporal_store(l_tot, &pml[1]);
+    }
+    return;
+  }
   f32x4 *mo = reinterpret_cast<f32x4 *>(lds);                                  // [w][mt][lane]
   float *mm = reinterpret_cast<float *>(lds + 4 * kMT * 64 * 16);              // [w][lane][m,l]
 #pragma unroll
@@ -942,6 +1008,8 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
     hipLaunchKernelGGL((verify_partial_mfma_kernel<128, 2, 2, true>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2)
     hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+  else if (kD == 64 && R <= 32 && !(direct && steps <= 2))       // (one piece of 200 tokens: 6.98 / 7.04 us)
+    hipLaunchKernelGGL((verify_partial_mfma_kernel<64, 1, 0, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (steps <= 3)       // (a second step in flight pays from 4 steps on: -0.15 us at the 7 steps of a 26k chain)
     hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else

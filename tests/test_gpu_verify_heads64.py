@@ -55,6 +55,15 @@ def test_batches_and_long_contexts(sp, oracle, lengths, n_q, nodes):
     _run(sp, oracle, 28, 4, lengths, n_q, nodes)
 
 
+@pytest.mark.parametrize("Hq,Hkv,n_q,nodes", [(2, 2, 1, 0), (15, 1, 1, 0), (8, 1, 2, 0), (17, 1, 1, 0), (12, 4, 0, 10), (16, 2, 4, 0),
+                                              (11, 1, 3, 0)])
+@pytest.mark.parametrize("lengths", [(31,), (128, 129), (160, 95, 1), (257,), (420, 33), (5000,), (3301, 2000, 64, 1290), (26080,)])
+def test_rows_of_two_wavefronts(sp, oracle, Hq, Hkv, n_q, nodes, lengths):
+    """1 to 32 rows per KV head, shared out by token: a wavefront takes one of the two tiles of a step.  33: the other way.
+    One piece and several, pieces that end in, at and behind either tile of either stream."""
+    _run(sp, oracle, Hq, Hkv, lengths, n_q, nodes, peaked=lengths[0] % 2 == 1)
+
+
 @pytest.mark.parametrize("Hq,Hkv,lengths,nodes", [(28, 4, (26112,), 60), (32, 8, tuple(4129 + 300 * (i % 3 - 1) for i in range(12)), 30)])
 def test_two_row_tiles_over_long_pieces(sp, oracle, Hq, Hkv, lengths, nodes):
     """More than ten steps per piece at blocks of 128 rows: two steps in flight, the number of steps odd (13 at 26k)

@@ -35,6 +35,7 @@ COVERAGE = {
     "verify_combine_tiled_kernel<unsigned short, 128, 16>": (A, "test_c5_bf16_26k_chain8_layer", "more than 32 splits per sequence"),
     "verify_combine_tiled_kernel<unsigned short, 128, 8>": (A, "test_paper_sized_trees_at_26k_context", "17 to 32 splits (30-, 48-node trees)"),
     "verify_combine_tiled_kernel<unsigned short, 128, 4>": (A, "test_c3_bf16_26k_tree60", "at most 16 splits (C3, C4, batches)"),
+    "verify_partial_mfma_kernel<64, 1, 0, false>": (V64, "test_rows_of_two_wavefronts", "up to 32 rows"),
     "verify_partial_mfma_kernel<64, 1, 1, false>": (V64, "test_rows_and_contexts", "up to 64 rows, short contexts"),
     "verify_partial_mfma_kernel<64, 2, 1, false>": (V64, "test_batches_and_long_contexts", "26k chain, ragged batch"),
     "verify_partial_mfma_kernel<64, 1, 2, false>": (V64, "test_rows_and_contexts", "70, 240 and 480 rows"),
