@@ -611,24 +611,27 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
 #pragma unroll
     for (int x = 0; x < 3; ++x) m_new = fmaxf(m_new, pm4[(2 * x + wr) * 128]);
     const float a0 = fast_exp2(m_run[0] - m_new);
-    float l_tot = l_mine * a0;
-#pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] *= a0;
+    float ax[3], l_tot = l_mine * a0;
 #pragma unroll
     for (int x = 0; x < 3; ++x) {
-      const float ax = fast_exp2(pm4[(2 * x + wr) * 128] - m_new);
-      l_tot += pm4[(2 * x + wr) * 128 + 1] * ax;
-#pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] += po4[((2 * x + wr) * kMT + mt) * 64] * ax;
+      ax[x] = fast_exp2(pm4[(2 * x + wr) * 128] - m_new);
+      l_tot += pm4[(2 * x + wr) * 128 + 1] * ax[x];
     }
+    // each state by its share of the sum, before they meet: values near the end of the range would leave it added up
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+#pragma unroll
+    for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] *= a0 * inv_l;
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+      for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] += po4[((2 * x + wr) * kMT + mt) * 64] * (ax[x] * inv_l);
     if (direct) {
       if (!row_ok[0]) return;
       const int64_t orow = ((int64_t)b * a.n_q + i_row[0]) * a.Hq + h[0];
       bf16_t *out = (bf16_t *)a.out + orow * kD + 4 * c4;
 #pragma unroll
       for (int mt = 0; mt < kMT; ++mt) {
-        const f32x4 r = o_acc[0][mt] * inv_l;
+        const f32x4 r = o_acc[0][mt];
         *reinterpret_cast<u32x2 *>(out + 16 * mt) = (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
       }
       if (a.lse != nullptr && c4 == 0) a.lse[orow] = lse_of<kWide>(m_new, l_tot);
@@ -637,7 +640,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     const int64_t unit = ((int64_t)slot * a.Hkv + c) * rbs64 + rb;
     f32x4 *po = reinterpret_cast<f32x4 *>(a.part_o) + (unit * 4 + wr) * (kMT * 64) + lane;
 #pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) __builtin_nontemporal_store(o_acc[0][mt] * inv_l, &po[mt * 64]);
+    for (int mt = 0; mt < kMT; ++mt) __builtin_nontemporal_store(o_acc[0][mt], &po[mt * 64]);
     if (c4 == 0) {
       float *pml = a.part_ml + (unit * kRowsPerWG + 16 * wr + n) * kMlFloats;
       __builtin_nontemporal_store(m_new, &pml[0]);

@@ -117,6 +117,22 @@ def test_an_infinite_value_in_the_last_row_stays_infinite(sp, L):
     assert torch.isfinite(out).all()
 
 
+@pytest.mark.parametrize("n_q,at", [(1, (0, 32)), (1, (0, 64)), (1, (32, 64)), (40, (0, 64)), (40, (32, 64))])
+def test_values_near_the_end_of_the_range(sp, n_q, at):
+    """One piece, two tokens that share the whole weight, in states of their own (up to 32 rows of a KV head four, one per
+    tile of a step; 40 rows two, one per stream): their mean is in range, the sum of their values is not."""
+    import torch
+    L, Hkv = 270, 32
+    q = torch.ones(n_q, Hkv, 64, device="cuda").bfloat16()
+    k = torch.full((L + n_q, Hkv, 64), -8.0, device="cuda").bfloat16()
+    v = torch.zeros_like(k)
+    k[list(at)] = 8.0
+    v[list(at)] = 3e38
+    out, lse = sp.verify_attn(q, k, v, np.array([0, L + n_q], dtype=np.int32), None, n_q)
+    assert torch.all(out == v[at[0], 0, 0])              # (scores 128 apart: the others weigh nothing)
+    assert float((lse - (64.0 + np.log(2.0))).abs().max()) <= 2e-5
+
+
 def test_scratch_without_room_for_padded_rows_takes_the_plain_alu_kernels(sp, oracle):
     """64 sequences of one row over 64 KV heads: the matrix-core partials (64-row units) are far larger
     than the plain-ALU ones.  The static scratch and a caller's small workspace still serve the call."""
