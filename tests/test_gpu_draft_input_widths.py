@@ -141,3 +141,20 @@ def test_an_infinite_gamma_gives_infinities(sp, H, M=1):
     kc, vc = (torch.zeros(M, Hkv, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
     sp.draft_qkv_append(z, gam, 1e-6, w, None, one, one, np.arange(M), Hq, kc, vc)
     assert torch.isposinf(vc).all()
+
+
+@pytest.mark.parametrize("H", [504, 1024, 3584, 4104])
+@pytest.mark.parametrize("M", [1, 2, 3, 8, 9, 17])
+@pytest.mark.parametrize("inf", [float("inf"), float("-inf")])
+def test_an_infinite_gamma_in_a_batch_gives_infinities(sp, H, M, inf):
+    """Of either sign, at one row, two lanes a row, sixteen rows to a block, and a second block.  Beside a product without
+    low bits and one with them."""
+    import torch
+    Hq, Hkv, d = 4, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(H)
+    z, w = _bf(g, M, H).abs() + 0.5, _bf(g, (Hq + 2 * Hkv) * d, H, std=0.05).abs() + 0.25
+    gam, one = torch.ones(H, dtype=torch.bfloat16, device="cuda"), torch.ones(M, d // 2, device="cuda")
+    gam[H - 4], gam[H - 3], gam[H - 2] = 1.0078125, inf, 1.0
+    kc, vc = (torch.zeros(M, Hkv, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    sp.draft_qkv_append(z, gam, 1e-6, w, None, one, one, np.arange(M), Hq, kc, vc)
+    assert torch.all(vc == inf)
