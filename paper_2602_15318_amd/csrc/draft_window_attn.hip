@@ -80,7 +80,8 @@ draft_window_attn_kernel(DraftArgs a, DraftTable tab) {
     for (int u = 0; u < kUnroll; ++u) {
       const int64_t off = (tok_base + pos[u]) * a.stride_tok;
       kw[u] = *(const u32x4 *)(K + off);
-      vw[u] = *(const vword_t *)(V + off);
+      vw[u] = vword_t{};                   // past the end no value: a duplicate of an infinite one would give 0 * inf
+      if (j0 + u * STEP < n) vw[u] = *(const vword_t *)(V + off);
     }
     if (j0 + STEP * kUnroll < n) positions(j0 + STEP * kUnroll);
     // one softmax update for the round

@@ -52,3 +52,24 @@ def test_shares_and_rounds(sp, dtype, d, B, Hq, Hkv, layout):
             err = (out[b].double() - ref).abs().max() / max(1.0, float(ref.abs().max()))
             assert float(err) <= ATOL[dtype], (window, b, float(err))
             assert float((lse[b].double() - torch.logsumexp(s, dim=1)).abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv", [(2, 6, 2), (3, 32, 4), (9, 24, 8)])
+def test_an_infinite_value_in_the_last_token_stays_infinite(sp, dtype, d, B, Hq, Hkv):
+    """The token that fills up a window's last round: with no weight there, and nothing of it in the other columns."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(d)
+    step = _step(dtype, d)
+    for window in (1, 5, step + 1, 2 * step + 1, 9 * step - 1):
+        n = window + 3
+        q, k, v = (torch.randn(m, h, d, generator=g, device="cuda").to(TORCH_DTYPE[dtype]) for m, h in ((B, Hq), (B * n, Hkv), (B * n, Hkv)))
+        last = n * torch.arange(1, B + 1, device="cuda") - 1
+        v[last, 1, 7] = float("inf")
+        at = np.arange(B + 1, dtype=np.int32) * n
+        out, _ = sp.draft_window_attn(q, k, v, at, torch.arange(n, dtype=torch.int32, device="cuda").repeat(B), at, window)
+        own = out[:, Hq // Hkv:2 * (Hq // Hkv), 7]
+        assert torch.isposinf(own).all(), window
+        own.zero_()
+        assert torch.isfinite(out).all(), window
