@@ -180,7 +180,7 @@ def _stream_ptr(stream) -> int:
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
-_native.setup(_check, _stream_ptr, np.ndarray)
+_native.setup(_check, _stream_ptr, np.ndarray, *(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _native.FUNCTIONS))
 
 
 def _parent_stride(parent: Optional[torch.Tensor], n_q: int, B: int) -> int:

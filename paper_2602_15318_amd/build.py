@@ -41,8 +41,7 @@ def build(verbose: bool = False, extra=()) -> str:
     _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
           "-isystem", os.path.join(torch, "include"), "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"),
           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "binding.cpp"), "-o", NATIVE,
-          "-L" + HERE, "-l:libsparrow.so", "-L" + os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
-          "-Wl,-rpath,$ORIGIN"], verbose)
+          "-L" + os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"], verbose)
     return LIB
 
 

@@ -14,11 +14,26 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cstring>
+
 #include "../../include/sparrow.h"
 
 namespace {
 
 PyObject *g_check, *g_stream_ptr, *g_ndarray;            // binding._check, binding._stream_ptr, numpy.ndarray
+
+// The library's functions, in the copy of the library that binding.py has loaded: linked by name, the loader could map
+// another one, and _check would read the wrong copy's error text.
+#define SPARROW_FUNCTIONS(f) \
+  f(verify_attn_workspace) f(verify_attn) f(draft_window_attn) f(accept_workspace) f(accept_trees) f(hsr_fc) f(draft_qkv_append)
+struct Library {
+#define SPARROW_MEMBER(n) decltype(&sparrow_##n) n;
+  SPARROW_FUNCTIONS(SPARROW_MEMBER)
+} lib;
+#define SPARROW_NAME(n) "sparrow_" #n,
+constexpr const char *kFunctions[] = {SPARROW_FUNCTIONS(SPARROW_NAME)};
+constexpr int kNumFunctions = sizeof(kFunctions) / sizeof(kFunctions[0]);
+static_assert(sizeof(Library) == kNumFunctions * sizeof(void *), "one address after the other");
 
 PyObject *new_ref(PyObject *o) {
   Py_INCREF(o);
@@ -197,7 +212,7 @@ PyObject *verify_attn(PyObject *const *a) {
   made(lse);
   at::Tensor ws;
   if (none(a[10])) {
-    const size_t bytes = sparrow_verify_attn_workspace(&d, (int32_t)B, n_q, (int64_t)cu.data()[B] - cu.data()[0]);
+    const size_t bytes = lib.verify_attn_workspace(&d, (int32_t)B, n_q, (int64_t)cu.data()[B] - cu.data()[0]);
     if (bytes > 0) ws = at::empty({(int64_t)bytes}, q.options().dtype(at::kByte));
   } else {
     ws = tensor(a[10]);
@@ -206,7 +221,7 @@ PyObject *verify_attn(PyObject *const *a) {
   void *const pq = ptr(q), *const pk = ptr(k), *const pv = ptr(v), *const po = ptr(tensor(out.get())), *const pl = opt_ptr(lse.get());
   void *const pw = ws.defined() ? ptr(ws) : nullptr;
   const size_t ws_bytes = ws.defined() ? (size_t)bytes_of(ws) : 0;
-  call([&] { return sparrow_verify_attn(&d, pq, pk, pv, cu.data(), parent, (int32_t)B, n_q, po, (float *)pl, pw, ws_bytes, st); });
+  call([&] { return lib.verify_attn(&d, pq, pk, pv, cu.data(), parent, (int32_t)B, n_q, po, (float *)pl, pw, ws_bytes, st); });
   return PyTuple_Pack(2, out.get(), lse.get());
 }
 
@@ -228,7 +243,7 @@ PyObject *draft_window_attn(PyObject *const *a) {
   void *const pq = ptr(q), *const pk = ptr(k), *const pv = ptr(v), *const pi = ptr(idx), *const po = ptr(tensor(out.get()));
   void *const pl = opt_ptr(lse.get());
   call([&] {
-    return sparrow_draft_window_attn(&d, pq, pk, pv, cu.data(), (const int32_t *)pi, ct.data(), (int32_t)B, window, po,
+    return lib.draft_window_attn(&d, pq, pk, pv, cu.data(), (const int32_t *)pi, ct.data(), (int32_t)B, window, po,
                                      (float *)pl, nullptr, 0, st);
   });
   return PyTuple_Pack(2, out.get(), lse.get());
@@ -248,7 +263,7 @@ PyObject *accept(PyObject *const *a) {
   void *const drafts = opt_ptr(a[2]);
   at::Tensor ws;
   if (none(a[6])) {
-    const size_t bytes = sparrow_accept_workspace(code, B, n_q, (int32_t)H, (int32_t)V);
+    const size_t bytes = lib.accept_workspace(code, B, n_q, (int32_t)H, (int32_t)V);
     if (bytes > 0) ws = at::empty({(int64_t)bytes}, hid.options().dtype(at::kByte));
   } else {
     ws = tensor(a[6]);
@@ -261,7 +276,7 @@ PyObject *accept(PyObject *const *a) {
   const size_t ws_bytes = ws.defined() ? (size_t)bytes_of(ws) : 0;
   int32_t *const pi = (int32_t *)ptr(ids), *const pl = (int32_t *)ptr(len), *const pp = (int32_t *)ptr(path), *const pb = (int32_t *)ptr(bonus);
   call([&] {
-    return sparrow_accept_trees(code, ph, pw, (const int32_t *)drafts, parent, (int32_t)parent_stride, B, n_q, (int32_t)H, (int32_t)V,
+    return lib.accept_trees(code, ph, pw, (const int32_t *)drafts, parent, (int32_t)parent_stride, B, n_q, (int32_t)H, (int32_t)V,
                                 pi, pl, pp, pb, ps, ws_bytes, st);
   });
   Object r(PyDict_New());
@@ -295,7 +310,7 @@ PyObject *hsr_fc(PyObject *const *a) {
   made(out);
   void *const st = stream_arg(a[6]);
   void *const pe = ptr(embed), *const pt = ptr(tok), *const ph = ptr(h), *const pw = ptr(w), *const po = ptr(tensor(out.get()));
-  call([&] { return sparrow_hsr_fc(code, pe, (const int32_t *)pt, ph, pw, bias, (int32_t)M, (int32_t)H, (int32_t)embed.size(0), po, st); });
+  call([&] { return lib.hsr_fc(code, pe, (const int32_t *)pt, ph, pw, bias, (int32_t)M, (int32_t)H, (int32_t)embed.size(0), po, st); });
   return out.release();
 }
 
@@ -331,7 +346,7 @@ PyObject *draft_qkv_append(PyObject *const *a) {
   void *const pz = ptr(z), *const pn = ptr(norm), *const pw = ptr(w), *const pc = ptr(cs), *const ps = ptr(sn), *const pk = ptr(k),
              *const pv = ptr(v), *const po = ptr(tensor(out.get()));
   call([&] {
-    return sparrow_draft_qkv_append(&desc, pz, pn, eps, pw, bias, (const float *)pc, (const float *)ps, rows.data(), (int32_t)M,
+    return lib.draft_qkv_append(&desc, pz, pn, eps, pw, bias, (const float *)pc, (const float *)ps, rows.data(), (int32_t)M,
                                     (int32_t)H, po, pk, pv, st);
   });
   return out.release();
@@ -343,7 +358,7 @@ PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
     PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
     return nullptr;
   }
-  if (at::impl::torch_function_mode_enabled()) return new_ref(Py_NotImplemented);
+  if (g_check == nullptr || at::impl::torch_function_mode_enabled()) return new_ref(Py_NotImplemented);
   try {
     return kCall(args);
   } catch (const NotHere &) {
@@ -355,12 +370,21 @@ PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
   }
 }
 
-// setup(check, stream_ptr, ndarray)
+// setup(check, stream_ptr, ndarray, addresses of FUNCTIONS...)
 PyObject *setup(PyObject *, PyObject *const *args, Py_ssize_t n) {
-  if (n != 3) {
+  if (n != 3 + kNumFunctions) {
     PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
     return nullptr;
   }
+  void *at[kNumFunctions];
+  for (int i = 0; i < kNumFunctions; ++i) {
+    at[i] = PyLong_AsVoidPtr(args[3 + i]);
+    if (at[i] == nullptr) {
+      if (!PyErr_Occurred()) PyErr_Format(PyExc_ValueError, "%s has no address", kFunctions[i]);
+      return nullptr;
+    }
+  }
+  std::memcpy(&lib, at, sizeof(lib));
   g_check = new_ref(args[0]);
   g_stream_ptr = new_ref(args[1]);
   g_ndarray = new_ref(args[2]);
@@ -379,4 +403,14 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__native(void) {
+  Object m(PyModule_Create(&module)), names(PyTuple_New(kNumFunctions));
+  if (m.get() == nullptr || names.get() == nullptr) return nullptr;
+  for (int i = 0; i < kNumFunctions; ++i) {
+    PyObject *s = PyUnicode_FromString(kFunctions[i]);
+    if (s == nullptr) return nullptr;
+    PyTuple_SET_ITEM(names.get(), i, s);
+  }
+  if (PyObject_SetAttrString(m.get(), "FUNCTIONS", names.get()) != 0) return nullptr;
+  return m.release();
+}

@@ -1,5 +1,9 @@
 """binding.py's native part against its general code: what it leaves to that code (CPU), and that both routes of a call
 give the same results, of the same types and shapes, or the same exception (GPU)."""
+import os
+import shutil
+import subprocess
+import sys
 import types
 
 import numpy as np
@@ -86,6 +90,36 @@ def test_what_is_left_to_the_general_code(name):
     assert n >= 4
     with torch.overrides.TorchFunctionMode():
         assert fn(*_native_args(name, args)) is NotImplemented
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _python(code, **env):
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env={**os.environ, **env}, stdout=subprocess.PIPE,
+                       stderr=subprocess.PIPE, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    return r.stdout.splitlines(), r.stderr
+
+
+def test_both_routes_call_the_library_beside_the_package(tmp_path):
+    """Also with another libsparrow.so on the loader's search path: one is mapped, and a refusal by the native part's route
+    reads that one's error text."""
+    shutil.copy(sp.library_path(), tmp_path / "libsparrow.so")
+    out, _ = _python("""
+import types
+import numpy as np, torch
+import paper_2602_15318_amd as sp
+z, one = torch.zeros(1, 4, 64), np.array([0, 1], np.int32)
+try:
+    sp.draft_window_attn(z, z, z, one, torch.zeros(1, dtype=torch.int32), one, -1, stream=types.SimpleNamespace(cuda_stream=0))
+except sp.SparrowError as e:
+    print(e)
+for path in sorted({l.split()[-1] for l in open("/proc/self/maps") if l.rstrip().endswith("libsparrow.so")}):
+    print(path)
+""", LD_LIBRARY_PATH=f"{tmp_path}:{os.environ.get('LD_LIBRARY_PATH', '')}")
+    assert out[1:] == [sp.library_path()]
+    assert "window = -1 must be positive" in out[0]
 
 
 def _flat(r):
