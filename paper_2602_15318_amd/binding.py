@@ -11,6 +11,10 @@ from __future__ import annotations
 
 import ctypes
 import os
+import re
+import sys
+import types
+import warnings
 from typing import Optional, Sequence
 
 import numpy as np
@@ -123,11 +127,27 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
-try:
-    from . import _native
-except ImportError as e:
-    raise ImportError("_native.so, the binding's native part, is missing or does not load: build it with "
-                      "`python -m paper_2602_15318_amd.build` (or __graft_entry__.build())") from e
+
+
+def _load_native():
+    """_native.so; where it is missing, does not load or was built for another torch or Python, functions that leave every
+    call to the code below (which is slower on the host and otherwise the same)."""
+    here = f"torch {re.match('[0-9.]*[0-9]', torch.__version__)[0]}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+    try:
+        from . import _native as native
+        built_for = getattr(native, "BUILT_FOR", "another state of the source")
+        if built_for == here:
+            return native
+        reason = f"was built for {built_for} and this is {here}"
+    except ImportError as e:
+        reason = f"does not load ({e})"
+    warnings.warn(f"_native.so, the binding's native part, {reason}: calls take longer on the host.  Build it with "
+                  "`python -m paper_2602_15318_amd.build` (or __graft_entry__.build())", RuntimeWarning, stacklevel=2)
+    calls = ("verify_attn", "draft_window_attn", "accept", "hsr_fc", "draft_qkv_append")
+    return types.SimpleNamespace(FUNCTIONS=(), setup=lambda *a: None, **{n: lambda *a: NotImplemented for n in calls})
+
+
+_native = _load_native()
 
 
 def library_path() -> str:

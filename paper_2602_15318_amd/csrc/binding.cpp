@@ -13,6 +13,7 @@
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cstring>
 
@@ -30,8 +31,13 @@ struct Library {
 #define SPARROW_MEMBER(n) decltype(&sparrow_##n) n;
   SPARROW_FUNCTIONS(SPARROW_MEMBER)
 } lib;
+#define SPARROW_STRING_OF(x) #x
+#define SPARROW_STRING(x) SPARROW_STRING_OF(x)
 #define SPARROW_NAME(n) "sparrow_" #n,
 constexpr const char *kFunctions[] = {SPARROW_FUNCTIONS(SPARROW_NAME)};
+// Code compiled against the headers of one torch and one Python reads another's objects wrongly, without an error:
+// binding.py takes this part only where it runs under the same ones.
+constexpr char kBuiltFor[] = "torch " TORCH_VERSION ", Python " SPARROW_STRING(PY_MAJOR_VERSION) "." SPARROW_STRING(PY_MINOR_VERSION);
 constexpr int kNumFunctions = sizeof(kFunctions) / sizeof(kFunctions[0]);
 static_assert(sizeof(Library) == kNumFunctions * sizeof(void *), "one address after the other");
 
@@ -411,6 +417,8 @@ PyMODINIT_FUNC PyInit__native(void) {
     if (s == nullptr) return nullptr;
     PyTuple_SET_ITEM(names.get(), i, s);
   }
-  if (PyObject_SetAttrString(m.get(), "FUNCTIONS", names.get()) != 0) return nullptr;
+  if (PyObject_SetAttrString(m.get(), "FUNCTIONS", names.get()) != 0 ||
+      PyModule_AddStringConstant(m.get(), "BUILT_FOR", kBuiltFor) != 0)
+    return nullptr;
   return m.release();
 }

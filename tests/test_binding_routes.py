@@ -122,6 +122,24 @@ for path in sorted({l.split()[-1] for l in open("/proc/self/maps") if l.rstrip()
     assert "window = -1 must be positive" in out[0]
 
 
+@pytest.mark.parametrize("prepare", ["import torch; torch.__version__ = torch.torch_version.TorchVersion('1.2.3')",
+                                     "import sys; sys.modules['paper_2602_15318_amd._native'] = None"])
+def test_a_native_part_that_does_not_fit_is_not_used(prepare):
+    """Built for another torch, or not there: the general code takes every call, and the import says so."""
+    out, err = _python(prepare + """
+import types
+import numpy as np, torch
+import paper_2602_15318_amd as sp
+z, one = torch.zeros(1, 4, 64), np.array([0, 1], np.int32)
+try:
+    sp.draft_window_attn(z, z, z, one, torch.zeros(1, dtype=torch.int32), one, -1, stream=types.SimpleNamespace(cuda_stream=0))
+except sp.SparrowError as e:
+    print(e)
+""")
+    assert "window = -1 must be positive" in out[0]
+    assert "RuntimeWarning" in err and "python -m paper_2602_15318_amd.build" in err
+
+
 def _flat(r):
     if isinstance(r, dict):
         return [x for k in sorted(r) for x in (k, r[k])]
