@@ -441,7 +441,7 @@ hsr_fc_few_kernel(HsrFcArgs a) {
 // arithmetic came to 1.7 us a compute unit behind the last weights.  Before / now, us: 3,584 columns, 28/4 heads of 128
 // 9.9 / 8.4; 5,120, 40/8 of 128 21.4 / 17.1; 4,096, 32/8 of 128 12.0 / 11.0; 1,024, 16/4 of 64 4.3 / 4.0; two rows of
 // 640, 8/2 of 64 4.15 / 3.8.
-constexpr int kGemvMaxWaves = 16;
+constexpr int kGemvMinWaves = 4, kGemvMaxWaves = 16;
 
 template <int KS>             // slices in flight: at least H / 512, or 8
 __global__ void __launch_bounds__(kGemvMaxWaves * 64)
@@ -465,6 +465,7 @@ draft_qkv_gemv_kernel(DraftQkvArgs a) {
   const __amdgpu_buffer_rsrc_t rs_g = weight_rows((const bf16_t *)a.gamma);
   // the activations of this thread: 8 columns, twice where KS * 64 threads are more than the workgroup has
   constexpr int kChunks = KS * 64;
+  static_assert(kChunks <= 2 * 64 * kGemvMinWaves, "two chunks of activations per thread");
   float s0 = 0.f, s1 = 0.f, ssq = 0.f;
   // operands of the end, first of all: in order, they would wait for the weights
   const bool is_v = hd >= a.Hq + a.Hkv;
@@ -512,17 +513,12 @@ draft_qkv_gemv_kernel(DraftQkvArgs a) {
     if constexpr (kOwn) {
       terms(x[0], g[0], h_own, l_own);
     } else {
-      for (int c = tid, y = 0; c < kChunks; c += (int)blockDim.x, ++y) {
-        u32x4 xc = x[0], gc = g[0];
-        if (y == 1) { xc = x[1]; gc = g[1]; }
-        if (y > 1) {                                         // a narrow workgroup's further chunks
-          const int k = k0 + 8 * c;
-          const unsigned int off = k < H ? (unsigned int)k * 2u : kPastEnd;
-          xc = __builtin_amdgcn_raw_buffer_load_b128(rs_z, off, 0, 0);
-          gc = __builtin_amdgcn_raw_buffer_load_b128(rs_g, off, 0, 0);
-        }
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const int c = tid + y * (int)blockDim.x;
+        if (c >= kChunks) break;
         u32x4 hv, lv;
-        terms(xc, gc, hv, lv);
+        terms(x[y], g[y], hv, lv);
         uh[c] = hv;
         ul[c] = lv;
       }
@@ -624,7 +620,7 @@ hipError_t launch_draft_qkv_any(const DraftQkvArgs &a, hipStream_t st) {
   // from the caches and the staged kernel's latency shows (256 columns 2.9 us; staged 6.0, plain ALU 4.6).
   if (a.M == 1 || (a.M == 2 && a.H <= 1024)) {
     // as many wavefronts per workgroup as put one workgroup on every compute unit
-    const int pairs = n_heads * (a.d / 2), nw = std::min(std::max((pairs * a.M + 255) / 256, 4), kGemvMaxWaves);
+    const int pairs = n_heads * (a.d / 2), nw = std::min(std::max((pairs * a.M + 255) / 256, kGemvMinWaves), kGemvMaxWaves);
     const dim3 grid((pairs + nw - 1) / nw, a.M), block(nw * 64);
     if (slices <= 1) hipLaunchKernelGGL(draft_qkv_gemv_kernel<1>, grid, block, 0, st, a);
     else if (slices <= 4) hipLaunchKernelGGL(draft_qkv_gemv_kernel<4>, grid, block, 0, st, a);
