@@ -107,7 +107,8 @@ template <int kD> constexpr bool kWideState = kD == 64;
 // of two.  One step in flight: two are slower here (124 registers against 99).  us a call with the combine pass, two
 // wavefronts / all: four ragged sequences of 6,001, 16/4 heads, chain of 8 12.9 / 12.3, eight of 3,000, 32/8, 8 19.6 /
 // 16.7, sixteen of 3,000, 16/4, one row 19.35 / 16.1, six of 9,000, 32/4, 4 20.0 / 16.8, one of 26,000, 14/2, 2 12.9 /
-// 12.2, of 24,004, 16/4, 8 13.5 / 13.0; with two steps in flight 12.9, 17.1, 16.9, 17.4, 12.9, 13.6.
+// 12.2, of 24,004, 16/4, 8 13.5 / 13.0; with two steps in flight 12.9, 17.1, 16.9, 17.4, 12.9, 13.6.  In one piece of up to two
+// steps, without a combine pass: one of 60, 4/2, 4 4.1 / 3.9, four of 200, 16/4, 4 6.0 / 5.2, sixteen of 250, 8/8, 16 7.5 / 6.8.
 // kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
 template <int kD, int kPrefetch, int kTilesOfRows, bool kPing>
@@ -1011,7 +1012,7 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
     hipLaunchKernelGGL((verify_partial_mfma_kernel<128, 2, 2, true>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (qt == 2)
     hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
-  else if (kD == 64 && R <= 32 && !(direct && steps <= 2))       // (one piece of 200 tokens: 6.98 / 7.04 us)
+  else if (kD == 64 && R <= 32)
     hipLaunchKernelGGL((verify_partial_mfma_kernel<64, 1, 0, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
   else if (steps <= 3)       // (a second step in flight pays from 4 steps on: -0.15 us at the 7 steps of a 26k chain)
     hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);

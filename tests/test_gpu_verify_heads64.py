@@ -118,11 +118,12 @@ def test_an_infinite_value_in_the_last_row_stays_infinite(sp, L):
 
 
 @pytest.mark.parametrize("n_q,at", [(1, (0, 32)), (1, (0, 64)), (1, (32, 64)), (40, (0, 64)), (40, (32, 64))])
-def test_values_near_the_end_of_the_range(sp, n_q, at):
+@pytest.mark.parametrize("L", [80, 270])
+def test_values_near_the_end_of_the_range(sp, n_q, at, L):
     """One piece, two tokens that share the whole weight, in states of their own (up to 32 rows of a KV head four, one per
     tile of a step; 40 rows two, one per stream): their mean is in range, the sum of their values is not."""
     import torch
-    L, Hkv = 270, 32
+    Hkv = 32
     q = torch.ones(n_q, Hkv, 64, device="cuda").bfloat16()
     k = torch.full((L + n_q, Hkv, 64), -8.0, device="cuda").bfloat16()
     v = torch.zeros_like(k)
