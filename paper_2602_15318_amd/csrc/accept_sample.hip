@@ -376,8 +376,8 @@ accept_sample_kernel(SampleArgs a) {
 // kStage = 0: that workgroup does everything.  Where a pass takes it longer than two more launches, three kernels: 1,
 // the walk up to the first residual sum; residual_sums_kernel, that pass by the whole chip; 2, the rest from there
 // (further rejections at the same node, and nodes further down, again by one workgroup).  One kernel that fetched level
-// by level / as here, us of kernels: 4 chains of 8 over 64,003 27.7 / 13.2, 6 of 3 over 152,064 38.4 / 14.4, 6 trees of 25
-// over 16,724 19.3 / 12.3; at 6,828 in one kernel (5 trees of 62) 29.0 / 17.0.
+// by level / as here, us of kernels: 4 chains of 8 over 64,003 27.7 / 13.2, 6 of 3 over 152,064 38.4 / 14.4; in one
+// kernel, 5 trees of 62 over 6,828 29.0 / 17.0.
 constexpr int kMaxRejections = SPARROW_MAX_NQ;
 constexpr int kAhead = 4;
 
@@ -658,9 +658,11 @@ hipError_t launch_logit_stats(const SampleArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Up to here one workgroup walks a sequence alone: a pass over 16,384 tokens is one round of loads for its 16 wavefronts,
-// and two launches more are 5 us.
-constexpr int kOneWorkgroupVocab = 16384;
+// Up to here one workgroup walks a sequence alone: two rounds of loads for its 16 wavefronts, against two launches more.
+// One kernel / three, us a call with its lm_head (256 columns): four chains of 8 over 16,000 18.8 / 20.9, 18,000 20.9 / 22.8,
+// 24,000 22.6 / 23.1, 32,000 23.4 / 23.4, 48,000 28.7 / 26.8, 64,003 32.5 / 29.2; six trees of 25 over 24,000 39.7 / 41.0,
+// 32,000 40.9 / 41.8; one chain of 5 over 24,000 18.9 / 19.0, 32,000 20.6 / 20.6, 64,003 28.4 / 25.2.
+constexpr int kOneWorkgroupVocab = 32768;
 
 hipError_t launch_accept_sample(const SampleArgs &a, hipStream_t st) {
   if (a.draft_q == nullptr) {

@@ -110,17 +110,18 @@ def test_accept_sample_q_matches_oracle(sp, oracle, dtype, H, V, B, n_q, tree, T
     assert len(walked) >= 2, f"all graded walks had the same length {walked}: the cases are too easy"
 
 
-# Above 16,384 tokens the first residual's sums are the whole chip's work, the walk in front of it and the rest of the
+# Above 32,768 tokens the first residual's sums are the whole chip's work, the walk in front of it and the rest of the
 # walk (siblings, nodes below an accepted sibling, the draw) kernels of their own; up to there one workgroup does it all.
-@pytest.mark.parametrize("V", [16384, 16385, 20480, 40003])
+@pytest.mark.parametrize("V", [16384, 16385, 20480, 32768, 32769, 40003])
 @pytest.mark.parametrize("tree,B,n_q", [("chain", 3, 5), ("tree", 2, 13), ("per-seq", 3, 12)])
 def test_vocabularies(sp, oracle, V, tree, B, n_q):
     test_accept_sample_q_matches_oracle(sp, oracle, "bf16", 64, V, B, n_q, tree, 1.0, False)
 
 
-def test_residuals_of_siblings_over_a_large_vocabulary(sp, oracle):
+@pytest.mark.parametrize("V", [20011, 36867])
+def test_residuals_of_siblings_over_a_large_vocabulary(sp, oracle, V):
     """Siblings that are rejected one after the other, and accepted after others were: counted on the CPU."""
-    dtype, H, V, B, n_q, T = "bf16", 64, 20011, 4, 24, 1.0
+    dtype, H, B, n_q, T = "bf16", 64, 4, 24, 1.0
     parent = np.array([-1] * 6 + [0, 0, 1, 1, 2, 2, 3, 3, 4, 4, 5, 5, 6, 6, 8, 8, 10, 12], dtype=np.int32)
     cfg = wl.Config("asq", dtype, 4, 1, 64, B, (((wl.TEXT, 8),),) * B, 8, n_q, True, H, V)
     graded, late, nested = 0, 0, 0

@@ -127,7 +127,7 @@ COVERAGE = {
     "logit_stats_kernel<4>": (AS, "test_vocabularies", "longer chunks"),
     "accept_sample_kernel": (AS, "test_accept_sample_matches_oracle", "deterministic children"),
     # <0: all, 1: up to the first residual's sums, 2: from there>
-    "accept_sample_q_kernel<0>": (ASQ, "test_accept_sample_q_matches_oracle", "sampled draft, up to 16,384 tokens"),
+    "accept_sample_q_kernel<0>": (ASQ, "test_accept_sample_q_matches_oracle", "sampled draft, up to 32,768 tokens"),
     "accept_sample_q_kernel<1>": (ASQ, "test_vocabularies", "above"),
     "residual_sums_kernel": (ASQ, "test_vocabularies", "above"),
     "accept_sample_q_kernel<2>": (ASQ, "test_residuals_of_siblings_over_a_large_vocabulary", "above"),
