@@ -1,8 +1,8 @@
 // Input side of the draft model for any hidden size (a multiple of 8), bf16: the hidden-state-reuse
 // projection (Eq. 1) and the draft layer's RMSNorm / QKV / rotary step with the K/V append.  gfx950.
 // Hidden sizes of 7 and 8 whole slices of 512 have kernels of their own (hsr_input.hip), in which the
-// number of slices is a compile-time constant and no column needs a check: 6 rows at 3,584 take
-// 11.2 + 12.1 us there, 12.3 + 22.6 here.
+// number of slices is a compile-time constant and no column needs a check: QKV of 2 to 8 rows takes 12.3 to 12.9 us at
+// 3,584 there and 17.2 to 18.6 here, at 4,096 14.7 to 15.3 and 18.9 to 20.5; FC of 6 rows at 3,584 11.1 and 12.3.
 //
 // Both steps are skinny GEMMs (at most 64 activation rows), bound by the weight stream:
 //   - one workgroup per tile of 16 weight rows (grid.y = blocks of 16 activation rows);
@@ -21,9 +21,9 @@
 // One activation row (QKV: also two of up to 1,024 columns) runs a wavefront per output feature or rotary
 // pair instead (QKV: at every width), two to four rows of FC a wavefront per two features.
 //
-// Measured (FC + QKV, one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64, six
-// rows 141 + 67 -> 9.3 + 10.2 us, one row 56 + 22 -> 7.3 + 6.8; hidden 5,120, 40/8 heads of 128, 16 rows
-// 823 + 447 -> 31.6 + 32.5 us; hidden 1,024, 16/4 heads of 64, six rows 36 + 21 -> 4.8 + 6.5.
+// Measured (FC + QKV, weights from memory; one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64,
+// six rows 141 + 67 -> 10.3 + 9.5 us, one row 56 + 22 -> 8.1 + 6.2; hidden 5,120, 40/8 heads of 128, 16 rows 823 + 447 ->
+// 38.1 + 34.7 us; hidden 1,024, 16/4 heads of 64, six rows 36 + 21 -> 5.3 + 6.3.
 #include <algorithm>
 
 #include "common.hpp"
@@ -58,11 +58,11 @@ __device__ __forceinline__ float low_term(float u, float hi) { return __builtin_
 // kFew (norm folded in, at most 8 rows): lanes n and n ^ 8 share row n & 7 and hold one half of a slice's columns each, so
 // that a whole slice takes 64 registers and half the arithmetic.  A matrix instruction's 16 columns then meet weights of
 // one half: columns below 8 are right where they are the first half's, the others where they are the second half's; two
-// sums, added at the end.  The registers left allow a slice's activations to be asked for before its weights and
-// multiplied while those are on their way (behind them, two halves one after the other, the arithmetic and a second round
-// trip came after the last weights).  Before / now, us: 2,560 columns, 40/8 heads of 64, six rows 10.8 / 9.3; 5,120,
-// 40/8 of 128, two rows 31.9 / 23.8, eight 32.4 / 26.2; 1,536, 24/4 of 64, five 7.55 / 7.05; 256, 4/1 of 64, three
-// 6.1 / 5.3.
+// sums, added at the end.  The registers left allow a slice's activations to be asked for before its weights (behind them,
+// in two halves one after the other, came a second round trip).  Their arithmetic, half of what it was, still runs after
+// the wait for the weights: nothing keeps the compiler from moving it there, to its first use.  Before / now, us: 2,560
+// columns, 40/8 heads of 64, six rows 10.8 / 9.4; 5,120, 40/8 of 128, two rows 31.9 / 24.5, eight 32.4 / 26.7; 1,536, 24/4
+// of 64, five 7.55 / 6.95; 256, 4/1 of 64, three 6.1 / 5.2.
 // ---------------------------------------------------------------------------------------------
 template <bool kNorm, bool kFew, class WRow, class XLoad, class Epi>
 __device__ __forceinline__ void skinny_gemm(const bf16_t *W, int K, WRow wrow, XLoad xload, const bf16_t *gamma,
@@ -357,13 +357,16 @@ hsr_fc_any_gemv_kernel(HsrFcArgs a) {
 }
 
 // FC, two to four activation rows: a wavefront owns two output features.  The activations of KS slices (of the
-// embeddings, then of the hidden states: a slice lies in one of them) go straight to LDS, once per workgroup, ahead of the
-// weights; a weight row's slices are all on their way at once, and every 16 bytes of activations read from LDS meet both
-// features.  The staged kernel brings each wavefront's slices in two or three rounds and leaves compute units without a
-// tile.  Staged / here, us: 2,048 columns, two rows 7.8 / 5.7; 640, two 4.3 / 3.1; 2,560, four 10.0 / 8.8; 5,120, two
-// 28.2 / 23.5, four 28.6 / 25.9; 1,536, four 6.8 / 5.7; 256, three 3.8 / 3.5.  From five rows on LDS reads and dot products
-// catch up with the weights: 2,560, eight rows 10.7 / 12.75, 4,096, seven 16.4 / 21.4; and at 3,584 and 4,096 columns the
-// kernels of whole slices are as fast at two rows and faster at four (12.3 / 14.5).
+// embeddings, then of the hidden states: a slice lies in one of them) go to LDS without passing through registers, once
+// per workgroup, ahead of the weights; a weight row's slices are all on their way at once, and every 16 bytes of
+// activations read from LDS meet both features.  The activations do not flow: the token ids are read by a load that the
+// compiler waits for in every trip of the loop, and its wait takes in the trip's load before, which it does not count.  A
+// wavefront thus makes MM * KS / nw round trips one after the other, 8 at four rows of 2,560, before its weights.  The
+// staged kernel brings each wavefront's slices in two or three rounds and leaves compute units without a tile.  Staged /
+// here, us: 2,048 columns, two rows 7.8 / 5.7; 640, two 4.3 / 3.1; 2,560, four 10.0 / 8.8; 5,120, two 28.2 / 23.5, four
+// 28.6 / 25.9; 1,536, four 6.8 / 5.7; 256, three 3.8 / 3.5.  Above four rows, and at 3,584 and 4,096 columns (where the
+// kernels of whole slices are as fast at two rows and faster at four, 12.3 / 14.5), this form is the slower one: 2,560, eight
+// rows 10.7 / 12.75, 4,096, seven 16.4 / 21.4.
 constexpr int kFewWaves = 8;
 
 template <int MM, int KS>     // rows (the last ones may be empty), slices in flight
