@@ -79,7 +79,7 @@ float scale_log2_of(const sparrow_attn_desc *d) {
 
 // Tokens per context split.  Aim at about one workgroup per compute unit: the split partials are
 // pure overhead traffic, so no more splits than it takes to occupy the chip.
-int plan_chunk(const sparrow_attn_desc *d, int32_t n_q, int64_t total_tokens, bool mfma) {
+int plan_chunk(const sparrow_attn_desc *d, int32_t n_q, int64_t total_tokens, bool mfma, int *slots_out = nullptr) {
   const int R = n_q * (d->n_q_heads / d->n_kv_heads);
   const int rbs = mfma ? verify_mfma_row_blocks(d->dtype, R) : (R + 15) / 16;
   int slots;
@@ -93,6 +93,7 @@ int plan_chunk(const sparrow_attn_desc *d, int32_t n_q, int64_t total_tokens, bo
     slots = kNumCU / (d->n_kv_heads * rbs);
   }
   if (slots < 1) slots = 1;
+  if (slots_out) *slots_out = slots;
   int64_t chunk = (total_tokens + slots - 1) / slots;
   chunk = (int64_t)round_up((size_t)chunk, 32);
   if (chunk < 64) chunk = 64;
@@ -115,6 +116,7 @@ int direct_rows(const sparrow_attn_desc *d, int32_t B, int32_t n_q) {
 // call's total token count so that the workspace query and the call always agree.
 bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
   return verify_partial_mfma_supported(d->dtype, d->head_dim) &&
+         d->n_q_heads / d->n_kv_heads < 32768 &&               // (row numbers are divided by their reciprocal there)
          d->kv_stride_token < (1ll << 24) &&
          total_tokens * d->kv_stride_token * (d->dtype == SPARROW_BF16 ? 2 : 4) < (1ll << 31);
 }
@@ -123,23 +125,41 @@ bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
 // workgroup per compute unit that plan_chunk aims at; each sequence is then cut into equal pieces,
 // so that every workgroup of the call streams about the same number of bytes.  Returns the longest
 // piece in tokens.
+// bf16: pieces are whole steps of 64 tokens where that matters, up to 8 steps (a step of two 32-token tiles, half of it empty,
+// takes as long, and fewer pieces leave less to combine; longer pieces lose compute units by it, eight of 26,120 tokens
+// 75.5 -> 78.8 us).  Pieces of 32 / 64, us a call: chain of 5 over 4,096 tokens 9.45 / 9.1, over 6,000 10.2 / 9.55, of 8 over
+// 26,112 16.6 / 16.3, 16 nodes over 5,000 14.1 / 13.2, four ragged sequences of 6,001, 16/4 heads of 64, chain of 8 11.4 /
+// 11.0.  Sequences of one length are cut alike, so that the kernels need no table: two chains of 4 over 6,000 with 31 and 32
+// pieces / 32 each 12.6 / 11.3, eight of 5 over 1,000 11.3 / 10.4.  Neither takes more scratch than the query says.
 int plan_splits(const sparrow_attn_desc *d, const int32_t *cu_seqlens, int32_t B, int32_t n_q, int64_t total,
                 bool mfma, SeqTable *tab) {
-  const int chunk0 = plan_chunk(d, n_q, total, mfma);
+  int slots;
+  int chunk0 = plan_chunk(d, n_q, total, mfma, &slots);
+  const bool steps64 = mfma && d->dtype == SPARROW_BF16;
+  if (steps64 && chunk0 <= 512) chunk0 = (chunk0 + 63) / 64 * 64;
   const int slot_budget = (int)((total + chunk0 - 1) / chunk0);
   memset(tab, 0, sizeof(*tab));
   for (int b = 0; b <= B; ++b) tab->cu_len[b] = cu_seqlens[b];
   int chunk = 0;
   int ns[SPARROW_MAX_BATCH];
   int used = 0;
+  bool equal = steps64 && slots >= B;
+  for (int b = 1; b < B; ++b) equal &= cu_seqlens[b + 1] - cu_seqlens[b] == cu_seqlens[1] - cu_seqlens[0];
   for (int b = 0; b < B; ++b) {
     const int len = cu_seqlens[b + 1] - cu_seqlens[b];
+    if (equal) {
+      int piece = split_len(len, slots / B);
+      if (piece <= 512) piece = (piece + 63) / 64 * 64;
+      ns[b] = (len + piece - 1) / piece;
+      used += ns[b];
+      continue;
+    }
     ns[b] = (int)((int64_t)len * slot_budget / (total > 0 ? total : 1));
     if (ns[b] < 1) ns[b] = 1;
     used += ns[b];
   }
   // hand the slots lost to rounding down to the sequences with the longest pieces
-  while (used < slot_budget) {
+  while (!equal && used < slot_budget) {
     int worst = 0;
     double worst_len = -1.0;
     for (int b = 0; b < B; ++b) {
@@ -155,6 +175,7 @@ int plan_splits(const sparrow_attn_desc *d, const int32_t *cu_seqlens, int32_t B
     const int piece = split_len(len, ns[b]);
     if (piece > chunk) chunk = piece;
   }
+  for (int b = B + 1; b <= SPARROW_MAX_BATCH; ++b) tab->cu_split[b] = INT32_MAX;     // see seq_of_slot
   return chunk;
 }
 
@@ -562,6 +583,7 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
   a.q = q; a.k = k; a.v = v; a.parent = parent;
   a.parent_stride = parent ? desc->parent_stride : 0;
   a.B = B; a.n_q = n_q; a.Hq = desc->n_q_heads; a.Hkv = desc->n_kv_heads; a.d = desc->head_dim;
+  a.g = a.Hq / a.Hkv; a.inv_g = 1.0f / (float)a.g;
   a.chunk = chunk; a.n_slots = tab.cu_split[B];
   a.scale_log2 = scale_log2_of(desc);
   a.stride_tok = desc->kv_stride_token; a.stride_head = desc->kv_stride_head;

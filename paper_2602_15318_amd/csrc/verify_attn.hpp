@@ -21,6 +21,8 @@ struct VerifyArgs {
   const int32_t *parent;  // device, or nullptr for a chain
   int32_t parent_stride;  // 0: one tree [n_q] for all sequences; else sequence b's tree at parent + b*stride
   int32_t B, n_q, Hq, Hkv, d;
+  int32_t g;              // Hq / Hkv
+  float inv_g;            // 1 / g
   int32_t chunk;          // longest split of the call, in tokens (the kernels derive each
                           // sequence's own split length from SeqTable)
   int32_t n_slots;        // cu_split[B]
@@ -44,10 +46,16 @@ __host__ __device__ __forceinline__ int split_len(int len, int ns) {
   return ((len + ns - 1) / ns + 31) / 32 * 32;
 }
 
-// Which sequence owns split slot `slot` (linear scan; B <= SPARROW_MAX_BATCH).
-__device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int B, int slot) {
+// Which sequence owns split slot `slot`: as many as end at or before it.  Sixteen ends come with one load and are counted on
+// the scalar unit (one after the other they were a round trip each ahead of a workgroup's first load); those past the
+// call's sequences are out of any slot's reach.
+__device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int slot) {
   int b = 0;
-  while (b + 1 < B && tab.cu_split[b + 1] <= slot) ++b;
+  do {
+    const int b0 = b;
+#pragma unroll
+    for (int k = 1; k <= 16; ++k) b += (unsigned int)(tab.cu_split[b0 + k] - slot - 1) >> 31;      // ends <= slot
+  } while ((b & 15) == 0 && b > 0 && b < SPARROW_MAX_BATCH && tab.cu_split[b + 1] <= slot);
   return b;
 }
 

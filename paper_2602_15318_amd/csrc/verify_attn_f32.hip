@@ -68,7 +68,7 @@ verify_partial_f32_kernel(VerifyArgs a, SeqTable tab, int rbs) {
   const int rb = ((int)blockIdx.x >> 3) % rbs, slot = ((int)blockIdx.x >> 3) / rbs * 8 + ((int)blockIdx.x & 7);
   if (slot >= a.n_slots) return;                           // padding of the last round of 8 (uniform)
   const int c = blockIdx.y;
-  const int b = seq_of_slot(tab, a.B, slot);
+  const int b = seq_of_slot(tab, slot);
   const int cl0 = tab.cu_len[b], len = tab.cu_len[b + 1] - cl0;
   const int piece = split_len(len, tab.cu_split[b + 1] - tab.cu_split[b]);
   const int L = len - a.n_q;

@@ -33,7 +33,7 @@ verify_partial_generic_kernel(VerifyArgs a, SeqTable tab) {
   const int slot = blockIdx.x, c = blockIdx.y, rb = blockIdx.z;
   const int g = a.Hq / a.Hkv;
   const int R = a.n_q * g;
-  const int b = seq_of_slot(tab, a.B, slot);
+  const int b = seq_of_slot(tab, slot);
   const int len = tab.cu_len[b + 1] - tab.cu_len[b];   // L_b + n_q
   const int L = len - a.n_q;
   const int piece = split_len(len, tab.cu_split[b + 1] - tab.cu_split[b]);

@@ -82,6 +82,13 @@ struct PieceTable {
   int32_t piece[SPARROW_MAX_BATCH];
 };
 
+// rho / g for rows of one KV head (or group / slots of a flat grid), by the reciprocal: half a step off, which is far more
+// than what two roundings of the product are off while quotient x g stays below 2^21 (g below 32,768 at 64 rows).
+__device__ __forceinline__ int row_div(int rho, float inv_g) { return (int)(((float)rho + 0.5f) * inv_g); }
+
+// What `shape` of the partial pass holds beside the row blocks (from bit 3 up)
+constexpr int kShapeFlat = 1, kShapeDirect = 2, kShapeTable = 4, kShapeBits = 3;
+
 // Heads of 64 keep the intermediate state of an attention row in 32 bits (as the plain-ALU kernel
 // does): probabilities enter the output MFMA as three bf16 terms that add up to their 24 bits, row
 // sums are added up on the vector ALU, split partials are stored in fp32.  Heads of 128 round
@@ -113,7 +120,9 @@ template <int kD> constexpr bool kWideState = kD == 64;
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
 template <int kD, int kPrefetch, int kTilesOfRows, bool kPing>
 __global__ void __launch_bounds__(256 * kStreams)
-verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, int flat, int direct) {
+verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t stride_head, int stride_tok, int cl0_one,
+                           int len_one, int ns_one, int piece_one, int n_slots, int shape, VerifyArgs a, SeqTable tab,
+                           PieceTable pt) {
   constexpr bool kPairs = kTilesOfRows == 0;
   constexpr int kQT = kPairs ? 1 : kTilesOfRows;
   constexpr int kSub = 128 / kD;                           // 32-token tiles per stream per step
@@ -125,6 +134,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   static_assert(!kPairs || (kSub == 2 && kQT == 1 && !kPing), "two tiles a step, rows for two wavefronts");
   constexpr int kKS = kD / 32, kMT = kD / 16;              // MFMA k-steps of a score, 16-wide d-tiles
   constexpr bool kWide = kWideState<kD>;
+  constexpr bool kShare = !kPing;                          // both streams merge and store
   // [stream][buf][K,V][kSub tiles]; after the main loop the first 34 KB are reused for the merge
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int kStepBytes = kSub * kTile * kRowBytes;     // K (or V) rows of one stream step
@@ -139,62 +149,70 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   const int tid = threadIdx.x & 255, lane = threadIdx.x & 63;
   const int n = lane & 15, c4 = lane >> 4;
   const int wr = kPairs ? w & 1 : w, u0 = kPairs ? w >> 1 : 0;      // rows 16 wr .. of each 64; first tile of a step
+  const int part = kPairs ? strm * 2 + u0 : strm;         // of the wavefronts that hold a row
   // Workgroup -> (sequence, KV head, split of the sequence, row block).  Workgroups are handed to
   // the 8 XCDs round-robin by their linear index and gridDim.x is a multiple of 8, so x & 7 is
   // the XCD; the row blocks of one split stream the same K/V and get x values that are equal
   // modulo 8 and adjacent in that XCD's order: they run at the same time on one XCD and all but
   // the first fetch of a tile hit its L2.  (Only the speed depends on the round-robin placement.)
   // Two grid shapes:
-  //  - (x, KV head, sequence): everything the first K/V load needs comes from ONE round of scalar
-  //    loads of the arguments (the sequence's table entries are addressed by blockIdx.z) and no
-  //    division -- at decode-time sizes the whole kernel lasts ~13 us and every dependent round
-  //    trip before the first load shows.  x is sized for the sequence with the most splits; the
-  //    XCD of a split is rotated by its global number, so that the splits of all heads and
-  //    sequences together are dealt evenly to the XCDs.
+  //  - (x, KV head, sequence): x is sized for the sequence with the most splits; the XCD of a split is rotated by
+  //    its global number, so that the splits of all heads and sequences together are dealt evenly to the XCDs.
   //  - flat (x only; for ragged batches, where the first shape would launch mostly padding):
   //    x enumerates (global split, KV head) and the sequence is searched in the split table.
+  // At decode-time sizes the whole kernel lasts 6 to 13 us and every dependent round trip before the first load
+  // shows.  The arguments that it needs are leading scalars, which reach the registers with the launch: one sequence, or
+  // several of one length, read nothing before it.  Sequences that differ read their table entries, a line of the arguments
+  // or two, 0.4 us; the flat grid the table and then the entries.  (One round of loads of all arguments before: chain of 5
+  // over 8,192 tokens 11.5 us a call, now 11.3, both with the combine pass of that time.)
   const int xj = blockIdx.x >> 3, xcd = blockIdx.x & 7;
-  const int bz = blockIdx.z;               // (0 on the flat grid: no need to wait for `flat` to know it)
-  const int cl0_z = tab.cu_len[bz], cl1_z = tab.cu_len[bz + 1];
-  const int cs0_z = tab.cu_split[bz], cs1_z = tab.cu_split[bz + 1];
-  const int piece_z = pt.piece[bz];
-  // an empty statement that takes these values as scalar-register inputs: the compiler has to
-  // have all of them loaded here, which makes it issue their loads together, ahead of the
-  // branches below, instead of one round per use
-  asm volatile("" ::"s"(rbs), "s"(flat), "s"(cl0_z), "s"(cl1_z), "s"(cs0_z), "s"(cs1_z), "s"(piece_z),
-               "s"(a.k), "s"(a.v), "s"(a.stride_tok), "s"(a.stride_head), "s"(a.n_q), "s"(a.n_slots),
-               "s"(a.Hkv));
+  const int rbs = shape >> kShapeBits;
+  const bool flat = (shape & kShapeFlat) != 0, direct = (shape & kShapeDirect) != 0;
   int rb = 0, sq = xj;
   if (rbs > 1) { rb = xj % rbs; sq = xj / rbs; }
-  int b = bz, c, s_loc;
-  int cl0 = cl0_z, len = cl1_z - cl0_z, cs0 = cs0_z, ns = cs1_z - cs0_z, piece = piece_z;
+  int b = 0, c, s_loc, cl0 = cl0_one, len = len_one, cs0 = 0, ns = ns_one, piece = piece_one;
   if (flat) {
     const int grp = sq * 8 + xcd;                          // global split + n_slots * KV head
-    if (grp >= a.n_slots * a.Hkv) return;                  // padding of the last round of 8
-    const int gslot = grp % a.n_slots;
-    c = grp / a.n_slots;
-    b = seq_of_slot(tab, a.B, gslot);
+    if (grp >= len_one) return;                            // padding of the last round of 8
+    c = __builtin_amdgcn_readfirstlane(row_div(grp, __builtin_amdgcn_rcpf((float)n_slots)));
+    const int gslot = grp - c * n_slots;
+    // (an empty statement that takes these as scalar-register inputs: their lines come with the ends that the search reads,
+    // and the entries of the sequence found are then at hand)
+    asm volatile("" ::"s"(tab.cu_len[0]), "s"(tab.cu_len[16]), "s"(pt.piece[0]), "s"(pt.piece[15]), "s"(tab.cu_split[0]),
+                 "s"(tab.cu_split[1]), "s"(tab.cu_split[16]));
+    b = seq_of_slot(tab, gslot);
     cl0 = tab.cu_len[b]; len = tab.cu_len[b + 1] - cl0;
     cs0 = tab.cu_split[b]; ns = tab.cu_split[b + 1] - cs0;
     piece = pt.piece[b];
     s_loc = gslot - cs0;
   } else {
     c = blockIdx.y;
-    s_loc = sq * 8 + ((xcd - (cs0 + a.n_slots * c)) & 7);  // split within the sequence
+    b = blockIdx.z;
+    if (!(shape & kShapeTable)) {                          // sequences of one length (or one sequence): no table is read
+      cl0 += b * len;
+      cs0 = b * ns;
+    } else {
+      cl0 = tab.cu_len[b]; len = tab.cu_len[b + 1] - cl0;
+      cs0 = tab.cu_split[b]; ns = tab.cu_split[b + 1] - cs0;
+      piece = pt.piece[b];
+      // an empty statement that takes these values as scalar-register inputs: the compiler has to have all of them
+      // loaded here, which makes it issue their loads together, instead of one round per use
+      asm volatile("" ::"s"(cl0), "s"(len), "s"(cs0), "s"(ns), "s"(piece));
+    }
+    s_loc = sq * 8 + ((xcd - (cs0 + n_slots * c)) & 7);    // split within the sequence
     if (s_loc >= ns) return;                               // padding of the grid (uniform)
   }
   const int slot = cs0 + s_loc;
-  const int L = len - a.n_q;
   const int t0 = min(len, s_loc * piece);
   const int t1 = min(len, t0 + piece);
   const int n_tiles = (t1 - t0 + kTile - 1) / kTile;                    // of the workgroup
   const int n_steps = (n_tiles + kStreams * kSub - 1) / (kStreams * kSub);   // loop trips
   // K/V of this sequence and head; a token row is addressed by a 32-bit byte offset from here
   // (the host checks that a sequence's K/V spans less than 2 GB)
-  const int64_t seq_off = (int64_t)cl0 * a.stride_tok + (int64_t)c * a.stride_head;
-  const unsigned char *Kg = (const unsigned char *)((const bf16_t *)a.k + seq_off);
-  const unsigned char *Vg = (const unsigned char *)((const bf16_t *)a.v + seq_off);
-  const unsigned int row_bytes = (unsigned int)a.stride_tok * 2u;
+  const int64_t seq_off = (int64_t)cl0 * stride_tok + (int64_t)c * stride_head;
+  const unsigned char *Kg = (const unsigned char *)((const bf16_t *)k_base + seq_off);
+  const unsigned char *Vg = (const unsigned char *)((const bf16_t *)v_base + seq_off);
+  const unsigned int row_bytes = (unsigned int)stride_tok * 2u;
 
   // ---- loader: in step `st` stream `strm` owns tiles (st*kStreams + strm)*kSub .. +kSub, i.e.
   // 32*kSub consecutive tokens; thread -> rows tid/kChunks + kLdRows j, 16-byte chunk tid%kChunks.  Rows past
@@ -249,56 +267,55 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   if (kPing) issue(Kg, 1, k_next);
   __builtin_amdgcn_sched_barrier(0);      // the first step is on its way before anything else is worked out
 
-  const int g = a.Hq / a.Hkv;
+  const int L = len - a.n_q;
+  const int g = a.g;
   const int R = a.n_q * g;
-  const int rbs64 = (R + kRowsPerWG - 1) / kRowsPerWG;     // 64-row units of the partial layout
   // ---- this lane's query rows: one per row tile
   bool row_ok[kQT];
-  int i_row[kQT], h[kQT];
+  int i_row[kQT], h[kQT];                         // h: within the KV head's group
   int n_act = 0;                                  // row tiles of this wavefront that hold rows
 #pragma unroll
   for (int qt = 0; qt < kQT; ++qt) {
     const int rho = (rb * kQT + qt) * kRowsPerWG + 16 * wr + n;
     row_ok[qt] = rho < R;
     if ((rb * kQT + qt) * kRowsPerWG + 16 * wr < R) n_act = qt + 1;
-    i_row[qt] = row_ok[qt] ? rho / g : 0;
-    h[qt] = row_ok[qt] ? c * g + rho % g : 0;
+    // rows past R take the data of row 0 (in bounds); what comes of them is not used
+    i_row[qt] = row_ok[qt] ? row_div(rho, a.inv_g) : 0;
+    h[qt] = row_ok[qt] ? rho - i_row[qt] * g : 0;
   }
+  const int64_t q_row0 = (int64_t)b * a.n_q * a.Hq + (int64_t)c * g;     // of the call: row (b, 0), first head of the group
 
+  u32x4 qv[kQT][kKS];
+#pragma unroll
+  for (int qt = 0; qt < kQT; ++qt) {
+    const unsigned int at = (unsigned int)(i_row[qt] * a.Hq + h[qt]) * (2u * kD) + 16u * (unsigned int)c4;
+    const unsigned char *qp = (const unsigned char *)a.q + q_row0 * (2 * kD) + at;
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) qv[qt][ks] = *(const u32x4 *)(qp + 64 * ks);
+  }
+  // The memory pipeline of a compute unit serves requests in issue order and a wavefront
+  // issues all its loads back to back: without this barrier the look-ahead of the wavefronts
+  // that issue first would queue ahead of the FIRST step of the others (measured: 3 us of
+  // skew between the two streams).
+  if (kPrefetch > 1) __syncthreads();
+#pragma unroll
+  for (int p = 1; p < kPrefetch; ++p) {
+    issue(Vg, p, vst[p]);
+    issue(Kg, kPing ? p + 1 : p, kst[p]);
+  }
+  // Loads retire in order: Q (and the first step before it) have landed once at most the
+  // loads issued after Q are outstanding (other counters untouched).
+  constexpr int kAfterQ = (kPrefetch - 1) * 2 * kLd;
+  static_assert(kAfterQ < 64, "vmcnt is a 6-bit counter");
   bf16x8 qreg[kQT][kKS];
-  {
-    u32x4 qv[kQT][kKS];
-#pragma unroll
-    for (int qt = 0; qt < kQT; ++qt) {
-      // rows past R read row 0 (in bounds) and are zeroed below
-      const int64_t qrow = row_ok[qt] ? ((int64_t)b * a.n_q + i_row[qt]) * a.Hq + h[qt] : 0;
-      const bf16_t *qp = (const bf16_t *)a.q + qrow * kD + 8 * c4;
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) qv[qt][ks] = *(const u32x4 *)(qp + 32 * ks);
-    }
-    // The memory pipeline of a compute unit serves requests in issue order and a wavefront
-    // issues all its loads back to back: without this barrier the look-ahead of the wavefronts
-    // that issue first would queue ahead of the FIRST step of the others (measured: 3 us of
-    // skew between the two streams).
-    if (kPrefetch > 1) __syncthreads();
-#pragma unroll
-    for (int p = 1; p < kPrefetch; ++p) {
-      issue(Vg, p, vst[p]);
-      issue(Kg, kPing ? p + 1 : p, kst[p]);
-    }
-    // Loads retire in order: Q (and the first step before it) have landed once at most the
-    // loads issued after Q are outstanding (other counters untouched).
-    constexpr int kAfterQ = (kPrefetch - 1) * 2 * kLd;
-    static_assert(kAfterQ < 64, "vmcnt is a 6-bit counter");
+  auto take_q = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (kAfterQ & 15) | ((kAfterQ >> 4) << 14));
 #pragma unroll
     for (int qt = 0; qt < kQT; ++qt)
 #pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) {
-        if (!row_ok[qt]) qv[qt][ks] = (u32x4){0u, 0u, 0u, 0u};
-        qreg[qt][ks] = __builtin_bit_cast(bf16x8, qv[qt][ks]);
-      }
-  }
+      for (int ks = 0; ks < kKS; ++ks) qreg[qt][ks] = __builtin_bit_cast(bf16x8, qv[qt][ks]);
+  };
+  if (kQT > 1) take_q();                          // (what follows has no registers to wait in)
   // draft rows a row may attend (bit j <=> draft row j); only needed if the split reaches them
   unsigned long long anc[kQT];
 #pragma unroll
@@ -316,7 +333,8 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   const int k_swz = swz<kD>(n);
   const int s16 = lane & 15;                       // source lane index within the 16-lane group
   const int v_row = 4 * c4 + (s16 >> 2);           // token within a 16-token slab
-  const int v_swz = swz<kD>(v_row);
+  // (o_acc[.][i] is d-tile i ^ (the first of the wavefront's own), chosen by the chunks that it reads)
+  const int v_swz = swz<kD>(v_row) ^ (kPairs ? 2 * part : kShare ? kMT * strm : 0);
   const int v_off = v_row * kRowBytes + ((s16 & 1) << 3);   // + chunk (2*mt + ((s16>>1)&1)) ^ swz
   const int v_chb = (s16 >> 1) & 1;
 
@@ -327,13 +345,21 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int qt = 0; qt < kQT; ++qt) {
-    m_run[qt] = kNegBig;
-    l_acc[qt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int qt = 0; qt < kQT; ++qt) {
+      m_run[qt] = kNegBig;
+      l_acc[qt] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) o_acc[qt][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  }
+      for (int mt = 0; mt < kMT; ++mt) {
+        o_acc[qt][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (kQT == 1) asm volatile("" : "+v"(o_acc[qt][mt]));     // now, and not behind the wait
+      }
+    }
+  };
+  if (kQT == 1) clear();                          // (several row tiles have no registers to spare for it)
+  if (kQT == 1) take_q();
+  if (kQT > 1) clear();
 
   f32x4 s[kQT][kSlabs];                           // scores of a step, S^T
   bf16x8 pb[kQT][kSubW];                          // its probabilities, P^T
@@ -371,7 +397,7 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         // numbers, their distances to L and the shift counts out on EVERY step, ahead of the
         // branch -- some 20 vector instructions per row tile that all but one step throw away)
         int tb_e = tb;
-        asm volatile("" : "+s"(tb_e));
+        asm volatile("" : "+v"(tb_e));
 #pragma unroll
         for (int j = 0; j < kSlabs; ++j)
 #pragma unroll
@@ -394,9 +420,11 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
         const float m_new = fmaxf(m_run[qt], quad_max(mx));
         const float alpha = fast_exp2(m_run[qt] - m_new);
         m_run[qt] = m_new;
-        if (kMfmaRowSum) l_acc[qt] *= alpha; else l_acc[qt][0] *= alpha;
+        if (st > 0) {                                        // (of the first step nothing has been added up)
+          if (kMfmaRowSum) l_acc[qt] *= alpha; else l_acc[qt][0] *= alpha;
 #pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) o_acc[qt][mt] *= alpha;
+          for (int mt = 0; mt < kMT; ++mt) o_acc[qt][mt] *= alpha;
+        }
       }
 #pragma unroll
       for (int u = 0; u < kSubW; ++u) {
@@ -589,363 +617,427 @@ verify_partial_mfma_kernel(VerifyArgs a, SeqTable tab, PieceTable pt, int rbs, i
     }
   }
 
-  // ---- merge the two streams (stream 1 -> LDS -> stream 0) and write the split's partials in
-  // register layout: [slot][kv head][row block][wavefront][pair of d-tiles][lane] x 8 halves, so
-  // that every store instruction writes 1 KB of contiguous memory.
+  // ---- merge the states of a row and write the split's partials in register layout: [slot][kv head][row block]
+  // [wavefront][pair of d-tiles][lane] x 8 halves, so that every store instruction writes 1 KB of contiguous memory.
+  // The d-tiles are shared out over the wavefronts that hold a row (o_acc[.][i] is d-tile i of the wavefront's own
+  // order, the first ones its own): each sends the others theirs through LDS and normalises and stores its own.
   if constexpr (kPairs) {
-    // four wavefronts hold a row (two streams, two tiles of a step): the other three's states meet the first's
-    const int part = strm * 2 + u0;
-    f32x4 *po4 = reinterpret_cast<f32x4 *>(lds) + lane;                        // [part - 1][wr][mt][lane]
-    float *pm4 = reinterpret_cast<float *>(lds + 6 * kMT * 1024) + 2 * lane;   // [part - 1][wr][lane][m, l]
+    // four wavefronts hold a row (two streams, two tiles of a step) and a d-tile each: o_acc[0][i] is tile part ^ i
+    static_assert(kMT == 4, "a d-tile per wavefront");
+    f32x4 *po4 = reinterpret_cast<f32x4 *>(lds) + lane;                        // [part][i - 1][wr][lane]
+    float *pm4 = reinterpret_cast<float *>(lds + 24 * 1024) + 2 * lane;        // [part][wr][lane][m, l]
     const float l_mine = quad_sum(l_acc[0][0]);
     __syncthreads();
-    if (part > 0) {
-      const int at4 = (part - 1) * 2 + wr;
 #pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) po4[(at4 * kMT + mt) * 64] = o_acc[0][mt];
-      pm4[at4 * 128] = m_run[0];
-      pm4[at4 * 128 + 1] = l_mine;
-    }
+    for (int i = 1; i < 4; ++i) po4[(((part ^ i) * 3 + i - 1) * 2 + wr) * 64] = o_acc[0][i];
+    pm4[(part * 2 + wr) * 128] = m_run[0];
+    pm4[(part * 2 + wr) * 128 + 1] = l_mine;
     __syncthreads();
-    if (part > 0 || n_act == 0) return;
-    float m_new = m_run[0];
+    if (n_act == 0) return;
+    float m_x[3], m_new = m_run[0];
 #pragma unroll
-    for (int x = 0; x < 3; ++x) m_new = fmaxf(m_new, pm4[(2 * x + wr) * 128]);
+    for (int i = 1; i < 4; ++i) {
+      m_x[i - 1] = pm4[((part ^ i) * 2 + wr) * 128];
+      m_new = fmaxf(m_new, m_x[i - 1]);
+    }
     const float a0 = fast_exp2(m_run[0] - m_new);
     float ax[3], l_tot = l_mine * a0;
 #pragma unroll
-    for (int x = 0; x < 3; ++x) {
-      ax[x] = fast_exp2(pm4[(2 * x + wr) * 128] - m_new);
-      l_tot += pm4[(2 * x + wr) * 128 + 1] * ax[x];
+    for (int i = 1; i < 4; ++i) {
+      ax[i - 1] = fast_exp2(m_x[i - 1] - m_new);
+      l_tot += pm4[((part ^ i) * 2 + wr) * 128 + 1] * ax[i - 1];
     }
     // each state by its share of the sum, before they meet: values near the end of the range would leave it added up
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    f32x4 r = o_acc[0][0] * (a0 * inv_l);
 #pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] *= a0 * inv_l;
-#pragma unroll
-    for (int x = 0; x < 3; ++x)
-#pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) o_acc[0][mt] += po4[((2 * x + wr) * kMT + mt) * 64] * (ax[x] * inv_l);
+    for (int i = 1; i < 4; ++i) r += po4[((part * 3 + i - 1) * 2 + wr) * 64] * (ax[i - 1] * inv_l);
     if (direct) {
       if (!row_ok[0]) return;
-      const int64_t orow = ((int64_t)b * a.n_q + i_row[0]) * a.Hq + h[0];
-      bf16_t *out = (bf16_t *)a.out + orow * kD + 4 * c4;
-#pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) {
-        const f32x4 r = o_acc[0][mt];
-        *reinterpret_cast<u32x2 *>(out + 16 * mt) = (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
-      }
-      if (a.lse != nullptr && c4 == 0) a.lse[orow] = lse_of<kWide>(m_new, l_tot);
+      const int64_t orow = q_row0 + i_row[0] * a.Hq + h[0];
+      *reinterpret_cast<u32x2 *>((bf16_t *)a.out + orow * kD + 16 * part + 4 * c4) =
+          (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
+      if (a.lse != nullptr && part == 0 && c4 == 0) a.lse[orow] = lse_of<kWide>(m_new, l_tot);
       return;
     }
-    const int64_t unit = ((int64_t)slot * a.Hkv + c) * rbs64 + rb;
+    const int64_t unit = ((int64_t)slot * a.Hkv + c) * ((R + kRowsPerWG - 1) / kRowsPerWG) + rb;
     f32x4 *po = reinterpret_cast<f32x4 *>(a.part_o) + (unit * 4 + wr) * (kMT * 64) + lane;
-#pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) __builtin_nontemporal_store(o_acc[0][mt], &po[mt * 64]);
-    if (c4 == 0) {
+    __builtin_nontemporal_store(r, &po[part * 64]);
+    if (part == 0 && c4 == 0) {
       float *pml = a.part_ml + (unit * kRowsPerWG + 16 * wr + n) * kMlFloats;
       __builtin_nontemporal_store(m_new, &pml[0]);
       __builtin_nontemporal_store(l_tot, &pml[1]);
     }
     return;
   }
-  f32x4 *mo = reinterpret_cast<f32x4 *>(lds);                                  // [w][mt][lane]
-  float *mm = reinterpret_cast<float *>(lds + 4 * kMT * 64 * 16);              // [w][lane][m,l]
+  constexpr int kOwn = kShare ? kMT / 2 : kMT;                                 // d-tiles of a stream: strm * kOwn ..
+  f32x4 *mo = reinterpret_cast<f32x4 *>(lds) + w * kOwn * 64 + lane;           // [stream][w][own tile][lane]
+  float *mm = reinterpret_cast<float *>(lds + 4 * kMT * 1024) + (w * 64 + lane) * 2;     // [stream][w][lane][m,l]
 #pragma unroll
   for (int qt = 0; qt < kQT; ++qt) {
     const float l_mine = kMfmaRowSum ? l_acc[qt][0] : quad_sum(l_acc[qt][0]);
     __syncthreads();                    // all tile reads (and the previous merge) done: LDS is free
-    if (strm == 1) {
+    if (kShare || strm == 1) {
 #pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) mo[(w * kMT + mt) * 64 + lane] = o_acc[qt][mt];
-      mm[(w * 64 + lane) * 2] = m_run[qt];
-      mm[(w * 64 + lane) * 2 + 1] = l_mine;
+      for (int i = 0; i < kOwn; ++i) mo[((strm ^ 1) * 4 * kOwn + i) * 64] = o_acc[qt][kMT - kOwn + i];
     }
+    mm[strm * 512] = m_run[qt];
+    mm[strm * 512 + 1] = l_mine;
     __syncthreads();
-    if (strm == 0 && qt < n_act) {
-      const float m1 = mm[(w * 64 + lane) * 2], l1 = mm[(w * 64 + lane) * 2 + 1];
+    if (qt < n_act && (kShare || strm == 0)) {
+      const float m1 = mm[(strm ^ 1) * 512], l1 = mm[(strm ^ 1) * 512 + 1];
       const float m_new = fmaxf(m_run[qt], m1);
       const float a0 = fast_exp2(m_run[qt] - m_new), a1 = fast_exp2(m1 - m_new);
       // unit = (split, KV head, block of 64 rows).  The split's output is stored normalised
       // (o / l: a convex combination of V rows, of the magnitude of V) in fp16, two d-tiles per
-      // 16-byte store; m, l and a per-row power-of-two scale c in fp32.  c is 1 unless the row's
-      // largest |o / l| would leave the fp16 range (|V| beyond 16384), then o / (l c) is stored.
-      const int64_t unit = ((int64_t)slot * a.Hkv + c) * rbs64 + rb * kQT + qt;
+      // 16-byte store; m and l in fp32, and a power-of-two scale c per half of the row, two bf16.  c is 1 unless
+      // the half's largest |o / l| would leave the fp16 range (|V| beyond 16384), then o / (l c) is stored.
+      const int64_t unit = ((int64_t)slot * a.Hkv + c) * ((R + kRowsPerWG - 1) / kRowsPerWG) + rb * kQT + qt;
       const float l_tot = l_mine * a0 + l1 * a1;
       const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;
       const float s0 = a0 * inv_l, s1 = a1 * inv_l;
+      f32x4 r[kOwn];
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i) r[i] = o_acc[qt][i] * s0 + mo[(strm * 4 * kOwn + i) * 64] * s1;
       if (direct) {
         // the split is the whole sequence: the merged streams are the result (the rows and columns
         // of a lane as in the combine pass)
         if (row_ok[qt]) {
-          const int64_t orow = ((int64_t)b * a.n_q + i_row[qt]) * a.Hq + h[qt];
-          bf16_t *out = (bf16_t *)a.out + orow * kD + 4 * c4;
+          const int64_t orow = q_row0 + i_row[qt] * a.Hq + h[qt];
+          bf16_t *out = (bf16_t *)a.out + orow * kD + 16 * kOwn * strm + 4 * c4;
 #pragma unroll
-          for (int mt = 0; mt < kMT; ++mt) {
-            const f32x4 r = o_acc[qt][mt] * s0 + mo[(w * kMT + mt) * 64 + lane] * s1;
-            *reinterpret_cast<u32x2 *>(out + 16 * mt) = (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
-          }
-          if (a.lse != nullptr && c4 == 0) a.lse[orow] = lse_of<kWide>(m_new, l_tot);
+          for (int i = 0; i < kOwn; ++i)
+            *reinterpret_cast<u32x2 *>(out + 16 * i) = (u32x2){pack_bf16x2(r[i][0], r[i][1]), pack_bf16x2(r[i][2], r[i][3])};
+          if (a.lse != nullptr && strm == 0 && c4 == 0) a.lse[orow] = lse_of<kWide>(m_new, l_tot);
         }
         continue;
       }
+      float *pml = a.part_ml + (unit * kRowsPerWG + 16 * w + n) * kMlFloats;
+      if (strm == 0 && c4 == 0) {
+        __builtin_nontemporal_store(m_new, &pml[0]);
+        __builtin_nontemporal_store(l_tot, &pml[1]);
+      }
       if (kWide) {
         // fp32 partials: [unit][wavefront][d-tile][lane] x 4 floats
-        f32x4 *po = reinterpret_cast<f32x4 *>(a.part_o) + (unit * 4 + w) * (kMT * 64) + lane;
+        f32x4 *po = reinterpret_cast<f32x4 *>(a.part_o) + (unit * 4 + w) * (kMT * 64) + strm * kOwn * 64 + lane;
 #pragma unroll
-        for (int mt = 0; mt < kMT; ++mt)
-          __builtin_nontemporal_store(o_acc[qt][mt] * s0 + mo[(w * kMT + mt) * 64 + lane] * s1, &po[mt * 64]);
-        if (c4 == 0) {
-          float *pml = a.part_ml + (unit * kRowsPerWG + 16 * w + n) * kMlFloats;
-          __builtin_nontemporal_store(m_new, &pml[0]);
-          __builtin_nontemporal_store(l_tot, &pml[1]);
-        }
+        for (int i = 0; i < kOwn; ++i) __builtin_nontemporal_store(r[i], &po[i * 64]);
         continue;
       }
       float amax = 0.f;
 #pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) {
-        o_acc[qt][mt] = o_acc[qt][mt] * s0 + mo[(w * kMT + mt) * 64 + lane] * s1;
+      for (int i = 0; i < kOwn; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fabsf(o_acc[qt][mt][i]));
-      }
-      amax = quad_max(amax);                       // over the row's kD values
-      float cscale = 1.0f, inv_c = 1.0f;
-      if (amax > 16384.f) {                        // exponent of amax / 16384, rounded up
-        const int e = (int)((__float_as_uint(amax) >> 23) & 0xff) - 127 - 13;
-        cscale = __uint_as_float((unsigned int)(127 + e) << 23);
-        inv_c = __uint_as_float((unsigned int)(127 - e) << 23);
-      }
-      u32x4 *po = reinterpret_cast<u32x4 *>(a.part_o) + (unit * 4 + w) * (kMT / 2 * 64) + lane;
+        for (int e = 0; e < 4; ++e) amax = fmaxf(amax, fabsf(r[i][e]));
+      amax = quad_max(amax);                       // over half of the row's kD values
+      unsigned int cbits = 0x3f80u;                // 1 as bf16
+      if (__builtin_amdgcn_ballot_w64(amax > 16384.f) != 0ull) {
+        const int e = amax > 16384.f ? (int)((__float_as_uint(amax) >> 23) & 0xff) - 127 - 13 : 0;   // of amax / 16384, up
+        cbits = (unsigned int)(127 + e) << 7;
+        const float inv_c = __uint_as_float((unsigned int)(127 - e) << 23);
 #pragma unroll
-      for (int pr = 0; pr < kMT / 2; ++pr) {
-        const f32x4 x = o_acc[qt][2 * pr] * inv_c, y = o_acc[qt][2 * pr + 1] * inv_c;
+        for (int i = 0; i < kOwn; ++i) r[i] *= inv_c;
+      }
+      u32x4 *po = reinterpret_cast<u32x4 *>(a.part_o) + (unit * 4 + w) * (kMT / 2 * 64) + strm * (kOwn / 2) * 64 + lane;
+#pragma unroll
+      for (int pr = 0; pr < kOwn / 2; ++pr) {
+        const f32x4 x = r[2 * pr], y = r[2 * pr + 1];
         __builtin_nontemporal_store((u32x4){pack_f16x2(x[0], x[1]), pack_f16x2(x[2], x[3]),
                                             pack_f16x2(y[0], y[1]), pack_f16x2(y[2], y[3])}, &po[pr * 64]);
       }
-      if (c4 == 0) {
-        float *pml = a.part_ml + (unit * kRowsPerWG + 16 * w + n) * kMlFloats;
-        __builtin_nontemporal_store(m_new, &pml[0]);
-        __builtin_nontemporal_store(l_tot, &pml[1]);
-        __builtin_nontemporal_store(cscale, &pml[2]);
-      }
+      if (kShare && c4 == 0) __builtin_nontemporal_store((bf16_t)cbits, reinterpret_cast<bf16_t *>(&pml[2]) + strm);
+      if (!kShare && c4 == 0) __builtin_nontemporal_store(__uint_as_float(cbits << 16 | cbits), &pml[2]);
     }
   }
 }
 
-// Combine for the tiled partial layout above.  One workgroup of 16 wavefronts per (sequence, KV
-// head, 16-row tile, 16-wide d tile); wavefront ws merges splits ws, ws+16, ... with 4 splits (8
-// bytes per lane each) in flight at a time, so the usual 64 splits cost one memory round trip; the
-// running results are merged through LDS.  The pass is bound by its dependent chain (launch, one
-// load round trip, the exponentials, the LDS merge, the store), not by bytes: measured per C5 layer
-// with 4 wavefronts x 16 splits and two d-tiles per workgroup 20.6 us, one d-tile 19.0 us, 8 x 8
-// 18.7 us, 16 x 4 18.5 us.
-constexpr int kCombInFlight = 4;
+// Combine for the tiled partial layout above.  What bounds these kernels is not bytes (4 MB a call) but how many load
+// instructions a compute unit has to issue (16 cycles each, whatever their width) and the instructions around them, one
+// wavefront per SIMD; then a round trip to memory and the end of a launch.  So the addresses are scalar offsets of buffer
+// loads, a split's (m, l, c) is fetched and turned into a weight by one of the four lanes that need it and handed to the
+// others across lanes, and the arguments that the first load needs arrive in registers (leading scalars of the kernel).
+//
+// Up to 32 splits: one workgroup per (sequence, KV head, 16-row tile, kTiles d-tiles of 16); wavefront ws merges splits ws,
+// ws + kWaves, ..., four of them at a time, and the wavefronts' states meet in LDS.
+// kWaves = 1 and 2 (at most four and eight splits: batches, thousands of output tiles): two d-tiles each, as the number of
+// wavefronts sets the pace.  12 trees of 30 nodes over 4,099 tokens, 32/8 heads: 54.0 us a call with four wavefronts of one
+// d-tile, 49.2 with one of two (both with the partial pass); 12 of 2 over 700, 16/8 14.9 / 12.9.
+// kWaves = 4 and 8 (9 to 32 splits): two d-tiles, one with fp32 partials, whose loads are twice as wide; us a call,
+// loads of every lane's own (m, l, c) with 64-bit addresses / here: 30 nodes over 26,112 (32 splits) 27.1 / 26.5, 60 over
+// 12,000 (16) 25.1 / 24.2, four chains of 8 over 2,000 (16) 11.6 / 11.4.
+typedef __attribute__((ext_vector_type(3))) unsigned int u32x3;
 
-__device__ __forceinline__ f32x4 partial_values(const u32x2 &w) { return unpack_f16x4(w.x, w.y); }
-__device__ __forceinline__ f32x4 partial_values(const f32x4 &w) { return w; }
+struct CombineArgs {                               // what a combine kernel's scalar arguments say, in its own terms
+  const unsigned char *part_o, *part_ml;
+  void *res;
+  float *lse;
+  int ns_one, units, Hq, g, n_q, shape;
+};
 
-// kCombWaves = 16 for the decode-time case (one sequence cut into ~64 splits); 8 or 4 when no
-// sequence of the call has more than 32 or 16 splits (draft trees, batches), where 16 wavefronts
-// per output tile would mostly find nothing to merge.
-template <class T, int kD, int kCombWaves>
-__global__ void __launch_bounds__(64 * kCombWaves)
-verify_combine_tiled_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
-  __shared__ f32x4 xo[kCombWaves][64];
-  __shared__ float xm[kCombWaves][64], xl[kCombWaves][64];
-  const int b = blockIdx.z;
-  const int s0 = tab.cu_split[b], s1 = tab.cu_split[b + 1];
-  // all scalar arguments in one round of loads (see the partial pass)
-  asm volatile("" ::"s"(rbs), "s"(g), "s"(s0), "s"(s1), "s"(a.n_q), "s"(a.Hq), "s"(a.Hkv), "s"(a.part_o),
-               "s"(a.part_ml), "s"(a.out), "s"(a.lse));
-  const int unit_in_seq = blockIdx.x;            // (c * rbs + rb) * 4 + wq
-  const int wq = unit_in_seq & 3, crb = unit_in_seq >> 2;
-  int rb = 0, c = crb;
-  if (rbs > 1) { rb = crb % rbs; c = crb / rbs; }
-  const int mt = blockIdx.y;                     // d-tile: half (mt & 1) of the stored pair mt >> 1
-  const int ws = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n = lane & 15, c4 = lane >> 4;
-  const int R = a.n_q * g;
-  if (rb * kRowsPerWG + 16 * wq >= R) return;    // tile without rows (uniform)
+template <class T, int kD, int kWaves>
+__device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTable &tab) {
+  const unsigned char *part_o = a.part_o, *part_ml = a.part_ml;
+  const int ns_one = a.ns_one, units = a.units, Hq = a.Hq, g = a.g, n_q = a.n_q, shape = a.shape;
+  constexpr int kInFlight = 4;
+  constexpr int kTiles = kWaves > 2 && (kWideState<kD> || std::is_same<T, float>::value) ? 1 : 2;
   constexpr bool kWide = kWideState<kD> || std::is_same<T, float>::value;    // fp32 partials
-  typedef typename std::conditional<kWide, f32x4, u32x2>::type part_t;      // 4 values of a lane
-  const part_t *po = reinterpret_cast<const part_t *>(a.part_o);
-  float m_run = kNegBig, l_run = 0.f;
-  f32x4 o = {0.f, 0.f, 0.f, 0.f};
-  for (int sb = s0 + ws; sb < s1; sb += kCombWaves * kCombInFlight) {
-    float ms[kCombInFlight], ls[kCombInFlight], cs[kCombInFlight];
-    part_t pa[kCombInFlight];
-#pragma unroll
-    for (int u = 0; u < kCombInFlight; ++u) {
-      const int s = min(sb + kCombWaves * u, s1 - 1);
-      const int64_t unit = ((int64_t)s * a.Hkv + c) * rbs + rb;
-      const float *pml = a.part_ml + (unit * kRowsPerWG + 16 * wq + n) * kMlFloats;
-      ms[u] = __builtin_nontemporal_load(&pml[0]);
-      ls[u] = __builtin_nontemporal_load(&pml[1]);
-      cs[u] = kWide ? 1.f : __builtin_nontemporal_load(&pml[2]);
-      pa[u] = __builtin_nontemporal_load(kWide ? &po[((unit * 4 + wq) * (kD / 16) + mt) * 64 + lane]
-                                               : &po[((((unit * 4 + wq) * (kD / 32) + (mt >> 1)) * 64 + lane) << 1) + (mt & 1)]);
-    }
-    float mx = m_run;
-#pragma unroll
-    for (int u = 0; u < kCombInFlight; ++u) if (sb + kCombWaves * u < s1) mx = fmaxf(mx, ms[u]);
-    const float alpha = fast_exp2(m_run - mx);
-    m_run = mx;
-    l_run *= alpha; o *= alpha;
-#pragma unroll
-    for (int u = 0; u < kCombInFlight; ++u) {
-      // weight of the split: its share of the softmax denominator (its output is normalised)
-      const bool in = sb + kCombWaves * u < s1;
-      const float wgt = in ? fast_exp2(ms[u] - mx) * ls[u] : 0.f;
-      l_run += wgt;
-      if (kWide && !in) pa[u] = part_t{};          // (uniform; a duplicate of an infinite partial: no 0 * inf)
-      o += partial_values(pa[u]) * (wgt * cs[u]);
-    }
-  }
-  xo[ws][lane] = o;
-  xm[ws][lane] = m_run; xl[ws][lane] = l_run;
-  __syncthreads();
-  if (ws == 0) {
-    float m = xm[0][lane];
-#pragma unroll
-    for (int k = 1; k < kCombWaves; ++k) m = fmaxf(m, xm[k][lane]);
-    float l = 0.f;
-    f32x4 r = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < kCombWaves; ++k) {
-      const float wgt = fast_exp2(xm[k][lane] - m);
-      l = fmaf(xl[k][lane], wgt, l);
-      r += xo[k][lane] * wgt;
-    }
-    const int rho = rb * kRowsPerWG + 16 * wq + n;
-    if (rho < R) {
-      const int i_row = rho / g, h = c * g + rho % g;
-      const int64_t orow = ((int64_t)b * a.n_q + i_row) * a.Hq + h;
-      const float inv = 1.0f / l;
-      T *out = (T *)a.out + orow * kD + 16 * mt + 4 * c4;
-      if constexpr (std::is_same<T, float>::value)
-        *reinterpret_cast<f32x4 *>(out) = r * inv;
-      else
-        *reinterpret_cast<u32x2 *>(out) = (u32x2){pack_bf16x2(r[0] * inv, r[1] * inv), pack_bf16x2(r[2] * inv, r[3] * inv)};
-      if (a.lse != nullptr && mt == 0 && c4 == 0) a.lse[orow] = lse_of<kWide>(m, l);
-    }
-  }
-}
-
-// Batches of at most eight or four splits a sequence bring thousands of output tiles, and the number of wavefronts and of
-// their loads sets the pace, not the chain: 2 wavefronts or 1 (which has no merge), two d-tiles each.  The kernel above
-// with four wavefronts / this one, us a call with the partial pass: 12 trees of 30 nodes over 4,099 tokens, 32/8 heads 54.0 /
-// 49.2, 8 of 20 over 1,500, 64/8 31.8 / 27.3, 16 chains of 8 over 2,000, 28/4 22.2 / 20.7, 12 of 2 over 700, 16/8
-// 14.9 / 12.9, 4 trees of 60 over 8,000, 28/4 50.5 / 47; heads of 64 (fp32 partials) as fast.  One wavefront with one
-// d-tile or four: 20 trees 31.8 and 27.6, 12 chains 13.1 and 14.2.  Two d-tiles with 4 wavefronts, up to 16 splits: 0.97
-// to 1.01 of the speed.
-template <class T, int kD, int kCombWaves>
-__global__ void __launch_bounds__(64 * kCombWaves)
-verify_combine_few_kernel(VerifyArgs a, SeqTable tab, int rbs, int g) {
-  constexpr int kTiles = 2;                      // d-tiles of a wavefront: the two of a 16-byte pair of fp16 partials
-  __shared__ f32x4 xo[kCombWaves][kTiles][64];
-  __shared__ float xm[kCombWaves][64], xl[kCombWaves][64];
+  constexpr int kMine = kInFlight / 4;             // splits whose (m, l, c) a lane loads: those of its four lanes make a round
+  constexpr int kQuarter = kWide ? 64 * kD : 4096; // bytes of 16 rows of a unit: a wavefront of the partial pass
+  constexpr int kLoad = !kWide && kTiles == 1 ? 8 : 16;
+  __shared__ f32x4 xo[kWaves][kTiles][64];
+  __shared__ float xm[kWaves][16], xl[kWaves][16];
+  const int rbs = shape >> 1;
   const int b = blockIdx.z;
-  const int s0 = tab.cu_split[b], s1 = tab.cu_split[b + 1];
-  // all scalar arguments in one round of loads (see the partial pass)
-  asm volatile("" ::"s"(rbs), "s"(g), "s"(s0), "s"(s1), "s"(a.n_q), "s"(a.Hq), "s"(a.Hkv), "s"(a.part_o),
-               "s"(a.part_ml), "s"(a.out), "s"(a.lse));
-  const int unit_in_seq = blockIdx.x;            // (c * rbs + rb) * 4 + wq
-  const int wq = unit_in_seq & 3, crb = unit_in_seq >> 2;
-  int rb = 0, c = crb;
-  if (rbs > 1) { rb = crb % rbs; c = crb / rbs; }
-  const int mt = blockIdx.y * kTiles;            // first d-tile
+  int s0 = b * ns_one, ns = ns_one;
+  if (shape & 1) {                                 // sequences that differ
+    s0 = tab.cu_split[b]; ns = tab.cu_split[b + 1] - s0;
+  }
+  const int wq = blockIdx.x & 3, unit = blockIdx.x >> 2;       // 16 rows of unit KV head * rbs + row block
+  const int mt = blockIdx.y * kTiles;              // first d-tile: half (mt & 1) of the stored pair mt >> 1
   const int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int n = lane & 15, c4 = lane >> 4;
-  const int R = a.n_q * g;
-  if (rb * kRowsPerWG + 16 * wq >= R) return;    // tile without rows (uniform)
-  constexpr bool kWide = kWideState<kD> || std::is_same<T, float>::value;    // fp32 partials
+  // This wavefront's splits are ws, ws + kWaves, ... of the sequence's.  Their offsets fit 32 bits: several splits a
+  // sequence mean no more than a few hundred units a split.
+  const int64_t first = ((int64_t)s0 * units + unit) * 4 + wq;
+  const __amdgpu_buffer_rsrc_t rs_o = __builtin_amdgcn_make_buffer_rsrc((void *)(part_o + first * kQuarter), (short)0, (int)0x7fffffff, 0x00027000);
+  const __amdgpu_buffer_rsrc_t rs_ml = __builtin_amdgcn_make_buffer_rsrc((void *)(part_ml + first * (16 * 4 * kMlFloats)), (short)0, (int)0x7fffffff, 0x00027000);
+  const unsigned int step_o = (unsigned int)units * (4 * kQuarter), step_ml = (unsigned int)units * (64 * 4 * kMlFloats);
+  const unsigned int at_o = (unsigned int)lane * 16u + (kLoad == 8 ? 8u * (mt & 1) : 0u);
+  const unsigned int tile_o = (unsigned int)(kWide ? mt : mt >> 1) * 1024u;
   f32x4 o[kTiles];
   float m_run = kNegBig, l_run = 0.f;
 #pragma unroll
   for (int t = 0; t < kTiles; ++t) o[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  for (int sb = s0 + ws; sb < s1; sb += kCombWaves * kCombInFlight) {
-    float ms[kCombInFlight], ls[kCombInFlight], cs[kCombInFlight];
-    u32x4 pa[kCombInFlight][kWide ? kTiles : 1];
+  for (int sb = ws; sb < ns; sb += kWaves * kInFlight) {
+    typedef typename std::conditional<kLoad == 8, u32x2, u32x4>::type part_t;
+    part_t pa[kInFlight][kWide ? kTiles : 1];
+    float ml[kMine][3];
 #pragma unroll
-    for (int u = 0; u < kCombInFlight; ++u) {
-      const int s = min(sb + kCombWaves * u, s1 - 1);
-      const int64_t unit = ((int64_t)s * a.Hkv + c) * rbs + rb;
-      if constexpr (kWide) {
+    for (int j = 0; j < kMine; ++j) {
+      const int s = min(sb + kWaves * (c4 + 4 * j), ns - 1);
+      const u32x3 w = __builtin_amdgcn_raw_buffer_load_b96(rs_ml, __umul24(s, step_ml) + (unsigned int)n * (4 * kMlFloats), 0, 2);
+      ml[j][0] = __uint_as_float(w.x); ml[j][1] = __uint_as_float(w.y); ml[j][2] = __uint_as_float(w.z);
+    }
 #pragma unroll
-        for (int t = 0; t < kTiles; ++t)
-          pa[u][t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.part_o) + ((unit * 4 + wq) * (kD / 16) + mt + t) * 64 + lane);
+    for (int u = 0; u < kInFlight; ++u) {
+      const unsigned int so = (unsigned int)min(sb + kWaves * u, ns - 1) * step_o + tile_o;
+      if constexpr (kLoad == 8) {
+        pa[u][0] = __builtin_amdgcn_raw_buffer_load_b64(rs_o, at_o, so, 2);
       } else {
-        pa[u][0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.part_o) + ((unit * 4 + wq) * (kD / 32) + (mt >> 1)) * 64 + lane);
+#pragma unroll
+        for (int t = 0; t < (kWide ? kTiles : 1); ++t) pa[u][t] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, at_o, so + 1024u * t, 2);
       }
-      const float *pml = a.part_ml + (unit * kRowsPerWG + 16 * wq + n) * kMlFloats;
-      ms[u] = __builtin_nontemporal_load(&pml[0]);
-      ls[u] = __builtin_nontemporal_load(&pml[1]);
-      cs[u] = kWide ? 1.f : __builtin_nontemporal_load(&pml[2]);
     }
     float mx = m_run;
 #pragma unroll
-    for (int u = 0; u < kCombInFlight; ++u) if (sb + kCombWaves * u < s1) mx = fmaxf(mx, ms[u]);
+    for (int j = 0; j < kMine; ++j) mx = sb + kWaves * (c4 + 4 * j) < ns ? fmaxf(mx, ml[j][0]) : mx;
+    mx = quad_max(mx);
+    // weight of a split: its share of the softmax denominator (its output is normalised), worked out by one of the four
+    // lanes of a row and handed to the others
+    float wgt[kInFlight], sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) {
+      const float x = sb + kWaves * (c4 + 4 * j) < ns ? fast_exp2(ml[j][0] - mx) * ml[j][1] : 0.f;
+      sum += x;
+      const unsigned int cb = __float_as_uint(ml[j][2]);
+      const float sc = kWide ? 1.f : __uint_as_float(mt < kD / 32 ? cb << 16 : cb & 0xffff0000u);
+      const unsigned int xc = __float_as_uint(x * sc);
+      const auto r = __builtin_amdgcn_permlane16_swap(xc, xc, false, false);
+      const auto r0 = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false);
+      const auto r1 = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
+      wgt[4 * j] = __uint_as_float(r0[0]); wgt[4 * j + 1] = __uint_as_float(r1[0]);
+      wgt[4 * j + 2] = __uint_as_float(r0[1]); wgt[4 * j + 3] = __uint_as_float(r1[1]);
+    }
     const float alpha = fast_exp2(m_run - mx);
     m_run = mx;
-    l_run *= alpha;
+    l_run = l_run * alpha + quad_sum(sum);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) o[t] *= alpha;
 #pragma unroll
-    for (int u = 0; u < kCombInFlight; ++u) {
-      // weight of the split: its share of the softmax denominator (its output is normalised)
-      const bool in = sb + kCombWaves * u < s1;
-      const float wgt = in ? fast_exp2(ms[u] - mx) * ls[u] : 0.f;
-      l_run += wgt;
+    for (int u = 0; u < kInFlight; ++u) {
+      const bool in = sb + kWaves * u < ns;        // (uniform; past the end no 0 * inf)
+#pragma unroll
+      for (int t = 0; t < (kWide ? kTiles : 1); ++t) if (!in) pa[u][t] = part_t{};
 #pragma unroll
       for (int t = 0; t < kTiles; ++t) {
         f32x4 x;
-        if constexpr (kWide) {
-          if (!in) pa[u][t] = (u32x4){0u, 0u, 0u, 0u};         // (uniform; a duplicate of an infinite partial: no 0 * inf)
-          x = __builtin_bit_cast(f32x4, pa[u][t]);
-        } else {
-          x = t == 0 ? unpack_f16x4(pa[u][0].x, pa[u][0].y) : unpack_f16x4(pa[u][0].z, pa[u][0].w);
-        }
-        o[t] += x * (wgt * cs[u]);
+        if constexpr (kWide) x = __builtin_bit_cast(f32x4, pa[u][t]);
+        else if constexpr (kTiles == 1) x = unpack_f16x4(pa[u][0].x, pa[u][0].y);
+        else x = t == 0 ? unpack_f16x4(pa[u][0].x, pa[u][0].y) : unpack_f16x4(pa[u][0].z, pa[u][0].w);
+        o[t] += x * wgt[u];
       }
     }
   }
+  // where this lane's row goes
+  int rb = 0, c = unit;
+  if (rbs > 1) { rb = unit % rbs; c = unit / rbs; }
+  const int rho = rb * kRowsPerWG + 16 * wq + n, i_row = row_div(rho, __builtin_amdgcn_rcpf((float)g));
+  const bool row_ok = rho < n_q * g;
+  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(i_row * Hq + rho - i_row * g);
+  int t0 = 0;                                      // the d-tiles that this wavefront stores: all, or one
   float m = m_run, l = l_run;
-  if constexpr (kCombWaves > 1) {
+  if constexpr (kWaves > 1) {
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) xo[ws][t][lane] = o[t];
-    xm[ws][lane] = m_run; xl[ws][lane] = l_run;
+    if (c4 == 0) { xm[ws][n] = m_run; xl[ws][n] = l_run; }
     __syncthreads();
-    if (ws != 0) return;
-    m = xm[0][lane];
+    if (ws >= kTiles) return;
+    t0 = ws;
+    m = xm[0][n];
 #pragma unroll
-    for (int k = 1; k < kCombWaves; ++k) m = fmaxf(m, xm[k][lane]);
+    for (int k = 1; k < kWaves; ++k) m = fmaxf(m, xm[k][n]);
     l = 0.f;
+    o[0] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < kTiles; ++t) o[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < kCombWaves; ++k) {
-      const float wgt = fast_exp2(xm[k][lane] - m);
-      l = fmaf(xl[k][lane], wgt, l);
-#pragma unroll
-      for (int t = 0; t < kTiles; ++t) o[t] += xo[k][t][lane] * wgt;
+    for (int k = 0; k < kWaves; ++k) {
+      const float x = fast_exp2(xm[k][n] - m);
+      l = fmaf(xl[k][n], x, l);
+      o[0] += xo[k][t0][lane] * x;
     }
   }
-  const int rho = rb * kRowsPerWG + 16 * wq + n;
-  if (rho >= R) return;
-  const int i_row = rho / g, h = c * g + rho % g;
-  const int64_t orow = ((int64_t)b * a.n_q + i_row) * a.Hq + h;
+  if (!row_ok) return;
   const float inv = 1.0f / l;
 #pragma unroll
-  for (int t = 0; t < kTiles; ++t) {
-    const f32x4 r = o[t];
-    T *out = (T *)a.out + orow * kD + 16 * (mt + t) + 4 * c4;
-    if constexpr (std::is_same<T, float>::value)
-      *reinterpret_cast<f32x4 *>(out) = r * inv;
-    else
-      *reinterpret_cast<u32x2 *>(out) = (u32x2){pack_bf16x2(r[0] * inv, r[1] * inv), pack_bf16x2(r[2] * inv, r[3] * inv)};
+  for (int t = 0; t < (kWaves > 1 ? 1 : kTiles); ++t) {
+    const f32x4 r = o[t] * inv;
+    T *out = (T *)a.res + orow * kD + 16 * (mt + t0 + t) + 4 * c4;
+    if constexpr (std::is_same<T, float>::value) *reinterpret_cast<f32x4 *>(out) = r;
+    else *reinterpret_cast<u32x2 *>(out) = (u32x2){pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
   }
-  if (a.lse != nullptr && mt == 0 && c4 == 0) a.lse[orow] = lse_of<kWide>(m, l);
+  if (a.lse != nullptr && mt + t0 == 0 && c4 == 0) a.lse[orow] = lse_of<kWide>(m, l);
+}
+
+// (two names, so that the few-splits instances can be told apart in traces)
+template <class T, int kD, int kWaves>
+__global__ void __launch_bounds__(64 * kWaves)
+verify_combine_tiled_kernel(const unsigned char *part_o, const unsigned char *part_ml, void *res, float *lse, int ns_one, int units,
+                            int Hq, int g, int n_q, int shape, SeqTable tab) {
+  combine_rows16<T, kD, kWaves>({part_o, part_ml, res, lse, ns_one, units, Hq, g, n_q, shape}, tab);
+}
+template <class T, int kD, int kWaves>
+__global__ void __launch_bounds__(64 * kWaves)
+verify_combine_few_kernel(const unsigned char *part_o, const unsigned char *part_ml, void *res, float *lse, int ns_one, int units,
+                          int Hq, int g, int n_q, int shape, SeqTable tab) {
+  combine_rows16<T, kD, kWaves>({part_o, part_ml, res, lse, ns_one, units, Hq, g, n_q, shape}, tab);
+}
+
+// More splits than that (and 17 to 32 of calls with few row blocks): one workgroup per (sequence, KV head, 4 rows, 32
+// columns), so that one sequence's few output rows fill the chip, 224 workgroups instead of 128 for a chain of 8 with 28/4
+// heads.  Four lanes of a column take four splits side by side, so that a wavefront merges 16 splits with four loads of
+// 16 bytes a lane (eight with fp32 partials) and one of (m, l, c).  Combine pass alone, us, 16 wavefronts over 16 rows and one
+// d-tile / here: chain of 8 over 26,112 tokens 4.1 / 2.75, of 5 over 8,192 3.8 / 2.5, of 4 over 12,000 4.0 / 2.7; with the
+// partial pass, one KV head, chain of 8 over 16,000 (256 splits) 16.8 / 12.6.  17 to 32 splits, 8 wavefronts over 16 rows
+// / here: up to 8 units (KV heads x row blocks of 64) a sequence 8.7 / 8.5 (chain of 8 over 2,000), four ragged chains of 8
+// over 2,000 11.9 / 11.4; 16 units (30 nodes over 5,000) 13.9 / 14.9.
+template <class T, int kD, int kWaves>
+__global__ void __launch_bounds__(64 * kWaves)
+verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *part_ml, void *res, float *lse, int ns_one, int units,
+                       int Hq, int g, int n_q, int shape, SeqTable tab) {
+  constexpr bool kWide = kWideState<kD> || std::is_same<T, float>::value;    // fp32 partials
+  constexpr int kQuarter = kWide ? 64 * kD : 4096; // bytes of 16 rows of a unit: a wavefront of the partial pass
+  constexpr unsigned int kPastEnd = 0x80000000u;   // a buffer offset that reads as zero
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  __shared__ f32x2 xo[kWaves][64], xml[kWaves][4];
+  const int rbs = shape >> 1;
+  const int b = blockIdx.z;
+  int s0 = b * ns_one, ns = ns_one;
+  if (shape & 1) {                                 // sequences that differ
+    s0 = tab.cu_split[b]; ns = tab.cu_split[b + 1] - s0;
+  }
+  const int rows4 = blockIdx.x & 15, unit = blockIdx.x >> 4;   // four rows of unit KV head * rbs + row block
+  const int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = lane & 3, c4 = (lane >> 2) & 3, ss = lane >> 4;
+  const int64_t first = (int64_t)s0 * units + unit;
+  const __amdgpu_buffer_rsrc_t rs_o = __builtin_amdgcn_make_buffer_rsrc((void *)(part_o + first * (4 * kQuarter)), (short)0, (int)0x7fffffff, 0x00027000);
+  const __amdgpu_buffer_rsrc_t rs_ml = __builtin_amdgcn_make_buffer_rsrc((void *)(part_ml + first * (64 * 4 * kMlFloats)), (short)0, (int)0x7fffffff, 0x00027000);
+  const unsigned int step_o = (unsigned int)units * (4 * kQuarter), step_ml = (unsigned int)units * (64 * 4 * kMlFloats);
+  const unsigned int tile = (unsigned int)(rows4 >> 2) * kQuarter + (unsigned int)blockIdx.y * (kWide ? 2048u : 1024u);
+  const unsigned int at_o = tile + (unsigned int)(c4 * 16 + 4 * (rows4 & 3) + r) * 16u;
+  const unsigned int at_ml = (unsigned int)(4 * rows4 + r) * (4 * kMlFloats);
+  float o[8], m_run = kNegBig, l_run = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = 0.f;
+  for (int base = 16 * ws; base < ns; base += 16 * kWaves) {
+    const int s_own = base + 4 * c4 + ss;
+    const u32x3 ml = __builtin_amdgcn_raw_buffer_load_b96(rs_ml, s_own < ns ? (unsigned int)s_own * step_ml + at_ml : kPastEnd, 0, 0);
+    u32x4 pa[4][kWide ? 2 : 1];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int s = base + 4 * ((c4 + j) & 3) + ss;
+      const unsigned int at = s < ns ? (unsigned int)s * step_o + at_o : kPastEnd;
+#pragma unroll
+      for (int t = 0; t < (kWide ? 2 : 1); ++t) pa[j][t] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, at, 1024 * t, 2);
+    }
+    const float m_own = s_own < ns ? __uint_as_float(ml.x) : kNegBig;
+    float mx = fmaxf(m_run, m_own);
+    mx = fmaxf(mx, dpp_f32<0x128>(mx));
+    mx = fmaxf(mx, dpp_f32<0x124>(mx));
+    mx = quad_max(mx);
+    const float w = fast_exp2(m_own - mx) * __uint_as_float(ml.y);
+    const float wc = kWide ? w : w * __uint_as_float(blockIdx.y < kD / 64 ? ml.z << 16 : ml.z & 0xffff0000u);
+    const float alpha = fast_exp2(m_run - mx);
+    m_run = mx;
+    l_run = l_run * alpha + w;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] *= alpha;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float x = j == 0 ? wc : j == 1 ? dpp_f32<0x12C>(wc) : j == 2 ? dpp_f32<0x128>(wc) : dpp_f32<0x124>(wc);
+      f32x4 lo, hi;
+      if constexpr (kWide) { lo = __builtin_bit_cast(f32x4, pa[j][0]); hi = __builtin_bit_cast(f32x4, pa[j][1]); }
+      else { lo = unpack_f16x4(pa[j][0].x, pa[j][0].y); hi = unpack_f16x4(pa[j][0].z, pa[j][0].w); }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[e] = fmaf(lo[e], x, o[e]);
+        o[4 + e] = fmaf(hi[e], x, o[4 + e]);
+      }
+    }
+  }
+  // sums over the splits of the wavefront's four lanes of a column; two of the eight columns are left to a lane
+  float y[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(o[e]), __float_as_uint(o[4 + e]), false, false);
+    y[e] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  }
+  f32x2 z;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(y[e]), __float_as_uint(y[2 + e]), false, false);
+    z[e] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  }
+  l_run += dpp_f32<0x128>(l_run);
+  l_run += dpp_f32<0x124>(l_run);
+  l_run = quad_sum(l_run);
+  int rb = 0, c = unit;
+  if (rbs > 1) { rb = unit % rbs; c = unit / rbs; }
+  const int rho = rb * kRowsPerWG + 4 * rows4 + r, i_row = row_div(rho, __builtin_amdgcn_rcpf((float)g));
+  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(i_row * Hq + rho - i_row * g);
+  float m = m_run, l = l_run;
+  if constexpr (kWaves > 1) {
+    xo[ws][lane] = z;
+    if (lane < 4) xml[ws][r] = (f32x2){m_run, l_run};
+    __syncthreads();
+    if (ws != 0) return;
+    f32x2 q[kWaves];
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) { q[k] = xml[k][r]; m = fmaxf(m, q[k][0]); }
+    l = 0.f;
+    z = (f32x2){0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+      const float x = fast_exp2(q[k][0] - m);
+      l = fmaf(q[k][1], x, l);
+      z += xo[k][lane] * x;
+    }
+  }
+  if (rho >= n_q * g) return;
+  const float inv = 1.0f / l;
+  z *= inv;
+  T *out = (T *)res + orow * kD + 32 * blockIdx.y + 16 * (ss >> 1) + 4 * c4 + 2 * (ss & 1);
+  if constexpr (std::is_same<T, float>::value) *reinterpret_cast<f32x2 *>(out) = z;
+  else *reinterpret_cast<unsigned int *>(out) = pack_bf16x2(z[0], z[1]);
+  if (lse != nullptr && blockIdx.y == 0 && (lane & ~3) == 0) lse[orow] = lse_of<kWide>(m, l);
 }
 
 }  // namespace
@@ -981,6 +1073,15 @@ int verify_mfma_row_blocks(int dtype, int R) {
 //   the pace.
 static bool half_step_pays(int steps, int rbs) { return rbs > 1 && steps >= 14; }
 
+// All sequences of a call of one length, cut alike: the kernels then work out a sequence's place from its number.  (Table
+// entries are 0.3 to 0.4 us ahead of a workgroup's first load: they are in lines of the arguments that nothing else reads.)
+static bool equal_sequences(const VerifyArgs &a, const SeqTable &tab) {
+  for (int b = 1; b < a.B; ++b)
+    if (tab.cu_len[b + 1] - tab.cu_len[b] != tab.cu_len[1] - tab.cu_len[0] || tab.cu_split[b + 1] - tab.cu_split[b] != tab.cu_split[1])
+      return false;
+  return true;
+}
+
 template <int kD>
 static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
   const int R = a.n_q * (a.Hq / a.Hkv);
@@ -994,30 +1095,36 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
   }
   // grid shape: one x range per (KV head, sequence) unless that would launch mostly padding
   const int x3d = (max_ns + 7) / 8 * 8;
-  const int flat = (int64_t)a.n_slots * 4 < (int64_t)x3d * a.B * 3;      // fewer than 3/4 of the slots real
+  // (fewer than 3/4 of the slots real; the kernel divides group numbers by reciprocals)
+  const int flat = (int64_t)a.n_slots * 4 < (int64_t)x3d * a.B * 3 && (int64_t)a.n_slots * a.Hkv < (1 << 20);
   dim3 grid(x3d * rbs, a.Hkv, a.B), block(256 * kStreams);
   if (flat) grid = dim3((a.n_slots * a.Hkv + 7) / 8 * 8 * rbs, 1, 1);
   constexpr int kSub = 128 / kD;
   constexpr int kLdsBytes = kStreams * 2 * 2 * kSub * kTile * kD * 2;
   static_assert(kLdsBytes <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
-  const int direct = a.direct;
+  const int shape = rbs << kShapeBits | (flat ? kShapeFlat : 0) | (a.direct ? kShapeDirect : 0) | (equal_sequences(a, tab) ? 0 : kShapeTable);
+  const int len0 = flat ? a.n_slots * a.Hkv : tab.cu_len[1] - tab.cu_len[0], ns0 = tab.cu_split[1];
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a.k, a.v, a.stride_head, (int)a.stride_tok, (int)tab.cu_len[0], len0, ns0,
+                       (int)pt.piece[0], a.n_slots, shape, a, tab, pt);
+  };
   const int steps = (a.chunk / kTile + kStreams * kSub - 1) / (kStreams * kSub);   // of a full split
   const int tiles = (R + kRowsPerWG - 1) / kRowsPerWG;
   const int qt = (tiles + rbs - 1) / rbs;
   if (qt == 3)      // a second tile in flight does not fit the registers (and the step is compute-bound)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 3, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    go(verify_partial_mfma_kernel<kD, 1, 3, false>);
   else if (qt == 2 && steps <= 10)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    go(verify_partial_mfma_kernel<kD, 1, 2, false>);
   else if (qt == 2 && kD == 128 && half_step_pays(steps, rbs))
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<128, 2, 2, true>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    go(verify_partial_mfma_kernel<128, 2, 2, true>);
   else if (qt == 2)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 2, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    go(verify_partial_mfma_kernel<kD, 2, 2, false>);
   else if (kD == 64 && R <= 32)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<64, 1, 0, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    go(verify_partial_mfma_kernel<64, 1, 0, false>);
   else if (steps <= 3)       // (a second step in flight pays from 4 steps on: -0.15 us at the 7 steps of a 26k chain)
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 1, 1, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    go(verify_partial_mfma_kernel<kD, 1, 1, false>);
   else
-    hipLaunchKernelGGL((verify_partial_mfma_kernel<kD, 2, 1, false>), grid, block, kLdsBytes, st, a, tab, pt, rbs, flat, direct);
+    go(verify_partial_mfma_kernel<kD, 2, 1, false>);
   return hipGetLastError();
 }
 
@@ -1030,19 +1137,22 @@ template <class T, int kD>
 static hipError_t launch_combine(const VerifyArgs &a, const SeqTable &tab, hipStream_t st) {
   const int R = a.n_q * (a.Hq / a.Hkv);
   const int rbs = (R + kRowsPerWG - 1) / kRowsPerWG;
-  const dim3 grid(a.Hkv * rbs * 4, kD / 16, a.B), pairs(a.Hkv * rbs * 4, kD / 32, a.B);
   int max_ns = 0;
   for (int b = 0; b < a.B; ++b) max_ns = std::max(max_ns, tab.cu_split[b + 1] - tab.cu_split[b]);
-  if (max_ns > 32)
-    hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 16>), grid, dim3(64 * 16), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  else if (max_ns > 16)
-    hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 8>), grid, dim3(64 * 8), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  else if (max_ns > 8)
-    hipLaunchKernelGGL((verify_combine_tiled_kernel<T, kD, 4>), grid, dim3(64 * 4), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  else if (max_ns > 4)
-    hipLaunchKernelGGL((verify_combine_few_kernel<T, kD, 2>), pairs, dim3(64 * 2), 0, st, a, tab, rbs, a.Hq / a.Hkv);
-  else
-    hipLaunchKernelGGL((verify_combine_few_kernel<T, kD, 1>), pairs, dim3(64), 0, st, a, tab, rbs, a.Hq / a.Hkv);
+  const int shape = rbs << 1 | !equal_sequences(a, tab), units = a.Hkv * rbs;
+  constexpr int kTiles = kWideState<kD> || std::is_same<T, float>::value ? 1 : 2;      // of more than two wavefronts
+  auto go = [&](auto kern, int waves, int groups, int tiles) {      // row groups of a unit, d-tiles of a workgroup
+    hipLaunchKernelGGL(kern, dim3(units * groups, kD / 16 / tiles, a.B), dim3(64 * waves), 0, st, (const unsigned char *)a.part_o,
+                       (const unsigned char *)a.part_ml, a.out, a.lse, (int)tab.cu_split[1], units, a.Hq, a.g, a.n_q, shape, tab);
+  };
+  if (max_ns > 128) go(verify_combine_long_kernel<T, kD, 16>, 16, 16, 2);
+  else if (max_ns > 64) go(verify_combine_long_kernel<T, kD, 8>, 8, 16, 2);
+  else if (max_ns > 32) go(verify_combine_long_kernel<T, kD, 4>, 4, 16, 2);
+  else if (max_ns > 16 && units <= 8) go(verify_combine_long_kernel<T, kD, 2>, 2, 16, 2);
+  else if (max_ns > 16) go(verify_combine_tiled_kernel<T, kD, 8>, 8, 4, kTiles);
+  else if (max_ns > 8) go(verify_combine_tiled_kernel<T, kD, 4>, 4, 4, kTiles);
+  else if (max_ns > 4) go(verify_combine_few_kernel<T, kD, 2>, 2, 4, 2);
+  else go(verify_combine_few_kernel<T, kD, 1>, 1, 4, 2);
   return hipGetLastError();
 }
 

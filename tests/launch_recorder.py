@@ -57,13 +57,13 @@ def _child(shim):
 
     def on_launch(stub, grid, block, lds, args):
         one = {"kernel": names[stub], "grid": list(grid[:3]), "block": list(block[:3]), "lds": lds}
-        if one["kernel"].startswith("verify_partial_mfma_kernel"):      # (VerifyArgs, SeqTable, PieceTable, rbs, flat, ...)
-            table = ctypes.cast(args[1], ctypes.POINTER(i32))
+        if one["kernel"].startswith("verify_partial_mfma_kernel"):      # (ten scalars, the last one "shape"; VerifyArgs, SeqTable, PieceTable)
+            table = ctypes.cast(args[11], ctypes.POINTER(i32))
             B = next(b for b in range(1, MAX_BATCH + 1) if b == MAX_BATCH or table[b + 1] == 0)
             cu = table[MAX_BATCH + 1:MAX_BATCH + 2 + B]
             one["splits"] = [y - x for x, y in zip(cu, cu[1:])]
-            one["pieces"] = ctypes.cast(args[2], ctypes.POINTER(i32))[:B]
-            one["flat"] = bool(ctypes.cast(args[4], ctypes.POINTER(i32))[0])
+            one["pieces"] = ctypes.cast(args[12], ctypes.POINTER(i32))[:B]
+            one["flat"] = bool(ctypes.cast(args[9], ctypes.POINTER(i32))[0] & 1)
         seen.append(one)
 
     p32 = ctypes.POINTER(ctypes.c_uint32)

@@ -51,7 +51,7 @@ def test_long_tree_cases(launches):
 
 
 def test_combine_of_few_splits(launches):
-    """One wavefront up to four splits a sequence, two up to eight, four, eight and sixteen above;
+    """One wavefront up to four splits a sequence, two up to eight, four up to sixteen;
     test_gpu_verify_few_splits.py runs the first two at both head sizes."""
     from test_gpu_verify_few_splits import CASES
     for d in (64, 128):
@@ -59,8 +59,43 @@ def test_combine_of_few_splits(launches):
         for (heads, lens, most), run in zip(CASES, got):
             assert max(run[0]["splits"]) == most, (heads, lens, run[0]["splits"])
             assert run[1]["kernel"] == f"verify_combine_few_kernel<unsigned short, {d}, {1 if most <= 4 else 2}>", (heads, lens)
-    got = launches([verify(28, 4, 5, [n] * B) for B, n in ((1, 26112), (2, 26112), (4, 26112), (1, 1024))])
-    assert [run[1]["kernel"][-4:] for run in got] == [" 16>", ", 8>", ", 4>", ", 4>"]
+    got = launches([verify(28, 4, 5, [n] * B) for B, n in ((4, 26112), (1, 1024))])
+    assert {run[1]["kernel"] for run in got} == {"verify_combine_tiled_kernel<unsigned short, 128, 4>"}
+
+
+def test_combine_of_many_splits(launches):
+    """16 splits a wavefront, and eight wavefronts over 16-row tiles where 17 to 32 splits meet many row blocks;
+    test_gpu_verify_long_splits.py runs them."""
+    from test_gpu_verify_long_splits import CASES
+    seen = set()
+    for d in (64, 128):
+        got = launches([verify(*heads, lens, d=d) for heads, lens, _ in CASES])
+        for (heads, lens, most), run in zip(CASES, got):
+            if d == 128:
+                assert max(run[0]["splits"]) == most, (heads, lens, run[0]["splits"])
+            most = max(run[0]["splits"])
+            units = heads[1] * -(-heads[0] // heads[1] * heads[2] // 64)
+            kernel = run[1]["kernel"]
+            if most > 32 or (most > 16 and units <= 8):
+                assert kernel == f"verify_combine_long_kernel<unsigned short, {d}, {min(w for w in (2, 4, 8, 16) if 16 * w >= most or w == 16)}>"
+            elif most > 16:
+                assert kernel == f"verify_combine_tiled_kernel<unsigned short, {d}, 8>"
+            seen.add(kernel)
+    assert {f"verify_combine_long_kernel<unsigned short, {d}, {w}>" for d in (64, 128) for w in (2, 4, 8, 16)} <= seen
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_pieces(launches, d):
+    """Pieces are whole 32-token tiles that cover a sequence, none but the last one of a sequence short; up to 512 tokens of
+    equal sequences they are whole steps, and none is empty."""
+    calls = [verify(28, 4, 5, lens, d=d) for n in (70, 300, 1000, 2049, 4101, 8197, 11111, 26117, 40000) for lens in
+             ([n], [n, n], [n] * 7, [n, n // 3 + 8], [n, n // 2 + 7, n // 5 + 9, n])]
+    for c, run in zip(calls, launches(calls)):
+        equal = len(set(c["lens"])) == 1
+        for n, s, p in zip(c["lens"], run[0]["splits"], run[0]["pieces"]):
+            assert p % 32 == 0 and s * p >= n, (c, run[0])
+            if equal and len(run) == 2:
+                assert (s - 1) * p < n and (p % 64 == 0 or p > 448), (c, run[0])
 
 
 def test_lm_head_cases_straight_to_lds(launches):

@@ -22,7 +22,7 @@ A, AC, AS, ASQ, T, H, C, G = ("test_gpu_parity_attn.py", "test_gpu_parity_accept
 VF, TS = "test_gpu_verify_f32.py", "test_gpu_tree_sizes.py"
 V64, LM, HW = "test_gpu_verify_heads64.py", "test_gpu_lm_head_widths.py", "test_gpu_draft_input_widths.py"
 VP, VL = "test_gpu_verify_plain_alu.py", "test_gpu_verify_long_trees.py"
-DW, VC = "test_gpu_draft_windows.py", "test_gpu_verify_few_splits.py"
+DW, VC, VM = "test_gpu_draft_windows.py", "test_gpu_verify_few_splits.py", "test_gpu_verify_long_splits.py"
 
 COVERAGE = {
     # ---- verification attention, matrix cores, bf16: <head_dim, steps in flight, row tiles, streams half a step apart>
@@ -32,7 +32,6 @@ COVERAGE = {
     "verify_partial_mfma_kernel<128, 2, 2, true>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree: several blocks of 128 rows, long splits"),
     "verify_partial_mfma_kernel<128, 2, 2, false>": (VL, "test_split_ends", "one block of 128 rows over long splits; several over shorter ones"),
     "verify_partial_mfma_kernel<128, 1, 3, false>": (A, "test_paper_sized_trees_at_26k_context", "48-, 44- and 25-node trees: blocks of 192 rows"),
-    "verify_combine_tiled_kernel<unsigned short, 128, 16>": (A, "test_c5_bf16_26k_chain8_layer", "more than 32 splits per sequence"),
     "verify_combine_tiled_kernel<unsigned short, 128, 8>": (A, "test_paper_sized_trees_at_26k_context", "17 to 32 splits (30-, 48-node trees)"),
     "verify_combine_tiled_kernel<unsigned short, 128, 4>": (A, "test_c3_bf16_26k_tree60", "at most 16 splits (C3, C4, batches)"),
     "verify_partial_mfma_kernel<64, 1, 0, false>": (V64, "test_rows_of_two_wavefronts", "up to 32 rows"),
@@ -41,20 +40,34 @@ COVERAGE = {
     "verify_partial_mfma_kernel<64, 1, 2, false>": (V64, "test_rows_and_contexts", "70, 240 and 480 rows"),
     "verify_partial_mfma_kernel<64, 2, 2, false>": (V64, "test_two_row_tiles_over_long_pieces", "60 nodes at 26k, 12 trees of 30 at 4k"),
     "verify_partial_mfma_kernel<64, 1, 3, false>": (V64, "test_rows_and_contexts", "175 rows"),
-    "verify_combine_tiled_kernel<unsigned short, 64, 16>": (V64, "test_batches_and_long_contexts", "26k chain: 64 splits"),
     "verify_combine_tiled_kernel<unsigned short, 64, 8>": (V64, "test_batches_and_long_contexts", "17 to 32 splits"),
     "verify_combine_tiled_kernel<unsigned short, 64, 4>": (V64, "test_rows_and_contexts", "short contexts"),
     # fp32: <head_dim, row tiles>, <storage type, head_dim, wavefronts>
     "verify_partial_f32_kernel<64, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
     "verify_partial_f32_kernel<64, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
-    "verify_combine_tiled_kernel<float, 64, 16>": (VF, "test_batches_and_long_contexts", ""),
     "verify_combine_tiled_kernel<float, 64, 8>": (VF, "test_rows_and_contexts", ""),
     "verify_combine_tiled_kernel<float, 64, 4>": (VF, "test_rows_and_contexts", ""),
     "verify_partial_f32_kernel<128, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
     "verify_partial_f32_kernel<128, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
-    "verify_combine_tiled_kernel<float, 128, 16>": (VF, "test_batches_and_long_contexts", ""),
     "verify_combine_tiled_kernel<float, 128, 8>": (VF, "test_rows_and_contexts", ""),
     "verify_combine_tiled_kernel<float, 128, 4>": (VF, "test_rows_and_contexts", ""),
+    # merged 16 splits a wavefront: <storage type, head_dim, wavefronts>
+    "verify_combine_long_kernel<unsigned short, 64, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<unsigned short, 64, 4>": (VM, "test_many_splits", "up to 64"),
+    "verify_combine_long_kernel<unsigned short, 64, 8>": (VM, "test_many_splits", "up to 128"),
+    "verify_combine_long_kernel<unsigned short, 64, 16>": (VM, "test_many_splits", "more"),
+    "verify_combine_long_kernel<unsigned short, 128, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<unsigned short, 128, 4>": (VM, "test_many_splits", "up to 64"),
+    "verify_combine_long_kernel<unsigned short, 128, 8>": (VM, "test_many_splits", "up to 128"),
+    "verify_combine_long_kernel<unsigned short, 128, 16>": (VM, "test_many_splits", "more"),
+    "verify_combine_long_kernel<float, 64, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<float, 64, 4>": (VM, "test_many_splits", "up to 64"),
+    "verify_combine_long_kernel<float, 64, 8>": (VM, "test_many_splits", "up to 128"),
+    "verify_combine_long_kernel<float, 64, 16>": (VM, "test_many_splits", "more"),
+    "verify_combine_long_kernel<float, 128, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<float, 128, 4>": (VM, "test_many_splits", "up to 64"),
+    "verify_combine_long_kernel<float, 128, 8>": (VM, "test_many_splits", "up to 128"),
+    "verify_combine_long_kernel<float, 128, 16>": (VM, "test_many_splits", "more"),
     # ---- verification attention, plain ALU: <storage type, head_dim>
     # at most 8 and 4 splits per sequence
     "verify_combine_few_kernel<unsigned short, 128, 2>": (VC, "test_few_splits", ""),
