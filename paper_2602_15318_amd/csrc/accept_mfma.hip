@@ -342,7 +342,16 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
   const unsigned char *const hid0 = (const unsigned char *)a.hidden + (int64_t)row0 * row_bytes;
   const unsigned int hid_bytes = (unsigned int)min(BM, a.M - row0) * row_bytes;
   u32x4 sg[kLd];
-  int is_tile = 0, is_k = 0;                                 // the step the next issue() fetches
+  // Rows of about a multiple of 4 KB, up to 64 hidden rows: the workgroups of an XCD start three steps apart and walk the
+  // hidden size round.  All of them at one column of such rows meet in a few of the memory channels; at other widths the
+  // columns of a step lie spread and this changes nothing (0.98 to 1.02).  us with the finalize pass, together / apart:
+  // 36 rows of 2,048 x 64,003 61 / 52, 64 rows 60 / 52, 48 of 4,096 x 64,000 112 / 91, 24 of 6,144 x 32,000 83 / 77.  One
+  // step apart 56, two 54, five 53 at the first.  With 128 rows 72 / 70 (100 of 2,048), 137 / 134 (128 of 4,096), but the
+  // scalar work of it costs the other widths (124 of 3,584 x 152,064 273 / 281); 256 rows wait for their sums.
+  constexpr bool kApart = kDirect && BM <= 64;
+  const bool apart = kApart && ((row_bytes + 256u) & 4095u) <= 512u;
+  const int k_first = apart ? __builtin_amdgcn_readfirstlane(3 * (stream >> 3) % nk) : 0;
+  int is_tile = 0, is_k = k_first;                                 // the step the next issue() fetches
   auto issue = [&](int buf) {
     const int v0 = (stream + min(is_tile, max(n_tiles - 1, 0)) * n_streams) * VT;
     const int rows = min(VT, max(V - v0, 0));
@@ -368,7 +377,8 @@ lm_head_tiled_kernel(AcceptArgs a, int blocks_m) {
       for (int j = 0; j < kLdM; ++j)
         sg[kLdV + j] = __builtin_amdgcn_raw_buffer_load_b128(rs_m, off + (unsigned int)(kLdRows * j) * row_bytes, 0, 0);
     }
-    if (++is_k == nk) { is_k = 0; ++is_tile; }
+    if (++is_k == nk) is_k = 0;
+    if (is_k == k_first) ++is_tile;
   };
   auto stash = [&]() {
     unsigned char *p = smem + ld_row * kRow + ((ld_pos ^ gm_swz<kRow>(ld_row)) << 4);

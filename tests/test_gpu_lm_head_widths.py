@@ -106,6 +106,15 @@ def test_rows_straight_to_lds(sp, H, V, M):
     assert torch.all((ids == got[:, None].to(ids.dtype)).any(dim=1))
 
 
+@pytest.mark.parametrize("H,M", [(1920, 33), (1928, 33), (2040, 64), (2048, 33), (2056, 64), (2176, 40), (2184, 40), (4096, 48),
+                                 (6144, 17)])
+@pytest.mark.parametrize("V", [30011, 140001])
+def test_columns_walked_round(sp, H, V, M):
+    """Rows within 256 bytes of a multiple of 4 KB (and just outside): workgroups that start at different columns, with a short
+    last step in the middle of a tile's walk, one tile per workgroup and several."""
+    test_rows_straight_to_lds(sp, H, V, M)
+
+
 @pytest.mark.parametrize("H", [256, 520, 1000, 2568, 3584, 5120])
 @pytest.mark.parametrize("M", [1, 17, 33, 65, 129, 300])
 @pytest.mark.parametrize("dtype,limit", [("bfloat16", 0.62e-7), ("float32", 0.9e-7)])
