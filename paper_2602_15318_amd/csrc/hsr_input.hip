@@ -434,6 +434,10 @@ hipError_t launch_draft_qkv(int dtype, const DraftQkvArgs &a, hipStream_t st) {
   const int rbs = (a.M + 15) / 16;
   const int n_heads = a.Hq + 2 * a.Hkv;
   if (dtype == SPARROW_BF16 && a.M == 1) return launch_draft_qkv_any(a, st);      // a wavefront per rotary pair
+  // Two to eight rows whose weights take one workgroup per compute unit: one slice a wavefront, all at once (6 rows of 4,096,
+  // 16/4 heads of 64 13.4 -> 9.0 us).  With two per compute unit, which do not fit it side by side, the other way round: 6 rows
+  // of 3,584, 28/4 of 128 15.8 against 12.7, 4 of 4,096, 32/8 of 128 17.7 against 15.5.
+  if (hsr_mfma_supported(dtype, a.H) && a.M <= 8 && n_heads * (a.d / 2) <= 2048) return launch_draft_qkv_any(a, st);
   if (hsr_mfma_supported(dtype, a.H)) {
     // two tiles per workgroup (d / 16 tiles per head: an even number): 144 workgroups at 36 heads
     // of 128 stay within one round on 256 compute units

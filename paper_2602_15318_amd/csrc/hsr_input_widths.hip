@@ -22,7 +22,7 @@
 // pair instead (QKV: at every width), two to four rows of FC a wavefront per two features.
 //
 // Measured (FC + QKV, weights from memory; one plain-ALU wavefront per feature before): hidden 2,560, 40/8 heads of 64,
-// six rows 141 + 67 -> 10.3 + 9.5 us, one row 56 + 22 -> 8.1 + 6.2; hidden 5,120, 40/8 heads of 128, 16 rows 823 + 447 ->
+// six rows 141 + 67 -> 8.5 + 7.7 us, one row 56 + 22 -> 8.1 + 6.2; hidden 5,120, 40/8 heads of 128, 16 rows 823 + 447 ->
 // 38.1 + 34.7 us; hidden 1,024, 16/4 heads of 64, six rows 36 + 21 -> 5.3 + 6.3.
 #include <algorithm>
 
@@ -303,6 +303,225 @@ draft_qkv_any_kernel(DraftQkvArgs a) {
     }
   };
   skinny_gemm<true, kFew>((const bf16_t *)a.w, H, wrow, xload, (const bf16_t *)a.gamma, row0, a.M, smem, epi);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Few activation rows (at most 8) whose weights are all on their way at once: a wavefront per slice of kCols columns, one
+// slice each, and as many weight rows per workgroup (at most 16) as give every compute unit the same number.  skinny_gemm
+// brings the slices in rounds (10 of 5,120 columns by 5 wavefronts), deals whole tiles of 16 rows (160 workgroups for 2,560
+// features, 320 in two rounds for 5,120) and, for QKV, makes the activations' terms behind the weights, on five wavefronts of
+// which two share a SIMD; slices of 256 columns halve what a wavefront makes, and the empty statements keep it under the
+// weights' flight.  us, skinny_gemm / here: FC of 6 rows, 2,560 columns 10.0 / 8.5, 5 of 1,536 6.75 / 5.7, 8 of 2,048 8.55 /
+// 7.6, 5 of 3,072 11.7 / 10.05; QKV of 6 rows, 2,560 columns, 40/8 heads of 64 9.25 / 7.7, 2 of it 9.2 / 7.6, 5 of 3,072,
+// 24/8 of 128 17.1 / 12.9, 3 of 256, 4/1 of 64 5.6 / 4.4.  QKV with slices of 512: 9.0 (223 registers).
+// ---------------------------------------------------------------------------------------------
+constexpr int kOnceWaves = 16;
+
+// Rows per workgroup for n rows (or pairs), at most `most`: a whole number of workgroups per compute unit, all of one size.
+inline int even_rows(int n, int most) {
+  const int per_cu = (n + 256 * most - 1) / (256 * most);
+  return (n + 256 * per_cu - 1) / (256 * per_cu);
+}
+constexpr int once_lds_bytes(int nw, int rows, int cols) { return nw * rows * cols * 2 + nw * 1024 + nw * 64; }
+
+// Wavefront 0 runs epi(D, sum): as skinny_gemm's, lane n + 16 c4 with n < 8 has the results of activation row n and weight rows
+// 4 c4 + i.  rows: how many are fetched (the others of 16 read as zero and cost no memory), stg_rows: at least that;
+// at(r): element offset of fetched row r (uniform); staged(x): the fetched row that is row x of the product (any row in range
+// where the result is not used).  The activations of a slice of kCols columns are shared out as in skinny_gemm's kFew.
+// Operands of the end come in by more(), called when the weights have been asked for.
+template <bool kNorm, int kCols, class At, class Staged, class XLoad, class More, class Epi>
+__device__ __forceinline__ void skinny_once(const bf16_t *W, int K, int rows, int stg_rows, At at, Staged staged, XLoad xload,
+                                            const bf16_t *gamma, int M, unsigned char *smem, More more, Epi epi) {
+  constexpr int kPerLoad = 512 / kCols, kLoads = 16 / kPerLoad, kLanes = 64 / kPerLoad;      // rows of a load, loads, lanes of a row
+  constexpr int kX = kCols / 64, kBytes = 2 * kCols;                                         // activation k-steps of a lane
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = (int)blockDim.x >> 6;
+  const int n = lane & 15, c4 = lane >> 4;
+  unsigned char *stg = smem + w * stg_rows * kBytes;
+  f32x4 *red = reinterpret_cast<f32x4 *>(smem + nw * stg_rows * kBytes);                     // [nw][64]
+  float *ssq_lds = reinterpret_cast<float *>(smem + nw * stg_rows * kBytes + nw * 1024);     // [nw][16]
+  const int m = n & 7;
+  const bool m_ok = m < M;
+  u32x4 buf[kLoads], xr[kX], gr[kNorm ? kX : 1];
+  const int sub = lane / kLanes, ld_ch = lane % kLanes;    // row of a load, 16-byte chunk of it
+  auto issue = [&]() __attribute__((always_inline)) {
+    const int64_t first = at(0);
+    const __amdgpu_buffer_rsrc_t rs = weight_rows(W + first);
+    const int k = kCols * w + 8 * ld_ch;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int r0 = i * kPerLoad, r1 = r0 + kPerLoad - 1;
+      const unsigned int o0 = r0 < rows ? (unsigned int)((at(r0) - first) * 2) : kPastEnd;
+      const unsigned int o1 = r1 < rows ? (unsigned int)((at(r1) - first) * 2) : kPastEnd;
+      const unsigned int o = sub ? o1 : o0;
+      buf[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, k < K && o != kPastEnd ? o + (unsigned int)k * 2u : kPastEnd, 0, 2);
+    }
+  };
+  auto load_x = [&]() __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs_g = weight_rows(gamma);
+#pragma unroll
+    for (int ks = 0; ks < kX; ++ks) {
+      const int k = kCols * w + 32 * ks + 8 * c4 + kCols / 2 * (n >> 3);
+      xr[ks] = xload(m, k, m_ok && k < K);
+      if (kNorm) gr[ks] = __builtin_amdgcn_raw_buffer_load_b128(rs_g, k < K ? (unsigned int)k * 2u : kPastEnd, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  float ssq = 0.f;
+  if (kNorm) {                            // activations first: their terms are made under the weights' flight
+    load_x();
+    issue();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < kX; ++ks) {
+      float xf[8], gf[8], lo[8];
+      unsigned int hb[8];
+      Elem<bf16_t>::unpack(xr[ks], xf);
+      Elem<bf16_t>::unpack(gr[kNorm ? ks : 0], gf);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        ssq = fmaf(xf[e], xf[e], ssq);
+        const float u = xf[e] * gf[e];
+        hb[e] = __float_as_uint(u) & 0xffff0000u;
+        lo[e] = low_term(u, __uint_as_float(hb[e]));
+      }
+      xr[ks] = (u32x4){(hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3], (hb[4] >> 16) | hb[5], (hb[6] >> 16) | hb[7]};
+      gr[kNorm ? ks : 0] = (u32x4){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
+      asm volatile("" : "+v"(xr[ks]), "+v"(gr[kNorm ? ks : 0]));     // here, and not where it is used, behind the weights
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {                                // weights first: the activations' addresses wait for the token ids
+    issue();
+    __builtin_amdgcn_sched_barrier(0);
+    load_x();
+  }
+  if (w == 0) more();
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    const int r = i * kPerLoad + sub;
+    if (r < rows) *reinterpret_cast<u32x4 *>(stg + r * kBytes + (((ld_ch & ~15) | ((ld_ch & 15) ^ r)) << 4)) = buf[i];
+  }
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  const int nr = staged(n);
+#pragma unroll
+  for (int kh = 0; kh < kX; ++kh)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int ch = 4 * (kX * h + kh) + c4;
+      const bf16x8 a = *reinterpret_cast<const bf16x8 *>(stg + nr * kBytes + (((ch & ~15) | ((ch & 15) ^ nr)) << 4));
+      acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, xr[kh]), acc[h], 0, 0, 0);
+      if (kNorm) acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, gr[kNorm ? kh : 0]), acc[h], 0, 0, 0);
+    }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[1][e] = lane_xor<8>(acc[1][e], lane);
+  red[w * 64 + lane] = acc[0] + acc[1];
+  if (kNorm) {
+    ssq += lane_xor<8>(ssq, lane);
+    ssq += lane_xor<16>(ssq, lane);
+    ssq += lane_xor<32>(ssq, lane);
+    if (c4 == 0) ssq_lds[w * 16 + n] = ssq;
+  }
+  __syncthreads();
+  if (w != 0) return;
+  float s2 = 0.f;
+  if (kNorm)
+    for (int ww = 0; ww < nw; ++ww) s2 += ssq_lds[ww * 16 + n];
+  f32x4 sum = red[lane];
+  for (int ww = 1; ww < nw; ++ww) sum += red[ww * 64 + lane];
+  epi(sum, s2);
+}
+
+// Eq. 1, five to eight rows
+__global__ void __launch_bounds__(kOnceWaves * 64)
+hsr_fc_once_kernel(HsrFcArgs a, int rows) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int H = a.H, f_tile = (int)blockIdx.x * rows;
+  const bf16_t *E = (const bf16_t *)a.embed, *Hp = (const bf16_t *)a.h_prev;
+  const int lane = threadIdx.x & 63, n = lane & 15, c4 = lane >> 4;
+  int tok = (n & 7) < a.M ? a.token_ids[n & 7] : 0;
+  tok = min(max(tok, 0), a.vocab - 1);
+  auto at = [&](int r) { return (int64_t)(f_tile + r) * (2 * H); };
+  auto xload = [&](int mm, int k, bool ok) -> u32x4 {          // eight columns lie in one half of the concatenation
+    const int kk = ok ? k : 0, mr = ok ? mm : 0;
+    const u32x4 v = *(const u32x4 *)(kk < H ? E + (int64_t)tok * H + kk : Hp + (int64_t)mr * H + (kk - H));
+    return ok ? v : (u32x4){0u, 0u, 0u, 0u};
+  };
+  const int left = min(rows, H - f_tile);                      // rows of this workgroup (even, as H and rows are)
+  unsigned int bw[2] = {0u, 0u};
+  auto more = [&]() {
+    if (a.bias == nullptr) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (4 * c4 + 2 * i < left) bw[i] = *(const unsigned int *)((const bf16_t *)a.bias + f_tile + 4 * c4 + 2 * i);
+  };
+  auto epi = [&](f32x4 r, float) {
+    if (n >= a.M) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (4 * c4 + 2 * i < left)
+        *(unsigned int *)((bf16_t *)a.z + (int64_t)n * H + f_tile + 4 * c4 + 2 * i) =
+            pack_bf16x2(r[2 * i] + bf16lo_to_f32(bw[i]), r[2 * i + 1] + bf16hi_to_f32(bw[i]));
+  };
+  auto staged = [&](int x) { return min(x, left - 1); };
+  skinny_once<false, 512>((const bf16_t *)a.w, 2 * H, left, rows, at, staged, xload, nullptr, a.M, smem, more, epi);
+}
+
+// Draft layer input, two to eight rows: `pairs` rotary pairs per workgroup, numbered through the heads; weight row j of a tile
+// is pair j's first feature, row 8 + j its second, so that both sit in lanes l and l ^ 32 of the result.
+__global__ void __launch_bounds__(kOnceWaves * 64)
+draft_qkv_once_kernel(DraftQkvArgs a, int pairs) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int H = a.H, d = a.d, half = d >> 1, sh = d == 128 ? 6 : 5;
+  const int n_pairs = (a.Hq + 2 * a.Hkv) * half, p_tile = (int)blockIdx.x * pairs;
+  const int lane = threadIdx.x & 63, n = lane & 15, c4 = lane >> 4, hi = c4 >> 1;
+  const int left = min(pairs, n_pairs - p_tile);
+  auto at = [&](int r) {
+    const int second = r >= pairs, p = p_tile + min(r - (second ? pairs : 0), left - 1);
+    return (int64_t)((p >> sh) * d + (p & (half - 1)) + (second ? half : 0)) * H;
+  };
+  auto staged = [&](int x) { return (x >> 3) * pairs + min(x & 7, pairs - 1); };
+  const __amdgpu_buffer_rsrc_t rs_z = weight_rows((const bf16_t *)a.z);
+  auto xload = [&](int mm, int k, bool ok) -> u32x4 {
+    return __builtin_amdgcn_raw_buffer_load_b128(rs_z, ok ? (unsigned int)(mm * H + k) * 2u : kPastEnd, 0, 0);
+  };
+  const bool m_ok = n < a.M;
+  bf16_t b[4] = {0, 0, 0, 0};
+  float cs[4], sn[4];
+  auto more = [&]() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = p_tile + min(4 * (c4 & 1) + i, left - 1), f = p & (half - 1);
+      if (a.bias != nullptr) b[i] = ((const bf16_t *)a.bias)[(p >> sh) * d + hi * half + f];
+      cs[i] = a.rope_cos[(m_ok ? n : 0) * half + f];
+      sn[i] = a.rope_sin[(m_ok ? n : 0) * half + f];
+    }
+  };
+  auto epi = [&](f32x4 res, float ssq) {
+    const float rstd = 1.0f / sqrtf(ssq / (float)H + a.eps);
+    int kv_row = 0;
+#pragma unroll
+    for (int mm = 0; mm < 8; ++mm) {
+      const int r = a.kv_rows[mm];
+      if (n == mm) kv_row = r;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = 4 * (c4 & 1) + i, p = p_tile + min(j, left - 1), hd = p >> sh, feat = hi * half + (p & (half - 1));
+      const float y = fmaf(res[i], rstd, bf16_to_f32(b[i]));
+      const float partner = lane_xor<32>(y, lane);      // the other half of the rotary pair
+      const bool is_v = hd >= a.Hq + a.Hkv;
+      const float o = is_v ? y : hi ? fmaf(partner, sn[i], y * cs[i]) : fmaf(-partner, sn[i], y * cs[i]);
+      if (!m_ok || j >= left) continue;
+      if (hd < a.Hq) {
+        ((bf16_t *)a.q_out)[((int64_t)n * a.Hq + hd) * d + feat] = f32_to_bf16(o);
+      } else {
+        const int c = is_v ? hd - a.Hq - a.Hkv : hd - a.Hq;
+        ((bf16_t *)(is_v ? a.v_cache : a.k_cache))[(int64_t)kv_row * a.stride_tok + (int64_t)c * a.stride_head + feat] = f32_to_bf16(o);
+      }
+    }
+  };
+  skinny_once<true, 256>((const bf16_t *)a.w, H, 2 * pairs, 2 * pairs, at, staged, xload, (const bf16_t *)a.gamma, a.M, smem, more, epi);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -614,6 +833,16 @@ hipError_t launch_hsr_fc_any(const HsrFcArgs &a, hipStream_t st) {
     if (slices <= 4) return a.M <= 2 ? launch_few<2, 4>(a, st) : launch_few<4, 4>(a, st);
     return a.M <= 2 ? launch_few<2, 10>(a, st) : launch_few<4, 10>(a, st);
   }
+  // five to eight rows: at once, where the slices' wavefronts fit a workgroup and their rows its 160 KB (up to 3,072 columns)
+  if (a.M <= 8 && slices <= kOnceWaves) {
+    const int rows = (even_rows(a.H, 16) + 1) / 2 * 2;
+    if (once_lds_bytes(slices, rows, kSlice) <= 160 * 1024) {
+      static const hipError_t attr = hipFuncSetAttribute((const void *)hsr_fc_once_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (attr != hipSuccess) return attr;
+      hipLaunchKernelGGL(hsr_fc_once_kernel, dim3((a.H + rows - 1) / rows), dim3(slices * 64), once_lds_bytes(slices, rows, kSlice), st, a, rows);
+      return hipGetLastError();
+    }
+  }
   return launch_skinny<hsr_fc_any_kernel>(skinny_waves(K), dim3((a.H + 15) / 16, (a.M + 15) / 16), a, st);
 }
 
@@ -629,6 +858,14 @@ hipError_t launch_draft_qkv_any(const DraftQkvArgs &a, hipStream_t st) {
     else if (slices <= 4) hipLaunchKernelGGL(draft_qkv_gemv_kernel<4>, grid, block, 0, st, a);
     else if (slices <= 7) hipLaunchKernelGGL(draft_qkv_gemv_kernel<7>, grid, block, 0, st, a);
     else hipLaunchKernelGGL(draft_qkv_gemv_kernel<8>, grid, block, 0, st, a);
+    return hipGetLastError();
+  }
+  const int nw = (a.H + 255) / 256;          // two to eight rows, up to 4,096 columns: at once
+  if (a.M <= 8 && nw <= kOnceWaves) {
+    const int n_pairs = n_heads * (a.d / 2), pairs = even_rows(n_pairs, 8);
+    static const hipError_t attr = hipFuncSetAttribute((const void *)draft_qkv_once_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(draft_qkv_once_kernel, dim3((n_pairs + pairs - 1) / pairs), dim3(nw * 64), once_lds_bytes(nw, 2 * pairs, 256), st, a, pairs);
     return hipGetLastError();
   }
   const dim3 grid(n_heads * (a.d / 16), (a.M + 15) / 16);

@@ -124,6 +124,16 @@ def test_draft_qkv_of_few_rows(sp, H, Hq, Hkv, d, M):
     test_draft_qkv_append(sp, H, Hq, Hkv, d, M)
 
 
+@pytest.mark.parametrize("H,Hq,Hkv,d", [(24, 3, 1, 64), (264, 7, 1, 128), (2560, 40, 8, 64), (3072, 24, 8, 128), (3080, 5, 5, 64),
+                                        (4088, 9, 3, 64), (4096, 16, 4, 64), (3584, 16, 8, 128)])
+@pytest.mark.parametrize("M", [2, 5, 8])
+def test_one_slice_a_wavefront(sp, H, Hq, Hkv, d, M):
+    """Two to eight rows, all weights at once: 1 to 8 rotary pairs and 2 to 12 features a workgroup, the last one with fewer,
+    tiles that cross heads, short last slices, 1 to 16 wavefronts."""
+    test_hsr_fc(sp, H, M)
+    test_draft_qkv_append(sp, H, Hq, Hkv, d, M)
+
+
 @pytest.mark.parametrize("H,Hq,Hkv,d", [(3584, 28, 4, 128), (4096, 6, 2, 64)])
 def test_draft_qkv_of_one_row_at_whole_slices(sp, H, Hq, Hkv, d):
     test_draft_qkv_append(sp, H, Hq, Hkv, d, 1)

@@ -164,14 +164,16 @@ COVERAGE = {
     "draft_qkv_mfma_kernel<7, 1>": (H, "test_draft_qkv_append", "bf16-28-4-128-3584"),
     "draft_qkv_mfma_kernel<8, 1>": (H, "test_draft_qkv_append", "bf16-32-8-128-4096"),
     # hidden sizes other than 3,584 and 4,096; one row: <slices of a weight row in flight>
-    "hsr_fc_any_kernel": (HW, "test_hsr_fc", "five rows and more"),
+    "hsr_fc_any_kernel": (HW, "test_hsr_fc", "nine rows and more, five above 3,072"),
     # <rows, slices in flight>
     "hsr_fc_few_kernel<2, 4>": (HW, "test_hsr_fc", "two rows, hidden up to 1,024"),
     "hsr_fc_few_kernel<4, 4>": (HW, "test_hsr_fc_of_few_rows", "three and four rows, hidden up to 1,024"),
     "hsr_fc_few_kernel<2, 10>": (HW, "test_hsr_fc", "two rows"),
     "hsr_fc_few_kernel<4, 10>": (HW, "test_hsr_fc_of_few_rows", "three and four rows"),
     # <at most eight rows>
-    "draft_qkv_any_kernel<true>": (HW, "test_draft_qkv_of_few_rows", "two to eight rows (from three up to 1,024 columns)"),
+    "draft_qkv_any_kernel<true>": (HW, "test_draft_qkv_append", "two to eight rows above 4,096 columns"),
+    "draft_qkv_once_kernel": (HW, "test_one_slice_a_wavefront", "two to eight rows (from three up to 1,024 columns)"),
+    "hsr_fc_once_kernel": (HW, "test_one_slice_a_wavefront", "five to eight rows, hidden up to 3,072"),
     "draft_qkv_any_kernel<false>": (HW, "test_draft_qkv_append", "more"),
     "hsr_fc_any_gemv_kernel<4>": (HW, "test_hsr_fc", "hidden up to 1,024"),
     "hsr_fc_any_gemv_kernel<8>": (HW, "test_hsr_fc", "hidden 1,280"),
