@@ -59,6 +59,10 @@ __device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int slot) {
   return b;
 }
 
+// rho / g for rows of one KV head (or group / slots of a flat grid), by the reciprocal: half a step off, which is far more
+// than what two roundings of the product are off while quotient x g stays below 2^21 (g below 32,768 at 64 rows).
+__device__ __forceinline__ int row_div(int rho, float inv_g) { return (int)(((float)rho + 0.5f) * inv_g); }
+
 // Natural-log sum-exp of a row: reference point m (log2 units) and sum l.  kWide: rounded once at its full
 // size.  (m may lie below the row's maximum; log2(l) is then larger than in the plain-ALU kernels and so are
 // the roundings of the other form.  Root mean square error over 6,000 fp32 tokens, 60 rows, heads of 128:

@@ -82,10 +82,6 @@ struct PieceTable {
   int32_t piece[SPARROW_MAX_BATCH];
 };
 
-// rho / g for rows of one KV head (or group / slots of a flat grid), by the reciprocal: half a step off, which is far more
-// than what two roundings of the product are off while quotient x g stays below 2^21 (g below 32,768 at 64 rows).
-__device__ __forceinline__ int row_div(int rho, float inv_g) { return (int)(((float)rho + 0.5f) * inv_g); }
-
 // What `shape` of the partial pass holds beside the row blocks (from bit 3 up)
 constexpr int kShapeFlat = 1, kShapeDirect = 2, kShapeTable = 4, kShapeBits = 3;
 
