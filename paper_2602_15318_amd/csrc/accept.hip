@@ -84,8 +84,12 @@ __global__ void __launch_bounds__(256) lm_head_generic_kernel(AcceptArgs a) {
 }
 
 // One workgroup of 16 wavefronts per sequence: wavefront w reduces the candidates of its rows w,
-// w+16, ... (64 lanes stride over the row's candidates, then a butterfly), then one thread walks the
+// w+16, ... (64 lanes stride over the row's candidates, then a butterfly), then one wavefront walks the
 // sequence's chain / tree.  (One workgroup for all sequences took 18 us at 8 x 31 rows.)
+// What bounds it: the loads of one compute unit (16 cycles an instruction; four candidates by one where rows are whole
+// 16 bytes) and the walk, in which lane j now holds node j and a ballot finds the child (a thread that looked through the
+// nodes in LDS paid some 100 cycles for each).  us in a trace, before / now: 8 trees of 30 nodes, 256 candidates
+// a row 8.2 / 4.8, a chain of 4, 16 candidates 3.6 / 2.2, of 8, 256 candidates 4.3 / 4.2.
 __global__ void __launch_bounds__(1024) accept_finalize_kernel(AcceptArgs a) {
   __shared__ int32_t tgt[SPARROW_MAX_NQ + 1];
   __shared__ int32_t dr_s[SPARROW_MAX_NQ], par_s[SPARROW_MAX_NQ];
@@ -101,60 +105,74 @@ __global__ void __launch_bounds__(1024) accept_finalize_kernel(AcceptArgs a) {
   // two rows per wavefront at a time (rows r and r + 16): their candidate loads are in flight
   // together, and the 64-lane argmax runs on the vector ALU (maximum, then the lowest index
   // among the lanes that hold it)
-  constexpr int kU = 16;                                 // independent loads in flight per lane and row
+  const int per = (a.n_cand & 3) == 0 ? 256 : 64;        // candidates of a load: rows of whole 16 bytes, or not
   for (int r0 = w; r0 < n_rows; r0 += 32) {
-    float bv[2];
-    int bi[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) { bv[h] = -INFINITY; bi[h] = 0x7fffffff; }
-    for (int c0 = lane; c0 < a.n_cand; c0 += 64 * kU) {
-      float v[2][kU];
-      int i[2][kU];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int r = base + min(r0 + 16 * h, n_rows - 1);   // the second row may not exist: a valid duplicate
-        const float *cv = a.cand_val + (int64_t)r * a.n_cand;
-        const int32_t *ci = a.cand_idx + (int64_t)r * a.n_cand;
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const int c = c0 + 64 * u;
-          const bool in = c < a.n_cand;
-          v[h][u] = in ? cv[c] : -INFINITY;
-          i[h][u] = in ? ci[c] : 0x7fffffff;
-        }
-      }
+    const int rows = r0 + 16 < n_rows ? 2 : 1;
+    float bv[2] = {-INFINITY, -INFINITY};
+    int bi[2] = {0x7fffffff, 0x7fffffff};
+    constexpr int kU = 4;                                // loads in flight per row; those past the row's end are left out
+    for (int c0 = 0; c0 < a.n_cand; c0 += per * kU) {
+      f32x4 v[2][kU];
+      u32x4 x[2][kU];
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int u = 0; u < kU; ++u)
-          if (v[h][u] > bv[h] || (v[h][u] == bv[h] && i[h][u] < bi[h])) { bv[h] = v[h][u]; bi[h] = i[h][u]; }
+        for (int u = 0; u < kU; ++u) {
+          if (h >= rows || c0 + per * u >= a.n_cand) continue;             // (uniform)
+          const int64_t at = (int64_t)(base + r0 + 16 * h) * a.n_cand;
+          const int c = c0 + per * u + (per == 256 ? 4 * lane : lane);
+          v[h][u] = (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+          x[h][u] = (u32x4){0x7fffffffu, 0x7fffffffu, 0x7fffffffu, 0x7fffffffu};
+          if (c >= a.n_cand) continue;
+          if (per == 256) {
+            v[h][u] = *reinterpret_cast<const f32x4 *>(a.cand_val + at + c);
+            x[h][u] = *reinterpret_cast<const u32x4 *>(a.cand_idx + at + c);
+          } else {
+            v[h][u][0] = a.cand_val[at + c];
+            x[h][u][0] = (unsigned int)a.cand_idx[at + c];
+          }
+        }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          if (h >= rows || c0 + per * u >= a.n_cand) continue;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int i = (int)x[h][u][e];
+            if (v[h][u][e] > bv[h] || (v[h][u][e] == bv[h] && i < bi[h])) { bv[h] = v[h][u][e]; bi[h] = i; }
+          }
+        }
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
+      if (h >= rows) continue;
       const int r = r0 + 16 * h;
       const float wv = wave_max_valu(bv[h]);
       const int wi = wave_min_valu(bv[h] == wv ? bi[h] : 0x7fffffff);
-      if (lane == 0 && r < n_rows) { tgt[r] = wi; a.target_ids[base + r] = wi; }
+      if (lane == 0) { tgt[r] = wi; a.target_ids[base + r] = wi; }
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    int32_t *path = a.accept_path + (int64_t)b * a.n_q;
-    int cur = -1, len = 0;
-    // every accepted node has a larger index than its parent: at most n_q steps
+  if (w == 0) {
+    // lane j: node j and its row's token.  The child is the lowest node that fits; it has a larger index than its
+    // parent, so there are at most n_q steps.
+    const bool node = lane < a.n_q;
+    const int dr = node ? dr_s[lane] : -1, par = node ? par_s[lane] : -2, mine = node ? tgt[lane + 1] : 0;
+    int cur = -1, len = 0, tok = __builtin_amdgcn_readfirstlane(tgt[0]), path = -1;
     for (;;) {
-      const int tok = tgt[cur + 1];
-      int next = -1;
-      for (int j = cur + 1; j < a.n_q; ++j) {
-        if (par_s[j] == cur && dr_s[j] == tok) { next = j; break; }
-      }
-      if (next < 0) break;
-      path[len++] = next;
-      cur = next;
+      const unsigned long long fit = __builtin_amdgcn_ballot_w64(node && lane > cur && par == cur && dr == tok);
+      if (fit == 0ull) break;
+      cur = __builtin_ctzll(fit);
+      if (lane == len) path = cur;
+      ++len;
+      tok = __builtin_amdgcn_readlane(mine, cur);
     }
-    a.accept_len[b] = len;
-    a.bonus_id[b] = tgt[cur + 1];
-    for (int j = len; j < a.n_q; ++j) path[j] = -1;
+    if (node) a.accept_path[(int64_t)b * a.n_q + lane] = path;
+    if (lane == 0) {
+      a.accept_len[b] = len;
+      a.bonus_id[b] = tok;
+    }
   }
 }
 

@@ -246,13 +246,14 @@ tree_select_small_kernel(SelectArgs a) {
 // found bit by bit on order-preserving integer keys (the number of entries that reach a candidate: one ballot
 // per register); entries above it are kept, and of those equal to it the first in pool order.  No barrier and
 // no rank counting: 200 entries 8 us, 689 entries 9.4 to 12, against 9.5 and 30 for a workgroup that ranked by
-// counting.
+// counting.  With four registers for up to 256 entries, without a test for each of 32, 200 entries
+// take 5.8 in a trace (32 registers 11.5).
+template <int kRegs>
 __global__ void __launch_bounds__(64)
 tree_select_kernel(SelectArgs a) {
-  constexpr int kRegs = kTreeMaxPool / 64;
-  __shared__ int new_id[kTreeMaxPool];
+  __shared__ int new_id[64 * kRegs];
   const int lane = threadIdx.x;
-  const int n = a.n_pool, keep = min(a.total, n), regs = (n + 63) / 64;
+  const int n = a.n_pool, keep = min(a.total, n), regs = kRegs <= 4 ? kRegs : (n + 63) / 64;
   unsigned int key[kRegs];                // 0 for lanes past the pool: below every score's key
 #pragma unroll
   for (int r = 0; r < kRegs; ++r) {
@@ -324,7 +325,8 @@ hipError_t launch_tree_expand(const ExpandArgs &a, hipStream_t st) {
 
 hipError_t launch_tree_select(const SelectArgs &a, hipStream_t st) {
   if (a.n_pool <= kSelectSmall) hipLaunchKernelGGL(tree_select_small_kernel, dim3(1), dim3(64), 0, st, a);
-  else hipLaunchKernelGGL(tree_select_kernel, dim3(1), dim3(64), 0, st, a);
+  else if (a.n_pool <= 256) hipLaunchKernelGGL(tree_select_kernel<4>, dim3(1), dim3(64), 0, st, a);
+  else hipLaunchKernelGGL(tree_select_kernel<kTreeMaxPool / 64>, dim3(1), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 

@@ -66,6 +66,12 @@ def test_selection_sizes(sp, n, total):
             assert got.cpu().tolist() == list(want), (n, total, kind)
 
 
+@pytest.mark.parametrize("n", [129, 191, 192, 193, 255, 256, 257])
+@pytest.mark.parametrize("total", [1, 30, 64])
+def test_selection_of_pools_around_four_registers(sp, n, total):
+    test_selection_sizes(sp, n, total)
+
+
 @pytest.mark.parametrize("width", [1, 3, 13, 16])
 def test_expansion_widths(sp, width):
     import torch

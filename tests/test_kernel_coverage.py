@@ -152,7 +152,8 @@ COVERAGE = {
     "topk_chunk_kernel<16>": (TS, "test_topk_vocabularies", "up to 262,144"),
     "topk_merge_kernel": (T, "test_draft_topk", ""),
     "tree_expand_kernel": (T, "test_tree_expand_and_select", ""),
-    "tree_select_kernel": (TS, "test_selection_sizes", "pools above 128"),
+    "tree_select_kernel<4>": (TS, "test_selection_sizes", "pools above 128"),
+    "tree_select_kernel<32>": (TS, "test_selection_sizes", "pools above 256"),
     "tree_select_small_kernel": (T, "test_tree_expand_and_select", "pools up to 128"),
     # ---- draft input and post-accept commit
     "hsr_fc_generic_kernel<float>": (H, "test_hsr_fc", "f32-4-1-64-256"),
