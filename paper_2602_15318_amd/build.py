@@ -13,6 +13,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsparrow.so")
 NATIVE = os.path.join(HERE, "_native.so")
 
+# The preload count puts the leading scalar arguments of a kernel into scalar registers at launch: a
+# wavefront's first load waits for no load of arguments (0.3 to 0.4 us on kernels of 6 to 13 us).
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-mllvm", "-amdgpu-kernarg-preload-count=16",

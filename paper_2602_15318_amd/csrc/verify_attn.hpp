@@ -83,7 +83,7 @@ int verify_f32_row_blocks(int R);
 int verify_mfma_row_blocks(int dtype, int R);
 // Its partials use a tiled layout of their own: workspace floats per (split, KV head, block of 64
 // rows) unit, and the matching combine pass.
-constexpr int kMlFloats = 3;              // per row of a partial: max, sum, output scale
+constexpr int kMlFloats = 3;              // per row of a partial: max, sum, output scales of the two stored halves (two bf16)
 int64_t verify_mfma_unit_floats_o(int dtype, int head_dim);
 int64_t verify_mfma_unit_floats_ml();
 hipError_t launch_verify_combine_mfma(int dtype, const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
