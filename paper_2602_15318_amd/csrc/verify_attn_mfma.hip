@@ -753,14 +753,13 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
 // loads, a split's (m, l, c) is fetched and turned into a weight by one of the four lanes that need it and handed to the
 // others across lanes, and the arguments that the first load needs arrive in registers (leading scalars of the kernel).
 //
-// Up to 32 splits: one workgroup per (sequence, KV head, 16-row tile, kTiles d-tiles of 16); wavefront ws merges splits ws,
+// Up to 16 splits: one workgroup per (sequence, KV head, 16-row tile, kTiles d-tiles of 16); wavefront ws merges splits ws,
 // ws + kWaves, ..., four of them at a time, and the wavefronts' states meet in LDS.
 // kWaves = 1 and 2 (at most four and eight splits: batches, thousands of output tiles): two d-tiles each, as the number of
 // wavefronts sets the pace.  12 trees of 30 nodes over 4,099 tokens, 32/8 heads: 54.0 us a call with four wavefronts of one
 // d-tile, 49.2 with one of two (both with the partial pass); 12 of 2 over 700, 16/8 14.9 / 12.9.
-// kWaves = 4 and 8 (9 to 32 splits): two d-tiles, one with fp32 partials, whose loads are twice as wide; us a call,
-// loads of every lane's own (m, l, c) with 64-bit addresses / here: 30 nodes over 26,112 (32 splits) 27.1 / 26.5, 60 over
-// 12,000 (16) 25.1 / 24.2, four chains of 8 over 2,000 (16) 11.6 / 11.4.
+// kWaves = 4 (9 to 16 splits): two d-tiles, one with fp32 partials, whose loads are twice as wide; us a call, loads of every
+// lane's own (m, l, c) with 64-bit addresses / here: 60 nodes over 12,000 25.1 / 24.2.
 typedef __attribute__((ext_vector_type(3))) unsigned int u32x3;
 
 struct CombineArgs {                               // what a combine kernel's scalar arguments say, in its own terms
@@ -917,14 +916,19 @@ verify_combine_few_kernel(const unsigned char *part_o, const unsigned char *part
   combine_rows16<T, kD, kWaves>({part_o, part_ml, res, lse, ns_one, units, Hq, g, n_q, shape}, tab);
 }
 
-// More splits than that (and 17 to 32 of calls with few row blocks): one workgroup per (sequence, KV head, 4 rows, 32
+// More splits than that, and 9 to 16 of calls with few row blocks: one workgroup per (sequence, KV head, 4 rows, 32
 // columns), so that one sequence's few output rows fill the chip, 224 workgroups instead of 128 for a chain of 8 with 28/4
 // heads.  Four lanes of a column take four splits side by side, so that a wavefront merges 16 splits with four loads of
 // 16 bytes a lane (eight with fp32 partials) and one of (m, l, c).  Combine pass alone, us, 16 wavefronts over 16 rows and one
 // d-tile / here: chain of 8 over 26,112 tokens 4.1 / 2.75, of 5 over 8,192 3.8 / 2.5, of 4 over 12,000 4.0 / 2.7; with the
-// partial pass, one KV head, chain of 8 over 16,000 (256 splits) 16.8 / 12.6.  17 to 32 splits, 8 wavefronts over 16 rows
-// / here: up to 8 units (KV heads x row blocks of 64) a sequence 8.7 / 8.5 (chain of 8 over 2,000), four ragged chains of 8
-// over 2,000 11.9 / 11.4; 16 units (30 nodes over 5,000) 13.9 / 14.9.
+// partial pass, one KV head, chain of 8 over 16,000 (256 splits) 16.8 / 12.6.
+// Four rows are 64 bytes of a 128-byte line of the partials: the two workgroups of a line lie eight apart, on one XCD, so
+// that it comes to one L2 and not to two.  Neighbours / eight apart, us a call: chain of 8 over 26,112 16.2 / 15.8, of 5 over
+// 8,192 10.2 / 9.95, over 3,300 9.05 / 8.6, one KV head over 16,000 12.5 / 11.5, 16 nodes over 5,000 13.2 / 12.2.
+// Against wavefronts over 16-row tiles: 17 to 32 splits (eight of them) 30 nodes over 26,112 27.3 / 26.9, two of 30 over up to
+// 4,000 16.15 / 15.6, four of 20 over up to 6,000 23.9 / 23.6; 9 to 16 splits (four), 4 to 8 units (KV heads x row blocks of
+// 64) a chain of 5 over 600 7.5 / 7.3, of 8 over 900 8.0 / 7.65, four ragged of 8 over 2,000 10.9 / 10.8, but 28 units, 60
+// nodes over 5,000 17.5 / 17.7 and over 26,112 39.6 / 40.0.
 template <class T, int kD, int kWaves>
 __global__ void __launch_bounds__(64 * kWaves)
 verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *part_ml, void *res, float *lse, int ns_one, int units,
@@ -940,7 +944,8 @@ verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *par
   if (shape & 1) {                                 // sequences that differ
     s0 = tab.cu_split[b]; ns = tab.cu_split[b + 1] - s0;
   }
-  const int rows4 = blockIdx.x & 15, unit = blockIdx.x >> 4;   // four rows of unit KV head * rbs + row block
+  // four rows of unit KV head * rbs + row block
+  const int rows4 = (blockIdx.x & 7) * 2 + (blockIdx.x >> 3 & 1), unit = blockIdx.x >> 4;
   const int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & 3, c4 = (lane >> 2) & 3, ss = lane >> 4;
   const int64_t first = (int64_t)s0 * units + unit;
@@ -1144,8 +1149,8 @@ static hipError_t launch_combine(const VerifyArgs &a, const SeqTable &tab, hipSt
   if (max_ns > 128) go(verify_combine_long_kernel<T, kD, 16>, 16, 16, 2);
   else if (max_ns > 64) go(verify_combine_long_kernel<T, kD, 8>, 8, 16, 2);
   else if (max_ns > 32) go(verify_combine_long_kernel<T, kD, 4>, 4, 16, 2);
-  else if (max_ns > 16 && units <= 8) go(verify_combine_long_kernel<T, kD, 2>, 2, 16, 2);
-  else if (max_ns > 16) go(verify_combine_tiled_kernel<T, kD, 8>, 8, 4, kTiles);
+  else if (max_ns > 16) go(verify_combine_long_kernel<T, kD, 2>, 2, 16, 2);
+  else if (max_ns > 8 && units <= 8) go(verify_combine_long_kernel<T, kD, 1>, 1, 16, 2);
   else if (max_ns > 8) go(verify_combine_tiled_kernel<T, kD, 4>, 4, 4, kTiles);
   else if (max_ns > 4) go(verify_combine_few_kernel<T, kD, 2>, 2, 4, 2);
   else go(verify_combine_few_kernel<T, kD, 1>, 1, 4, 2);

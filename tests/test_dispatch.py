@@ -59,12 +59,12 @@ def test_combine_of_few_splits(launches):
         for (heads, lens, most), run in zip(CASES, got):
             assert max(run[0]["splits"]) == most, (heads, lens, run[0]["splits"])
             assert run[1]["kernel"] == f"verify_combine_few_kernel<unsigned short, {d}, {1 if most <= 4 else 2}>", (heads, lens)
-    got = launches([verify(28, 4, 5, [n] * B) for B, n in ((4, 26112), (1, 1024))])
+    got = launches([verify(28, 4, n_q, [n] * B) for B, n, n_q in ((4, 26112, 25), (1, 12000, 60))])
     assert {run[1]["kernel"] for run in got} == {"verify_combine_tiled_kernel<unsigned short, 128, 4>"}
 
 
 def test_combine_of_many_splits(launches):
-    """16 splits a wavefront, and eight wavefronts over 16-row tiles where 17 to 32 splits meet many row blocks;
+    """16 splits a wavefront, and four wavefronts over 16-row tiles where 9 to 16 splits meet many row blocks;
     test_gpu_verify_long_splits.py runs them."""
     from test_gpu_verify_long_splits import CASES
     seen = set()
@@ -76,12 +76,12 @@ def test_combine_of_many_splits(launches):
             most = max(run[0]["splits"])
             units = heads[1] * -(-heads[0] // heads[1] * heads[2] // 64)
             kernel = run[1]["kernel"]
-            if most > 32 or (most > 16 and units <= 8):
-                assert kernel == f"verify_combine_long_kernel<unsigned short, {d}, {min(w for w in (2, 4, 8, 16) if 16 * w >= most or w == 16)}>"
-            elif most > 16:
-                assert kernel == f"verify_combine_tiled_kernel<unsigned short, {d}, 8>"
+            if most > 16 or (most > 8 and units <= 8):
+                assert kernel == f"verify_combine_long_kernel<unsigned short, {d}, {min(w for w in (1, 2, 4, 8, 16) if 16 * w >= most or w == 16)}>"
+            elif most > 8:
+                assert kernel == f"verify_combine_tiled_kernel<unsigned short, {d}, 4>"
             seen.add(kernel)
-    assert {f"verify_combine_long_kernel<unsigned short, {d}, {w}>" for d in (64, 128) for w in (2, 4, 8, 16)} <= seen
+    assert {f"verify_combine_long_kernel<unsigned short, {d}, {w}>" for d in (64, 128) for w in (1, 2, 4, 8, 16)} <= seen
 
 
 @pytest.mark.parametrize("d", [64, 128])

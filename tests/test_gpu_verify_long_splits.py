@@ -1,4 +1,4 @@
-"""Combine pass of sequences with many splits (2, 4, 8 and 16 wavefronts that merge 16 each), with rows that leave groups of
+"""Combine pass of sequences with many splits (1, 2, 4, 8 and 16 wavefronts that merge 16 each), with rows that leave groups of
 four and 16-row tiles partly empty, and sequences of one length, whose place the kernels work out without a table, beside
 ragged ones.  test_dispatch.py holds the bf16 cases against the library's launches."""
 import numpy as np
@@ -13,7 +13,8 @@ from gpu_util import check_attn, run_verify  # noqa: E402
 # (query heads, KV heads, draft rows), rows of each sequence, most splits of a sequence in bf16 with heads of 128
 CASES = [((8, 1, 8), (9001,), 141), ((5, 1, 3), (8100, 8100), 127), ((6, 2, 5), (8000,), 125), ((6, 2, 1), (4161,), 66),
          ((28, 4, 9), (4096,), 64), ((12, 4, 3), (2150,), 34), ((12, 4, 3), (1200,), 19), ((28, 4, 5), (2048, 2048), 32),
-         ((4, 1, 7), (3000, 700, 40, 1500), 47), ((16, 4, 4), (1000,) * 8, 8), ((28, 4, 30), (5030,), 27)]
+         ((4, 1, 7), (3000, 700, 40, 1500), 47), ((16, 4, 4), (1000,) * 8, 8), ((28, 4, 30), (5030,), 27),
+         ((12, 4, 3), (600,), 10), ((28, 4, 60), (5030,), 16)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

@@ -32,39 +32,39 @@ COVERAGE = {
     "verify_partial_mfma_kernel<128, 2, 2, true>": (A, "test_c3_bf16_26k_tree60", "C3 60-node tree: several blocks of 128 rows, long splits"),
     "verify_partial_mfma_kernel<128, 2, 2, false>": (VL, "test_split_ends", "one block of 128 rows over long splits; several over shorter ones"),
     "verify_partial_mfma_kernel<128, 1, 3, false>": (A, "test_paper_sized_trees_at_26k_context", "48-, 44- and 25-node trees: blocks of 192 rows"),
-    "verify_combine_tiled_kernel<unsigned short, 128, 8>": (A, "test_paper_sized_trees_at_26k_context", "17 to 32 splits (30-, 48-node trees)"),
-    "verify_combine_tiled_kernel<unsigned short, 128, 4>": (A, "test_c3_bf16_26k_tree60", "at most 16 splits (C3, C4, batches)"),
+    "verify_combine_tiled_kernel<unsigned short, 128, 4>": (A, "test_c3_bf16_26k_tree60", "9 to 16 splits of several row blocks (C3)"),
     "verify_partial_mfma_kernel<64, 1, 0, false>": (V64, "test_rows_of_two_wavefronts", "up to 32 rows"),
     "verify_partial_mfma_kernel<64, 1, 1, false>": (V64, "test_rows_and_contexts", "up to 64 rows, short contexts"),
     "verify_partial_mfma_kernel<64, 2, 1, false>": (V64, "test_batches_and_long_contexts", "26k chain, ragged batch"),
     "verify_partial_mfma_kernel<64, 1, 2, false>": (V64, "test_rows_and_contexts", "70, 240 and 480 rows"),
     "verify_partial_mfma_kernel<64, 2, 2, false>": (V64, "test_two_row_tiles_over_long_pieces", "60 nodes at 26k, 12 trees of 30 at 4k"),
     "verify_partial_mfma_kernel<64, 1, 3, false>": (V64, "test_rows_and_contexts", "175 rows"),
-    "verify_combine_tiled_kernel<unsigned short, 64, 8>": (V64, "test_batches_and_long_contexts", "17 to 32 splits"),
     "verify_combine_tiled_kernel<unsigned short, 64, 4>": (V64, "test_rows_and_contexts", "short contexts"),
     # fp32: <head_dim, row tiles>, <storage type, head_dim, wavefronts>
     "verify_partial_f32_kernel<64, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
     "verify_partial_f32_kernel<64, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
-    "verify_combine_tiled_kernel<float, 64, 8>": (VF, "test_rows_and_contexts", ""),
     "verify_combine_tiled_kernel<float, 64, 4>": (VF, "test_rows_and_contexts", ""),
     "verify_partial_f32_kernel<128, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
     "verify_partial_f32_kernel<128, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
-    "verify_combine_tiled_kernel<float, 128, 8>": (VF, "test_rows_and_contexts", ""),
     "verify_combine_tiled_kernel<float, 128, 4>": (VF, "test_rows_and_contexts", ""),
     # merged 16 splits a wavefront: <storage type, head_dim, wavefronts>
-    "verify_combine_long_kernel<unsigned short, 64, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<unsigned short, 64, 1>": (VM, "test_many_splits", "9 to 16 splits, few row blocks"),
+    "verify_combine_long_kernel<unsigned short, 64, 2>": (VM, "test_many_splits", "17 to 32 splits"),
     "verify_combine_long_kernel<unsigned short, 64, 4>": (VM, "test_many_splits", "up to 64"),
     "verify_combine_long_kernel<unsigned short, 64, 8>": (VM, "test_many_splits", "up to 128"),
     "verify_combine_long_kernel<unsigned short, 64, 16>": (VM, "test_many_splits", "more"),
-    "verify_combine_long_kernel<unsigned short, 128, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<unsigned short, 128, 1>": (VM, "test_many_splits", "9 to 16 splits, few row blocks"),
+    "verify_combine_long_kernel<unsigned short, 128, 2>": (VM, "test_many_splits", "17 to 32 splits"),
     "verify_combine_long_kernel<unsigned short, 128, 4>": (VM, "test_many_splits", "up to 64"),
     "verify_combine_long_kernel<unsigned short, 128, 8>": (VM, "test_many_splits", "up to 128"),
     "verify_combine_long_kernel<unsigned short, 128, 16>": (VM, "test_many_splits", "more"),
-    "verify_combine_long_kernel<float, 64, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<float, 64, 1>": (VM, "test_many_splits", "9 to 16 splits, few row blocks"),
+    "verify_combine_long_kernel<float, 64, 2>": (VM, "test_many_splits", "17 to 32 splits"),
     "verify_combine_long_kernel<float, 64, 4>": (VM, "test_many_splits", "up to 64"),
     "verify_combine_long_kernel<float, 64, 8>": (VM, "test_many_splits", "up to 128"),
     "verify_combine_long_kernel<float, 64, 16>": (VM, "test_many_splits", "more"),
-    "verify_combine_long_kernel<float, 128, 2>": (VM, "test_many_splits", "17 to 32 splits, few row blocks"),
+    "verify_combine_long_kernel<float, 128, 1>": (VM, "test_many_splits", "9 to 16 splits, few row blocks"),
+    "verify_combine_long_kernel<float, 128, 2>": (VM, "test_many_splits", "17 to 32 splits"),
     "verify_combine_long_kernel<float, 128, 4>": (VM, "test_many_splits", "up to 64"),
     "verify_combine_long_kernel<float, 128, 8>": (VM, "test_many_splits", "up to 128"),
     "verify_combine_long_kernel<float, 128, 16>": (VM, "test_many_splits", "more"),
