@@ -14,7 +14,8 @@ from gpu_util import check_attn, run_verify  # noqa: E402
 CASES = [((8, 1, 8), (9001,), 141), ((5, 1, 3), (8100, 8100), 127), ((6, 2, 5), (8000,), 125), ((6, 2, 1), (4161,), 66),
          ((28, 4, 9), (4096,), 64), ((12, 4, 3), (2150,), 34), ((12, 4, 3), (1200,), 19), ((28, 4, 5), (2048, 2048), 32),
          ((4, 1, 7), (3000, 700, 40, 1500), 47), ((16, 4, 4), (1000,) * 8, 8), ((28, 4, 30), (5030,), 27),
-         ((12, 4, 3), (600,), 10), ((28, 4, 60), (5030,), 16)]
+         ((12, 4, 3), (600,), 10), ((28, 4, 60), (5030,), 16),
+         ((64, 32, 4), (2011,), 8)]                     # fp32: 16 splits of 32 units
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
