@@ -43,10 +43,10 @@ COVERAGE = {
     # fp32: <head_dim, row tiles>, <storage type, head_dim, wavefronts>
     "verify_partial_f32_kernel<64, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
     "verify_partial_f32_kernel<64, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
-    "verify_combine_tiled_kernel<float, 64, 4>": (VF, "test_rows_and_contexts", ""),
+    "verify_combine_tiled_kernel<float, 64, 4>": (VM, "test_many_splits", "9 to 16 splits of many row blocks"),
     "verify_partial_f32_kernel<128, 1>": (VF, "test_rows_and_contexts", "up to 64 rows"),
     "verify_partial_f32_kernel<128, 2>": (VF, "test_rows_and_contexts", "more than 64 rows"),
-    "verify_combine_tiled_kernel<float, 128, 4>": (VF, "test_rows_and_contexts", ""),
+    "verify_combine_tiled_kernel<float, 128, 4>": (VM, "test_many_splits", "9 to 16 splits of many row blocks"),
     # merged 16 splits a wavefront: <storage type, head_dim, wavefronts>
     "verify_combine_long_kernel<unsigned short, 64, 1>": (VM, "test_many_splits", "9 to 16 splits, few row blocks"),
     "verify_combine_long_kernel<unsigned short, 64, 2>": (VM, "test_many_splits", "17 to 32 splits"),
