@@ -93,6 +93,7 @@ int plan_chunk(const sparrow_attn_desc *d, int32_t n_q, int64_t total_tokens, bo
     slots = kNumCU / (d->n_kv_heads * rbs);
   }
   if (slots < 1) slots = 1;
+  if (mfma) slots = std::min(slots, verify_mfma_max_splits(d->dtype, d->head_dim, (int64_t)d->n_kv_heads * ((R + 63) / 64)));
   if (slots_out) *slots_out = slots;
   int64_t chunk = (total_tokens + slots - 1) / slots;
   chunk = (int64_t)round_up((size_t)chunk, 32);

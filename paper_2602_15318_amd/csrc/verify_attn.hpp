@@ -86,6 +86,8 @@ int verify_mfma_row_blocks(int dtype, int R);
 constexpr int kMlFloats = 3;              // per row of a partial: max, sum, output scales of the two stored halves (two bf16)
 int64_t verify_mfma_unit_floats_o(int dtype, int head_dim);
 int64_t verify_mfma_unit_floats_ml();
+// Splits of a sequence whose partials the combine pass can address, of `units` (KV heads x blocks of 64 rows) each.
+int verify_mfma_max_splits(int dtype, int head_dim, int64_t units);
 hipError_t launch_verify_combine_mfma(int dtype, const VerifyArgs &a, const SeqTable &tab, hipStream_t st);
 // Second pass: merge the per-split partials of every (row, head).
 hipError_t launch_verify_combine(int dtype, const VerifyArgs &a, const SeqTable &tab,

@@ -791,8 +791,8 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
   const int mt = blockIdx.y * kTiles;              // first d-tile: half (mt & 1) of the stored pair mt >> 1
   const int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int n = lane & 15, c4 = lane >> 4;
-  // This wavefront's splits are ws, ws + kWaves, ... of the sequence's.  Their offsets fit 32 bits: several splits a
-  // sequence mean no more than a few hundred units a split.
+  // This wavefront's splits are ws, ws + kWaves, ... of the sequence's, at 32-bit offsets from its first one
+  // (verify_mfma_max_splits).
   const int64_t first = ((int64_t)s0 * units + unit) * 4 + wq;
   const __amdgpu_buffer_rsrc_t rs_o = __builtin_amdgcn_make_buffer_rsrc((void *)(part_o + first * kQuarter), (short)0, (int)0x7fffffff, 0x00027000);
   const __amdgpu_buffer_rsrc_t rs_ml = __builtin_amdgcn_make_buffer_rsrc((void *)(part_ml + first * (16 * 4 * kMlFloats)), (short)0, (int)0x7fffffff, 0x00027000);
@@ -1055,6 +1055,16 @@ bool verify_partial_mfma_supported(int dtype, int head_dim) {
 // halves, or of floats.
 int64_t verify_mfma_unit_floats_o(int dtype, int head_dim) { return dtype == SPARROW_F32 ? 64 * head_dim : 4096; }
 int64_t verify_mfma_unit_floats_ml() { return kRowsPerWG * kMlFloats; }
+
+// The combine pass addresses the splits of a sequence by 31-bit offsets from the first one, and multiplies 24 bits for those
+// of (m, l, c).  A few hundred units as a rule, but the plan gives one KV head eight splits (fp32: 16) however many rows it
+// has: from 4,369 units (fp32, heads of 128; 64: 8,739) or 18,725 (bf16) on it gets fewer, where thousands of row blocks fill
+// the chip by themselves.
+int verify_mfma_max_splits(int dtype, int head_dim, int64_t units) {
+  if (units * verify_mfma_unit_floats_ml() * 4 >= 1 << 24) return 1;
+  const int64_t unit_o = verify_mfma_unit_floats_o(dtype, head_dim) * 4;
+  return (int)std::min<int64_t>(1 + (0x7fffffff - unit_o) / (units * unit_o), INT32_MAX);
+}
 
 // Row blocks (workgroups per split and KV head) for R rows: blocks of three 64-row tiles unless
 // blocks of two leave fewer empty tiles (7 tiles: 2+2+2+1 beats 3+3+1, measured).

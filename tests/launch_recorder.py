@@ -1,7 +1,7 @@
 """Which kernels the library launches for a call, found on the CPU: the calls run in a child process against
 launch_recorder.c in the place of the HIP runtime, with made-up device addresses that nothing reads.
 
-A call is a dict: {"call": "verify", "Hq", "Hkv", "d", "n_q", "lens", "layout", "own"} (bf16; lens: rows of each sequence,
+A call is a dict: {"call": "verify", "dtype", "Hq", "Hkv", "d", "n_q", "lens", "layout", "own"} (dtype: bf16 or f32; lens: rows of each sequence,
 draft rows included; layout: "token", "head" or "pair", as kv_strides says; own: a tree per sequence), or
 {"call": "accept" | "topk", "dtype", "M", "H", "V"}."""
 import ctypes
@@ -23,7 +23,8 @@ def kv_strides(layout, T, Hkv, d):
 
 def record(calls, tmp):
     """The launches of every call, in order: {"kernel", "grid", "block", "lds"}; for the partial pass of verification
-    on the matrix cores also "splits" and "pieces" (per sequence) and "flat"."""
+    on the matrix cores also "splits" and "pieces" (per sequence) and "flat" (bf16), for its combine pass "splits" (of the
+    first sequence) and "units" (KV heads x blocks of 64 rows)."""
     shim = os.path.join(str(tmp), "launch_recorder.so")
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", shim, os.path.join(HERE, "launch_recorder.c")], check=True)
     if not os.path.exists(LIB):
@@ -64,6 +65,8 @@ def _child(shim):
             one["splits"] = [y - x for x, y in zip(cu, cu[1:])]
             one["pieces"] = ctypes.cast(args[12], ctypes.POINTER(i32))[:B]
             one["flat"] = bool(ctypes.cast(args[9], ctypes.POINTER(i32))[0] & 1)
+        if re.match("verify_combine_(tiled|few|long)_kernel", one["kernel"]):     # (four pointers, splits, units, ...)
+            one["splits"], one["units"] = (ctypes.cast(args[i], ctypes.POINTER(i32))[0] for i in (4, 5))
         seen.append(one)
 
     p32 = ctypes.POINTER(ctypes.c_uint32)
@@ -76,7 +79,7 @@ def _child(shim):
         if c["call"] == "verify":
             B, n_q, lens = len(c["lens"]), c["n_q"], c["lens"]
             st, sh = kv_strides(c.get("layout", "token"), sum(lens), c["Hkv"], c["d"])
-            desc = _Desc(1, c["Hq"], c["Hkv"], c["d"], 0.0, st, sh, n_q if c.get("own") else 0)
+            desc = _Desc({"f32": 0, "bf16": 1}[c.get("dtype", "bf16")], c["Hq"], c["Hkv"], c["d"], 0.0, st, sh, n_q if c.get("own") else 0)
             cu = (i32 * (B + 1))(*[sum(lens[:b]) for b in range(B + 1)])
             rc = lib.sparrow_verify_attn(ctypes.byref(desc), at, at, at, cu, at, B, n_q, at, at, at, ws, None)
         else:

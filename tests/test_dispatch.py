@@ -10,8 +10,8 @@ def launches(tmp_path_factory):
     return lambda calls: record(calls, tmp)
 
 
-def verify(Hq, Hkv, n_q, lens, layout="token", own=False, d=128):
-    return dict(call="verify", Hq=Hq, Hkv=Hkv, d=d, n_q=n_q, lens=list(lens), layout=layout, own=own)
+def verify(Hq, Hkv, n_q, lens, layout="token", own=False, d=128, dtype="bf16"):
+    return dict(call="verify", dtype=dtype, Hq=Hq, Hkv=Hkv, d=d, n_q=n_q, lens=list(lens), layout=layout, own=own)
 
 
 IN_STEP, HALF_STEP = "verify_partial_mfma_kernel<128, 2, 2, false>", "verify_partial_mfma_kernel<128, 2, 2, true>"
@@ -82,6 +82,23 @@ def test_combine_of_many_splits(launches):
                 assert kernel == f"verify_combine_tiled_kernel<unsigned short, {d}, 4>"
             seen.add(kernel)
     assert {f"verify_combine_long_kernel<unsigned short, {d}, {w}>" for d in (64, 128) for w in (1, 2, 4, 8, 16)} <= seen
+
+
+@pytest.mark.parametrize("dtype,d,unit_bytes,most", [("bf16", 64, 16384, 8), ("bf16", 128, 16384, 8), ("f32", 64, 16384, 16),
+                                                      ("f32", 128, 32768, 16)])
+def test_combine_offsets(launches, dtype, d, unit_bytes, most):
+    """The combine kernels address a sequence's splits by 31-bit offsets from its first one, and those of (m, l, c), 12
+    bytes a row, by a product of 24 bits: so many query heads per KV head that the plan's splits lie further apart get fewer."""
+    units = sorted({g + i for s in range(1, most) for g in [(2 ** 31 - 1) // (s * unit_bytes)] for i in (-2, -1, 0, 1)} | {64, 2000, 21845, 21846})
+    units = [u for u in units if u < 32768]
+    got = launches([verify(u, 1, 64, [26000], d=d, dtype=dtype) for u in units])
+    splits = {}
+    for u, run in zip(units, got):
+        assert run[1]["units"] == u, (u, run)
+        splits[u] = run[1]["splits"]
+        assert (splits[u] - 1) * u * unit_bytes + unit_bytes <= 2 ** 31 - 1, (u, run)
+        assert u * 64 * 12 < 2 ** 24 or splits[u] == 1, (u, run)
+    assert splits[2000] == most and splits[21846] == 1
 
 
 @pytest.mark.parametrize("d", [64, 128])

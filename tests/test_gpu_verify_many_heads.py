@@ -1,0 +1,34 @@
+"""Verification with thousands of query heads per KV head: partials whose splits lie near 2 GiB apart.  A row's output is a
+function of its own query, so the oracle is given a few heads of each KV head, the first and the last among them.
+test_dispatch.py holds the plan against the offsets' limits on the CPU."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import check_attn  # noqa: E402
+
+
+def check_heads(oracle, dtype, d, Hkv, g, n_q, tokens):
+    import torch
+
+    import paper_2602_15318_amd as sp
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(g)
+    q = torch.randn(n_q, Hkv * g, d, device="cuda", dtype=tdt, generator=gen)
+    k, v = (torch.randn(tokens, Hkv, d, device="cuda", dtype=tdt, generator=gen) for _ in range(2))
+    cu = np.array([0, tokens], dtype=np.int32)
+    print(f"{dtype} d={d} {Hkv * g}/{Hkv} heads, {n_q} rows, {tokens} tokens", flush=True)
+    out, lse = sp.verify_attn(q, k, v, cu, None, n_q)
+    torch.cuda.synchronize()
+    some = sorted({0, 1, g // 3, g // 2, g - 2, g - 1})
+    heads = torch.tensor([c * g + h for c in range(Hkv) for h in some], device="cuda")
+    f64 = lambda t: t.double().cpu().numpy()
+    ref, ref_lse = oracle.verify_attn(f64(q[:, heads]), f64(k), f64(v), cu, None, n_q)
+    check_attn(f64(out[:, heads]), ref, dtype, f"{Hkv * g}/{Hkv} heads of {d}")
+    assert np.abs(f64(lse[:, heads]) - ref_lse).max() <= (4e-3 if dtype == "bf16" else 2e-5)
+
+
+@pytest.mark.parametrize("dtype,d,g", [("f32", 128, 4367), ("f32", 128, 4400), ("bf16", 128, 18726), ("bf16", 64, 21846)])
+def test_splits_near_2_gib_apart(oracle, dtype, d, g):
+    check_heads(oracle, dtype, d, 1, g, 64, 2000)
