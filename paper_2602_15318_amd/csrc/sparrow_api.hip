@@ -117,7 +117,6 @@ int direct_rows(const sparrow_attn_desc *d, int32_t B, int32_t n_q) {
 // call's total token count so that the workspace query and the call always agree.
 bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
   return verify_partial_mfma_supported(d->dtype, d->head_dim) &&
-         d->n_q_heads / d->n_kv_heads < 32768 &&               // (row numbers are divided by their reciprocal there)
          d->kv_stride_token < (1ll << 24) &&
          total_tokens * d->kv_stride_token * (d->dtype == SPARROW_BF16 ? 2 : 4) < (1ll << 31);
 }
@@ -584,7 +583,7 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
   a.q = q; a.k = k; a.v = v; a.parent = parent;
   a.parent_stride = parent ? desc->parent_stride : 0;
   a.B = B; a.n_q = n_q; a.Hq = desc->n_q_heads; a.Hkv = desc->n_kv_heads; a.d = desc->head_dim;
-  a.g = a.Hq / a.Hkv; a.inv_g = 1.0f / (float)a.g;
+  a.g = a.Hq / a.Hkv; a.inv_g = kBelow / (float)a.g;
   a.chunk = chunk; a.n_slots = tab.cu_split[B];
   a.scale_log2 = scale_log2_of(desc);
   a.stride_tok = desc->kv_stride_token; a.stride_head = desc->kv_stride_head;

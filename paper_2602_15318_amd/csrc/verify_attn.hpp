@@ -22,7 +22,7 @@ struct VerifyArgs {
   int32_t parent_stride;  // 0: one tree [n_q] for all sequences; else sequence b's tree at parent + b*stride
   int32_t B, n_q, Hq, Hkv, d;
   int32_t g;              // Hq / Hkv
-  float inv_g;            // 1 / g
+  float inv_g;            // kBelow / g, see row_and_head
   int32_t chunk;          // longest split of the call, in tokens (the kernels derive each
                           // sequence's own split length from SeqTable)
   int32_t n_slots;        // cu_split[B]
@@ -59,9 +59,18 @@ __device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int slot) {
   return b;
 }
 
-// rho / g for rows of one KV head (or group / slots of a flat grid), by the reciprocal: half a step off, which is far more
-// than what two roundings of the product are off while quotient x g stays below 2^21 (g below 32,768 at 64 rows).
-__device__ __forceinline__ int row_div(int rho, float inv_g) { return (int)(((float)rho + 0.5f) * inv_g); }
+// a / n by the reciprocal: half a step off, which is far more than what two roundings of the product are off while a < 2^20.
+__device__ __forceinline__ int div_by_rcp(int a, float inv_n) { return (int)(((float)a + 0.5f) * inv_n); }
+
+// Draft row and head (within the group of g) of row rho of a KV head.  The reciprocal is below 1/g by more than the roundings
+// of the product (four of at most 2^-23 each), so that the quotient, at most 64, is right or one short, for every g.
+constexpr float kBelow = 1.0f - 0x1p-20f;
+struct RowHead { int row, head; };
+__device__ __forceinline__ RowHead row_and_head(int rho, int g, float inv_g_below) {
+  int row = (int)((float)rho * inv_g_below), head = rho - row * g;
+  if (head >= g) { ++row; head -= g; }
+  return {row, head};
+}
 
 // Natural-log sum-exp of a row: reference point m (log2 units) and sum l.  kWide: rounded once at its full
 // size.  (m may lie below the row's maximum; log2(l) is then larger than in the plain-ALU kernels and so are

@@ -170,7 +170,7 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
   if (flat) {
     const int grp = sq * 8 + xcd;                          // global split + n_slots * KV head
     if (grp >= len_one) return;                            // padding of the last round of 8
-    c = __builtin_amdgcn_readfirstlane(row_div(grp, __builtin_amdgcn_rcpf((float)n_slots)));
+    c = __builtin_amdgcn_readfirstlane(div_by_rcp(grp, __builtin_amdgcn_rcpf((float)n_slots)));
     const int gslot = grp - c * n_slots;
     // (an empty statement that takes these as scalar-register inputs: their lines come with the ends that the search reads,
     // and the entries of the sequence found are then at hand)
@@ -276,8 +276,9 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
     row_ok[qt] = rho < R;
     if ((rb * kQT + qt) * kRowsPerWG + 16 * wr < R) n_act = qt + 1;
     // rows past R take the data of row 0 (in bounds); what comes of them is not used
-    i_row[qt] = row_ok[qt] ? row_div(rho, a.inv_g) : 0;
-    h[qt] = row_ok[qt] ? rho - i_row[qt] * g : 0;
+    const RowHead rh = row_and_head(rho, g, a.inv_g);
+    i_row[qt] = row_ok[qt] ? rh.row : 0;
+    h[qt] = row_ok[qt] ? rh.head : 0;
   }
   const int64_t q_row0 = (int64_t)b * a.n_q * a.Hq + (int64_t)c * g;     // of the call: row (b, 0), first head of the group
 
@@ -866,9 +867,10 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
   // where this lane's row goes
   int rb = 0, c = unit;
   if (rbs > 1) { rb = unit % rbs; c = unit / rbs; }
-  const int rho = rb * kRowsPerWG + 16 * wq + n, i_row = row_div(rho, __builtin_amdgcn_rcpf((float)g));
+  const int rho = rb * kRowsPerWG + 16 * wq + n;
+  const RowHead rh = row_and_head(rho, g, kBelow * __builtin_amdgcn_rcpf((float)g));
   const bool row_ok = rho < n_q * g;
-  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(i_row * Hq + rho - i_row * g);
+  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.row * Hq + rh.head);
   int t0 = 0;                                      // the d-tiles that this wavefront stores: all, or one
   float m = m_run, l = l_run;
   if constexpr (kWaves > 1) {
@@ -1012,8 +1014,9 @@ verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *par
   l_run = quad_sum(l_run);
   int rb = 0, c = unit;
   if (rbs > 1) { rb = unit % rbs; c = unit / rbs; }
-  const int rho = rb * kRowsPerWG + 4 * rows4 + r, i_row = row_div(rho, __builtin_amdgcn_rcpf((float)g));
-  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(i_row * Hq + rho - i_row * g);
+  const int rho = rb * kRowsPerWG + 4 * rows4 + r;
+  const RowHead rh = row_and_head(rho, g, kBelow * __builtin_amdgcn_rcpf((float)g));
+  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.row * Hq + rh.head);
   float m = m_run, l = l_run;
   if constexpr (kWaves > 1) {
     xo[ws][lane] = z;

@@ -84,13 +84,18 @@ def test_combine_of_many_splits(launches):
     assert {f"verify_combine_long_kernel<unsigned short, {d}, {w}>" for d in (64, 128) for w in (1, 2, 4, 8, 16)} <= seen
 
 
+def test_any_number_of_heads_on_the_matrix_cores(launches):
+    for dtype in ("bf16", "f32"):
+        for run in launches([verify(g, 1, n_q, [900], dtype=dtype) for g in (32767, 32768, 100003) for n_q in (1, 64)]):
+            assert run[0]["kernel"].startswith("verify_partial_mfma_kernel" if dtype == "bf16" else "verify_partial_f32_kernel"), run
+
+
 @pytest.mark.parametrize("dtype,d,unit_bytes,most", [("bf16", 64, 16384, 8), ("bf16", 128, 16384, 8), ("f32", 64, 16384, 16),
                                                       ("f32", 128, 32768, 16)])
 def test_combine_offsets(launches, dtype, d, unit_bytes, most):
     """The combine kernels address a sequence's splits by 31-bit offsets from its first one, and those of (m, l, c), 12
     bytes a row, by a product of 24 bits: so many query heads per KV head that the plan's splits lie further apart get fewer."""
     units = sorted({g + i for s in range(1, most) for g in [(2 ** 31 - 1) // (s * unit_bytes)] for i in (-2, -1, 0, 1)} | {64, 2000, 21845, 21846})
-    units = [u for u in units if u < 32768]
     got = launches([verify(u, 1, 64, [26000], d=d, dtype=dtype) for u in units])
     splits = {}
     for u, run in zip(units, got):

@@ -32,3 +32,8 @@ def check_heads(oracle, dtype, d, Hkv, g, n_q, tokens):
 @pytest.mark.parametrize("dtype,d,g", [("f32", 128, 4367), ("f32", 128, 4400), ("bf16", 128, 18726), ("bf16", 64, 21846)])
 def test_splits_near_2_gib_apart(oracle, dtype, d, g):
     check_heads(oracle, dtype, d, 1, g, 64, 2000)
+
+
+@pytest.mark.parametrize("dtype,d,g,n_q,tokens", [("bf16", 128, 32769, 33, 700), ("bf16", 64, 65537, 17, 90), ("f32", 64, 50021, 9, 700)])
+def test_groups_whose_rows_take_more_than_20_bits(oracle, dtype, d, g, n_q, tokens):
+    check_heads(oracle, dtype, d, 1, g, n_q, tokens)
