@@ -285,7 +285,7 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
   u32x4 qv[kQT][kKS];
 #pragma unroll
   for (int qt = 0; qt < kQT; ++qt) {
-    const unsigned int at = (unsigned int)(i_row[qt] * a.Hq + h[qt]) * (2u * kD) + 16u * (unsigned int)c4;
+    const int64_t at = (int64_t)(i_row[qt] * a.Hq + h[qt]) * (2 * kD) + 16 * c4;      // (64 rows of 266,305 heads pass 4 GiB)
     const unsigned char *qp = (const unsigned char *)a.q + q_row0 * (2 * kD) + at;
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) qv[qt][ks] = *(const u32x4 *)(qp + 64 * ks);

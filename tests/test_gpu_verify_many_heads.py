@@ -1,4 +1,5 @@
-"""Verification with thousands of query heads per KV head: partials whose splits lie near 2 GiB apart.  A row's output is a
+"""Verification with thousands of query heads per KV head: partials whose splits lie near 2 GiB apart, queries of more than
+4 GiB.  A row's output is a
 function of its own query, so the oracle is given a few heads of each KV head, the first and the last among them.
 test_dispatch.py holds the plan against the offsets' limits on the CPU."""
 import numpy as np
@@ -37,3 +38,7 @@ def test_splits_near_2_gib_apart(oracle, dtype, d, g):
 @pytest.mark.parametrize("dtype,d,g,n_q,tokens", [("bf16", 128, 32769, 33, 700), ("bf16", 64, 65537, 17, 90), ("f32", 64, 50021, 9, 700)])
 def test_groups_whose_rows_take_more_than_20_bits(oracle, dtype, d, g, n_q, tokens):
     check_heads(oracle, dtype, d, 1, g, n_q, tokens)
+
+
+def test_queries_of_more_than_4_gib(oracle):
+    check_heads(oracle, "bf16", 128, 9, 29600, 64, 80)
