@@ -125,25 +125,23 @@ bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
 // workgroup per compute unit that plan_chunk aims at; each sequence is then cut into equal pieces,
 // so that every workgroup of the call streams about the same number of bytes.  Returns the longest
 // piece in tokens.
-// bf16: pieces are whole steps of 64 tokens where that matters, up to 8 steps (a step of two 32-token tiles, half of it empty,
-// takes as long, and fewer pieces leave less to combine; longer pieces lose compute units by it, eight of 26,120 tokens
-// 75.5 -> 78.8 us).  Pieces of 32 / 64, us a call: chain of 5 over 4,096 tokens 9.45 / 9.1, over 6,000 10.2 / 9.55, of 8 over
-// 26,112 16.6 / 16.3, 16 nodes over 5,000 14.1 / 13.2, four ragged sequences of 6,001, 16/4 heads of 64, chain of 8 11.4 /
-// 11.0.  Sequences of one length are cut alike, so that the kernels need no table: two chains of 4 over 6,000 with 31 and 32
-// pieces / 32 each 12.6 / 11.3, eight of 5 over 1,000 11.3 / 10.4.  Neither takes more scratch than the query says.
+// bf16 sequences of one length (or one sequence) are cut alike, so that the kernels need no table: two chains of 4 over 6,000
+// with 31 and 32 pieces / 32 each 12.6 / 11.3, eight of 5 over 1,000 11.3 / 10.4.  How many pieces follows from whole steps
+// of 64 tokens, up to 8 steps (a step of two 32-token tiles, half of it empty, takes as long, and fewer pieces leave less to
+// combine; longer pieces lose compute units by it, eight of 26,120 tokens 75.5 -> 78.8 us); the pieces themselves are even
+// again (split_len), of no more steps.  From 32 / 64 tokens, us a call: chain of 5 over 4,096 tokens 9.45 / 9.1, over 6,000
+// 10.2 / 9.55, of 8 over 26,112 16.6 / 16.3, 16 nodes over 5,000 14.1 / 13.2.  Neither takes more scratch than the query says.
 int plan_splits(const sparrow_attn_desc *d, const int32_t *cu_seqlens, int32_t B, int32_t n_q, int64_t total,
                 bool mfma, SeqTable *tab) {
   int slots;
-  int chunk0 = plan_chunk(d, n_q, total, mfma, &slots);
-  const bool steps64 = mfma && d->dtype == SPARROW_BF16;
-  if (steps64 && chunk0 <= 512) chunk0 = (chunk0 + 63) / 64 * 64;
+  const int chunk0 = plan_chunk(d, n_q, total, mfma, &slots);
   const int slot_budget = (int)((total + chunk0 - 1) / chunk0);
   memset(tab, 0, sizeof(*tab));
   for (int b = 0; b <= B; ++b) tab->cu_len[b] = cu_seqlens[b];
   int chunk = 0;
   int ns[SPARROW_MAX_BATCH];
   int used = 0;
-  bool equal = steps64 && slots >= B;
+  bool equal = mfma && d->dtype == SPARROW_BF16 && slots >= B;
   for (int b = 1; b < B; ++b) equal &= cu_seqlens[b + 1] - cu_seqlens[b] == cu_seqlens[1] - cu_seqlens[0];
   for (int b = 0; b < B; ++b) {
     const int len = cu_seqlens[b + 1] - cu_seqlens[b];

@@ -1,4 +1,7 @@
 """The kernels that calls are sent to, and how their work is cut, on the CPU (launch_recorder.py)."""
+import math
+import random
+
 import pytest
 
 from launch_recorder import record
@@ -108,16 +111,44 @@ def test_combine_offsets(launches, dtype, d, unit_bytes, most):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_pieces(launches, d):
-    """Pieces are whole 32-token tiles that cover a sequence, none but the last one of a sequence short; up to 512 tokens of
-    equal sequences they are whole steps, and none is empty."""
-    calls = [verify(28, 4, 5, lens, d=d) for n in (70, 300, 1000, 2049, 4101, 8197, 11111, 26117, 40000) for lens in
-             ([n], [n, n], [n] * 7, [n, n // 3 + 8], [n, n // 2 + 7, n // 5 + 9, n])]
+    """Pieces are whole 32-token tiles that cover a sequence.  Sequences of one length get as many as whole 64-token steps allow
+    (up to 8 steps): none is empty, and none takes more steps than an even share of the slots."""
+    sizes = (70, 300, 642, 1000, 1538, 2049, 4101, 7173, 8197, 11111, 26117, 40000)
+    calls = [verify(*heads, 5, lens, d=d) for heads in ((28, 4), (16, 8), (32, 32)) for n in sizes for lens in
+             ([n], [n, n], [n] * 4, [n] * 7, [n] * 8, [n, n // 3 + 8], [n, n // 2 + 7, n // 5 + 9, n])
+             if sum(lens) * heads[1] * d * 2 < 2 ** 31]
     for c, run in zip(calls, launches(calls)):
         equal = len(set(c["lens"])) == 1
         for n, s, p in zip(c["lens"], run[0]["splits"], run[0]["pieces"]):
             assert p % 32 == 0 and s * p >= n, (c, run[0])
             if equal and len(run) == 2:
-                assert (s - 1) * p < n and (p % 64 == 0 or p > 448), (c, run[0])
+                share = -(-n // (256 // c["Hkv"] // len(c["lens"])))
+                steps = -(-share // 64) if share <= 512 else -(-share // 32) / 2
+                assert s == math.ceil(n / (64 * steps)) and (s - 1) * p < n and p <= 64 * steps, (c, run[0])
+
+
+def plan_by_proportion(lens, slots):
+    """Splits of sequences that differ: about `slots` pieces of whole 32-token tiles dealt in proportion to the lengths, what is
+    left to the longest pieces; a sequence's pieces are equal."""
+    total = sum(lens)
+    budget = -(-total // max(64, -(-(-(-total // slots)) // 32) * 32))
+    ns = [max(1, n * budget // total) for n in lens]
+    while sum(ns) < budget:
+        ns[max(range(len(lens)), key=lambda b: lens[b] / ns[b])] += 1
+    return ns
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_ragged_batches_use_every_slot(launches, d):
+    """Sequences that differ are cut by proportion into as many pieces of 32-token grain as there are slots; a coarser grain
+    of their budget leaves compute units idle and makes the longest piece longer."""
+    rng = random.Random(d)
+    calls = [((28, 4, 1), (1538, 1948, 1219, 903)), ((28, 4, 8), (791, 1218, 734, 1574, 955, 1113, 1699, 1688)),
+             ((28, 4, 6), (1448, 1229, 693, 2084, 1911, 2213, 1384, 1933)), ((28, 4, 8), (6110, 6049, 2670, 2093))]
+    calls += [((28, 4, rng.randint(1, 9)), tuple(rng.randint(600, 6000) for _ in range(rng.randint(2, 9)))) for _ in range(100)]
+    for (heads, lens), run in zip(calls, launches([verify(*heads, lens, d=d) for heads, lens in calls])):
+        if len(run) == 2 and len(set(lens)) > 1:
+            assert run[0]["splits"] == plan_by_proportion(lens, 64), (heads, lens, run[0])
 
 
 def test_lm_head_cases_straight_to_lds(launches):
