@@ -763,6 +763,13 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
 // lane's own (m, l, c) with 64-bit addresses / here: 60 nodes over 12,000 25.1 / 24.2.
 typedef __attribute__((ext_vector_type(3))) unsigned int u32x3;
 
+// KV head and row block of a unit (for rows' numbers in it: a combine workgroup without rows leaves before it loads).
+__device__ __forceinline__ RowHead head_and_block(int unit, int rbs) {
+  if (rbs == 1) return {unit, 0};
+  const RowHead cr = row_and_head(unit, rbs, kBelow * __builtin_amdgcn_rcpf((float)rbs));
+  return {__builtin_amdgcn_readfirstlane(cr.row), __builtin_amdgcn_readfirstlane(cr.head)};
+}
+
 struct CombineArgs {                               // what a combine kernel's scalar arguments say, in its own terms
   const unsigned char *part_o, *part_ml;
   void *res;
@@ -782,13 +789,15 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
   constexpr int kLoad = !kWide && kTiles == 1 ? 8 : 16;
   __shared__ f32x4 xo[kWaves][kTiles][64];
   __shared__ float xm[kWaves][16], xl[kWaves][16];
-  const int rbs = shape >> 1;
+  const int wq = blockIdx.x & 3, unit = blockIdx.x >> 2;       // 16 rows of unit KV head * rbs + row block
+  const RowHead cr = head_and_block(unit, shape >> 1);
+  const int c = cr.row, rho0 = cr.head * kRowsPerWG + 16 * wq;
+  if (rho0 >= n_q * g) return;                     // tile without rows (uniform)
   const int b = blockIdx.z;
   int s0 = b * ns_one, ns = ns_one;
   if (shape & 1) {                                 // sequences that differ
     s0 = tab.cu_split[b]; ns = tab.cu_split[b + 1] - s0;
   }
-  const int wq = blockIdx.x & 3, unit = blockIdx.x >> 2;       // 16 rows of unit KV head * rbs + row block
   const int mt = blockIdx.y * kTiles;              // first d-tile: half (mt & 1) of the stored pair mt >> 1
   const int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int n = lane & 15, c4 = lane >> 4;
@@ -865,9 +874,7 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
     }
   }
   // where this lane's row goes
-  int rb = 0, c = unit;
-  if (rbs > 1) { rb = unit % rbs; c = unit / rbs; }
-  const int rho = rb * kRowsPerWG + 16 * wq + n;
+  const int rho = rho0 + n;
   const RowHead rh = row_and_head(rho, g, kBelow * __builtin_amdgcn_rcpf((float)g));
   const bool row_ok = rho < n_q * g;
   const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.row * Hq + rh.head);
@@ -919,8 +926,8 @@ verify_combine_few_kernel(const unsigned char *part_o, const unsigned char *part
 }
 
 // More splits than that, and 9 to 16 of calls with few row blocks: one workgroup per (sequence, KV head, 4 rows, 32
-// columns), so that one sequence's few output rows fill the chip, 224 workgroups instead of 128 for a chain of 8 with 28/4
-// heads.  Four lanes of a column take four splits side by side, so that a wavefront merges 16 splits with four loads of
+// columns), so that one sequence's few output rows fill the chip: 224 workgroups that have rows for a chain of 8 with 28/4
+// heads (of 256; the others leave), not 128.  Four lanes of a column take four splits side by side, so that a wavefront merges 16 splits with four loads of
 // 16 bytes a lane (eight with fp32 partials) and one of (m, l, c).  Combine pass alone, us, 16 wavefronts over 16 rows and one
 // d-tile / here: chain of 8 over 26,112 tokens 4.1 / 2.75, of 5 over 8,192 3.8 / 2.5, of 4 over 12,000 4.0 / 2.7; with the
 // partial pass, one KV head, chain of 8 over 16,000 (256 splits) 16.8 / 12.6.
@@ -940,14 +947,16 @@ verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *par
   constexpr unsigned int kPastEnd = 0x80000000u;   // a buffer offset that reads as zero
   typedef __attribute__((ext_vector_type(2))) float f32x2;
   __shared__ f32x2 xo[kWaves][64], xml[kWaves][4];
-  const int rbs = shape >> 1;
+  // four rows of unit KV head * rbs + row block
+  const int rows4 = (blockIdx.x & 7) * 2 + (blockIdx.x >> 3 & 1), unit = blockIdx.x >> 4;
+  const RowHead cr = head_and_block(unit, shape >> 1);
+  const int c = cr.row, rho0 = cr.head * kRowsPerWG + 4 * rows4;
+  if (rho0 >= n_q * g) return;                     // group without rows (uniform)
   const int b = blockIdx.z;
   int s0 = b * ns_one, ns = ns_one;
   if (shape & 1) {                                 // sequences that differ
     s0 = tab.cu_split[b]; ns = tab.cu_split[b + 1] - s0;
   }
-  // four rows of unit KV head * rbs + row block
-  const int rows4 = (blockIdx.x & 7) * 2 + (blockIdx.x >> 3 & 1), unit = blockIdx.x >> 4;
   const int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & 3, c4 = (lane >> 2) & 3, ss = lane >> 4;
   const int64_t first = (int64_t)s0 * units + unit;
@@ -1012,9 +1021,7 @@ verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *par
   l_run += dpp_f32<0x128>(l_run);
   l_run += dpp_f32<0x124>(l_run);
   l_run = quad_sum(l_run);
-  int rb = 0, c = unit;
-  if (rbs > 1) { rb = unit % rbs; c = unit / rbs; }
-  const int rho = rb * kRowsPerWG + 4 * rows4 + r;
+  const int rho = rho0 + r;
   const RowHead rh = row_and_head(rho, g, kBelow * __builtin_amdgcn_rcpf((float)g));
   const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.row * Hq + rh.head);
   float m = m_run, l = l_run;

@@ -109,6 +109,13 @@ def test_combine_offsets(launches, dtype, d, unit_bytes, most):
     assert splits[2000] == most and splits[21846] == 1
 
 
+def test_combine_kernels_of_row_counts(launches):
+    """test_gpu_verify_long_splits.py runs every combine kernel's workgroups with and without rows."""
+    for Hkv, lens, kernels in ((1, [4500], {"long"}), (12, [3000] * 2, {"tiled"}), (12, [1300] * 4, {"few"}), (12, [1000, 900] * 4, {"few"})):
+        got = launches([verify(Hkv * rows, Hkv, 1, lens) for rows in (1, 16, 64, 65, 130)])
+        assert {run[1]["kernel"].split("_")[2] for run in got} == kernels, (Hkv, lens, [run[1] for run in got])
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_pieces(launches, d):
     """Pieces are whole 32-token tiles that cover a sequence.  Sequences of one length get as many as whole 64-token steps allow

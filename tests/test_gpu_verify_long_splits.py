@@ -45,3 +45,24 @@ def test_large_values_in_one_half_of_a_row(oracle, half):
     big, _ = run_verify(sp, c)
     big[..., cols] *= 2.0 ** -100
     assert (big == out).all()
+
+
+# KV heads, rows of each sequence: 4-row groups, 16-row tiles of four, two and one wavefronts
+@pytest.mark.parametrize("Hkv,lens", [(1, (4500,)), (12, (3000, 3000)), (12, (1300,) * 4), (12, (1000, 900) * 4)])
+@pytest.mark.parametrize("rows", [1, 4, 5, 13, 16, 17, 32, 33, 48, 63, 64, 65, 69, 81, 128, 130, 193])
+def test_workgroups_with_and_without_rows(oracle, Hkv, lens, rows):
+    """One draft row, `rows` heads per KV head: workgroups of the combine pass whose rows none, some or all exist.  Outputs and
+    scratch are NaN beforehand: every output is written, by what the call itself wrote."""
+    import torch
+
+    import paper_2602_15318_amd as sp
+    from gpu_util import dev, host
+    cfg = wl.Config("R", "bf16", Hkv * rows, Hkv, 128, 1, None, 16, 4, False, 64, 128)
+    c = wl.verify_case(cfg, seed=rows, layouts=tuple(((wl.TEXT, n - 1),) for n in lens), n_q=1, parent=None)
+    q, k, v = (dev(x, "bf16") for x in (c.q, c.k, c.v))
+    ws = torch.full((sp.verify_attn_workspace_bytes(q, k, v, len(lens), 1, sum(lens)) // 4,), float("nan"), device="cuda")
+    out, lse = sp.verify_attn(q, k, v, c.cu_seqlens, None, 1, out=torch.full_like(q, float("nan")), workspace=ws)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.verify_attn(c.q, c.k, c.v, c.cu_seqlens, None, 1)
+    check_attn(host(out), ref, "bf16", f"{rows} rows, {lens}")
+    assert np.abs(host(lse) - ref_lse).max() <= 4e-3
