@@ -114,6 +114,12 @@ template <int kD> constexpr bool kWideState = kD == 64;
 // steps, without a combine pass: one of 60, 4/2, 4 4.1 / 3.9, four of 200, 16/4, 4 6.0 / 5.2, sixteen of 250, 8/8, 16 7.5 / 6.8.
 // kD = head size.  A step of a stream stages 8 KB of K and 8 KB of V at either size: one tile of 32
 // tokens at kD = 128, two at 64, so the loads in flight and the barriers per byte are the same.
+// LDS of a workgroup: two buffers of K and V tiles a stream.  After the main loop the first part is reused for the merge: 1 KB
+// a d-tile that one wavefront sends another (kPairs: three by each of eight; else as many as a row has, by each of four pairs),
+// then 8 bytes a lane of (m, l).
+template <int kD> constexpr int kLdsBytes = kStreams * 2 * 2 * (128 / kD) * kTile * kD * 2;
+template <int kD, bool kPairs> constexpr int kMergeTiles = (kPairs ? 24 : 4 * (kD / 16)) * 1024;
+template <int kD, bool kPairs> constexpr int kMergeBytes = kMergeTiles<kD, kPairs> + 4 * kStreams * 64 * 8;
 template <int kD, int kPrefetch, int kTilesOfRows, bool kPing>
 __global__ void __launch_bounds__(256 * kStreams)
 verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t stride_head, int stride_tok, int cl0_one,
@@ -131,9 +137,11 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
   constexpr int kKS = kD / 32, kMT = kD / 16;              // MFMA k-steps of a score, 16-wide d-tiles
   constexpr bool kWide = kWideState<kD>;
   constexpr bool kShare = !kPing;                          // both streams merge and store
-  // [stream][buf][K,V][kSub tiles]; after the main loop the first 34 KB are reused for the merge
+  // [stream][buf][K,V][kSub tiles]; the merge takes 36 KB of it (heads of 64: 20, kPairs 28)
+  static_assert(kMergeBytes<kD, kPairs> <= kLdsBytes<kD>, "the merge reuses the tiles' LDS");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int kStepBytes = kSub * kTile * kRowBytes;     // K (or V) rows of one stream step
+  static_assert(kLdsBytes<kD> == kStreams * 2 * 2 * kStepBytes, "");
   auto lds_at = [&](int strm_, int buf, int kv) {
     return lds + ((strm_ * 2 + buf) * 2 + kv) * kStepBytes;
   };
@@ -622,7 +630,7 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
     // four wavefronts hold a row (two streams, two tiles of a step) and a d-tile each: o_acc[0][i] is tile part ^ i
     static_assert(kMT == 4, "a d-tile per wavefront");
     f32x4 *po4 = reinterpret_cast<f32x4 *>(lds) + lane;                        // [part][i - 1][wr][lane]
-    float *pm4 = reinterpret_cast<float *>(lds + 24 * 1024) + 2 * lane;        // [part][wr][lane][m, l]
+    float *pm4 = reinterpret_cast<float *>(lds + kMergeTiles<kD, kPairs>) + 2 * lane;        // [part][wr][lane][m, l]
     const float l_mine = quad_sum(l_acc[0][0]);
     __syncthreads();
 #pragma unroll
@@ -669,7 +677,7 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
   }
   constexpr int kOwn = kShare ? kMT / 2 : kMT;                                 // d-tiles of a stream: strm * kOwn ..
   f32x4 *mo = reinterpret_cast<f32x4 *>(lds) + w * kOwn * 64 + lane;           // [stream][w][own tile][lane]
-  float *mm = reinterpret_cast<float *>(lds + 4 * kMT * 1024) + (w * 64 + lane) * 2;     // [stream][w][lane][m,l]
+  float *mm = reinterpret_cast<float *>(lds + kMergeTiles<kD, kPairs>) + (w * 64 + lane) * 2;     // [stream][w][lane][m,l]
 #pragma unroll
   for (int qt = 0; qt < kQT; ++qt) {
     const float l_mine = kMfmaRowSum ? l_acc[qt][0] : quad_sum(l_acc[qt][0]);
@@ -1121,12 +1129,11 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
   dim3 grid(x3d * rbs, a.Hkv, a.B), block(256 * kStreams);
   if (flat) grid = dim3((a.n_slots * a.Hkv + 7) / 8 * 8 * rbs, 1, 1);
   constexpr int kSub = 128 / kD;
-  constexpr int kLdsBytes = kStreams * 2 * 2 * kSub * kTile * kD * 2;
-  static_assert(kLdsBytes <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
+  static_assert(kLdsBytes<kD> <= 64 * 1024, "beyond 64 KB the kernel needs the dynamic-LDS attribute");
   const int shape = rbs << kShapeBits | (flat ? kShapeFlat : 0) | (a.direct ? kShapeDirect : 0) | (equal_sequences(a, tab) ? 0 : kShapeTable);
   const int len0 = flat ? a.n_slots * a.Hkv : tab.cu_len[1] - tab.cu_len[0], ns0 = tab.cu_split[1];
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, block, kLdsBytes, st, a.k, a.v, a.stride_head, (int)a.stride_tok, (int)tab.cu_len[0], len0, ns0,
+    hipLaunchKernelGGL(kern, grid, block, kLdsBytes<kD>, st, a.k, a.v, a.stride_head, (int)a.stride_tok, (int)tab.cu_len[0], len0, ns0,
                        (int)pt.piece[0], a.n_slots, shape, a, tab, pt);
   };
   const int steps = (a.chunk / kTile + kStreams * kSub - 1) / (kStreams * kSub);   // of a full split
