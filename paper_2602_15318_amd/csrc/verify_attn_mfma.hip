@@ -792,7 +792,7 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
   constexpr int kInFlight = 4;
   constexpr int kTiles = kWaves > 2 && (kWideState<kD> || std::is_same<T, float>::value) ? 1 : 2;
   constexpr bool kWide = kWideState<kD> || std::is_same<T, float>::value;    // fp32 partials
-  constexpr int kMine = kInFlight / 4;             // splits whose (m, l, c) a lane loads: those of its four lanes make a round
+  static_assert(kInFlight == 4, "the four lanes of a row load (m, l, c) of a round's splits, one each");
   constexpr int kQuarter = kWide ? 64 * kD : 4096; // bytes of 16 rows of a unit: a wavefront of the partial pass
   constexpr int kLoad = !kWide && kTiles == 1 ? 8 : 16;
   __shared__ f32x4 xo[kWaves][kTiles][64];
@@ -824,13 +824,8 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
   for (int sb = ws; sb < ns; sb += kWaves * kInFlight) {
     typedef typename std::conditional<kLoad == 8, u32x2, u32x4>::type part_t;
     part_t pa[kInFlight][kWide ? kTiles : 1];
-    float ml[kMine][3];
-#pragma unroll
-    for (int j = 0; j < kMine; ++j) {
-      const int s = min(sb + kWaves * (c4 + 4 * j), ns - 1);
-      const u32x3 w = __builtin_amdgcn_raw_buffer_load_b96(rs_ml, __umul24(s, step_ml) + (unsigned int)n * (4 * kMlFloats), 0, 2);
-      ml[j][0] = __uint_as_float(w.x); ml[j][1] = __uint_as_float(w.y); ml[j][2] = __uint_as_float(w.z);
-    }
+    const int s_own = sb + kWaves * c4;
+    const u32x3 ml = __builtin_amdgcn_raw_buffer_load_b96(rs_ml, __umul24(min(s_own, ns - 1), step_ml) + (unsigned int)n * (4 * kMlFloats), 0, 2);
 #pragma unroll
     for (int u = 0; u < kInFlight; ++u) {
       const unsigned int so = (unsigned int)min(sb + kWaves * u, ns - 1) * step_o + tile_o;
@@ -841,29 +836,19 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
         for (int t = 0; t < (kWide ? kTiles : 1); ++t) pa[u][t] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, at_o, so + 1024u * t, 2);
       }
     }
-    float mx = m_run;
-#pragma unroll
-    for (int j = 0; j < kMine; ++j) mx = sb + kWaves * (c4 + 4 * j) < ns ? fmaxf(mx, ml[j][0]) : mx;
-    mx = quad_max(mx);
+    const float mx = quad_max(s_own < ns ? fmaxf(m_run, __uint_as_float(ml.x)) : m_run);
     // weight of a split: its share of the softmax denominator (its output is normalised), worked out by one of the four
     // lanes of a row and handed to the others
-    float wgt[kInFlight], sum = 0.f;
-#pragma unroll
-    for (int j = 0; j < kMine; ++j) {
-      const float x = sb + kWaves * (c4 + 4 * j) < ns ? fast_exp2(ml[j][0] - mx) * ml[j][1] : 0.f;
-      sum += x;
-      const unsigned int cb = __float_as_uint(ml[j][2]);
-      const float sc = kWide ? 1.f : __uint_as_float(mt < kD / 32 ? cb << 16 : cb & 0xffff0000u);
-      const unsigned int xc = __float_as_uint(x * sc);
-      const auto r = __builtin_amdgcn_permlane16_swap(xc, xc, false, false);
-      const auto r0 = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false);
-      const auto r1 = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
-      wgt[4 * j] = __uint_as_float(r0[0]); wgt[4 * j + 1] = __uint_as_float(r1[0]);
-      wgt[4 * j + 2] = __uint_as_float(r0[1]); wgt[4 * j + 3] = __uint_as_float(r1[1]);
-    }
+    const float w_own = s_own < ns ? fast_exp2(__uint_as_float(ml.x) - mx) * __uint_as_float(ml.y) : 0.f;
+    const float sc = kWide ? 1.f : __uint_as_float(mt < kD / 32 ? ml.z << 16 : ml.z & 0xffff0000u);
+    const unsigned int wc = __float_as_uint(w_own * sc);
+    const auto w02 = __builtin_amdgcn_permlane16_swap(wc, wc, false, false);
+    const auto w0 = __builtin_amdgcn_permlane32_swap(w02[0], w02[0], false, false);
+    const auto w1 = __builtin_amdgcn_permlane32_swap(w02[1], w02[1], false, false);
+    const float wgt[kInFlight] = {__uint_as_float(w0[0]), __uint_as_float(w1[0]), __uint_as_float(w0[1]), __uint_as_float(w1[1])};
     const float alpha = fast_exp2(m_run - mx);
     m_run = mx;
-    l_run = l_run * alpha + quad_sum(sum);
+    l_run = l_run * alpha + quad_sum(w_own);
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) o[t] *= alpha;
 #pragma unroll
