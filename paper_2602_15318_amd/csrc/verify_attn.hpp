@@ -59,8 +59,12 @@ __device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int slot) {
   return b;
 }
 
-// a / n by the reciprocal: half a step off, which is far more than what two roundings of the product are off while a < 2^20.
-__device__ __forceinline__ int div_by_rcp(int a, float inv_n) { return (int)(((float)a + 0.5f) * inv_n); }
+// a / n for uniform numbers.  By the reciprocal while a < 2^20: half a step off, which is far more than what the roundings of
+// it and of the product are off.  Larger ones (tens of thousands of KV heads) take the integer division.
+__device__ __forceinline__ int div_uniform(int a, int n) {
+  if (a >= 1 << 20) return a / n;
+  return __builtin_amdgcn_readfirstlane((int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)n)));
+}
 
 // Draft row and head (within the group of g) of row rho of a KV head.  The reciprocal is below 1/g by more than the roundings
 // of the product (four of at most 2^-23 each), so that the quotient, at most 64, is right or one short, for every g.

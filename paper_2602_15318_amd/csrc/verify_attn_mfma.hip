@@ -178,7 +178,7 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
   if (flat) {
     const int grp = sq * 8 + xcd;                          // global split + n_slots * KV head
     if (grp >= len_one) return;                            // padding of the last round of 8
-    c = __builtin_amdgcn_readfirstlane(div_by_rcp(grp, __builtin_amdgcn_rcpf((float)n_slots)));
+    c = div_uniform(grp, n_slots);
     const int gslot = grp - c * n_slots;
     // (an empty statement that takes these as scalar-register inputs: their lines come with the ends that the search reads,
     // and the entries of the sequence found are then at hand)
@@ -774,8 +774,8 @@ typedef __attribute__((ext_vector_type(3))) unsigned int u32x3;
 // KV head and row block of a unit (for rows' numbers in it: a combine workgroup without rows leaves before it loads).
 __device__ __forceinline__ RowHead head_and_block(int unit, int rbs) {
   if (rbs == 1) return {unit, 0};
-  const RowHead cr = row_and_head(unit, rbs, kBelow * __builtin_amdgcn_rcpf((float)rbs));
-  return {__builtin_amdgcn_readfirstlane(cr.row), __builtin_amdgcn_readfirstlane(cr.head)};
+  const int c = div_uniform(unit, rbs);
+  return {c, unit - c * rbs};
 }
 
 struct CombineArgs {                               // what a combine kernel's scalar arguments say, in its own terms
@@ -1109,8 +1109,7 @@ static hipError_t launch_partial(const VerifyArgs &a, const SeqTable &tab, hipSt
   }
   // grid shape: one x range per (KV head, sequence) unless that would launch mostly padding
   const int x3d = (max_ns + 7) / 8 * 8;
-  // (fewer than 3/4 of the slots real; the kernel divides group numbers by reciprocals)
-  const int flat = (int64_t)a.n_slots * 4 < (int64_t)x3d * a.B * 3 && (int64_t)a.n_slots * a.Hkv < (1 << 20);
+  const int flat = (int64_t)a.n_slots * 4 < (int64_t)x3d * a.B * 3;      // fewer than 3/4 of the slots real
   dim3 grid(x3d * rbs, a.Hkv, a.B), block(256 * kStreams);
   if (flat) grid = dim3((a.n_slots * a.Hkv + 7) / 8 * 8 * rbs, 1, 1);
   constexpr int kSub = 128 / kD;

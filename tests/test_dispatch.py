@@ -93,6 +93,13 @@ def test_any_number_of_heads_on_the_matrix_cores(launches):
             assert run[0]["kernel"].startswith("verify_partial_mfma_kernel" if dtype == "bf16" else "verify_partial_f32_kernel"), run
 
 
+def test_any_number_of_kv_heads_on_one_grid_axis(launches):
+    """Short sequences of very many KV heads are numbered along x, like any others: a grid's other axes end at 65,535."""
+    lens = [([15] * 15 + [14], 70000), ([15] * 16, 70000), ([16], 1 << 20), ([40] * 3, 400000)]
+    for (ns, heads), run in zip(lens, launches([verify(heads, heads, 1, ns, "head", d=64) for ns, heads in lens])):
+        assert run[0]["flat"] and run[0]["grid"] == [len(ns) * heads, 1, 1], run
+
+
 @pytest.mark.parametrize("dtype,d,unit_bytes,most", [("bf16", 64, 16384, 8), ("bf16", 128, 16384, 8), ("f32", 64, 16384, 16),
                                                       ("f32", 128, 32768, 16)])
 def test_combine_offsets(launches, dtype, d, unit_bytes, most):

@@ -1,6 +1,6 @@
-"""Verification with thousands of query heads per KV head: partials whose splits lie near 2 GiB apart, queries of more than
-4 GiB.  A row's output is a
-function of its own query, so the oracle is given a few heads of each KV head, the first and the last among them.
+"""Verification with thousands of query heads per KV head, or of KV heads: partials whose splits lie near 2 GiB apart, queries
+of more than 4 GiB, numbers of (sequence, KV head) beyond 2^20.  A row's output is a function of its own query, so the oracle
+is given a few heads, the first and the last among them.
 test_dispatch.py holds the plan against the offsets' limits on the CPU."""
 import numpy as np
 import pytest
@@ -42,3 +42,23 @@ def test_groups_whose_rows_take_more_than_20_bits(oracle, dtype, d, g, n_q, toke
 
 def test_queries_of_more_than_4_gib(oracle):
     check_heads(oracle, "bf16", 128, 9, 29600, 64, 80)
+
+
+def test_ragged_batch_of_70000_kv_heads(oracle):
+    """(sequence, KV head) numbers beyond 2^20 on the one axis that such a call is launched on."""
+    import torch
+
+    import paper_2602_15318_amd as sp
+    Hkv, d, lens = 70000, 64, [15] * 15 + [14]
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q = torch.randn(len(lens), Hkv, d, device="cuda", dtype=torch.bfloat16, generator=gen)
+    k, v = (torch.randn(sum(lens), Hkv, d, device="cuda", dtype=torch.bfloat16, generator=gen) for _ in range(2))
+    cu = np.cumsum([0] + lens).astype(np.int32)
+    print(f"bf16 d={d} {Hkv} KV heads, {len(lens)} sequences", flush=True)
+    out, lse = sp.verify_attn(q, k, v, cu, None, 1)
+    torch.cuda.synchronize()
+    heads = torch.tensor([0, 1, 2, 65534, 65535, 65536, Hkv // 2, Hkv - 2, Hkv - 1], device="cuda")
+    f64 = lambda t: t[:, heads].double().cpu().numpy()
+    ref, ref_lse = oracle.verify_attn(f64(q), f64(k), f64(v), cu, None, 1)
+    check_attn(f64(out), ref, "bf16", f"{Hkv} KV heads")
+    assert np.abs(f64(lse) - ref_lse).max() <= 4e-3
