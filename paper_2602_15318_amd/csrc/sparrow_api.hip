@@ -581,7 +581,7 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
   a.q = q; a.k = k; a.v = v; a.parent = parent;
   a.parent_stride = parent ? desc->parent_stride : 0;
   a.B = B; a.n_q = n_q; a.Hq = desc->n_q_heads; a.Hkv = desc->n_kv_heads; a.d = desc->head_dim;
-  a.g = a.Hq / a.Hkv; a.inv_g = kBelow / (float)a.g;
+  a.g = a.Hq / a.Hkv; a.inv_g = 1.0f / (float)a.g;
   a.chunk = chunk; a.n_slots = tab.cu_split[B];
   a.scale_log2 = scale_log2_of(desc);
   a.stride_tok = desc->kv_stride_token; a.stride_head = desc->kv_stride_head;

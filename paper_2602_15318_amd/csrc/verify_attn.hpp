@@ -22,7 +22,7 @@ struct VerifyArgs {
   int32_t parent_stride;  // 0: one tree [n_q] for all sequences; else sequence b's tree at parent + b*stride
   int32_t B, n_q, Hq, Hkv, d;
   int32_t g;              // Hq / Hkv
-  float inv_g;            // kBelow / g, see row_and_head
+  float inv_g;            // 1 / g
   int32_t chunk;          // longest split of the call, in tokens (the kernels derive each
                           // sequence's own split length from SeqTable)
   int32_t n_slots;        // cu_split[B]
@@ -59,21 +59,26 @@ __device__ __forceinline__ int seq_of_slot(const SeqTable &tab, int slot) {
   return b;
 }
 
-// a / n for uniform numbers.  By the reciprocal while a < 2^20: half a step off, which is far more than what the roundings of
-// it and of the product are off.  Larger ones (tens of thousands of KV heads) take the integer division.
-__device__ __forceinline__ int div_uniform(int a, int n) {
-  if (a >= 1 << 20) return a / n;
-  return __builtin_amdgcn_readfirstlane((int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)n)));
+// a / n and the rest by the reciprocal of n (one bit off at most).  Half a step is more than the roundings are off while a < 2^20,
+// and for the rows of a KV head (a / n < 64) while n < 32,768; `large` (uniform) says that this does not hold, and the quotient
+// may be one off either way (a launch has fewer than 2^23 groups; n = 1 is exact).  Corrected in every call it lies ahead of
+// the query's loads: 6.8 -> 6.9 us a call over 200 tokens.
+struct QuotRest { int quot, rest; };
+__device__ __forceinline__ QuotRest div_by_rcp(int a, int n, float inv_n, bool large) {
+  int q = (int)(((float)a + 0.5f) * inv_n), r = a - q * n;
+  if (__builtin_expect(large, 0)) {
+    asm volatile("" : "+v"(q));                    // (empty: keeps it a branch)
+    if (r < 0) { --q; r += n; }
+    else if (r >= n) { ++q; r -= n; }
+  }
+  return {q, r};
 }
-
-// Draft row and head (within the group of g) of row rho of a KV head.  The reciprocal is below 1/g by more than the roundings
-// of the product (four of at most 2^-23 each), so that the quotient, at most 64, is right or one short, for every g.
-constexpr float kBelow = 1.0f - 0x1p-20f;
-struct RowHead { int row, head; };
-__device__ __forceinline__ RowHead row_and_head(int rho, int g, float inv_g_below) {
-  int row = (int)((float)rho * inv_g_below), head = rho - row * g;
-  if (head >= g) { ++row; head -= g; }
-  return {row, head};
+// Draft row and head (within the group of g) of row rho of a KV head
+__device__ __forceinline__ QuotRest row_and_head(int rho, int g, float inv_g) { return div_by_rcp(rho, g, inv_g, g >= 32768); }
+// The same of uniform numbers: of a group (split slot, KV head) or unit (KV head, row block)
+__device__ __forceinline__ QuotRest div_uniform(int a, int n) {
+  const QuotRest d = div_by_rcp(a, n, __builtin_amdgcn_rcpf((float)n), a >= 1 << 20);
+  return {__builtin_amdgcn_readfirstlane(d.quot), __builtin_amdgcn_readfirstlane(d.rest)};
 }
 
 // Natural-log sum-exp of a row: reference point m (log2 units) and sum l.  kWide: rounded once at its full

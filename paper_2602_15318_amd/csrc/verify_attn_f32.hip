@@ -131,9 +131,9 @@ verify_partial_f32_kernel(const void *k_base, const void *v_base, int64_t stride
     const int rho = (rb * kQT + qt) * 64 + 16 * w + n;
     row_ok[qt] = rho < R;
     if ((rb * kQT + qt) * 64 + 16 * w < R) n_act = qt + 1;
-    const RowHead rh = row_and_head(rho, g, a.inv_g);
-    i_row[qt] = row_ok[qt] ? rh.row : 0;
-    h[qt] = row_ok[qt] ? c * g + rh.head : 0;
+    const QuotRest rh = row_and_head(rho, g, a.inv_g);
+    i_row[qt] = row_ok[qt] ? rh.quot : 0;
+    h[qt] = row_ok[qt] ? c * g + rh.rest : 0;
     // rows past R read row 0 (in bounds) and are zeroed
     const int64_t qrow = row_ok[qt] ? ((int64_t)b * a.n_q + i_row[qt]) * a.Hq + h[qt] : 0;
     const float *qp = (const float *)a.q + qrow * kD + 4 * c4;

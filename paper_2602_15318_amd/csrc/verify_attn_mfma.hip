@@ -178,8 +178,9 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
   if (flat) {
     const int grp = sq * 8 + xcd;                          // global split + n_slots * KV head
     if (grp >= len_one) return;                            // padding of the last round of 8
-    c = div_uniform(grp, n_slots);
-    const int gslot = grp - c * n_slots;
+    const QuotRest cg = div_uniform(grp, n_slots);
+    const int gslot = cg.rest;
+    c = cg.quot;
     // (an empty statement that takes these as scalar-register inputs: their lines come with the ends that the search reads,
     // and the entries of the sequence found are then at hand)
     asm volatile("" ::"s"(tab.cu_len[0]), "s"(tab.cu_len[16]), "s"(pt.piece[0]), "s"(pt.piece[15]), "s"(tab.cu_split[0]),
@@ -284,9 +285,9 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
     row_ok[qt] = rho < R;
     if ((rb * kQT + qt) * kRowsPerWG + 16 * wr < R) n_act = qt + 1;
     // rows past R take the data of row 0 (in bounds); what comes of them is not used
-    const RowHead rh = row_and_head(rho, g, a.inv_g);
-    i_row[qt] = row_ok[qt] ? rh.row : 0;
-    h[qt] = row_ok[qt] ? rh.head : 0;
+    const QuotRest rh = row_and_head(rho, g, a.inv_g);
+    i_row[qt] = row_ok[qt] ? rh.quot : 0;
+    h[qt] = row_ok[qt] ? rh.rest : 0;
   }
   const int64_t q_row0 = (int64_t)b * a.n_q * a.Hq + (int64_t)c * g;     // of the call: row (b, 0), first head of the group
 
@@ -772,11 +773,7 @@ verify_partial_mfma_kernel(const void *k_base, const void *v_base, int64_t strid
 typedef __attribute__((ext_vector_type(3))) unsigned int u32x3;
 
 // KV head and row block of a unit (for rows' numbers in it: a combine workgroup without rows leaves before it loads).
-__device__ __forceinline__ RowHead head_and_block(int unit, int rbs) {
-  if (rbs == 1) return {unit, 0};
-  const int c = div_uniform(unit, rbs);
-  return {c, unit - c * rbs};
-}
+__device__ __forceinline__ QuotRest head_and_block(int unit, int rbs) { return rbs == 1 ? QuotRest{unit, 0} : div_uniform(unit, rbs); }
 
 struct CombineArgs {                               // what a combine kernel's scalar arguments say, in its own terms
   const unsigned char *part_o, *part_ml;
@@ -798,8 +795,8 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
   __shared__ f32x4 xo[kWaves][kTiles][64];
   __shared__ float xm[kWaves][16], xl[kWaves][16];
   const int wq = blockIdx.x & 3, unit = blockIdx.x >> 2;       // 16 rows of unit KV head * rbs + row block
-  const RowHead cr = head_and_block(unit, shape >> 1);
-  const int c = cr.row, rho0 = cr.head * kRowsPerWG + 16 * wq;
+  const QuotRest cr = head_and_block(unit, shape >> 1);
+  const int c = cr.quot, rho0 = cr.rest * kRowsPerWG + 16 * wq;
   if (rho0 >= n_q * g) return;                     // tile without rows (uniform)
   const int b = blockIdx.z;
   int s0 = b * ns_one, ns = ns_one;
@@ -868,9 +865,9 @@ __device__ __forceinline__ void combine_rows16(const CombineArgs &a, const SeqTa
   }
   // where this lane's row goes
   const int rho = rho0 + n;
-  const RowHead rh = row_and_head(rho, g, kBelow * __builtin_amdgcn_rcpf((float)g));
+  const QuotRest rh = row_and_head(rho, g, __builtin_amdgcn_rcpf((float)g));
   const bool row_ok = rho < n_q * g;
-  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.row * Hq + rh.head);
+  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.quot * Hq + rh.rest);
   int t0 = 0;                                      // the d-tiles that this wavefront stores: all, or one
   float m = m_run, l = l_run;
   if constexpr (kWaves > 1) {
@@ -942,8 +939,8 @@ verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *par
   __shared__ f32x2 xo[kWaves][64], xml[kWaves][4];
   // four rows of unit KV head * rbs + row block
   const int rows4 = (blockIdx.x & 7) * 2 + (blockIdx.x >> 3 & 1), unit = blockIdx.x >> 4;
-  const RowHead cr = head_and_block(unit, shape >> 1);
-  const int c = cr.row, rho0 = cr.head * kRowsPerWG + 4 * rows4;
+  const QuotRest cr = head_and_block(unit, shape >> 1);
+  const int c = cr.quot, rho0 = cr.rest * kRowsPerWG + 4 * rows4;
   if (rho0 >= n_q * g) return;                     // group without rows (uniform)
   const int b = blockIdx.z;
   int s0 = b * ns_one, ns = ns_one;
@@ -1015,8 +1012,8 @@ verify_combine_long_kernel(const unsigned char *part_o, const unsigned char *par
   l_run += dpp_f32<0x124>(l_run);
   l_run = quad_sum(l_run);
   const int rho = rho0 + r;
-  const RowHead rh = row_and_head(rho, g, kBelow * __builtin_amdgcn_rcpf((float)g));
-  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.row * Hq + rh.head);
+  const QuotRest rh = row_and_head(rho, g, __builtin_amdgcn_rcpf((float)g));
+  const int64_t orow = (int64_t)b * n_q * Hq + c * g + (int64_t)(rh.quot * Hq + rh.rest);
   float m = m_run, l = l_run;
   if constexpr (kWaves > 1) {
     xo[ws][lane] = z;
