@@ -130,9 +130,11 @@ bool use_mfma_verify(const sparrow_attn_desc *d, int64_t total_tokens) {
 // of 64 tokens, up to 8 steps (a step of two 32-token tiles, half of it empty, takes as long, and fewer pieces leave less to
 // combine; longer pieces lose compute units by it, eight of 26,120 tokens 75.5 -> 78.8 us); the pieces themselves are even
 // again (split_len), of no more steps.  From 32 / 64 tokens, us a call: chain of 5 over 4,096 tokens 9.45 / 9.1, over 6,000
-// 10.2 / 9.55, of 8 over 26,112 16.6 / 16.3, 16 nodes over 5,000 14.1 / 13.2.  Neither takes more scratch than the query says.
+// 10.2 / 9.55, of 8 over 26,112 16.6 / 16.3, 16 nodes over 5,000 14.1 / 13.2.  Neither takes more scratch than the query says,
+// but some such plans take more than the proportional one (two sequences of 85 rows 4 pieces, not 3): `by_proportion` asks for
+// that, where the scratch at hand holds no more.
 int plan_splits(const sparrow_attn_desc *d, const int32_t *cu_seqlens, int32_t B, int32_t n_q, int64_t total,
-                bool mfma, SeqTable *tab) {
+                bool mfma, SeqTable *tab, bool by_proportion = false) {
   int slots;
   const int chunk0 = plan_chunk(d, n_q, total, mfma, &slots);
   const int slot_budget = (int)((total + chunk0 - 1) / chunk0);
@@ -141,7 +143,7 @@ int plan_splits(const sparrow_attn_desc *d, const int32_t *cu_seqlens, int32_t B
   int chunk = 0;
   int ns[SPARROW_MAX_BATCH];
   int used = 0;
-  bool equal = mfma && d->dtype == SPARROW_BF16 && slots >= B;
+  bool equal = mfma && d->dtype == SPARROW_BF16 && slots >= B && !by_proportion;
   for (int b = 1; b < B; ++b) equal &= cu_seqlens[b + 1] - cu_seqlens[b] == cu_seqlens[1] - cu_seqlens[0];
   for (int b = 0; b < B; ++b) {
     const int len = cu_seqlens[b + 1] - cu_seqlens[b];
@@ -532,6 +534,13 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
   SeqTable tab;
   int chunk = plan_splits(desc, cu_seqlens, B, n_q, total, mfma, &tab);
   size_t need = verify_ws_bytes(desc, tab.cu_split[B], n_q, mfma);
+  const size_t have = static_ws ? (size_t)SPARROW_STATIC_WS_BYTES : workspace ? workspace_bytes : 0;
+  if (mfma && need > have) {
+    SeqTable tab_p;
+    const int chunk_p = plan_splits(desc, cu_seqlens, B, n_q, total, true, &tab_p, true);
+    const size_t need_p = verify_ws_bytes(desc, tab_p.cu_split[B], n_q, true);
+    if (need_p < need) { tab = tab_p; chunk = chunk_p; need = need_p; }
+  }
   // Heads of 64 and fp32 go to the plain-ALU kernels where only their partials fit the scratch at hand: those
   // have no padding to 64 rows (64 sequences of one row over 64 KV heads: 1 MB against 37 MB).  The
   // static scratch also refuses what it cannot hold for them, so its limit is one rule per shape.
@@ -539,7 +548,6 @@ static int verify_body(const sparrow_attn_desc *desc, const void *q, const void 
     SeqTable tab_g;
     const int chunk_g = plan_splits(desc, cu_seqlens, B, n_q, total, false, &tab_g);
     const size_t need_g = verify_ws_bytes(desc, tab_g.cu_split[B], n_q, false);
-    const size_t have = static_ws ? (size_t)SPARROW_STATIC_WS_BYTES : workspace ? workspace_bytes : 0;
     if ((need > have && need_g <= have) || (static_ws && need_g > have)) {
       mfma = false;
       tab = tab_g; chunk = chunk_g; need = need_g;

@@ -2,7 +2,7 @@
 launch_recorder.c in the place of the HIP runtime, with made-up device addresses that nothing reads.
 
 A call is a dict: {"call": "verify", "dtype", "Hq", "Hkv", "d", "n_q", "lens", "layout", "own"} (dtype: bf16 or f32; lens: rows of each sequence,
-draft rows included; layout: "token", "head" or "pair", as kv_strides says; own: a tree per sequence), or
+draft rows included; layout: "token", "head" or "pair", as kv_strides says; own: a tree per sequence; workspace: its bytes), or
 {"call": "accept" | "topk", "dtype", "M", "H", "V"}."""
 import ctypes
 import json
@@ -81,7 +81,8 @@ def _child(shim):
             st, sh = kv_strides(c.get("layout", "token"), sum(lens), c["Hkv"], c["d"])
             desc = _Desc({"f32": 0, "bf16": 1}[c.get("dtype", "bf16")], c["Hq"], c["Hkv"], c["d"], 0.0, st, sh, n_q if c.get("own") else 0)
             cu = (i32 * (B + 1))(*[sum(lens[:b]) for b in range(B + 1)])
-            rc = lib.sparrow_verify_attn(ctypes.byref(desc), at, at, at, cu, at, B, n_q, at, at, at, ws, None)
+            rc = lib.sparrow_verify_attn(ctypes.byref(desc), at, at, at, cu, at, B, n_q, at, at, at,
+                                         ctypes.c_size_t(c["workspace"]) if "workspace" in c else ws, None)
         else:
             code = {"f32": 0, "bf16": 1}[c["dtype"]]
             if c["call"] == "accept":                       # M sequences without draft rows

@@ -165,6 +165,19 @@ def test_ragged_batches_use_every_slot(launches, d):
             assert run[0]["splits"] == plan_by_proportion(lens, 64), (heads, lens, run[0])
 
 
+def test_equal_batches_fit_the_scratch_of_the_proportional_plan(launches):
+    """Sequences of one length, cut alike, may take more pieces than by proportion to the chip; scratch that holds no more than
+    those is not refused, and more scratch changes nothing."""
+    calls = [(Hkv, n_q, [n] * B) for Hkv in (4, 8, 32) for n_q in (1, 5, 9) for B in (1, 2, 4, 6, 8) for n in (66, 85, 100, 260, 807, 4995)]
+    tight = [plan_by_proportion(lens, 256 // Hkv) for Hkv, n_q, lens in calls]
+    unit = 64 * (4 * 64 + 12)                                # bytes of 64 rows of a split and KV head: fp16 values, (m, l, c)
+    few = launches([dict(verify(7 * Hkv, Hkv, n_q, lens), workspace=sum(ns) * Hkv * unit) for (Hkv, n_q, lens), ns in zip(calls, tight)])
+    many = launches([verify(7 * Hkv, Hkv, n_q, lens) for Hkv, n_q, lens in calls])
+    assert any(sum(m[0]["splits"]) > sum(ns) for m, ns in zip(many, tight) if len(m) == 2)
+    for c, ns, f, m in zip(calls, tight, few, many):
+        assert f == m or (sum(m[0]["splits"]) > sum(ns) and f[0]["splits"] == ns), (c, ns, f, m)
+
+
 def test_lm_head_cases_straight_to_lds(launches):
     """test_gpu_lm_head_widths.py runs every instance that loads straight to LDS: each row block with one tile per
     workgroup and, where its tiles have 128 rows, with several; and these instances from 17 rows up above 4,096 columns."""

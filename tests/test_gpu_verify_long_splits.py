@@ -8,7 +8,7 @@ import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-from gpu_util import check_attn, run_verify  # noqa: E402
+from gpu_util import check_attn, dev, host, run_verify  # noqa: E402
 
 # (query heads, KV heads, draft rows), rows of each sequence, most splits of a sequence in bf16 with heads of 128
 CASES = [((8, 1, 8), (9001,), 141), ((5, 1, 3), (8100, 8100), 127), ((6, 2, 5), (8000,), 125), ((6, 2, 1), (4161,), 66),
@@ -56,7 +56,6 @@ def test_workgroups_with_and_without_rows(oracle, Hkv, lens, rows):
     import torch
 
     import paper_2602_15318_amd as sp
-    from gpu_util import dev, host
     cfg = wl.Config("R", "bf16", Hkv * rows, Hkv, 128, 1, None, 16, 4, False, 64, 128)
     c = wl.verify_case(cfg, seed=rows, layouts=tuple(((wl.TEXT, n - 1),) for n in lens), n_q=1, parent=None)
     q, k, v = (dev(x, "bf16") for x in (c.q, c.k, c.v))
@@ -65,4 +64,21 @@ def test_workgroups_with_and_without_rows(oracle, Hkv, lens, rows):
     torch.cuda.synchronize()
     ref, ref_lse = oracle.verify_attn(c.q, c.k, c.v, c.cu_seqlens, None, 1)
     check_attn(host(out), ref, "bf16", f"{rows} rows, {lens}")
+    assert np.abs(host(lse) - ref_lse).max() <= 4e-3
+
+
+@pytest.mark.parametrize("splits", [29, 32])
+def test_equal_sequences_by_proportion_and_alike(oracle, splits):
+    """Eight sequences of 807 rows over 32 slots: scratch of 29 splits holds the plan by proportion, 32 are cut alike."""
+    import torch
+
+    import paper_2602_15318_amd as sp
+    cfg = wl.Config("R", "bf16", 32, 8, 128, 1, None, 16, 4, False, 64, 128)
+    c = wl.verify_case(cfg, seed=3, layouts=(((wl.TEXT, 802),),) * 8, n_q=5, parent=None)
+    q, k, v = (dev(x, "bf16") for x in (c.q, c.k, c.v))
+    ws = torch.full((splits * 8 * 64 * (4 * 64 + 12) // 4,), float("nan"), device="cuda")
+    out, lse = sp.verify_attn(q, k, v, c.cu_seqlens, None, 5, workspace=ws)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.verify_attn(c.q, c.k, c.v, c.cu_seqlens, None, 5)
+    check_attn(host(out), ref, "bf16", f"scratch of {splits} splits")
     assert np.abs(host(lse) - ref_lse).max() <= 4e-3
